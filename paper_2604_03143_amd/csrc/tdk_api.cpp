@@ -599,6 +599,8 @@ namespace {
 // row, and the layout of the caller's workspace.
 struct AttendPlan {
   int32_t chunk_tokens = 0, n_chunks = 0, n_parts = 0, max_rows = 0, n_pieces = 1, piece_tokens = 0;
+  bool    own_rows = false;        // one agent per wavefront (tdk_attend_rows_kernel)
+  int32_t max_agents = 0;
   int64_t rows = 0;
   size_t o_qrot = 0, o_qdiff = 0, o_part_o = 0, o_part_m = 0, o_part_l = 0, bytes = 0;
 };
@@ -616,6 +618,54 @@ bool attend_plan(const tdk_round* r, int32_t n_q, int32_t n_q_heads, AttendPlan&
   if (max_rows >= (int64_t)1 << 30) return false;
   p.max_rows = (int32_t)max_rows;
   p.rows = (int64_t)r->n_agents * n_q * n_q_heads;
+  p.max_agents = (int32_t)max_agents;
+  const int64_t agent_rows = (int64_t)n_q * G;
+  // Which kernels: one agent per wavefront, or the rows of a session's agents packed into one block.
+  //   Packed rows waste no place in the 32-row tiles, but their listed pages need a pass and partial results of their
+  //   own: better for few rows per agent (25 agents, one session: 28 against 49 us with 5 rows per agent and KV
+  //   head, 49 against 52 with 20; ten sessions: 268 against 329 us with 20 rows), worse from 33 rows on (40 rows:
+  //   94 against 70 us, ten sessions 575 against 460 us; 320 rows: 462 against 206 us).
+  //   With per-agent block orders the packed form needs a copy of every row per segment and reloads a tile's queries
+  //   lane by lane: it is better only with few rows per agent on a chip that is full without splitting lists
+  //   (5 rows: ten sessions 237 against 465 us, but one session 75 against 62 us; 20 rows: ten sessions 647 against
+  //   506 us, one session 107 against 70 us).
+  const int64_t lists = (int64_t)r->n_agents * r->model.num_kv_heads;
+  p.own_rows = agent_rows > 32 || r->total_master_rows == 0 || lists >= ((int64_t)1 << 27) ||
+               (r->rd.seg && (agent_rows > 16 || lists <= r->n_cus));
+  if (p.own_rows) {
+    const int64_t per_agent = (agent_rows + 31) / 32, cus = r->n_cus;
+    // Chunks of the span: workgroups of four wavefronts, two of which share a compute unit (each then takes about
+    // 1.6 times as long).  In units of a 64-token step (about 1.2 us): a workgroup starts up in 8, a step with
+    // per-agent block orders costs 2 (query reloads at the borders), a second launch to merge costs 6 and the
+    // traffic of the partial results.  (16 query tokens, 25 agents: 1, 2, 4, 8 chunks take 104, 74, 68, 79 us without
+    // listed pages; per-agent orders, 4 tokens: 1, 4, 8, 12 chunks 252, 87, 70, 85 us.)
+    double best = -1;
+    const int k_lo = (int)std::max<int64_t>(1, (max_span + 16383) / 16384);
+    for (int k = k_lo; k < k_lo + 32; ++k) {
+      const int64_t c = std::max<int64_t>(64, ((max_span + k - 1) / k + 63) / 64 * 64);
+      if (k > k_lo && c * (k - 1) >= max_span) continue;       // the same chunks as a smaller k
+      int64_t wgs = 0;
+      for (const auto& hs : r->sessions)
+        if (!hs.agents.empty()) wgs += (((int64_t)hs.span + c - 1) / c) * (((int64_t)hs.agents.size() * per_agent + 3) / 4);
+      wgs *= r->model.num_kv_heads;
+      const double one = (double)(c / 64) * (r->rd.seg ? 2 : 1) + 8;
+      const int64_t full = wgs / (2 * cus), rest = wgs % (2 * cus);
+      const double cost = one * (1.6 * (double)full + (rest == 0 ? 0.0 : rest > cus ? 1.6 : 1.0)) +
+                          (max_span > c ? 6 + (double)p.rows * ((double)max_span / (double)c + 1) * 1024 / 6e6 : 0.0);
+      if (best < 0 || cost < best) { best = cost; p.chunk_tokens = (int32_t)c; }
+    }
+    p.n_chunks = (int32_t)((max_span + p.chunk_tokens - 1) / p.chunk_tokens);
+    p.n_pieces = 0;
+    p.piece_tokens = 512;          // (no listed-pages pass: the merge finds no pieces)
+    p.n_parts = std::max(p.n_chunks, 1);
+    size_t off = 0;
+    auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
+    p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
+    p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
+    p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
+    p.bytes = std::max<size_t>(off, 256);
+    return true;
+  }
   // Tokens per workgroup of the master pass.  A workgroup walks its chunk in steps of 64 tokens; two
   // workgroups fit a compute unit at a time, so the pass takes about ceil(workgroups / slots) rounds of
   // (steps per chunk + a fixed start-up cost of about two steps).  Of the chunk sizes that the 128-bit page
@@ -653,8 +703,10 @@ bool attend_plan(const tdk_round* r, int32_t n_q, int32_t n_q_heads, AttendPlan&
   p.n_parts = p.n_chunks + p.n_pieces;
   size_t off = 0;
   auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-  p.o_qrot = place((size_t)p.rows * r->max_segments * kHeadDim * 2);
-  p.o_qdiff = place((size_t)p.rows * (r->rd.seg && r->seg_moved ? r->max_segments : 1) * kHeadDim * 2);
+  if (r->rd.seg) {                 // copies of every query row per segment
+    p.o_qrot = place((size_t)p.rows * r->max_segments * kHeadDim * 2);
+    p.o_qdiff = place((size_t)p.rows * (r->seg_moved ? r->max_segments : 1) * kHeadDim * 2);
+  }
   p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
   p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
   p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
@@ -723,11 +775,11 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const LayerDev l = layer_dev(io);
     const DiffDev d = diff_dev(in);
-    // blocks of the two passes share one launch when the round allows it (timed as the master pass)
-    const int64_t fused_blocks = (int64_t)r->model.num_kv_heads * r->rd.n_sessions * p.n_chunks * ((p.max_rows + 127) / 128) +
-                                 (int64_t)r->n_agents * ((r->model.num_kv_heads + 3) / 4) * std::min<int32_t>(p.n_pieces, 4);
-    if (!r->rd.seg && !r->diff_moved && (int64_t)a->n_q * at.group <= 32 && r->total_master_rows > 0 && fused_blocks < (1 << 30)) {
-      // (this launch rotates the query rows itself: no qrot kernel)
+    if (p.own_rows) {
+      TDK_LAUNCH(r, TDK_KERNEL_ATTEND_MASTER, s, launch_attend_rows(r->rd, l, d, at, p.max_agents, s));
+      if (p.n_chunks <= 1) return TDK_OK;
+    } else if (!r->rd.seg) {
+      // (master and listed pages in one launch, which also rotates the query rows itself)
       TDK_LAUNCH(r, TDK_KERNEL_ATTEND_MASTER, s, launch_attend_fused(r->rd, l, d, at, p.max_rows, s));
     } else {
       TDK_LAUNCH(r, TDK_KERNEL_ATTEND_QROT, s, launch_attend_qrot(r->rd, at, s));

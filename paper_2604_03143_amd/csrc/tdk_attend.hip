@@ -10,9 +10,10 @@
 // once per agent (the master pass).  Pages that an agent's diff lists are masked out of that product for
 // that agent's rows and come from the payload instead, with the same tile arithmetic (the listed-pages
 // pass, the "correct" half); a last kernel merges the partial results with their log-sum-exp weights.
-// For the decode case (identity layouts, stored diffs not moved, at most 32 rows per agent and KV head)
-// the two passes share one launch, which also rotates the query rows itself; other rounds run
-// tdk_attend_qrot_kernel, tdk_attend_master_kernel and tdk_attend_diff(16)_kernel one after another.
+// For the decode case (identity layouts, at most 32 rows per agent and KV head) the two passes share one launch,
+// which also rotates the query rows itself; rounds whose agents bring more rows, and most rounds with per-agent
+// block orders, give every wavefront one agent's rows (tdk_attend_rows_kernel); per-agent block orders with few rows
+// of many agents run tdk_attend_qrot_kernel, tdk_attend_master_kernel and tdk_attend_diff16_kernel one after another.
 #include "tdk_internal.h"
 
 #include <type_traits>
@@ -31,7 +32,7 @@ constexpr int kRowsPerWave = 32;     // query rows per wavefront (the N side of 
 constexpr int kRowsPerBlock = kRowsPerWave * kWaves;
 constexpr int kKsStride = kHeadDim + 8;   // bf16 elements per staged K row (+16 bytes: spreads LDS banks)
 constexpr int kBigTile = 2 * kTile;       // tokens per step of the master pass
-constexpr int kVsStride = kHeadDim + 16;  // bf16 elements per staged V row (+32 bytes: four consecutive rows' 32-byte
+constexpr int kVsStride = kHeadDim + 32;  // bf16 elements per staged V row (+64 bytes: four consecutive rows' 64-byte
                                           // pieces then fall into different LDS banks for the transposing reads)
 
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
@@ -337,6 +338,134 @@ __device__ __forceinline__ void softmax_pv16(const uint16_t* Vs, const f32x4a& s
   }
 }
 
+__device__ __forceinline__ float lo16(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float hi16(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Two pairs of a query row turned back by (c0, s0) and (c1, s1): y_a = x_a cos + x_b sin, y_b = x_b cos - x_a sin in
+// fp32, rounded to bf16.  wa, wb hold the a and the b elements (half style).
+__device__ __forceinline__ void turn_back_half(uint32_t wa, uint32_t wb, float c0, float s0, float c1, float s1, uint32_t& ya, uint32_t& yb) {
+  const float a0 = lo16(wa), a1 = hi16(wa), b0 = lo16(wb), b1 = hi16(wb);
+  ya = pack2(__builtin_fmaf(a0, c0, __fmul_rn(b0, s0)), __builtin_fmaf(a1, c1, __fmul_rn(b1, s1)));
+  yb = pack2(__builtin_fmaf(b0, c0, -__fmul_rn(a0, s0)), __builtin_fmaf(b1, c1, -__fmul_rn(a1, s1)));
+}
+// One pair held in one word (interleaved style).
+__device__ __forceinline__ uint32_t turn_back_pair(uint32_t w, float c, float s) {
+  const float a = lo16(w), b = hi16(w);
+  return pack2(__builtin_fmaf(a, c, __fmul_rn(b, s)), __builtin_fmaf(b, c, -__fmul_rn(a, s)));
+}
+
+// The fragments of a row for the 32-row tiles (fragment kk of a lane: elements 16 kk + 8 hh .. + 7), turned back by tab.
+__device__ __forceinline__ void turn_back32(const u32x4 (&raw)[8], const float* tab, bool interleaved, int hh, bf16x8 (&qf)[8]) {
+  if (!interleaved) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {             // fragments kk (elements a) and kk + 4 (elements b = a + 64)
+      u32x4 ya, yb;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int j = 16 * kk + 8 * hh + 2 * w;
+        uint32_t a, b;
+        turn_back_half(raw[kk][w], raw[kk + 4][w], tab[j], tab[kHalf + j], tab[j + 1], tab[kHalf + j + 1], a, b);
+        ya[w] = a; yb[w] = b;
+      }
+      qf[kk] = __builtin_bit_cast(bf16x8, ya);
+      qf[kk + 4] = __builtin_bit_cast(bf16x8, yb);
+    }
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {             // word w of a fragment holds the pair j = 8 kk + 4 hh + w
+      u32x4 y;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) { const int j = 8 * kk + 4 * hh + w; y[w] = turn_back_pair(raw[kk][w], tab[j], tab[kHalf + j]); }
+      qf[kk] = __builtin_bit_cast(bf16x8, y);
+    }
+  }
+}
+
+// The same for the 16-row tiles (fragment kk: elements 32 kk + 8 g .. + 7), in place.
+__device__ __forceinline__ void turn_back16(bf16x8 (&qf)[4], const float* tab, bool interleaved, int g) {
+  u32x4 raw[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) raw[kk] = __builtin_bit_cast(u32x4, qf[kk]);
+  if (!interleaved) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {             // fragments kk (elements a) and kk + 2 (elements b = a + 64)
+      u32x4 ya, yb;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        const int j = 32 * kk + 8 * g + 2 * w;
+        uint32_t a, b;
+        turn_back_half(raw[kk][w], raw[kk + 2][w], tab[j], tab[kHalf + j], tab[j + 1], tab[kHalf + j + 1], a, b);
+        ya[w] = a; yb[w] = b;
+      }
+      qf[kk] = __builtin_bit_cast(bf16x8, ya);
+      qf[kk + 2] = __builtin_bit_cast(bf16x8, yb);
+    }
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {             // word w of a fragment holds the pair j = 16 kk + 4 g + w
+      u32x4 y;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) { const int j = 16 * kk + 4 * g + w; y[w] = turn_back_pair(raw[kk][w], tab[j], tab[kHalf + j]); }
+      qf[kk] = __builtin_bit_cast(bf16x8, y);
+    }
+  }
+}
+
+// Loads a query row's B operands for the 32-row tiles: fragment kk of a lane holds elements 16 kk + 8 hh .. + 7.
+// tab != NULL turns the row back by that rotation.  All lanes of the wavefront use the same table; it goes through
+// lds_tab (128 floats of this wavefront), so that the fragments are turned one pair at a time with few registers.
+// A negative scale's sign travels with the rows.
+__device__ __forceinline__ void load_queries(const AttendDev& at, bool interleaved, int64_t out, bool on, const float* tab, float* lds_tab,
+                                             int lane, bf16x8 (&qf)[8]) {
+  const int hh = lane >> 5;
+  const uint32_t flip = at.q_flip ? 0x80008000u : 0u;
+  float2 t2 = make_float2(1.f, 0.f);
+  if (tab) t2 = reinterpret_cast<const float2*>(tab)[lane];
+  u32x4 raw[8];
+  const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim);
+  const uint32_t keep = on ? 0xffffffffu : 0u;             // (a row that does not exist reads another and is zero)
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk) {
+    const u32x4 v = qp[2 * kk + hh];
+    raw[kk] = u32x4{(v.x ^ flip) & keep, (v.y ^ flip) & keep, (v.z ^ flip) & keep, (v.w ^ flip) & keep};
+  }
+  if (!tab) {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
+    return;
+  }
+  wave_sync();                                           // an earlier table has been used
+  reinterpret_cast<float2*>(lds_tab)[lane] = t2;
+  wave_sync();
+  if (!interleaved) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      float c[8], sn[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) { c[e] = lds_tab[16 * kk + 8 * hh + e]; sn[e] = lds_tab[kHalf + 16 * kk + 8 * hh + e]; }
+      u32x4 ya, yb;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        uint32_t a, b;
+        turn_back_half(raw[kk][w], raw[kk + 4][w], c[2 * w], sn[2 * w], c[2 * w + 1], sn[2 * w + 1], a, b);
+        ya[w] = a; yb[w] = b;
+      }
+      qf[kk] = __builtin_bit_cast(bf16x8, ya);
+      qf[kk + 4] = __builtin_bit_cast(bf16x8, yb);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      u32x4 y;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) y[w] = turn_back_pair(raw[kk][w], lds_tab[8 * kk + 4 * hh + w], lds_tab[kHalf + 8 * kk + 4 * hh + w]);
+      qf[kk] = __builtin_bit_cast(bf16x8, y);
+      if (kk & 1) __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------------------------
@@ -354,12 +483,10 @@ __global__ __launch_bounds__(kBlock) void tdk_attend_qrot_kernel(const RoundDev 
   // the kernels after this one work with |scale|: a negative scale flips the sign of every query copy (exact)
   const uint32_t flip = at.q_flip ? 0x8000u : 0u;
   const float xa = __uint_as_float((uint32_t)(src[ia] ^ flip) << 16), xb = __uint_as_float((uint32_t)(src[ib] ^ flip) << 16);
-  // one copy per segment of the agent's layout (one for an identity layout): every segment has its own offset
-  const int seg0 = rd.seg ? rd.seg_off[agent] : agent;
-  const int nseg = rd.seg ? rd.seg_off[agent + 1] - seg0 : 1;
-  const float* tabs = rd.seg ? rd.segtab : rd.tab;
+  // one copy per segment of the agent's layout: every segment has its own offset
+  const int seg0 = rd.seg_off[agent], nseg = rd.seg_off[agent + 1] - seg0;
   for (int k = 0; k < nseg; ++k) {
-    const float* tab = tabs + (size_t)(seg0 + k) * (2 * kHalf);
+    const float* tab = rd.segtab + (size_t)(seg0 + k) * (2 * kHalf);
     uint16_t* dst = reinterpret_cast<uint16_t*>(at.qrot) + (row * at.max_seg + k) * kHeadDim;
     const float c = tab[lane], s = tab[kHalf + lane];
     // rotation by -delta: y_a = x_a cos + x_b sin, y_b = x_b cos - x_a sin
@@ -367,17 +494,14 @@ __global__ __launch_bounds__(kBlock) void tdk_attend_qrot_kernel(const RoundDev 
     dst[ib] = (uint16_t)(pack2(__builtin_fmaf(xb, c, -__fmul_rn(xa, s)), 0.f) & 0xffffu);
   }
   // the queries the listed pages meet: as they are, or turned back by the distance the stored values
-  // have moved since they were encoded
-  // (a segmented round whose stored diffs moved keeps one such copy per segment: diff_seg copies per row)
+  // have moved since they were encoded (then one such copy per segment: diff_seg copies per row)
   for (int k = 0; k < (at.diff_seg > 1 ? nseg : 1); ++k) {
     uint16_t* dst2 = reinterpret_cast<uint16_t*>(at.qdiff) + (row * at.diff_seg + k) * kHeadDim;
     uint16_t za = (uint16_t)(src[ia] ^ flip), zb = (uint16_t)(src[ib] ^ flip);
-    const float* td = nullptr;
-    if (!rd.seg && rd.agents[agent].diff_rot) td = rd.tab_diff + (size_t)agent * (2 * kHalf);
-    if (rd.seg && at.diff_seg > 1) td = rd.segtab_diff + (size_t)(seg0 + k) * (2 * kHalf);   // identity tables copy exactly
-    if (td) {
+    if (at.diff_seg > 1) {
+      const float* td = rd.segtab_diff + (size_t)(seg0 + k) * (2 * kHalf);   // identity tables copy exactly
       const float c2 = td[lane], s2 = td[kHalf + lane];
-      if (c2 != 1.f || s2 != 0.f || !rd.seg) {
+      if (c2 != 1.f || s2 != 0.f) {
         za = (uint16_t)(pack2(__builtin_fmaf(xa, c2, __fmul_rn(xb, s2)), 0.f) & 0xffffu);
         zb = (uint16_t)(pack2(__builtin_fmaf(xb, c2, -__fmul_rn(xa, s2)), 0.f) & 0xffffu);
       }
@@ -397,12 +521,11 @@ constexpr int kMasterLds = (kMasterKs + kMasterVs) * 2 + kRowsPerBlock * kMaskWo
 
 // One workgroup of the master pass: KV head h, chunk number `sc` = session * n_chunks + chunk, row block zb.
 // lds: kMasterLds bytes, 16-byte aligned.
-// QDIRECT (identity layouts only): the query rows are rotated back here, from the caller's q, instead of
-// being read from the copies the qrot kernel leaves (same arithmetic, so the same bits).
-template <bool SEG, bool QDIRECT = false>
+// Identity layouts: the query rows are rotated back here, from the caller's q.  SEG (per-agent block orders): they are
+// read from the copies that the qrot kernel leaves, one per segment.
+template <bool SEG>
 __device__ __forceinline__ void attend_master_body(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at,
                                                    unsigned char* lds, int h, int sc, int zb) {
-  static_assert(!(SEG && QDIRECT), "one rotation per row only");
   uint16_t* Ks = reinterpret_cast<uint16_t*>(lds);
   uint16_t* Vs = Ks + kMasterKs;
   uint64_t* s_mask = reinterpret_cast<uint64_t*>(Vs + kMasterVs);   // bit p: page p of this chunk is listed in the row's agent's diff
@@ -464,16 +587,7 @@ __device__ __forceinline__ void attend_master_body(const RoundDev& rd, const Lay
     seg_n = rd.seg_off[mine.agent + 1] - seg_base;
     while (seg_k + 1 < seg_n && rd.seg_src[seg_base + seg_k + 1] <= tok_begin) ++seg_k;
   }
-  if (!SEG && !QDIRECT) {
-    const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.qrot) + mine.out * kHeadDim);
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-      u32x4 v = {0, 0, 0, 0};
-      if (mine.agent >= 0) v = qp[2 * kk + hh];
-      qf[kk] = __builtin_bit_cast(bf16x8, v);
-    }
-  }
-  if (QDIRECT) {
+  if (!SEG) {
     // fragment kk of a lane = elements 16 kk + 8 hh .. + 7 of its row.  Rotation by -delta of the pair (a, b):
     // y_a = x_a cos + x_b sin, y_b = x_b cos - x_a sin, with pair j = (j, j + 64) or (2 j, 2 j + 1).
     u32x4 raw[8];
@@ -485,40 +599,7 @@ __device__ __forceinline__ void attend_master_body(const RoundDev& rd, const Lay
       if (mine.agent >= 0) v = qp[2 * kk + hh];
       raw[kk] = u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip};
     }
-    const float* tab = rd.tab + (size_t)(mine.agent >= 0 ? mine.agent : 0) * (2 * kHalf);
-    auto lo16 = [](uint32_t w) { return __uint_as_float(w << 16); };
-    auto hi16 = [](uint32_t w) { return __uint_as_float(w & 0xffff0000u); };
-    u32x4 rot[8];
-    if (!rd.interleaved) {
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {           // fragments kk (elements a) and kk + 4 (elements b = a + 64)
-        u32x4 ya, yb;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const int j = 16 * kk + 8 * hh + 2 * w;
-          const float c0 = tab[j], s0 = tab[kHalf + j], c1 = tab[j + 1], s1 = tab[kHalf + j + 1];
-          const float a0 = lo16(raw[kk][w]), a1 = hi16(raw[kk][w]), b0 = lo16(raw[kk + 4][w]), b1 = hi16(raw[kk + 4][w]);
-          ya[w] = pack2(__builtin_fmaf(a0, c0, __fmul_rn(b0, s0)), __builtin_fmaf(a1, c1, __fmul_rn(b1, s1)));
-          yb[w] = pack2(__builtin_fmaf(b0, c0, -__fmul_rn(a0, s0)), __builtin_fmaf(b1, c1, -__fmul_rn(a1, s1)));
-        }
-        rot[kk] = ya; rot[kk + 4] = yb;
-      }
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {           // word w of a fragment holds the pair j = 8 kk + 4 hh + w
-        u32x4 y;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const int j = 8 * kk + 4 * hh + w;
-          const float c = tab[j], sn = tab[kHalf + j];
-          const float a = lo16(raw[kk][w]), b = hi16(raw[kk][w]);
-          y[w] = pack2(__builtin_fmaf(a, c, __fmul_rn(b, sn)), __builtin_fmaf(b, c, -__fmul_rn(a, sn)));
-        }
-        rot[kk] = y;
-      }
-    }
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, rot[kk]);
+    turn_back32(raw, rd.tab + (size_t)(mine.agent >= 0 ? mine.agent : 0) * (2 * kHalf), rd.interleaved, hh, qf);
   }
   __syncthreads();
   const uint64_t* my_masks = s_mask + kMaskWords * (wave * kRowsPerWave + n);   // (read per step: two registers less)
@@ -650,13 +731,12 @@ __device__ __forceinline__ void attend_master_body(const RoundDev& rd, const Lay
   }
 }
 
-template <bool SEG>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void tdk_attend_master_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
                                                                    const AttendDev at, const int row_blocks) {
   __shared__ __attribute__((aligned(16))) unsigned char lds[kMasterLds];
   // one linear id (grid dimensions y and z stop at 65535): KV head fastest, then the row block, then the chunk
   const int h = blockIdx.x % rd.heads, rest = blockIdx.x / rd.heads;
-  attend_master_body<SEG>(rd, io, d, at, lds, h, rest / row_blocks, rest % row_blocks);
+  attend_master_body<true>(rd, io, d, at, lds, h, rest / row_blocks, rest % row_blocks);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -665,13 +745,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // listed tokens and has its own partial result, so there is nothing to combine inside the kernel; workgroups
 // whose piece lies past the end of the agent's list leave at once (the merge knows how many pieces an agent
 // has).  The K rows go straight from the payload into the MFMA operand registers, the V rows through one
-// row-major tile in LDS.  32 query rows at a time; more rows walk the piece again.
+// row-major tile in LDS.  32 query rows at a time.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPieceTiles = 16;                // 512 listed tokens per piece at most (small rounds use shorter pieces)
 
-// Vs: this wavefront's V tile, kTile * kVsStride bf16 elements; lane: 0..63.  QDIRECT (stored diffs not moved):
-// the listed pages meet the caller's rows as they are (but for the sign), no copies from the qrot kernel.
-template <bool SEGMOVED, bool QDIRECT = false>
+// Vs: this wavefront's V tile, kTile * kVsStride bf16 elements; lane: 0..63.
 __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const DiffDev& d, const AttendDev& at, uint16_t* Vs,
                                                    int h, int agent, int piece, int lane) {
   const int T = rd.page_tokens;
@@ -689,8 +767,6 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
   const int n = lane & 31, hh = lane >> 5;
   const int64_t row_e = (int64_t)rd.heads * kHeadDim, page_e = (int64_t)T * row_e;
   const uint16_t* pay = reinterpret_cast<const uint16_t*>(d.payload);
-  const int seg_base = SEGMOVED ? rd.seg_off[agent] : 0;
-  const int seg_n = SEGMOVED ? rd.seg_off[agent + 1] - seg_base : 1;
   // (offsets inside the agent's part of the payload fit 32 bits: at most 2 P pages of 64 KB or less)
   const uint16_t* apay = pay + lo * 2 * page_e;
   const uint32_t row_u = (uint32_t)row_e, page_u = (uint32_t)page_e, tile_u = (uint32_t)(kTile / T) * 2u * page_u;
@@ -704,19 +780,20 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
     const int qi = row_ok ? rem / at.group : 0, g = row_ok ? rem - qi * at.group : 0;
     const int64_t out = ((int64_t)agent * at.n_q + qi) * at.n_q_heads + h * at.group + g;
     bf16x8 qf[8];
-    auto load_q = [&](int k) {
-      const u32x4* qp = QDIRECT ? reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim)
-                                : reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.qdiff) +
-                                                                 (out * at.diff_seg + k) * kHeadDim);
-      const uint32_t flip = QDIRECT && at.q_flip ? 0x80008000u : 0u;
+    {
+      // the listed pages meet the caller's rows as they are, or turned back by the distance the stored values have moved
+      const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim);
+      const uint32_t flip = at.q_flip ? 0x80008000u : 0u;
+      u32x4 raw[8];
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         u32x4 v = {0, 0, 0, 0};
         if (row_ok) v = qp[2 * kk + hh];
-        qf[kk] = __builtin_bit_cast(bf16x8, u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip});
+        raw[kk] = u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip};
+        qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
       }
-    };
-    if (!SEGMOVED) load_q(0);
+      if (ad.diff_rot) turn_back32(raw, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, hh, qf);
+    }
     RowState rs;
     row_state_init(rs);
     // The next tile travels from the payload to registers while the current one is multiplied.  K: lane
@@ -749,15 +826,10 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
     for (int tile = tile_begin; tile < tile_end; ++tile) {
       wave_sync();                               // the previous tile has been consumed
       // bit t of valid: token t of the tile exists and lies inside the span (lanes 32..63 repeat lanes 0..31)
-      int seg_cur = 0;
       bool ok = false;
       {
         const int rr = (tile * kTile + n) % T, p = p_next;
-        if (p >= 0 && p < sd.pages && p * T + rr < sd.span) {
-          ok = true;
-          if (SEGMOVED)
-            while (seg_cur + 1 < seg_n && rd.seg_src[seg_base + seg_cur + 1] <= p * T + rr) ++seg_cur;
-        }
+        ok = p >= 0 && p < sd.pages && p * T + rr < sd.span;
       }
       const uint32_t valid = (uint32_t)__ballot(ok);
       if (valid != 0xffffffffu) {                // rows of tokens that do not count are staged as zeros
@@ -769,32 +841,7 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
 #pragma unroll
       for (int j = 0; j < 8; ++j) *reinterpret_cast<u32x4*>(Vs + (4 * j + st_row) * kVsStride + 8 * st_pc) = vreg[j];
       f32x16 sacc;
-      if (!SEGMOVED) {
-        scores32(kreg, qf, sacc);
-      } else {
-        // the tile's tokens come from up to four segments (two pages, two segments each), stored at
-        // different distances from today's positions: the scores are computed once per segment present,
-        // with the queries turned back by that segment's distance, and every token keeps its own
-        int sid[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sid[i] = __shfl(seg_cur, 8 * (i >> 2) + 4 * hh + (i & 3));
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
-        int done = -1;
-        while (true) {
-          int cand = (lane < kTile && ((valid >> lane) & 1u) && seg_cur > done) ? seg_cur : 0x7fffffff;
-#pragma unroll
-          for (int sft = 32; sft > 0; sft >>= 1) cand = min(cand, __shfl_xor(cand, sft));
-          if (cand == 0x7fffffff) break;
-          load_q(cand);
-          f32x16 pacc;
-          scores32(kreg, qf, pacc);
-#pragma unroll
-          for (int i = 0; i < 16; ++i)
-            if (sid[i] == cand) sacc[i] = pacc[i];
-          done = cand;
-        }
-      }
+      scores32(kreg, qf, sacc);
       wave_sync();                               // the V tile is complete
       if (tile + 1 < tile_end) fetch(tile + 1);  // the K registers are free: the scores are taken
       // score i of a lane belongs to token 8 (i / 4) + 4 hh + i % 4: four nibbles of `valid`
@@ -821,19 +868,10 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
 }
 
 // the pieces z, z + piece_grid, ... of one list, until one lies past its end
-template <bool SEGMOVED, bool QDIRECT = false>
 __device__ __forceinline__ void attend_diff32_body(const RoundDev& rd, const DiffDev& d, const AttendDev& at, uint16_t* Vs,
                                                    int h, int agent, int piece0, int lane) {
   for (int piece = piece0; piece < at.n_pieces; piece += at.piece_grid)
-    if (!attend_diff32_piece<SEGMOVED, QDIRECT>(rd, d, at, Vs, h, agent, piece, lane)) break;
-}
-
-template <bool SEGMOVED>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void tdk_attend_diff_kernel(const RoundDev rd, const DiffDev d, const AttendDev at) {
-  __shared__ __attribute__((aligned(16))) uint16_t Vs[kTile * kVsStride];
-  // one linear id: KV head fastest, then the agent, then the wavefront's number among those of its list
-  const int h = blockIdx.x % rd.heads, rest = blockIdx.x / rd.heads;
-  attend_diff32_body<SEGMOVED>(rd, d, at, Vs, h, rest % rd.n_agents, rest / rd.n_agents, threadIdx.x);
+    if (!attend_diff32_piece(rd, d, at, Vs, h, agent, piece, lane)) break;
 }
 
 // The same pass with 16 query rows per wavefront: used when an agent brings at most 16 rows per KV head
@@ -866,7 +904,8 @@ __device__ __forceinline__ bool attend_diff16_piece(const RoundDev& rd, const Di
   const int64_t out = ((int64_t)agent * at.n_q + qi) * at.n_q_heads + h * at.group + g;
   bf16x8 qf[4];
   auto load_q = [&](int k) {
-    // QDIRECT (stored diffs not moved): the listed pages meet the caller's rows as they are (but for the sign)
+    // QDIRECT (identity layouts): the listed pages meet the caller's rows as they are (but for the sign), or turned back
+    // by the distance the stored values have moved
     const u32x4* qp = QDIRECT ? reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim)
                               : reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.qdiff) +
                                                                (out * at.diff_seg + k) * kHeadDim);
@@ -877,6 +916,7 @@ __device__ __forceinline__ bool attend_diff16_piece(const RoundDev& rd, const Di
       if (row_ok) v = qp[4 * kk + g4];
       qf[kk] = __builtin_bit_cast(bf16x8, u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip});
     }
+    if (QDIRECT && ad.diff_rot) turn_back16(qf, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, g4);
   };
   if (!SEGMOVED) load_q(0);
   const int seg_base = SEGMOVED ? rd.seg_off[agent] : 0;
@@ -1007,8 +1047,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   attend_diff16_body<SEGMOVED>(rd, d, at, Vs, h, rest % rd.n_agents, rest / rd.n_agents, threadIdx.x);
 }
 
-// Both passes in one launch, for rounds with identity layouts whose stored diffs have not moved and few query
-// rows per agent: one ramp and one drain instead of two, and the listed-pages pass (bound by HBM) streams while
+// Both passes in one launch, for rounds with identity layouts and few query rows per agent: one ramp and one drain instead of two, and the listed-pages pass (bound by HBM) streams while
 // the master pass (bound by arithmetic and LDS latency) computes.  A workgroup of the listed-pages kind = four
 // wavefronts = four KV heads of one agent's piece; the pieces past 0, most of which leave at once, come last.
 // Where the kinds run (measured with clock stamps and the hardware ids of the compute units): the device deals
@@ -1049,15 +1088,572 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int h = m_id % rd.heads, rest = m_id / rd.heads;
     // the row blocks of one (chunk, KV head) get ids 8 apart: same XCD, one after the other, so the second
     // finds the tiles in that XCD's L2
-    attend_master_body<false, true>(rd, io, d, at, lds, h, rest / fg.row_blocks, rest % fg.row_blocks);
+    attend_master_body<false>(rd, io, d, at, lds, h, rest / fg.row_blocks, rest % fg.row_blocks);
   } else {
     const int piece = d_id / fg.n_diff0, rem = d_id - piece * fg.n_diff0;
     const int agent = rem / fg.head_groups, h = (rem - agent * fg.head_groups) * kWaves + (threadIdx.x >> 6);
     if (h >= rd.heads) return;
     uint16_t* Vs = reinterpret_cast<uint16_t*>(lds) + (threadIdx.x >> 6) * (kTile * kVsStride);
-    if (ROWS32) attend_diff32_body<false, true>(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
+    if (ROWS32) attend_diff32_body(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
     else attend_diff16_body<false, true>(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
   }
+}
+
+// ---------------------------------------------------------------------------------------------
+// One agent per wavefront: attention of rounds whose agents bring enough query rows of their own (prefill, and
+// every round with per-agent block orders).  A wavefront owns 32 query rows of ONE agent and KV head and
+// walks the span in 64-token steps; the four wavefronts of a workgroup share the master's K and V tiles in LDS,
+// whatever agents they belong to.  Because the rows of a wavefront have one agent, everything that depends on
+// the agent is uniform: the pages its diff lists (a bit mask in LDS; most steps have none and skip the masking),
+// the segment of its layout (one reload of the query fragments per border).  The same wavefront then adds the
+// listed pages from the payload to the same accumulators, so a span that is not split needs no partial results
+// and no merge.
+// The steps are software-pipelined: the score products of step i + 1 stand beside the exponentials of step i
+// in one basic block (the matrix cores and the vector units then work at the same time within a wavefront),
+// the K and V tiles are double-buffered with one barrier per step, and the rows of the tiles after that travel
+// to registers meanwhile.
+// What bounds it (25 agents x 64 query tokens x 40 heads over 5000 tokens, 2 wavefronts per SIMD, counters): matrix
+// cores busy 46 %, vector units 42 %, LDS 47 % of the time, about 1 us per wavefront and step; no single pipe is
+// full, the rest is waiting between dependent stages (score products, maxima, exponentials, second products) and at the
+// barrier.  64 rows per wavefront (half the LDS bytes per product, one wavefront per SIMD) measured the same.
+// Measured against rows of all agents in one block plus separate listed-pages and merge launches: 64 query tokens
+// per agent 462 -> 206 us, 16 tokens 140 -> 93 us, 8 tokens 94 -> 70 us.
+// ---------------------------------------------------------------------------------------------
+constexpr int kRowsMaskWords = 32;                        // 32-bit words of a wavefront's page mask
+constexpr int kRowsMaxPages = 32 * kRowsMaskWords;        // pages per chunk
+constexpr int kRowsMaxTokens = 16 * kRowsMaxPages;        // tokens per chunk
+
+struct RowsGrid {
+  int32_t blocks;       // workgroups (four wavefronts) per (session, KV head, chunk), for the largest session
+  int32_t per_agent;    // wavefronts per agent and KV head
+  int32_t direct;       // the span is one chunk: write out / lse here instead of partial results
+};
+
+struct RowsShared {
+  uint16_t k[2][kBigTile * kKsStride];
+  uint16_t v[2][kBigTile * kVsStride];
+  uint32_t border[kRowsMaxTokens / 32];                   // bit t: a segment of some agent begins at token t of the chunk
+  float tab[kWaves][2 * kHalf];                           // rotation table of the query rows being loaded
+  uint32_t mask[kWaves][kRowsMaskWords];                  // bit p: page p of the chunk is listed in the wavefront's agent's diff
+};
+static_assert(kWaves * kTile * (kKsStride + kVsStride) * 2 <= sizeof(RowsShared::k) + sizeof(RowsShared::v),
+              "the listed pages' tiles reuse the memory of the master's");
+
+// maximum of a value over the lane pair (n, n + 32)
+__device__ __forceinline__ float pair_max(float v) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <int NT>
+__device__ __forceinline__ void rows_max(const f32x16 (&s)[NT], float& mx) {
+  mx = s[0][0];
+#pragma unroll
+  for (int i = 1; i < 16 * NT - 1; i += 2)
+    mx = __builtin_elementwise_maximum(mx, __builtin_elementwise_maximum(s[i >> 4][i & 15], s[(i + 1) >> 4][(i + 1) & 15]));
+  mx = __builtin_elementwise_maximum(mx, s[NT - 1][15]);
+}
+
+// mx: each lane's maximum of the masked scores to come (unscaled).  A row's reference point moves when the
+// maximum has outgrown it by more than 8.
+__device__ __forceinline__ void rows_settle(float mx, float scale, RowState& st) {
+  constexpr float kLazy = 8.f;
+  const float m = pair_max(mx) * scale;
+  if (__any(m > st.m_run + kLazy || (st.m_run == -INFINITY && m != -INFINITY))) {
+    const float m_new = m > st.m_run + kLazy || st.m_run == -INFINITY ? fmaxf(st.m_run, m) : st.m_run;
+    const float alpha = __expf(st.m_run - (m_new == -INFINITY ? 0.f : m_new));     // 1 for the rows whose reference stays
+    st.l_run *= alpha;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) st.oacc[q][i] *= alpha;
+    st.m_run = m_new;
+  }
+}
+
+// NT tiles of 32 tokens: weights from the settled scores, sums, and O^T += V^T P^T (see pv_tr for the operands).
+template <int NT>
+__device__ __forceinline__ void rows_weights_pv(const uint16_t* Vs, const f32x16 (&s)[NT], float scale, int lane, RowState& st) {
+  constexpr float kLog2e = 1.4426950408889634f;
+  const float c2 = scale * kLog2e;
+  const float m2 = -(st.m_run == -INFINITY ? 0.f : st.m_run) * kLog2e;
+  const int i16 = lane & 15, blk = lane >> 4;
+  const uint16_t* base = Vs + (4 * (blk >> 1) + (i16 >> 2)) * kVsStride + 16 * (blk & 1) + 4 * (i16 & 3);
+#pragma unroll
+  for (int kk = 0; kk < 2 * NT; ++kk) {
+    float p[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kk >> 1][8 * (kk & 1) + j], c2, m2));
+      st.l_run += p[j];
+    }
+    u32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = pack2(p[2 * e], p[2 * e + 1]);
+    const bf16x8 pb = __builtin_bit_cast(bf16x8, w);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + (16 * kk) * kVsStride + 32 * q));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + (16 * kk + 8) * kVsStride + 32 * q));
+      const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+      const bf16x8 va = __builtin_bit_cast(bf16x8, u32x4{l2.x, l2.y, h2.x, h2.y});
+      st.oacc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb, st.oacc[q], 0, 0, 0);
+    }
+  }
+}
+
+__device__ __forceinline__ void rows_scores(const uint16_t* Ks, const bf16x8 (&qf)[8], int n, int hh, f32x16 (&s)[2]) {
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[t][i] = 0.f;
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(Ks + (kTile * t + n) * kKsStride + 16 * kk + 8 * hh));
+      s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], s[t], 0, 0, 0);
+    }
+}
+
+// One pipelined step: the score products of the next step's K tile (16 operands of 32 tokens x 16 elements), the
+// weights of this step's scores, and the products of this step's V tile (16 operands of 32 elements x 16 tokens).
+// The order is written down slot by slot, because a wavefront only keeps the matrix cores and the vector units
+// busy together if their instructions alternate: a slot is the product(s) of one operand, the LDS read of the
+// operand four slots ahead, and a few weights (scale and reference point in one fma, exp2, sum, packing), spread so
+// that a slot's vector work takes about as long as its products; the maxima of the new scores stand in the last
+// slots.  nx: the raw scores of the next step, mx: their maxima; s is used up.
+__device__ __forceinline__ void rows_step(const uint16_t* Ks, const uint16_t* Vs, const bf16x8 (&qf)[8], f32x16 (&s)[2],
+                                          f32x16 (&nx)[2], float& mx, float scale, int lane, RowState& st) {
+  constexpr float kLog2e = 1.4426950408889634f;
+  constexpr int kAhead = 4;
+  const int n = lane & 31, hh = lane >> 5, i16 = lane & 15, blk = lane >> 4;
+  const float c2 = scale * kLog2e;
+  const float m2 = -(st.m_run == -INFINITY ? 0.f : st.m_run) * kLog2e;
+  const uint16_t* kb = Ks + n * kKsStride + 8 * hh;
+  const uint16_t* vb = Vs + (4 * (blk >> 1) + (i16 >> 2)) * kVsStride + 16 * (blk & 1) + 4 * (i16 & 3);
+  auto k_op = [&](int j) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kb + (j & 1) * kTile * kKsStride + 16 * (j >> 1)));
+  };
+  auto v_op = [&](int j) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vb + 16 * (j >> 2) * kVsStride + 32 * (j & 3)));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vb + (16 * (j >> 2) + 8) * kVsStride + 32 * (j & 3)));
+    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+    return __builtin_bit_cast(bf16x8, u32x4{l2.x, l2.y, h2.x, h2.y});
+  };
+  // weight number w, in the order the second products need them: 16 tokens at a time
+  uint32_t pw[4][4];
+  auto weight = [&](int w) {
+    const int kk = w / 8, j = w % 8, t = kk >> 1, e = 8 * (kk & 1) + j;
+    s[t][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c2, m2));
+    st.l_run += s[t][e];
+    if (j & 1) pw[kk][j >> 1] = pack2(s[t][e - 1], s[t][e]);
+  };
+  // weights before the first product (while its operands arrive), per slot of the first and of the second products;
+  // the eight weights of 16 tokens must stand before the four slots that use them
+  constexpr int kWeights = 32, kPre = 4, kFirst = 1, kSecond = 2;
+  static_assert(kPre + 16 * kFirst >= 8 && kPre + 16 * kFirst + 4 * kSecond >= 16 && kPre + 16 * kFirst + 8 * kSecond >= 24 &&
+                kPre + 16 * kFirst + 12 * kSecond >= 32, "weights stand before their products");
+  bf16x8 ka[kAhead], va[kAhead];
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) ka[j] = k_op(j);
+#pragma unroll
+  for (int w = 0; w < kPre; ++w) weight(w);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    f32x16 c;
+    if (j < 2) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) c[i] = 0.f;
+    } else {
+      c = nx[j & 1];
+    }
+    nx[j & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[j % kAhead], qf[j >> 1], c, 0, 0, 0);
+    if (j + kAhead < 16) ka[j % kAhead] = k_op(j + kAhead);
+    else va[j % kAhead] = v_op(j + kAhead - 16);
+#pragma unroll
+    for (int w = 0; w < kFirst; ++w)
+      if (kPre + kFirst * j + w < kWeights) weight(kPre + kFirst * j + w);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  mx = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) {
+    const bf16x8 pb = __builtin_bit_cast(bf16x8, u32x4{pw[j >> 2][0], pw[j >> 2][1], pw[j >> 2][2], pw[j >> 2][3]});
+    st.oacc[j & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[j % kAhead], pb, st.oacc[j & 3], 0, 0, 0);
+    if (j + kAhead < 16) va[j % kAhead] = v_op(j + kAhead);
+#pragma unroll
+    for (int w = 0; w < kSecond; ++w)
+      if (kPre + 16 * kFirst + kSecond * j + w < kWeights) weight(kPre + 16 * kFirst + kSecond * j + w);
+    if (j >= 8) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int i = 4 * (j - 8) + 2 * q;
+        mx = __builtin_elementwise_maximum(mx, __builtin_elementwise_maximum(nx[i >> 4][i & 15], nx[i >> 4][(i & 15) + 1]));
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// The pages d.idx[l0 .. l1) of the agent's list, 32 tokens at a time, from the payload, through K and V tiles that
+// only this wavefront uses (kListedLds bytes).  The payload address of a listed token depends on its place in the list
+// alone, so the next tile travels to registers while this one is multiplied.  load_q(k) loads the query
+// fragments for tokens of segment k (SEGMOVED; otherwise called once with 0).
+constexpr int kListedLds = kTile * (kKsStride + kVsStride) * 2;
+
+template <bool SEGMOVED, class LoadQ>
+__device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d, const AttendDev& at, const SessionDev& sd, uint16_t* lds,
+                                            int h, int seg_base, int seg_n, int64_t l0, int n_pages, int lane, bf16x8 (&qf)[8],
+                                            LoadQ load_q, RowState& st) {
+  if (n_pages <= 0) return;
+  uint16_t* Ks = lds;
+  uint16_t* Vs = lds + kTile * kKsStride;
+  const int T = rd.page_tokens, lg = T == 16 ? 4 : 5, n = lane & 31, hh = lane >> 5, st_row = lane >> 4, st_pc = lane & 15;
+  const int n_tok = n_pages * T;
+  // (offsets inside the chunk's part of the payload fit 32 bits: at most 2 x 1024 pages of 64 KB or less)
+  const u32x4* pay = d.payload + (l0 * 2 * T * rd.heads + h) * 16 + st_pc;
+  const uint32_t row_u = (uint32_t)rd.heads * 16u, page_u = (uint32_t)T * row_u;
+  u32x4 kreg[8], vreg[8];
+  int p_next = -1;
+  auto fetch = [&](int t0) __attribute__((always_inline)) {      // (a token past the list's end reads the last one: no branch around the loads)
+    p_next = t0 + n < n_tok ? d.idx[l0 + ((t0 + n) >> lg)] : -1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int t = min(t0 + 4 * j + st_row, n_tok - 1);
+      const u32x4* p = pay + (uint32_t)(t >> lg) * 2u * page_u + (uint32_t)(t & (T - 1)) * row_u;
+      kreg[j] = p[0];
+      vreg[j] = p[page_u];
+    }
+  };
+  fetch(0);
+  if (!SEGMOVED) load_q(0);
+  for (int t0 = 0; t0 < n_tok; t0 += kTile) {
+    wave_sync();                                 // the previous tile has been consumed
+    int seg_cur = 0;
+    bool ok = false;
+    {
+      const int m = (p_next << lg) + ((t0 + n) & (T - 1));
+      if (p_next >= 0 && p_next < sd.pages && m < sd.span) {
+        ok = true;
+        if (SEGMOVED)
+          while (seg_cur + 1 < seg_n && rd.seg_src[seg_base + seg_cur + 1] <= m) ++seg_cur;
+      }
+    }
+    const uint32_t valid = (uint32_t)__ballot(ok);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      u32x4 v = vreg[j];
+      if (!((valid >> (4 * j + st_row)) & 1u)) v = u32x4{0, 0, 0, 0};      // rows of tokens that do not count
+      *reinterpret_cast<u32x4*>(Ks + (4 * j + st_row) * kKsStride + 8 * st_pc) = kreg[j];
+      *reinterpret_cast<u32x4*>(Vs + (4 * j + st_row) * kVsStride + 8 * st_pc) = v;
+    }
+    wave_sync();                                 // the tile is complete
+    if (t0 + kTile < n_tok) fetch(t0 + kTile);
+    f32x16 s[1];
+    auto scores = [&](f32x16 (&x)[1]) __attribute__((always_inline)) {
+      f32x16 y;                                  // two chains of products
+#pragma unroll
+      for (int i = 0; i < 16; ++i) { x[0][i] = 0.f; y[i] = 0.f; }
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(Ks + n * kKsStride + 16 * kk + 8 * hh));
+        if (kk & 1) y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], y, 0, 0, 0);
+        else x[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], x[0], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 16; ++i) x[0][i] += y[i];
+    };
+    if (!SEGMOVED) {
+      scores(s);
+    } else {
+      // tokens of several segments, stored at different distances from today's positions: scores once per
+      // segment present, with the queries turned back by that distance, and every token keeps its own
+      int sid[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sid[i] = __shfl(seg_cur, 8 * (i >> 2) + 4 * hh + (i & 3));
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[0][i] = 0.f;
+      int done = -1;
+      while (true) {
+        int cand = (lane < kTile && ((valid >> lane) & 1u) && seg_cur > done) ? seg_cur : 0x7fffffff;
+#pragma unroll
+        for (int sft = 32; sft > 0; sft >>= 1) cand = min(cand, __shfl_xor(cand, sft));
+        cand = __builtin_amdgcn_readfirstlane(cand);
+        if (cand == 0x7fffffff) break;
+        load_q(cand);
+        f32x16 x[1];
+        scores(x);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (sid[i] == cand) s[0][i] = x[0][i];
+        done = cand;
+      }
+    }
+    if (valid != 0xffffffffu) {
+      const uint32_t vs = valid >> (4 * hh);     // score i of a lane belongs to token 8 (i / 4) + 4 hh + i % 4
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (!((vs >> (8 * (i >> 2) + (i & 3))) & 1u)) s[0][i] = -INFINITY;
+    }
+    float mx;
+    rows_max<1>(s, mx);
+    rows_settle(mx, at.scale, st);
+    rows_weights_pv<1>(Vs, s, at.scale, lane, st);
+  }
+  wave_sync();
+}
+
+template <bool SEG, bool MOVED>   // MOVED (SEG only): some segment's stored diff sits at other positions
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev d, const AttendDev at, const RowsGrid rg) {
+  __shared__ __attribute__((aligned(16))) RowsShared sh;
+  const int h = blockIdx.x % rd.heads, rest = blockIdx.x / rd.heads;
+  const int wb = rest % rg.blocks, sc = rest / rg.blocks;
+  const int n_ch = max(at.n_chunks, 1);
+  const int session = sc / n_ch, chunk = sc - session * n_ch;
+  const SessionDev sd = rd.sess[session];
+  if (wb * kWaves >= sd.n_agents * rg.per_agent) return;
+  const int T = rd.page_tokens;
+  const int tok_begin = chunk * at.chunk_tokens;
+  if (tok_begin >= sd.span && !(rg.direct && sd.span == 0)) return;
+  const int tok_end = min(sd.span, tok_begin + at.chunk_tokens);
+  const int lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int a_local = (wb * kWaves + wave) / rg.per_agent;
+  const int r0 = (wb * kWaves + wave - a_local * rg.per_agent) * kRowsPerWave;
+  const bool active = a_local < sd.n_agents;            // (a wavefront without rows only helps to stage the tiles)
+  const int agent = active ? __builtin_amdgcn_readfirstlane(rd.order[sd.order_begin + a_local]) : 0;
+  const int per_agent_rows = at.n_q * at.group;
+
+  // this lane's query row
+  const bool row_ok = active && r0 + n < per_agent_rows;
+  const int rr = row_ok ? r0 + n : 0, qi = rr / at.group;
+  const int64_t out = ((int64_t)agent * at.n_q + qi) * at.n_q_heads + h * at.group + (rr - qi * at.group);
+  bf16x8 qf[8];
+  auto load_q = [&](const float* tab) __attribute__((always_inline)) {      // tab: turn the rows back by this rotation (NULL: as they are)
+    load_queries(at, rd.interleaved, out, row_ok, tab, sh.tab[wave], lane, qf);
+  };
+  int seg_base = 0, seg_n = 1, seg_k = 0;
+  if (SEG && active) {
+    seg_base = __builtin_amdgcn_readfirstlane(rd.seg_off[agent]);
+    seg_n = __builtin_amdgcn_readfirstlane(rd.seg_off[agent + 1]) - seg_base;
+  }
+
+  RowState st;
+  row_state_init(st);
+
+  // the part of the agent's list that falls into this chunk, and its page mask
+  int64_t l0 = 0, l1 = 0;
+  const int pg0 = tok_begin / T;
+  if (active && tok_end > tok_begin) {
+    int64_t lo = d.offset[agent], hi = lo + d.count[agent];
+    if (lo < 0) lo = 0;
+    if (hi > d.capacity) hi = d.capacity;
+    auto first_at = [&](int page) {                     // first entry >= page
+      int64_t a = lo, b = hi;
+      while (a < b) {
+        const int64_t mid = (a + b) >> 1;
+        if (d.idx[mid] < page) a = mid + 1; else b = mid;
+      }
+      return a;
+    };
+    l0 = first_at(pg0);
+    l1 = first_at((tok_end - 1) / T + 1);
+    if (l1 - l0 > kRowsMaxPages) l1 = l0 + kRowsMaxPages;                      // (a list this round did not produce)
+    if (lane < kRowsMaskWords) sh.mask[wave][lane] = 0u;
+    wave_sync();
+    for (int64_t a = l0 + lane; a < l1; a += 64) {
+      const int rel = d.idx[a] - pg0;
+      if (rel >= 0 && rel < kRowsMaxPages) atomicOr(&sh.mask[wave][rel >> 5], 1u << (rel & 31));
+    }
+    wave_sync();
+  }
+
+  // ---- the master's tokens ----
+  const int st_tok = threadIdx.x >> 4, st_pc = threadIdx.x & 15;
+  const int lg = T == 16 ? 4 : 5;
+  const uint32_t row_bytes = (uint32_t)rd.heads * 256u;
+  uint32_t voff[4];                                      // this thread's four rows of a whole tile
+#pragma unroll
+  for (int e = 0; e < 4; ++e) voff[e] = (uint32_t)(16 * e + st_tok) * row_bytes + 16u * st_pc;
+  u32x4 kreg[4], vreg[4];
+  auto put_k = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.k[buf] + (16 * e + st_tok) * kKsStride + 8 * st_pc) = kreg[e];
+  };
+  auto put_v = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.v[buf] + (16 * e + st_tok) * kVsStride + 8 * st_pc) = vreg[e];
+  };
+  // A step takes 64 tokens, or, with per-agent block orders, fewer: up to the next place where some wavefront of the
+  // workgroup enters another segment (agents of one session mostly have their borders in the same places), so
+  // that a step always lies in one segment of every agent.  Those places are the bits of sh.border.
+  if (SEG) {
+    for (int i = threadIdx.x; i < kRowsMaxTokens / 32; i += kBlock) sh.border[i] = 0u;
+    __syncthreads();
+    if (active)
+      for (int k = lane + 1; k < seg_n; k += 64) {
+        const int rel = rd.seg_src[seg_base + k] - tok_begin;
+        if (rel > 0 && rel < tok_end - tok_begin) atomicOr(&sh.border[rel >> 5], 1u << (rel & 31));
+      }
+    __syncthreads();
+  }
+  auto step_end = [&](int p) __attribute__((always_inline)) {            // where the step that begins at token p ends
+    int len = kBigTile;
+    if (SEG) {
+      const int rel = p + 1 - tok_begin, w = rel >> 5;
+      uint32_t x[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) x[q] = __builtin_amdgcn_readfirstlane(sh.border[min(w + q, kRowsMaxTokens / 32 - 1)]);
+      const uint64_t lo = ((uint64_t)x[1] << 32) | x[0], hi = x[2];
+      const uint64_t window = rel & 31 ? (lo >> (rel & 31)) | (hi << (64 - (rel & 31))) : lo;           // bit q: a border at p + 1 + q
+      if (window) len = min(kBigTile, __builtin_ctzll(window) + 1);
+    }
+    return min(p + len, tok_end);
+  };
+  const char* mk = reinterpret_cast<const char*>(io.master_k) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
+  const char* mv = reinterpret_cast<const char*>(io.master_v) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
+  // the tile of the step that begins at token p (rows behind the step belong to others or repeat the last token of
+  // the chunk; their scores are masked)
+  auto fetch = [&](const char* base, int p, u32x4 (&r)[4]) __attribute__((always_inline)) {
+    const int at_tok = min(p, tok_end - 1), left = tok_end - 1 - at_tok;
+    const char* tile = base + (int64_t)(at_tok - tok_begin) * row_bytes;
+    uint32_t off[4] = {voff[0], voff[1], voff[2], voff[3]};
+    if (left < kBigTile - 1)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) off[e] = (uint32_t)min(16 * e + st_tok, left) * row_bytes + 16u * st_pc;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = *reinterpret_cast<const u32x4*>(tile + off[e]);
+  };
+  // the two words of the page mask that hold a step's pages (read early, used by mask_scores)
+  auto mask_words = [&](int p) __attribute__((always_inline)) {
+    const int pg = (p - tok_begin) >> lg;
+    return make_uint2(sh.mask[wave][min(pg >> 5, kRowsMaskWords - 1)], sh.mask[wave][min((pg >> 5) + 1, kRowsMaskWords - 1)]);
+  };
+  // Masks the scores of the step [p, end): listed pages and tokens behind its end.  Few steps need it; those get
+  // their maxima again.
+  auto mask_scores = [&](int p, int end, uint2 words, f32x16 (&s)[2], float& mx) __attribute__((always_inline)) {
+    const int rel = p - tok_begin, pg = rel >> lg, n_pages = ((rel + kBigTile - 1) >> lg) - pg + 1;
+    const uint64_t both = ((uint64_t)__builtin_amdgcn_readfirstlane(words.y) << 32) | (uint32_t)__builtin_amdgcn_readfirstlane(words.x);
+    const uint32_t listed = (uint32_t)(both >> (pg & 31)) & ((1u << n_pages) - 1u);      // bit q: page pg + q is listed (at most five pages)
+    const int left = end - p;                            // tokens of this step
+    if (listed == 0u && left >= kBigTile) return;
+    uint64_t dead = left < kBigTile ? ~0ull << left : 0ull;                              // bit t: token t of the step does not count
+    const uint64_t page_bits = T == 16 ? 0xffffull : 0xffffffffull;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+      const int at_tok = (q << lg) - (rel & (T - 1));
+      if (((listed >> q) & 1u) && at_tok < kBigTile) dead |= at_tok >= 0 ? page_bits << at_tok : page_bits >> -at_tok;
+    }
+    const uint32_t d0 = (uint32_t)dead >> (4 * hh), d1 = (uint32_t)(dead >> 32) >> (4 * hh);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if ((d0 >> (8 * (e >> 2) + (e & 3))) & 1u) s[0][e] = -INFINITY;
+      if ((d1 >> (8 * (e >> 2) + (e & 3))) & 1u) s[1][e] = -INFINITY;
+    }
+    rows_max<2>(s, mx);
+  };
+  // this wavefront's segment at token p, and its query fragments
+  int seg_next = 0;                                      // where the next segment begins (0: nothing loaded yet)
+  auto enter = [&](int p) __attribute__((always_inline)) {
+    if (p < seg_next) return;
+    auto src = [&](int k) __attribute__((always_inline)) { return k < seg_n ? __builtin_amdgcn_readfirstlane(rd.seg_src[seg_base + k]) : 0x7fffffff; };
+    while (src(seg_k + 1) <= p) ++seg_k;
+    seg_next = src(seg_k + 1);
+    load_q(rd.segtab + (size_t)(seg_base + seg_k) * (2 * kHalf));
+  };
+  if (tok_end > tok_begin) {
+    f32x16 s0[2], s1[2];
+    // starts of the next step, of the one after it and of the third
+    int p1 = tok_begin, p2 = step_end(p1), p3 = step_end(p2);
+    fetch(mk, p1, kreg);
+    fetch(mv, p1, vreg);
+    put_k(0);
+    put_v(0);
+    fetch(mk, p2, kreg);
+    if (active) {
+      if (SEG) enter(p1);
+      else load_q(rd.tab + (size_t)agent * (2 * kHalf));
+    }
+    put_k(1);
+    __syncthreads();
+    if (active) {
+      float mx;
+      rows_scores(sh.k[0], qf, n, hh, s0);
+      rows_max<2>(s0, mx);
+      mask_scores(p1, p2, mask_words(p1), s0, mx);
+      rows_settle(mx, at.scale, st);
+    }
+    __syncthreads();                                     // the first step replaces its K tile
+    // the weights and second products of the step whose scores are s (buffers `odd`), and the scores of the next one
+    auto step = [&](int odd, f32x16 (&s)[2], f32x16 (&nx)[2]) __attribute__((always_inline)) {
+      if (SEG && active && p2 < tok_end) enter(p2);
+      fetch(mk, p3, kreg);                               // the tiles after that travel to registers meanwhile
+      fetch(mv, p2, vreg);
+      uint2 words = make_uint2(0u, 0u);
+      float mx;
+      if (active) {
+        words = mask_words(p2);
+        rows_step(sh.k[odd ^ 1], sh.v[odd], qf, s, nx, mx, at.scale, lane, st);      // (past the last step: scores that are not used)
+      }
+      put_k(odd);                                        // (nobody reads these two buffers in this step)
+      put_v(odd ^ 1);
+      if (active && p2 < tok_end) {
+        mask_scores(p2, p3, words, nx, mx);
+        rows_settle(mx, at.scale, st);
+      }
+      p1 = p2; p2 = p3; p3 = step_end(p3);
+      __syncthreads();
+    };
+    if (SEG) {
+      // (one copy of the step: two of them next to the reloads of the queries cost registers that spill; 83 -> 71 us)
+      for (int odd = 0; p1 < tok_end; odd ^= 1) {
+        step(odd, s0, s1);
+        s0[0] = s1[0];
+        s0[1] = s1[1];
+      }
+    } else {
+      while (p1 < tok_end) {
+        step(0, s0, s1);
+        if (p1 < tok_end) step(1, s1, s0);
+      }
+    }
+  }
+
+  // ---- the listed pages, from the payload ----
+  if (active) {
+    uint16_t* lds = reinterpret_cast<uint16_t*>(&sh) + wave * (kListedLds / 2);
+    if (SEG && MOVED) {
+      rows_listed<true>(rd, d, at, sd, lds, h, seg_base, seg_n, l0, (int)(l1 - l0), lane, qf,
+                            [&](int k) __attribute__((always_inline)) { load_q(rd.segtab_diff + (size_t)(seg_base + k) * (2 * kHalf)); }, st);
+    } else {
+      rows_listed<false>(rd, d, at, sd, lds, h, seg_base, seg_n, l0, (int)(l1 - l0), lane, qf,
+                             [&](int) __attribute__((always_inline)) { load_q(!SEG && rd.agents[agent].diff_rot != 0 ? rd.tab_diff + (size_t)agent * (2 * kHalf) : nullptr); }, st);
+    }
+  }
+
+  // lane (n, hh) holds elements 32 q + 8 j + 4 hh + (0..3) of row n
+  const float l_tot = st.l_run + __shfl_xor(st.l_run, 32);
+  if (!row_ok) return;
+  float4* po;
+  float f = 1.f;
+  if (rg.direct) {
+    po = reinterpret_cast<float4*>(at.out + out * kHeadDim);
+    f = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    if (hh == 0) at.lse[out] = l_tot > 0.f ? st.m_run + __logf(l_tot) : -INFINITY;
+  } else {
+    const int64_t slot = out * at.n_parts + chunk;
+    po = reinterpret_cast<float4*>(at.part_o + slot * kHeadDim);
+    if (hh == 0) { at.part_m[slot] = st.m_run; at.part_l[slot] = l_tot; }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      po[(32 * q + 8 * j + 4 * hh) >> 2] = make_float4(st.oacc[q][4 * j] * f, st.oacc[q][4 * j + 1] * f,
+                                                       st.oacc[q][4 * j + 2] * f, st.oacc[q][4 * j + 3] * f);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1146,8 +1742,7 @@ hipError_t launch_attend_master(const RoundDev& rd, const LayerDev& io, const Di
   const int64_t blocks = (int64_t)rd.heads * row_blocks * rd.n_sessions * at.n_chunks;
   if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)blocks);
-  if (rd.seg) hipLaunchKernelGGL(tdk_attend_master_kernel<true>, grid, dim3(kBlock), 0, st, rd, io, d, at, row_blocks);
-  else hipLaunchKernelGGL(tdk_attend_master_kernel<false>, grid, dim3(kBlock), 0, st, rd, io, d, at, row_blocks);
+  hipLaunchKernelGGL(tdk_attend_master_kernel, grid, dim3(kBlock), 0, st, rd, io, d, at, row_blocks);
   return hipGetLastError();
 }
 
@@ -1157,13 +1752,8 @@ hipError_t launch_attend_diff(const RoundDev& rd, const DiffDev& d, const Attend
   const int64_t blocks = (int64_t)rd.heads * rd.n_agents * at.piece_grid;
   if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)blocks);
-  if (at.n_q * at.group <= 16) {
-    if (at.diff_seg > 1) hipLaunchKernelGGL(tdk_attend_diff16_kernel<true>, grid, dim3(64), 0, st, rd, d, at);
-    else hipLaunchKernelGGL(tdk_attend_diff16_kernel<false>, grid, dim3(64), 0, st, rd, d, at);
-  } else {
-    if (at.diff_seg > 1) hipLaunchKernelGGL(tdk_attend_diff_kernel<true>, grid, dim3(64), 0, st, rd, d, at);
-    else hipLaunchKernelGGL(tdk_attend_diff_kernel<false>, grid, dim3(64), 0, st, rd, d, at);
-  }
+  if (at.diff_seg > 1) hipLaunchKernelGGL(tdk_attend_diff16_kernel<true>, grid, dim3(64), 0, st, rd, d, at);
+  else hipLaunchKernelGGL(tdk_attend_diff16_kernel<false>, grid, dim3(64), 0, st, rd, d, at);
   return hipGetLastError();
 }
 
@@ -1186,6 +1776,22 @@ hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const Dif
   if (blocks == 0) return hipSuccess;
   if (at.n_q * at.group > 16) hipLaunchKernelGGL(tdk_attend_fused_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), 0, st, rd, io, d, at, fg);
   else hipLaunchKernelGGL(tdk_attend_fused_kernel<false>, dim3((unsigned)blocks), dim3(kBlock), 0, st, rd, io, d, at, fg);
+  return hipGetLastError();
+}
+
+hipError_t launch_attend_rows(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at, int max_agents,
+                              hipStream_t st) {
+  RowsGrid rg;
+  rg.per_agent = (at.n_q * at.group + kRowsPerWave - 1) / kRowsPerWave;
+  rg.blocks = (int)(((int64_t)max_agents * rg.per_agent + kWaves - 1) / kWaves);
+  rg.direct = at.n_chunks <= 1;
+  const int64_t blocks = (int64_t)rd.heads * rg.blocks * rd.n_sessions * (at.n_chunks > 1 ? at.n_chunks : 1);
+  if (blocks == 0) return hipSuccess;
+  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
+  const dim3 grid((unsigned)blocks);
+  if (rd.seg && at.diff_seg > 1) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, true>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
+  else if (rd.seg) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
+  else hipLaunchKernelGGL((tdk_attend_rows_kernel<false, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
   return hipGetLastError();
 }
 

@@ -1,0 +1,120 @@
+"""The attention kernel that gives every wavefront one agent's query rows (more than 32 rows per agent and KV head, or
+per-agent block orders), at the sizes where its tiles end: rows around multiples of 32 and of a workgroup's 128, spans
+around multiples of a 64-token step and of a chunk, lists around a 32-token tile.  Bounds as in test_gpu_attend.py."""
+import numpy as np
+import pytest
+
+import attend_bounds as ab
+from paper_2604_03143_amd import workload as wl
+from helpers import OracleRun
+from test_gpu_attend import _case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("span", [1, 63, 64, 65, 128, 129, 200])
+@pytest.mark.parametrize("n_q", [33, 64, 65])
+def test_rows_and_spans_around_a_tile(tdo, span, n_q):
+    """One query head per KV head: 33, 64 and 65 rows per agent (two and three wavefronts), three agents, so that
+    workgroups mix agents and the last one has idle wavefronts."""
+    spec = wl.RoundSpec("rows1", 81, 1, 1, 128, 16, 1.0e6, 1, 3, 1, span, 3, 200, 0.3)
+    _case(tdo, spec, n_q, 1)
+
+
+@pytest.mark.parametrize("T,style,scale,grow", [(16, 0, -0.2, None), (32, 1, None, None), (16, 1, 1.0, (0, 16, 7, 250, 1)),
+                                                (32, 0, None, (5, 0, 33, 64, 1))])
+def test_page_sizes_styles_scales_and_moved_mirrors(tdo, T, style, scale, grow):
+    spec = wl.RoundSpec("rows2", 82, 1, 2, 128, T, 5.0e5, 1, 5, 3, 111, 3, 300, 0.3)
+    _case(tdo, spec, 9, 8, style=style, scale=scale, grow=grow)
+
+
+@pytest.mark.parametrize("frac,spans", [(0.15, (10, 421)), (1.0, (6, 80))])
+def test_span_cut_into_chunks(tdo, frac, spans):
+    """Few agents on a large chip: the span is cut into several chunks, whose lists begin inside the agent's list."""
+    spec = wl.RoundSpec("rows3", 83, 1, 2, 128, 16, 1.0e6, 1, 2, spans[0], spans[1], 3, 500, frac)
+    _case(tdo, spec, 17, 4)
+
+
+@pytest.mark.parametrize("n_q", [1, 6])
+@pytest.mark.parametrize("grow", [None, (0, 16, 7, 250)])
+def test_few_rows_with_stored_positions_moved(tdo, n_q, grow):
+    """Identity layouts with at most 32 rows per agent keep the shared launch, also when the stored diffs have moved
+    (3 and 18 rows per agent and KV head: 16-row and 32-row tiles for the listed pages)."""
+    for style in (0, 1):
+        spec = wl.RoundSpec("rows4", 84, 1, 2, 128, 16, 1.0e6, 1, 4, 3, 75, 3, 300, 0.4)
+        _case(tdo, spec, n_q, 6, style=style, grow=grow)
+
+
+@pytest.mark.parametrize("n_agents,H,n_q,Hq,T,moved", [(3, 1, 33, 1, 16, False), (40, 8, 1, 16, 16, False), (40, 8, 1, 16, 16, True),
+                                                       (40, 8, 3, 48, 32, True), (5, 2, 12, 8, 32, True)])
+def test_borders_of_blocks_anywhere(tdo, n_agents, H, n_q, Hq, T, moved):
+    """Agents whose segment borders differ from agent to agent (cuts at random tokens, the segments in random order):
+    steps end at the borders of every agent of a workgroup.  40 agents x 8 KV heads with few rows take the packed
+    form, the others one agent per wavefront."""
+    import torch
+    from paper_2604_03143_amd import tdk
+    import gpu_helpers as gh
+    span = 397
+    spec = wl.RoundSpec("rows5", 85, 1, H, 128, T, 1.0e6, 1, n_agents, 1, span, 300, 700, 0.25)
+    rnd = wl.make_round(spec)
+    g = np.random.default_rng([85, n_agents, T])
+    rnd.segments = []
+    for i in range(n_agents):
+        cuts = np.unique(np.concatenate([[0], np.sort(g.choice(np.arange(1, span // T), 4, replace=False)) * T + int(g.integers(0, T))]))
+        lens = np.diff(np.concatenate([cuts, [span]]))
+        order = g.permutation(len(cuts))
+        dst = np.empty(len(cuts), np.int64)
+        dst[order] = int(rnd.agent_pos0[i]) + np.concatenate([[0], np.cumsum(lens[order])[:-1]])
+        rnd.segments.append(np.stack([cuts, dst, lens], 1))
+    o = OracleRun(tdo, rnd)
+    o.rerotate(); o.perturb()
+    d = o.encode()
+    seg_diff = [sg[:, 1] - (37 + q) if moved else sg[:, 1] for q, sg in enumerate(rnd.segments)]
+    q = wl.f32_to_bf16_bits(g.standard_normal((n_agents, n_q, Hq, 128)).astype(np.float32))
+    scale = 1.0 / np.sqrt(128.0)
+    hr = tdo.HostRound(rnd, diff_pos0=rnd.agent_pos0, segment_diff_pos=seg_diff)
+    want_o, want_l, tol_o, tol_l = ab.expected_and_bounds(tdo, o.g, hr, o.mk, o.mv, d, q, n_q, Hq, scale)
+    r = tdk.round_from_workload(rnd, diff_pos0=rnd.agent_pos0, segment_diff_pos=seg_diff)
+    try:
+        n = int(d.offset[-1])
+        mk, mv = gh.up(o.mk), gh.up(o.mv)
+        cnt, off = torch.from_numpy(d.count).cuda(), torch.from_numpy(d.offset).cuda()
+        idx, pay = torch.from_numpy(d.idx[:n].copy()).cuda(), gh.up(d.payload[:n].copy())
+        dd = tdk.diff(cnt, off, idx, pay, n, torch.zeros(1, dtype=torch.int32, device="cuda"))
+        nbytes = tdk.tdk_attend_workspace_bytes(r, n_q, Hq)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        ws.fill_(0xFF)
+        out = torch.full((n_agents, n_q, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+        lse = torch.full((n_agents, n_q, Hq), float("nan"), dtype=torch.float32, device="cuda")
+        tdk.tdk_attend_shared(r, 0, tdk.layer_io(mk, mv, None, None, 0), dd,
+                              tdk.attend_io(gh.up(q), n_q, Hq, scale, out, lse, ws, nbytes))
+        torch.cuda.synchronize()
+        ab.assert_within(out.cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64),
+                         want_o, want_l, tol_o, tol_l, what=(n_agents, H, n_q, Hq, T, moved))
+    finally:
+        r.destroy()
+
+
+@pytest.mark.parametrize("n_q,Hq", [(1, 2), (40, 2)])
+def test_empty_spans(tdo, n_q, Hq):
+    """Rounds whose spans are all empty: out 0, log-sum-exp -inf, from stale memory."""
+    import torch
+    from paper_2604_03143_amd import tdk
+    import gpu_helpers as gh
+    spec = wl.RoundSpec("rows6", 86, 1, 2, 128, 16, 1.0e6, 1, 3, 1, 16, 3, 50, 0.2)
+    rnd = wl.make_round(spec, spans=[0], agents=[3])
+    r = tdk.round_from_workload(rnd)
+    try:
+        d = gh.DevDiff(3, 1, 2 * 16 * 256)
+        d.count.zero_(); d.offset.zero_()
+        q = torch.ones((3, n_q, Hq, 128), dtype=torch.bfloat16, device="cuda")
+        out = torch.full((3, n_q, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+        lse = torch.full((3, n_q, Hq), float("nan"), dtype=torch.float32, device="cuda")
+        nbytes = tdk.tdk_attend_workspace_bytes(r, n_q, Hq)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        ws.fill_(0xFF)
+        tdk.tdk_attend_shared(r, 0, tdk.layer_io(None, None, None, None, 0), d.c, tdk.attend_io(q, n_q, Hq, 0.1, out, lse, ws, nbytes))
+        torch.cuda.synchronize()
+        assert (out == 0).all() and torch.isneginf(lse).all()
+    finally:
+        r.destroy()
