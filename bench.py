@@ -522,7 +522,7 @@ def check_mode(args, tdk, wl, np, torch, dev):
     wall_ms = (time.perf_counter() - t0) * 1e3 / reps
     tdk.tdk_timing_enable(r, False)
     us = {}
-    for k in (tdk.KERNEL_KEYDIFF, tdk.KERNEL_SELECT, tdk.KERNEL_MASTER):
+    for k in (tdk.KERNEL_KEYDIFF, tdk.KERNEL_SELECT):
         ms, n = tdk.tdk_timing_read(r, k)
         us[tdk.tdk_kernel_name(k)] = round(ms / n * 1e3, 2)
     alg = (sum(int(x) for x in rnd.span_tokens) + n_tok) * (ROW_PAIR_BYTES // 2) + 4 * n_tok

@@ -23,7 +23,7 @@ extern "C" {
 #define TDK_KERNEL_SCATTER  5
 #define TDK_KERNEL_KEYDIFF  6
 #define TDK_KERNEL_SELECT   7
-#define TDK_KERNEL_MASTER   8
+#define TDK_KERNEL_MASTER   8    /* the choice of the masters: part of TDK_KERNEL_SELECT's launch, no launches of its own */
 #define TDK_KERNEL_ATTEND_QROT   9
 #define TDK_KERNEL_ATTEND_MASTER 10   /* also the launch that holds the master and the listed-pages pass together */
 #define TDK_KERNEL_ATTEND_DIFF   11   /* (no launches of its own when that shared launch is used)                  */

@@ -246,7 +246,7 @@ const char* tdk_kernel_name(int32_t kernel) {
     case TDK_KERNEL_SCATTER: return "tdk_scatter_kernel";
     case TDK_KERNEL_KEYDIFF: return "tdk_keydiff_kernel";
     case TDK_KERNEL_SELECT: return "tdk_select_kernel";
-    case TDK_KERNEL_MASTER: return "tdk_master_kernel";
+    case TDK_KERNEL_MASTER: return "tdk_select_kernel";
     case TDK_KERNEL_ATTEND_QROT: return "tdk_attend_qrot_kernel";
     case TDK_KERNEL_ATTEND_MASTER: return "tdk_attend_master_kernel";
     case TDK_KERNEL_ATTEND_DIFF: return "tdk_attend_diff_kernel";
@@ -328,6 +328,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   const size_t o_seg_src = place(any_segments ? seg_src.size() * sizeof(int32_t) : 0);
   const size_t o_flags = place((size_t)flag_off);
   const size_t o_qstate = place(16 * sizeof(int32_t));
+  const size_t o_tickets = place((size_t)n_sessions * sizeof(int32_t));
   r->blob_bytes = std::max<size_t>(off, 256);
 
   hipError_t e = hipGetDevice(&r->device);
@@ -355,7 +356,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   if (e == hipSuccess && any_segments) e = up(o_seg_off, seg_off.data(), seg_off.size() * sizeof(int32_t));
   if (e == hipSuccess && any_segments) e = up(o_seg_src, seg_src.data(), seg_src.size() * sizeof(int32_t));
   if (e == hipSuccess && flag_off) e = hipMemset(base + o_flags, 0, (size_t)flag_off);
-  if (e == hipSuccess) e = hipMemset(base + o_qstate, 0, 16 * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMemset(base + o_qstate, 0, o_tickets - o_qstate + (size_t)n_sessions * sizeof(int32_t));   // and the tickets behind it
   if (e != hipSuccess) return hip_fail(e, "upload of round descriptors");
 
   r->rd.work = reinterpret_cast<const WorkItem*>(base + o_work);
@@ -369,6 +370,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   r->rd.tab_diff = reinterpret_cast<const float*>(base + o_tab_diff);
   r->rd.flags = reinterpret_cast<uint8_t*>(base + o_flags);
   r->rd.q_state = reinterpret_cast<int32_t*>(base + o_qstate);
+  r->rd.tickets = reinterpret_cast<int32_t*>(base + o_tickets);
   r->rd.n_cus = r->n_cus;
   r->rd.seg = any_segments ? 1 : 0;
   r->rd.rowmap = any_segments ? reinterpret_cast<const int32_t*>(base + o_rowmap) : nullptr;
@@ -588,7 +590,6 @@ tdk_status tdk_check_layer(tdk_round* r, int32_t layer, const tdk_layer_io* io, 
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     TDK_LAUNCH(r, TDK_KERNEL_KEYDIFF, s, launch_keydiff(r->rd, layer_dev(io), pl, s));
     TDK_LAUNCH(r, TDK_KERNEL_SELECT, s, launch_select(r->rd, pl, s));
-    TDK_LAUNCH(r, TDK_KERNEL_MASTER, s, launch_master(r->rd, pl, s));
     return TDK_OK;
   });
 }

@@ -1609,10 +1609,12 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     };
     if (SEG) {
       // (one copy of the step: two of them next to the reloads of the queries cost registers that spill; 83 -> 71 us)
-      for (int odd = 0; p1 < tok_end; odd ^= 1) {
+      int odd = 0;
+      while (p1 < tok_end) {
         step(odd, s0, s1);
         s0[0] = s1[0];
         s0[1] = s1[1];
+        odd ^= 1;
       }
     } else {
       while (p1 < tok_end) {

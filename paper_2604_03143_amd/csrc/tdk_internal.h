@@ -30,6 +30,7 @@ struct RoundDev {
   uint8_t*          flags;   // [sum_i pages_i] scratch of encode
   unsigned long long* stamps;  // measurement only: [2 x work items] start / end clock of every work item, or NULL
   int32_t*          q_state; // [16] work queues: [0..7] next item of each XCD's queue, [8] workgroups that have left, [12] next item of a static launch's shared tail; all zero between launches
+  int32_t*          tickets; // [n_sessions] totals delivered so far in a check-layer call; zero between calls
   int64_t           agent_pages;           // sum over agents of their session's page count: the length of a page-kernel launch
   const WorkItem*   rwork;                 // the work list of the kernels that only read (compare, key difference): it may be coarser
   int32_t           n_rwork;
@@ -107,7 +108,6 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
 hipError_t launch_scatter(const RoundDev& rd, const LayerDev& io, const DiffDev& d, int planes, int grid, hipStream_t st);
 hipError_t launch_keydiff(const RoundDev& rd, const LayerDev& io, const PlanDev& pl, hipStream_t st);
 hipError_t launch_select(const RoundDev& rd, const PlanDev& pl, hipStream_t st);
-hipError_t launch_master(const RoundDev& rd, const PlanDev& pl, hipStream_t st);
 hipError_t launch_copy(u32x4* dst, const u32x4* src, size_t n16, hipStream_t st);
 hipError_t launch_fill(u32x4* dst, uint32_t word, size_t n16, hipStream_t st);
 
