@@ -10,7 +10,9 @@
 //     page's row offset are staged in LDS once per workgroup;
 //   - a wavefront always handles whole rows: lane l holds 8 consecutive elements of the low half
 //     and the 8 matching elements of the high half of head l/8, so both members of every rotation
-//     pair sit in the same lane and each load/store instruction covers whole 128-byte segments.
+//     pair sit in the same lane and each load/store instruction covers whole 128-byte segments;
+//   - a row of 1, 2 or 4 KV heads fills only part of a wavefront that way, so several rows of the page share each
+//     instruction then (PACK: as many as fill it, see Lane).
 #include "tdk_internal.h"
 
 #include <algorithm>
@@ -107,8 +109,7 @@ struct GroupSharedSeg {
   int32_t  agent[kMaxGroup];
 };
 
-template <int T>
-__device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& w, GroupSharedSeg& sh) {
+__device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& w, const int T, GroupSharedSeg& sh) {
   const int tid = threadIdx.x;
   for (int i = tid; i < w.ag_count * 64; i += kBlock) {
     const int g = i >> 6, which = (i >> 5) & 1, q = i & 31;
@@ -120,7 +121,7 @@ __device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& 
   }
   const SessionDev sd = rd.sess[w.session];
   for (int i = tid; i < w.ag_count * T; i += kBlock) {
-    const int g = i / T, r = i - g * T;
+    const int g = T == 16 ? i >> 4 : i >> 5, r = i & (T - 1);
     const AgentDev ad = rd.agents[rd.order[w.ag_begin + g]];
     const int m = w.page * T + r;
     sh.row[g][r] = m < sd.span ? rd.rowmap[ad.score_off + m] : 0;
@@ -133,8 +134,7 @@ __device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& 
   }
 }
 
-template <int T>
-__device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& w, GroupShared& sh) {
+__device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& w, const int T, GroupShared& sh) {
   const int tid = threadIdx.x;
   for (int i = tid; i < w.ag_count * 32; i += kBlock) {
     const int g = i >> 5, q = i & 31;
@@ -146,10 +146,10 @@ __device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& 
     const int a = rd.order[w.ag_begin + tid];
     const AgentDev ad = rd.agents[a];
     const int a0 = ad.pos0 + w.page * T;
-    const int lp = a0 / T - ad.lp_first;
+    const int lp = (T == 16 ? a0 >> 4 : a0 >> 5) - ad.lp_first;       // (positions are not negative)
     sh.pg0[tid] = rd.bt[ad.bt_off + lp];
     sh.pg1[tid] = (lp + 1 < ad.bt_len) ? rd.bt[ad.bt_off + lp + 1] : -1;
-    sh.off[tid] = a0 % T;
+    sh.off[tid] = a0 & (T - 1);
     sh.aux[tid] = 0;
     sh.agent[tid] = a;
   }
@@ -161,20 +161,50 @@ struct Lane {
   int v0, v1;        // chunk indices of its two V chunks
   bool kok, v0ok, v1ok;
   int jb;            // which 8-element block of the half this lane rotates
+  int rk, rv0, rv1;  // which of the rows that share an instruction the chunks belong to (0 unless PACK)
 };
 
-__device__ __forceinline__ Lane lane_geometry(int H) {
+// Rows that share an instruction.  A row of H heads is 8 H lanes wide (K: two chunks per lane) or 16 H chunks (V: two
+// per lane), so 8 / H rows fill a wavefront; the four wavefronts of a workgroup divide the page's rows among them,
+// so a 16-token page gives a wavefront at most 4 rows.
+__device__ __host__ __forceinline__ int rows_per_access(int H, int T) { const int n = 8 / H; return n < T / kWaves ? n : T / kWaves; }
+
+// PACK: H is 1, 2 or 4
+template <bool PACK>
+__device__ __forceinline__ Lane lane_geometry(int H, int T) {
   const int lane = threadIdx.x & 63;
   Lane L;
   L.jb = lane & 7;
-  L.klo = (lane >> 3) * 16 + L.jb;
-  L.khi = L.klo + 8;
-  L.kok = (lane >> 3) < H;
-  L.v0 = lane;
-  L.v1 = lane + 64;
-  L.v0ok = L.v0 < H * 16;
-  L.v1ok = L.v1 < H * 16;
+  L.rk = L.rv0 = L.rv1 = 0;
+  if (!PACK) {
+    L.klo = (lane >> 3) * 16 + L.jb;
+    L.khi = L.klo + 8;
+    L.kok = (lane >> 3) < H;
+    L.v0 = lane;
+    L.v1 = lane + 64;
+    L.v0ok = L.v0 < H * 16;
+    L.v1ok = L.v1 < H * 16;
+  } else {
+    const int n = rows_per_access(H, T), lgh = H == 4 ? 2 : H - 1;
+    L.rk = (lane >> 3) >> lgh;
+    L.klo = ((lane >> 3) & (H - 1)) * 16 + L.jb;
+    L.khi = L.klo + 8;
+    L.kok = L.rk < n;
+    L.rv0 = lane >> (4 + lgh);
+    L.rv1 = (lane + 64) >> (4 + lgh);
+    L.v0 = lane & (16 * H - 1);
+    L.v1 = lane & (16 * H - 1);
+    L.v0ok = L.rv0 < n;
+    L.v1ok = L.rv1 < n;
+  }
   return L;
+}
+
+// The k-th group of rows of a wavefront: the first row of the page it covers.
+template <bool PACK>
+__device__ __forceinline__ int group_row(int k, int H, int T) {
+  const int wave = threadIdx.x >> 6;
+  return PACK ? (wave + kWaves * k) * rows_per_access(H, T) : wave + kWaves * k;
 }
 
 __device__ __forceinline__ const float* tab_of(const GroupShared& sh, int g, int) { return sh.tab[g]; }
@@ -201,41 +231,54 @@ __device__ __forceinline__ void load_tab(const Shared& sh, int g, int r, int jb,
 template <int RPW>
 struct MasterRows {
   u32x4 kl[RPW], kh[RPW], v0[RPW], v1[RPW];
-  bool  valid[RPW];
+  bool  valid[RPW];                          // some row of the group lies inside the span
+  bool  kin[RPW], v0in[RPW], v1in[RPW];      // PACK: the rows of this lane's chunks do
+  template <bool PACK> __device__ __forceinline__ bool kok(const Lane& L, int k) const { return PACK ? L.kok && kin[k] : L.kok; }
+  template <bool PACK> __device__ __forceinline__ bool v0ok(const Lane& L, int k) const { return PACK ? L.v0ok && v0in[k] : L.v0ok; }
+  template <bool PACK> __device__ __forceinline__ bool v1ok(const Lane& L, int k) const { return PACK ? L.v1ok && v1in[k] : L.v1ok; }
 };
 
-template <int RPW, bool LOADV = true, bool LOADK = true>
-__device__ __forceinline__ void load_master(const RoundDev& rd, const LayerDev& io, const WorkItem& w,
+template <int RPW, bool PACK, bool LOADV = true, bool LOADK = true>
+__device__ __forceinline__ void load_master(const RoundDev& rd, const LayerDev& io, const WorkItem& w, const int T,
                                             const Lane& L, MasterRows<RPW>& M) {
-  constexpr int T = RPW * kWaves;
   const SessionDev sd = rd.sess[w.session];
-  const int wave = threadIdx.x >> 6;
   const int64_t row_u4 = (int64_t)rd.heads * 16;
 #pragma unroll
   for (int k = 0; k < RPW; ++k) {
-    const int m = w.page * T + wave + kWaves * k;
+    const int m = w.page * T + group_row<PACK>(k, rd.heads, T);
     M.valid[k] = m < sd.span;
+    if (PACK) { M.kin[k] = m + L.rk < sd.span; M.v0in[k] = m + L.rv0 < sd.span; M.v1in[k] = m + L.rv1 < sd.span; }
     const u32x4 z = {0, 0, 0, 0};
     M.kl[k] = z; M.kh[k] = z; M.v0[k] = z; M.v1[k] = z;
     if (M.valid[k]) {
-      const u32x4* rk = io.master_k + (sd.master_row0 + m) * row_u4;
-      const u32x4* rv = io.master_v + (sd.master_row0 + m) * row_u4;
-      if (LOADK && L.kok) { M.kl[k] = rk[L.klo]; M.kh[k] = rk[L.khi]; }
-      if (LOADV && L.v0ok) M.v0[k] = rv[L.v0];
-      if (LOADV && L.v1ok) M.v1[k] = rv[L.v1];
+      const u32x4* rk = io.master_k + (sd.master_row0 + m + (PACK ? L.rk : 0)) * row_u4;
+      const u32x4* rv0 = io.master_v + (sd.master_row0 + m + (PACK ? L.rv0 : 0)) * row_u4;
+      const u32x4* rv1 = PACK ? io.master_v + (sd.master_row0 + m + L.rv1) * row_u4 : rv0;
+      if (LOADK && M.template kok<PACK>(L, k)) { M.kl[k] = rk[L.klo]; M.kh[k] = rk[L.khi]; }
+      if (LOADV && M.template v0ok<PACK>(L, k)) M.v0[k] = rv0[L.v0];
+      if (LOADV && M.template v1ok<PACK>(L, k)) M.v1[k] = rv1[L.v1];
     }
   }
 }
 
-template <int T>
-__device__ __forceinline__ int64_t dest_row(const GroupSharedSeg& sh, int g, int r) { return sh.row[g][r]; }
+__device__ __forceinline__ int64_t dest_row(const GroupSharedSeg& sh, int, int g, int r) { return sh.row[g][r]; }
 
 // physical pool row of row r (0..T-1) of the master page for agent g of the group
-template <int T>
-__device__ __forceinline__ int64_t dest_row(const GroupShared& sh, int g, int r) {
+__device__ __forceinline__ int64_t dest_row(const GroupShared& sh, int T, int g, int r) {
   const int q = sh.off[g] + r;
   const int pg = q < T ? sh.pg0[g] : sh.pg1[g];
   return (int64_t)pg * T + (q & (T - 1));
+}
+
+// pool offsets (16-byte units) of a row group's chunks: one row for all lanes, or (PACK) each chunk's own
+struct Dest { int64_t k, v0, v1; };
+template <bool PACK, class Shared>
+__device__ __forceinline__ Dest dest_of(const Shared& sh, int T, int g, int r, const Lane& L, int64_t row_u4) {
+  Dest d;
+  d.k = dest_row(sh, T, g, PACK ? r + L.rk : r) * row_u4;
+  d.v0 = PACK ? dest_row(sh, T, g, r + L.rv0) * row_u4 : d.k;
+  d.v1 = PACK ? dest_row(sh, T, g, r + L.rv1) * row_u4 : d.k;
+  return d;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -367,14 +410,13 @@ struct Items {
   }
 };
 
-template <int RPW, bool IL, bool NT, bool SEG, bool Q>
+template <int RPW, bool PACK, bool IL, bool NT, bool SEG, bool Q>
 __global__ __launch_bounds__(kBlock) void tdk_rerotate_kernel(const RoundDev rd, const LayerDev io) {
-  constexpr int T = RPW * kWaves;
+  const int T = PACK ? rd.page_tokens : RPW * kWaves;
   __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
   __shared__ int s_item;
-  const Lane L = lane_geometry(rd.heads);
+  const Lane L = lane_geometry<PACK>(rd.heads, T);
   if (rd.nontemporal & 32) sweep_masters(rd, io, true, true);
-  const int wave = threadIdx.x >> 6;
   const int64_t row_u4 = (int64_t)rd.heads * 16;
   u32x4* pk = io.pool_k;
   u32x4* pv = io.pool_v;
@@ -382,9 +424,9 @@ __global__ __launch_bounds__(kBlock) void tdk_rerotate_kernel(const RoundDev rd,
   for (int item = items.first(rd, &s_item); item >= 0; item = items.next(rd, &s_item)) {
     stamp_begin(rd, item);
     const WorkItem w = items.at(rd, item);
-    stage_group<T>(rd, w, sh);
+    stage_group(rd, w, T, sh);
     MasterRows<RPW> M;
-    load_master<RPW>(rd, io, w, L, M);
+    load_master<RPW, PACK>(rd, io, w, T, L, M);
     lds_barrier();
     items.prefetch(rd);
     stamp_mid(rd, item, 2);
@@ -395,16 +437,17 @@ __global__ __launch_bounds__(kBlock) void tdk_rerotate_kernel(const RoundDev rd,
 #pragma unroll
       for (int k = 0; k < RPW; ++k) {
         if (!M.valid[k]) continue;
-        const int64_t base = dest_row<T>(sh, g, wave + kWaves * k) * row_u4;
-        if (L.kok) {
-          if (SEG) load_tab<IL>(sh, g, wave + kWaves * k, L.jb, c, s);
+        const int r = group_row<PACK>(k, rd.heads, T);
+        const Dest to = dest_of<PACK>(sh, T, g, r, L, row_u4);
+        if (M.template kok<PACK>(L, k)) {
+          if (SEG) load_tab<IL>(sh, g, PACK ? r + L.rk : r, L.jb, c, s);
           u32x4 olo, ohi;
           rotate16<IL>(M.kl[k], M.kh[k], c, s, olo, ohi);
-          st16<NT>(pk + base + L.klo, olo);
-          st16<NT>(pk + base + L.khi, ohi);
+          st16<NT>(pk + to.k + L.klo, olo);
+          st16<NT>(pk + to.k + L.khi, ohi);
         }
-        if (L.v0ok) st16<NT>(pv + base + L.v0, M.v0[k]);
-        if (L.v1ok) st16<NT>(pv + base + L.v1, M.v1[k]);
+        if (M.template v0ok<PACK>(L, k)) st16<NT>(pv + to.v0 + L.v0, M.v0[k]);
+        if (M.template v1ok<PACK>(L, k)) st16<NT>(pv + to.v1 + L.v1, M.v1[k]);
       }
     }
     stamp_end(rd, item);
@@ -447,22 +490,21 @@ __device__ __forceinline__ bool chunk_special(const u32x4 m) {
 }
 
 // PM: planes that take part (bit 0 = K, bit 1 = V); 3 is the paired diff, 1 / 2 the single-plane diffs
-template <int RPW, bool IL, int PM, bool SEG, bool NTL>
+template <int RPW, bool PACK, bool IL, int PM, bool SEG, bool NTL>
 __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, const LayerDev io, const float eps) {
-  constexpr int T = RPW * kWaves;
+  const int T = PACK ? rd.page_tokens : RPW * kWaves;
   constexpr bool DOK = (PM & 1) != 0, DOV = (PM & 2) != 0;
   __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
-  const Lane L = lane_geometry(rd.heads);
-  const int wave = threadIdx.x >> 6;
+  const Lane L = lane_geometry<PACK>(rd.heads, T);
   const int64_t row_u4 = (int64_t)rd.heads * 16;
   const u32x4* pk = io.pool_k;
   const u32x4* pv = io.pool_v;
   const int item = blockIdx.x;
   stamp_begin(rd, item);
   const WorkItem w = rd.rwork[item];
-  stage_group<T>(rd, w, sh);
+  stage_group(rd, w, T, sh);
   MasterRows<RPW> M;
-  load_master<RPW, DOV, DOK>(rd, io, w, L, M);
+  load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
   bool special[RPW];
 #pragma unroll
   for (int k = 0; k < RPW; ++k)
@@ -477,16 +519,16 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
   const u32x4 z = {0, 0, 0, 0};
   u32x4 akl[RPW], akh[RPW], av0[RPW], av1[RPW];
   auto request = [&](int g, int k) {
-    const int64_t base = dest_row<T>(sh, max(min(g, w.ag_count - 1), 0), wave + kWaves * k) * row_u4;
+    const Dest at = dest_of<PACK>(sh, T, max(min(g, w.ag_count - 1), 0), group_row<PACK>(k, rd.heads, T), L, row_u4);
     const bool ok = g < w.ag_count && M.valid[k];
     akl[k] = z; akh[k] = z; av0[k] = z; av1[k] = z;
     if (DOK) {
-      akl[k] = ld16<NTL>(ok && L.kok ? pk + base + L.klo : idle_k);
-      akh[k] = ld16<NTL>(ok && L.kok ? pk + base + L.khi : idle_k + 8);
+      akl[k] = ld16<NTL>(ok && M.template kok<PACK>(L, k) ? pk + at.k + L.klo : idle_k);
+      akh[k] = ld16<NTL>(ok && M.template kok<PACK>(L, k) ? pk + at.k + L.khi : idle_k + 8);
     }
     if (DOV) {
-      av0[k] = ld16<NTL>(ok && L.v0ok ? pv + base + L.v0 : idle_v);
-      av1[k] = ld16<NTL>(ok && L.v1ok ? pv + base + L.v1 : idle_v);
+      av0[k] = ld16<NTL>(ok && M.template v0ok<PACK>(L, k) ? pv + at.v0 + L.v0 : idle_v);
+      av1[k] = ld16<NTL>(ok && M.template v1ok<PACK>(L, k) ? pv + at.v1 + L.v1 : idle_v);
     }
   };
 #pragma unroll
@@ -499,19 +541,19 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
     for (int k = 0; k < RPW; ++k) {
       if (M.valid[k]) {
         u32x4 rlo = z, rhi = z;
-        if (DOK && SEG) load_tab<IL>(sh, g, wave + kWaves * k, L.jb, c, s);
+        if (DOK && SEG) load_tab<IL>(sh, g, group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
         if (DOK) rotate16<IL>(M.kl[k], M.kh[k], c, s, rlo, rhi);
         // rows whose bits all match the reference (the common case) need no fp32 compare
         uint32_t x = 0;
-        if (DOV) x |= (L.v0ok ? chunk_xor(av0[k], M.v0[k]) : 0u) | (L.v1ok ? chunk_xor(av1[k], M.v1[k]) : 0u);
-        if (DOK) x |= L.kok ? chunk_xor(akl[k], rlo) | chunk_xor(akh[k], rhi) : 0u;
+        if (DOV) x |= (M.template v0ok<PACK>(L, k) ? chunk_xor(av0[k], M.v0[k]) : 0u) | (M.template v1ok<PACK>(L, k) ? chunk_xor(av1[k], M.v1[k]) : 0u);
+        if (DOK) x |= M.template kok<PACK>(L, k) ? chunk_xor(akl[k], rlo) | chunk_xor(akh[k], rhi) : 0u;
         if (__any((int)(x != 0) | (int)special[k])) {
-          if (DOK && L.kok) {
+          if (DOK && M.template kok<PACK>(L, k)) {
             differs |= chunk_differs(akl[k], rlo, eps);
             differs |= chunk_differs(akh[k], rhi, eps);
           }
-          if (DOV && L.v0ok) differs |= chunk_differs(av0[k], M.v0[k], eps);
-          if (DOV && L.v1ok) differs |= chunk_differs(av1[k], M.v1[k], eps);
+          if (DOV && M.template v0ok<PACK>(L, k)) differs |= chunk_differs(av0[k], M.v0[k], eps);
+          if (DOV && M.template v1ok<PACK>(L, k)) differs |= chunk_differs(av1[k], M.v1[k], eps);
         }
       }
       request(g + 1, k);
@@ -715,7 +757,7 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
   if (total > d.capacity) total = d.capacity;
   const int row_u4 = rd.heads * 16;
   const int page_u4 = T * row_u4;
-  const Lane L = lane_geometry(rd.heads);
+  const Lane L = lane_geometry<false>(rd.heads, T);
   for (int64_t slot = first; slot < total; slot += stride) {
     if (threadIdx.x == 0) sh.owner = -1;
     __syncthreads();
@@ -829,10 +871,10 @@ __global__ __launch_bounds__(kBlock) void tdk_scatter_kernel(const RoundDev rd, 
   scatter_slots<IL>(rd, io, d, planes, ss, blockIdx.x, gridDim.x);
 }
 
-template <int RPW, bool IL, bool NT, int PM, bool SEG, bool Q>
+template <int RPW, bool PACK, bool IL, bool NT, int PM, bool SEG, bool Q>
 __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
                                                             const int n_scatter) {
-  constexpr int T = RPW * kWaves;
+  const int T = PACK ? rd.page_tokens : RPW * kWaves;
   __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
   __shared__ int s_item;
   constexpr bool DOK = (PM & 1) != 0, DOV = (PM & 2) != 0;
@@ -845,9 +887,8 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
     scatter_slots<IL>(rd, io, d, PM, ss, (int64_t)blockIdx.x - (rd.dyn_begin + rd.dyn_count), n_scatter);
     return;
   }
-  const Lane L = lane_geometry(rd.heads);
+  const Lane L = lane_geometry<PACK>(rd.heads, T);
   if (rd.nontemporal & 64) sweep_masters(rd, io, DOK, DOV);
-  const int wave = threadIdx.x >> 6;
   const int64_t row_u4 = (int64_t)rd.heads * 16;
   u32x4* pk = io.pool_k;
   u32x4* pv = io.pool_v;
@@ -855,9 +896,9 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
   for (int item = items.first(rd, &s_item); item >= 0; item = items.next(rd, &s_item)) {
     stamp_begin(rd, item);
     const WorkItem w = items.at(rd, item);
-    stage_group<T>(rd, w, sh);
+    stage_group(rd, w, T, sh);
     MasterRows<RPW> M;
-    load_master<RPW, DOV, DOK>(rd, io, w, L, M);
+    load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
     if (threadIdx.x < w.ag_count) {
       // skip-or-correct decision per block: is this page in the agent's index list?
       const int a = rd.order[w.ag_begin + threadIdx.x];
@@ -883,16 +924,17 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
 #pragma unroll
       for (int k = 0; k < RPW; ++k) {
         if (!M.valid[k]) continue;
-        const int64_t base = dest_row<T>(sh, g, wave + kWaves * k) * row_u4;
-        if (DOK && L.kok) {
-          if (SEG) load_tab<IL>(sh, g, wave + kWaves * k, L.jb, c, s);
+        const int r = group_row<PACK>(k, rd.heads, T);
+        const Dest to = dest_of<PACK>(sh, T, g, r, L, row_u4);
+        if (DOK && M.template kok<PACK>(L, k)) {
+          if (SEG) load_tab<IL>(sh, g, PACK ? r + L.rk : r, L.jb, c, s);
           u32x4 olo, ohi;
           rotate16<IL>(M.kl[k], M.kh[k], c, s, olo, ohi);
-          st16<NT>(pk + base + L.klo, olo);
-          st16<NT>(pk + base + L.khi, ohi);
+          st16<NT>(pk + to.k + L.klo, olo);
+          st16<NT>(pk + to.k + L.khi, ohi);
         }
-        if (DOV && L.v0ok) st16<NT>(pv + base + L.v0, M.v0[k]);
-        if (DOV && L.v1ok) st16<NT>(pv + base + L.v1, M.v1[k]);
+        if (DOV && M.template v0ok<PACK>(L, k)) st16<NT>(pv + to.v0 + L.v0, M.v0[k]);
+        if (DOV && M.template v1ok<PACK>(L, k)) st16<NT>(pv + to.v1 + L.v1, M.v1[k]);
       }
     }
     stamp_end(rd, item);
@@ -919,9 +961,9 @@ __global__ __launch_bounds__(kBlock) void tdk_fill_kernel(u32x4* __restrict__ ds
 // check layer: batched key-difference pass, important positions, master choice   [Sec. 4.2]
 // ---------------------------------------------------------------------------------------------
 
-// Sum of v over the 64 lanes of a wavefront with DPP row shifts and row broadcasts (no LDS
-// traffic); the total is valid in lane 63 only.
-__device__ __forceinline__ float wave_sum_to_lane63(float v) {
+// Sum of v over the `width` lanes of a row (64; or 8, 16, 32 with several rows per wavefront) with DPP row shifts and
+// row broadcasts (no LDS traffic); the total is valid in the last lane of each row only.
+__device__ __forceinline__ float row_sum_to_last_lane(float v, int width) {
   auto dpp = [](float x, auto ctrl, auto row_mask) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value,
                                                                    decltype(row_mask)::value, 0xf, false));
@@ -929,9 +971,9 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
   v += dpp(v, std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr:1
   v += dpp(v, std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});   // row_shr:2
   v += dpp(v, std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});   // row_shr:4
-  v += dpp(v, std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});   // row_shr:8 -> lane 15 of each row
-  v += dpp(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1, 3
-  v += dpp(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2, 3
+  if (width > 8) v += dpp(v, std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});   // row_shr:8 -> lane 15 of each row
+  if (width > 16) v += dpp(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1, 3
+  if (width > 32) v += dpp(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2, 3
   return v;
 }
 
@@ -940,19 +982,18 @@ __device__ __forceinline__ float wave_sum_to_lane63(float v) {
 // page per agent in flight, so the loads of one agent must overlap the arithmetic of the one before: see the
 // rolling requests below (482 -> 415 us on 250 agents x 5000 tokens; at a budget of 128 registers the compiler
 // spills, and a reload from scratch waits for every load issued before it, so the kernel runs at 3 waves per SIMD).
-template <int RPW, bool IL, bool SEG, bool NTL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW == 4 ? 3 : 1))) void tdk_keydiff_kernel(const RoundDev rd, const LayerDev io, const PlanDev pl) {
-  constexpr int T = RPW * kWaves;
+template <int RPW, bool PACK, bool IL, bool SEG, bool NTL>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4 ? 3 : 1))) void tdk_keydiff_kernel(const RoundDev rd, const LayerDev io, const PlanDev pl) {
+  const int T = PACK ? rd.page_tokens : RPW * kWaves;
   __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
-  __shared__ float s_score[kMaxGroup][T];
-  const Lane L = lane_geometry(rd.heads);
-  const int wave = threadIdx.x >> 6;
+  __shared__ float s_score[kMaxGroup][PACK ? 32 : RPW * kWaves];
+  const Lane L = lane_geometry<PACK>(rd.heads, T);
   const int64_t row_u4 = (int64_t)rd.heads * 16;
   const u32x4* pk = io.pool_k;
   const WorkItem w = rd.rwork[blockIdx.x];
-  stage_group<T>(rd, w, sh);
+  stage_group(rd, w, T, sh);
   MasterRows<RPW> M;
-  load_master<RPW, false>(rd, io, w, L, M);
+  load_master<RPW, PACK, false>(rd, io, w, T, L, M);
   if (threadIdx.x < w.ag_count) sh.aux[threadIdx.x] = rd.agents[sh.agent[threadIdx.x]].score_off;   // (own entry of sh.agent)
   lds_barrier();
   // Rolling requests: row k of the next agent is asked for as soon as row k of this one has been used, into the
@@ -964,8 +1005,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW == 4
   const u32x4* idle = io.master_k + (rd.sess[w.session].master_row0 + (int64_t)w.page * T) * row_u4 + L.jb;
   u32x4 akl[RPW], akh[RPW];
   auto request = [&](int g, int k) {
-    const int64_t base = dest_row<T>(sh, max(min(g, w.ag_count - 1), 0), wave + kWaves * k) * row_u4;
-    const bool ok = g < w.ag_count && M.valid[k] && L.kok;
+    const int64_t base = dest_row(sh, T, max(min(g, w.ag_count - 1), 0), group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0)) * row_u4;
+    const bool ok = g < w.ag_count && M.valid[k] && M.template kok<PACK>(L, k);
     const u32x4* lo = ok ? pk + base + L.klo : idle;
     const u32x4* hi = ok ? pk + base + L.khi : idle + 8;
     akl[k] = ld16<NTL>(lo); akh[k] = ld16<NTL>(hi);
@@ -977,7 +1018,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW == 4
     if (!SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
-      if (SEG) load_tab<IL>(sh, g, wave + kWaves * k, L.jb, c, s);
+      if (SEG) load_tab<IL>(sh, g, group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
       u32x4 rlo, rhi;
       rotate16<IL>(M.kl[k], M.kh[k], c, s, rlo, rhi);
       float acc = 0.f;
@@ -989,14 +1030,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW == 4
         acc = __builtin_fmaf(d2, d2, acc); acc = __builtin_fmaf(d3, d3, acc);
       }
       request(g + 1, k);
-      acc = wave_sum_to_lane63(L.kok ? acc : 0.f);
-      if ((threadIdx.x & 63) == 63) s_score[g][wave + kWaves * k] = acc;   // (no store to memory among the loads: the count of outstanding accesses stays exact)
+      const int width = PACK ? 8 * rd.heads : 64;
+      acc = row_sum_to_last_lane(L.kok ? acc : 0.f, width);
+      if ((threadIdx.x & (width - 1)) == width - 1 && (!PACK || L.kok)) s_score[g][group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0)] = acc;   // (no store to memory among the loads: the count of outstanding accesses stays exact)
     }
   }
   lds_barrier();
   const int rows = min(T, rd.sess[w.session].span - w.page * T);
   for (int i = threadIdx.x; i < w.ag_count * T; i += kBlock) {
-    const int g = i / T, r = i - g * T;
+    const int g = T == 16 ? i >> 4 : i >> 5, r = i & (T - 1);
     if (r < rows) pl.score[sh.aux[g] + w.page * T + r] = s_score[g][r];
   }
 }
@@ -1197,7 +1239,7 @@ __global__ __launch_bounds__(kBlock) void tdk_page_fill_product_kernel(u32x4* __
                                                                       const int32_t* __restrict__ ids, int n_pages, int group,
                                                                       int heads, uint32_t word) {
   constexpr int T = RPW * kWaves;
-  const Lane L = lane_geometry(heads);
+  const Lane L = lane_geometry<false>(heads, T);
   const int wave = threadIdx.x >> 6;
   const int64_t row_u4 = (int64_t)heads * 16;
   const u32x4 v = {word, word ^ threadIdx.x, word, blockIdx.x};
@@ -1220,7 +1262,7 @@ __global__ __launch_bounds__(kBlock) void tdk_page_read_product_kernel(const u32
                                                                       const int32_t* __restrict__ ids, int n_pages, int group,
                                                                       int heads, u32x4* __restrict__ sink) {
   constexpr int T = RPW * kWaves;
-  const Lane L = lane_geometry(heads);
+  const Lane L = lane_geometry<false>(heads, T);
   const int wave = threadIdx.x >> 6;
   const int64_t row_u4 = (int64_t)heads * 16;
   u32x4 acc = {0, 0, 0, 0};
@@ -1300,6 +1342,24 @@ static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, Kernel
 template <int V> using ic = std::integral_constant<int, V>;
 
 template <class F> static void with_rpw(int page_tokens, F f) { if (page_tokens == 16) f(ic<4>{}); else f(ic<8>{}); }
+// Row groups per wavefront, and whether a group holds several rows.  With 1, 2 or 4 KV heads a row alone would leave
+// seven eighths, three quarters or half of a wavefront idle in every access and as many requests less in flight
+// (37 agents x 2999 tokens, 4 heads, both planes stored and restored one at a time: 169 us with one row per access, 149
+// with two; drawn rounds with 1 or 2 heads up to 1.8 times); 3 heads keep one row (rows of 24 lanes do not divide the
+// page), 5 and more fill the wavefront by themselves.
+template <class F> static void with_rows(const RoundDev& rd, F f) {
+  const int H = rd.heads, T = rd.page_tokens;
+  if (H != 1 && H != 2 && H != 4) { with_rpw(T, [&](auto rpw) { f(rpw, std::false_type{}); }); return; }
+  switch (T / (kWaves * rows_per_access(H, T))) {
+    case 1: f(ic<1>{}, std::true_type{}); break;
+    case 2: f(ic<2>{}, std::true_type{}); break;
+    default: f(ic<4>{}, std::true_type{}); break;
+  }
+}
+// the cache policy as a type: packed rows are always streamed (one instantiation each)
+template <class P, class F> static void with_policy(P, bool nt, F f) {
+  if constexpr (P::value) { f(std::true_type{}); } else { if (nt) f(std::true_type{}); else f(std::false_type{}); }
+}
 template <class F> static void with_bool(bool b, F f) { if (b) f(std::true_type{}); else f(std::false_type{}); }
 template <class F> static void with_planes(int planes, F f) {
   if (planes == 1) f(ic<1>{}); else if (planes == 2) f(ic<2>{}); else f(ic<3>{});
@@ -1307,10 +1367,11 @@ template <class F> static void with_planes(int planes, F f) {
 
 hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
-  with_rpw(rd.page_tokens, [&](auto rpw) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 1) != 0, [&](auto nt) {
+  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_policy(pack, (rd.nontemporal & 1) != 0, [&](auto nt) {
     with_bool(rd.seg != 0, [&](auto sg) {
-      launch_write_pages(rd, tdk_rerotate_kernel<decltype(rpw)::value, decltype(il)::value, decltype(nt)::value, decltype(sg)::value, true>,
-                         tdk_rerotate_kernel<decltype(rpw)::value, decltype(il)::value, decltype(nt)::value, decltype(sg)::value, false>, 0, st, io);
+      constexpr int R = decltype(rpw)::value;
+      constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
+      launch_write_pages(rd, tdk_rerotate_kernel<R, P, I, N, G, true>, tdk_rerotate_kernel<R, P, I, N, G, false>, 0, st, io);
     });
   }); }); });
   return hipGetLastError();
@@ -1318,10 +1379,10 @@ hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t s
 
 hipError_t launch_flag(const RoundDev& rd, const LayerDev& io, float eps, int planes, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
-  with_rpw(rd.page_tokens, [&](auto rpw) { with_bool(rd.interleaved != 0, [&](auto il) { with_planes(planes, [&](auto pm) {
-    with_bool(rd.seg != 0, [&](auto sg) { with_bool((rd.nontemporal & 4) != 0, [&](auto ntl) {
-      hipLaunchKernelGGL((tdk_flag_kernel<decltype(rpw)::value, decltype(il)::value, decltype(pm)::value, decltype(sg)::value, decltype(ntl)::value>),
-                         dim3(rd.n_rwork), dim3(kBlock), 0, st, rd, io, eps);
+  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_planes(planes, [&](auto pm) {
+    with_bool(rd.seg != 0, [&](auto sg) { with_policy(pack, (rd.nontemporal & 4) != 0, [&](auto ntl) {
+      hipLaunchKernelGGL((tdk_flag_kernel<decltype(rpw)::value, decltype(pack)::value, decltype(il)::value, decltype(pm)::value, decltype(sg)::value,
+                                          decltype(ntl)::value>), dim3(rd.n_rwork), dim3(kBlock), 0, st, rd, io, eps);
     }); });
   }); }); });
   return hipGetLastError();
@@ -1346,10 +1407,11 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
   *scattered = false;
   if (rd.n_work == 0) return hipSuccess;
   if (rd.n_agents == 0 || d.capacity == 0) scatter_blocks = 0;
-  with_rpw(rd.page_tokens, [&](auto rpw) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 2) != 0, [&](auto nt) {
+  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_policy(pack, (rd.nontemporal & 2) != 0, [&](auto nt) {
     with_planes(planes, [&](auto pm) { with_bool(rd.seg != 0, [&](auto sg) {
-      *scattered = launch_write_pages(rd, tdk_decode_kernel<decltype(rpw)::value, decltype(il)::value, decltype(nt)::value, decltype(pm)::value, decltype(sg)::value, true>,
-                                      tdk_decode_kernel<decltype(rpw)::value, decltype(il)::value, decltype(nt)::value, decltype(pm)::value, decltype(sg)::value, false>,
+      constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;
+      constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
+      *scattered = launch_write_pages(rd, tdk_decode_kernel<R, P, I, N, M, G, true>, tdk_decode_kernel<R, P, I, N, M, G, false>,
                                       scatter_blocks, st, io, d, scatter_blocks);
     }); });
   }); }); });
@@ -1365,9 +1427,9 @@ hipError_t launch_scatter(const RoundDev& rd, const LayerDev& io, const DiffDev&
 
 hipError_t launch_keydiff(const RoundDev& rd, const LayerDev& io, const PlanDev& pl, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
-  with_rpw(rd.page_tokens, [&](auto rpw) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool(rd.seg != 0, [&](auto sg) {
-    with_bool((rd.nontemporal & 4) != 0, [&](auto ntl) {
-      hipLaunchKernelGGL((tdk_keydiff_kernel<decltype(rpw)::value, decltype(il)::value, decltype(sg)::value, decltype(ntl)::value>),
+  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool(rd.seg != 0, [&](auto sg) {
+    with_policy(pack, (rd.nontemporal & 4) != 0, [&](auto ntl) {
+      hipLaunchKernelGGL((tdk_keydiff_kernel<decltype(rpw)::value, decltype(pack)::value, decltype(il)::value, decltype(sg)::value, decltype(ntl)::value>),
                          dim3(rd.n_rwork), dim3(kBlock), 0, st, rd, io, pl);
     });
   }); }); });
