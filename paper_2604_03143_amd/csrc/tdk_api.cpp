@@ -479,10 +479,14 @@ static tdk_status encode_planes(tdk_round* r, int32_t layer, const tdk_layer_io*
     const LayerDev l = layer_dev(io);
     const DiffDev d = diff_dev(out);
     TDK_LAUNCH(r, TDK_KERNEL_FLAG, s, launch_flag(r->rd, l, eps, planes, s));
-    TDK_LAUNCH(r, TDK_KERNEL_COMPACT, s, launch_compact(r->rd, d, s));
     // the number of listed pages is known on the device only: a fixed grid strides over them
     const int grid = (int)std::min<int64_t>(std::min<int64_t>(out->capacity_pages, r->total_pages), 1 << 20);
-    TDK_LAUNCH(r, TDK_KERNEL_GATHER, s, launch_gather(r->rd, l, d, planes, grid, s));
+    if (lists_in_gather(r->rd)) {
+      TDK_LAUNCH(r, TDK_KERNEL_GATHER, s, launch_list_gather(r->rd, l, d, planes, grid, s));
+    } else {
+      TDK_LAUNCH(r, TDK_KERNEL_COMPACT, s, launch_compact(r->rd, d, s));
+      TDK_LAUNCH(r, TDK_KERNEL_GATHER, s, launch_gather(r->rd, l, d, planes, grid, s));
+    }
     return TDK_OK;
   });
 }
@@ -521,9 +525,13 @@ tdk_status tdk_diff_encode_static(tdk_round* r, int32_t layer, const tdk_layer_i
     const DiffDev d = diff_dev(out);
     const int planes = TDK_PLANE_K | TDK_PLANE_V;
     hipError_t e = launch_flag(rd, l, eps, planes, s);
-    if (e == hipSuccess) e = launch_compact(rd, d, s);
     const int grid = (int)std::min<int64_t>(std::min<int64_t>(out->capacity_pages, r->total_pages), 1 << 20);
-    if (e == hipSuccess) e = launch_gather(rd, l, d, planes, grid, s);
+    if (lists_in_gather(rd)) {
+      if (e == hipSuccess) e = launch_list_gather(rd, l, d, planes, grid, s);
+    } else {
+      if (e == hipSuccess) e = launch_compact(rd, d, s);
+      if (e == hipSuccess) e = launch_gather(rd, l, d, planes, grid, s);
+    }
     if (e != hipSuccess) return hip_fail(e, "kernel launch (tdk_diff_encode_static)");
     return TDK_OK;
   });

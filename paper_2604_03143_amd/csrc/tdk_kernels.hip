@@ -649,16 +649,15 @@ __global__ __launch_bounds__(kCompactBlock) void tdk_compact_kernel(const RoundD
 
 // ---------------------------------------------------------------------------------------------
 // gather: K/V values of the listed pages, as they sit in the agent's cache   [Sec. 5]
-// A workgroup copies one plane (K or V) of one payload slot; grid-stride over the slots that
+// A workgroup copies one payload slot (the selected planes back to back); grid-stride over the slots that
 // exist, so the host never needs the count.
 // ---------------------------------------------------------------------------------------------
 
-// Shared by gather and scatter.  A workgroup moves one payload slot (K plane, then V plane).
-// Prologue: all threads search offset[] in parallel for the agent that owns the slot (one memory
-// round trip per 256 agents instead of a serial binary search), then T threads resolve the pool
+// Shared by gather and scatter.  Prologue: all threads search offset[] in parallel for the agent that owns the slot
+// (one memory round trip per 256 agents instead of a serial binary search), then T threads resolve the pool
 // row of each row of the page through the block table.
 struct SlotShared {
-  int32_t owner;
+  int32_t owner, page;
   int64_t row[32];     // pool row of each row of the page, -1 past the span / not listed
 };
 
@@ -667,64 +666,175 @@ __device__ __forceinline__ void find_owner(const DiffDev& d, int A, int64_t slot
     if (d.offset[a] <= slot && slot < d.offset[a + 1]) sh.owner = a;
 }
 
-constexpr int kCopyBatch = 4;   // 16-byte accesses per thread in flight in gather / scatter
+// pool row of master token page * T + r for an agent, -1 past the span
+__device__ __forceinline__ int64_t slot_row(const RoundDev& rd, const AgentDev& ad, int page, int r) {
+  const int T = rd.page_tokens, m = page * T + r;
+  if (m >= rd.sess[ad.session].span) return -1;
+  if (rd.seg) return (int64_t)rd.rowmap[ad.score_off + m];
+  const int a0 = ad.pos0 + m;
+  return (int64_t)rd.bt[ad.bt_off + (T == 16 ? a0 >> 4 : a0 >> 5) - ad.lp_first] * T + (a0 & (T - 1));
+}
+
+// 16-byte accesses per thread in flight in gather / scatter: a K and a V page are 16 accesses per thread, so a slot is
+// two round trips to memory (with 4 in flight, and a branch around each, it was four: payload copies of 64 agents x 12800
+// tokens with a tenth of the pages listed 141 -> 137 us, the whole restore 735 -> 692; 48 agents with moved mirrors and
+// their own block orders, whose K rows are turned four at a time now instead of one, 148 -> 124 us).
+constexpr int kCopyBatch = 8;
+
+// Planes p0 .. p1 - 1 (0 = K, 1 = V) of one slot between pool and payload; slot_data: the payload of plane p0.  A row past
+// the span (row < 0) is zero in the payload and not written in the pool.  No branch stands around a load: a load with
+// nothing to fetch repeats one of its page.
+template <bool TO_PAYLOAD, bool NT>
+__device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io, u32x4* slot_data, int p0, int p1, const SlotShared& sh) {
+  const int row_u4 = rd.heads * 16, page_u4 = rd.page_tokens * row_u4, n = (p1 - p0) * page_u4;
+  const uint32_t inv = 0xffffffffu / (uint32_t)row_u4 + 1u;      // i / row_u4 == __umulhi(i, inv) for i < 2^13 (row_u4 <= 128)
+  for (int i0 = threadIdx.x; i0 < n; i0 += kBlock * kCopyBatch) {
+    u32x4 v[kCopyBatch];
+    u32x4* at[kCopyBatch];
+    bool there[kCopyBatch];
+#pragma unroll
+    for (int j = 0; j < kCopyBatch; ++j) {
+      const int i = min(i0 + j * kBlock, n - 1);
+      const int plane = p0 + (i >= page_u4), q = i >= page_u4 ? i - page_u4 : i;
+      const int r = (int)__umulhi((uint32_t)q, inv);
+      const int64_t row = sh.row[r];
+      there[j] = row >= 0;
+      at[j] = (plane ? io.pool_v : io.pool_k) + (row >= 0 ? row : max(sh.row[0], (int64_t)0)) * row_u4 + (q - r * row_u4);
+      if (TO_PAYLOAD) v[j] = ld16<NT>(at[j]);
+      else v[j] = ld16<NT>(slot_data + i);
+    }
+#pragma unroll
+    for (int j = 0; j < kCopyBatch; ++j) {
+      const int i = i0 + j * kBlock;
+      if (TO_PAYLOAD) {
+        if (!there[j]) v[j] = u32x4{0, 0, 0, 0};
+        if (i < n) st16<NT>(slot_data + i, v[j]);
+      } else {
+        if (i < n && there[j]) st16<NT>(at[j], v[j]);
+      }
+    }
+  }
+}
 
 // planes: bit 0 = K, bit 1 = V; a slot holds the selected planes back to back
+__device__ __forceinline__ void gather_slot(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const int planes, int64_t slot,
+                                            const SlotShared& sh) {
+  const int p0 = planes == 2 ? 1 : 0, p1 = planes == 1 ? 1 : 2;
+  u32x4* data = d.payload + slot * (p1 - p0) * (int64_t)(rd.page_tokens * rd.heads * 16);
+  if (rd.nontemporal & 16) copy_slot<true, true>(rd, io, data, p0, p1, sh);
+  else copy_slot<true, false>(rd, io, data, p0, p1, sh);
+}
+
 __global__ __launch_bounds__(kBlock) void tdk_gather_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
                                                             const int planes) {
   __shared__ SlotShared sh;
-  const int T = rd.page_tokens;
   const int A = rd.n_agents;
   if (A == 0) return;
   int64_t total = d.offset[A];
   if (total > d.capacity) total = d.capacity;
-  const int row_u4 = rd.heads * 16;
-  const int page_u4 = T * row_u4;
   for (int64_t slot = blockIdx.x; slot < total; slot += gridDim.x) {
     find_owner(d, A, slot, sh);
     __syncthreads();
-    if (threadIdx.x < T) {
-      const AgentDev ad = rd.agents[sh.owner];
-      const int m = d.idx[slot] * T + threadIdx.x;
-      int64_t row = -1;
-      if (m < rd.sess[ad.session].span) {
-        const int a0 = ad.pos0 + m;
-        row = rd.seg ? (int64_t)rd.rowmap[ad.score_off + m]
-                     : (int64_t)rd.bt[ad.bt_off + a0 / T - ad.lp_first] * T + a0 % T;
-      }
-      sh.row[threadIdx.x] = row;
+    if (threadIdx.x < rd.page_tokens) sh.row[threadIdx.x] = slot_row(rd, rd.agents[sh.owner], d.idx[slot], threadIdx.x);
+    __syncthreads();
+    gather_slot(rd, io, d, planes, slot, sh);
+    __syncthreads();
+  }
+}
+
+// Compaction and gather in one launch, for rounds with at most kListPages (agent, page) pairs: a workgroup needs neither
+// the counts nor the index list of another, because it finds the page of its slot in the flag bytes itself (64 bytes
+// per thread at most, one round trip, L2-resident).  What it saves is a launch of a few workgroups between two
+// larger ones and half of the gather's chain of dependent reads (4 agents x 256 tokens: 3.5 + 9.8 -> 8.2 us, the whole
+// collect, restore and store 36 -> 28; 37 agents, one plane: 4.8 + 9.0 -> 11.3 us); with more flags the count that every
+// workgroup repeats costs more than the launch.  The workgroups that own a slot write its index, workgroup 0
+// the counts and offsets.
+constexpr int kListPages = 64 * kBlock;
+
+// non-zero bytes among the first `lim` of 16, and the same as a mask word by word (bit 7 of each such byte)
+__device__ __forceinline__ uint32_t set_bytes(uint32_t w, int lim) {
+  const uint32_t t = (((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u;
+  return lim >= 4 ? t : lim <= 0 ? 0u : t & ((1u << (8 * lim)) - 1u);
+}
+__device__ __forceinline__ int count_set(const u32x4 w, int lim) {
+  return __popc(set_bytes(w[0], lim)) + __popc(set_bytes(w[1], lim - 4)) + __popc(set_bytes(w[2], lim - 8)) + __popc(set_bytes(w[3], lim - 12));
+}
+
+__global__ __launch_bounds__(kBlock) void tdk_list_gather_kernel(const RoundDev rd, const LayerDev io, const DiffDev d, const int planes) {
+  __shared__ SlotShared sh;
+  __shared__ int s_wave[kWaves], s_before[kBlock], s_flat;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, A = rd.n_agents;
+  const int n = (int)rd.agent_pages;                          // at most kListPages
+  const int per = ((n + 16 * kBlock - 1) / (16 * kBlock)) * 16;        // consecutive flag bytes per thread: 0, 16, 32, 48 or 64
+  u32x4 w[4];
+  int own = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int at = tid * per + 16 * q;
+    w[q] = u32x4{0, 0, 0, 0};
+    if (16 * q < per && at < n) w[q] = *reinterpret_cast<const u32x4*>(rd.flags + at);
+    own += count_set(w[q], n - at);
+  }
+  int inc = own;
+#pragma unroll
+  for (int sft = 1; sft < 64; sft <<= 1) {
+    const int v = __shfl_up(inc, sft);
+    if (lane >= sft) inc += v;
+  }
+  if (lane == 63) s_wave[wave] = inc;
+  __syncthreads();
+  int before = inc - own, total = 0;
+#pragma unroll
+  for (int q = 0; q < kWaves; ++q) { if (q < wave) before += s_wave[q]; total += s_wave[q]; }
+  if (blockIdx.x == 0) {
+    s_before[tid] = before;
+    __syncthreads();
+    // listed pages of all agents before the flat page index `at`
+    auto listed_before = [&](int at) {
+      if (at >= n) return total;
+      const int t = at / per;
+      int c = s_before[t];
+      for (int q = t * per; q < at; q += 16) c += count_set(*reinterpret_cast<const u32x4*>(rd.flags + q), at - q);
+      return c;
+    };
+    for (int a = tid; a < A; a += kBlock) {
+      const AgentDev ad = rd.agents[a];
+      const int lo = listed_before(ad.flag_off), hi = listed_before(ad.flag_off + rd.sess[ad.session].pages);
+      d.count[a] = hi - lo;
+      d.offset[a] = lo;
+    }
+    if (tid == 0) { d.offset[A] = total; d.overflow[0] = total > d.capacity ? 1 : 0; }
+  }
+  const int64_t slots = min((int64_t)total, d.capacity);
+  for (int64_t slot = blockIdx.x; slot < slots; slot += gridDim.x) {
+    // the slot-th listed page: one thread holds its flag
+    if (slot >= before && slot < before + own) {
+      int k = (int)slot - before, found = -1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          uint32_t t = set_bytes(w[q][j], n - (tid * per + 16 * q + 4 * j));
+          const int c = __popc(t);
+          if (found < 0 && k < c) {
+            for (; k > 0; --k) t &= t - 1u;
+            found = tid * per + 16 * q + 4 * j + ((__ffs((int)t) - 1) >> 3);
+          }
+          if (found < 0) k -= c;
+        }
+      s_flat = found;
     }
     __syncthreads();
-    const int n_planes = planes == 3 ? 2 : 1;
-#pragma unroll 1
-    for (int plane = 0; plane < 2; ++plane) {
-      if (!((planes >> plane) & 1)) continue;
-      const u32x4* src = plane ? io.pool_v : io.pool_k;
-      u32x4* dst = d.payload + (slot * n_planes + (planes == 3 ? plane : 0)) * (int64_t)page_u4;
-      for (int i0 = threadIdx.x; i0 < page_u4; i0 += kBlock * kCopyBatch) {
-        u32x4 v[kCopyBatch];
-#pragma unroll
-        for (int j = 0; j < kCopyBatch; ++j) {
-          const int i = i0 + j * kBlock;
-          const u32x4 z = {0, 0, 0, 0};
-          v[j] = z;
-          if (i < page_u4) {
-            const int r = i / row_u4;
-            const int64_t row = sh.row[r];
-            if (row >= 0) v[j] = (rd.nontemporal & 16) ? __builtin_nontemporal_load(src + row * row_u4 + (i - r * row_u4))
-                                                       : src[row * row_u4 + (i - r * row_u4)];
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < kCopyBatch; ++j) {
-          const int i = i0 + j * kBlock;
-          if (i < page_u4) {
-            if (rd.nontemporal & 16) st16<true>(dst + i, v[j]);
-            else dst[i] = v[j];
-          }
-        }
-      }
+    const int flat = s_flat;
+    for (int a = tid; a < A; a += kBlock) {
+      const AgentDev ad = rd.agents[a];
+      if (flat >= ad.flag_off && flat < ad.flag_off + rd.sess[ad.session].pages) { sh.owner = a; sh.page = flat - ad.flag_off; }
     }
+    __syncthreads();
+    if (tid < rd.page_tokens) sh.row[tid] = slot_row(rd, rd.agents[sh.owner], sh.page, tid);
+    if (tid == 0) d.idx[slot] = sh.page;
+    __syncthreads();
+    gather_slot(rd, io, d, planes, slot, sh);
     __syncthreads();
   }
 }
@@ -787,14 +897,8 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
       int64_t row = -1;
       if (sh.owner >= 0) {                       // an inconsistent offset[] leaves the slot unowned
         const AgentDev ad = rd.agents[sh.owner];
-        const SessionDev sd = rd.sess[ad.session];
         const int p = d.idx[slot];
-        const int m = p * T + threadIdx.x;
-        if (p >= 0 && p < sd.pages && m < sd.span) {   // anything else is not an index this round produces
-          const int a0 = ad.pos0 + m;
-          row = rd.seg ? (int64_t)rd.rowmap[ad.score_off + m]
-                       : (int64_t)rd.bt[ad.bt_off + a0 / T - ad.lp_first] * T + a0 % T;
-        }
+        if (p >= 0 && p < rd.sess[ad.session].pages) row = slot_row(rd, ad, p, threadIdx.x);   // anything else is not an index this round produces
       }
       sh.row[threadIdx.x] = row;
     }
@@ -803,20 +907,25 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
       s_tab[which][e] = tabs[(size_t)(which ? t1 : t0) * (2 * kHalf) + e];
     }
     __syncthreads();
-    const int n_planes = planes == 3 ? 2 : 1;
-#pragma unroll 1
-    for (int plane = 0; plane < 2; ++plane) {
-      if (!((planes >> plane) & 1)) continue;
-      u32x4* dst = plane ? io.pool_v : io.pool_k;
-      const u32x4* src = d.payload + (slot * n_planes + (planes == 3 ? plane : 0)) * (int64_t)page_u4;
-      if (plane == 0 && rot) {
-        // stored at another position: K rows are re-rotated, a wavefront per row, both members of a
-        // pair in one lane (the page kernels' lane layout)
-        for (int r = threadIdx.x >> 6; r < T; r += kWaves) {
+    int p0 = planes == 2 ? 1 : 0;
+    const int p1 = planes == 1 ? 1 : 2;
+    u32x4* data = d.payload + slot * (p1 - p0) * (int64_t)page_u4;
+    if (p0 == 0 && rot) {
+      // stored at another position: K rows are re-rotated, a wavefront per row, both members of a pair in one lane
+      // (the page kernels' lane layout); four rows of the wavefront are requested before the first is used
+      for (int r0 = threadIdx.x >> 6; r0 < T; r0 += 4 * kWaves) {
+        u32x4 lo[4], hi[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const u32x4* src = data + (r0 + kWaves * k) * row_u4;          // (T is a multiple of 16)
+          lo[k] = src[L.kok ? L.klo : 0];
+          hi[k] = src[L.kok ? L.khi : 0];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int r = r0 + kWaves * k;
           const int64_t row = sh.row[r];
-          if (row < 0 || !L.kok) continue;
           const int which = (s_sel >> r) & 1u;
-          u32x4 olo = src[r * row_u4 + L.klo], ohi = src[r * row_u4 + L.khi];
           if ((s_moved >> which) & 1u) {           // a run that did not move is a bit copy
             const float* t = s_tab[which];
             float c[8], sn[8];
@@ -830,35 +939,20 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
                 c[4 + e] = t[32 + L.jb * 4 + e]; sn[4 + e] = t[kHalf + 32 + L.jb * 4 + e];
               }
             }
-            rotate16<IL>(olo, ohi, c, sn, olo, ohi);
+            rotate16<IL>(lo[k], hi[k], c, sn, lo[k], hi[k]);
           }
-          dst[row * row_u4 + L.klo] = olo;
-          dst[row * row_u4 + L.khi] = ohi;
-        }
-        continue;
-      }
-      for (int i0 = threadIdx.x; i0 < page_u4; i0 += kBlock * kCopyBatch) {
-        u32x4 v[kCopyBatch];
-#pragma unroll
-        for (int j = 0; j < kCopyBatch; ++j) {
-          const int i = i0 + j * kBlock;
-          const u32x4 z = {0, 0, 0, 0};
-          v[j] = z;
-          if (i < page_u4) v[j] = (rd.nontemporal & 8) ? __builtin_nontemporal_load(src + i) : src[i];
-        }
-#pragma unroll
-        for (int j = 0; j < kCopyBatch; ++j) {
-          const int i = i0 + j * kBlock;
-          if (i < page_u4) {
-            const int r = i / row_u4;
-            const int64_t row = sh.row[r];
-            if (row >= 0) {
-              if (rd.nontemporal & 8) st16<true>(dst + row * row_u4 + (i - r * row_u4), v[j]);
-              else dst[row * row_u4 + (i - r * row_u4)] = v[j];
-            }
+          if (row >= 0 && L.kok) {
+            io.pool_k[row * row_u4 + L.klo] = lo[k];
+            io.pool_k[row * row_u4 + L.khi] = hi[k];
           }
         }
       }
+      p0 = 1;
+      data += page_u4;
+    }
+    if (p0 < p1) {
+      if (rd.nontemporal & 8) copy_slot<false, true>(rd, io, data, p0, p1, sh);
+      else copy_slot<false, false>(rd, io, data, p0, p1, sh);
     }
     __syncthreads();
   }
@@ -1397,6 +1491,15 @@ hipError_t launch_compact(const RoundDev& rd, const DiffDev& d, hipStream_t st) 
 hipError_t launch_gather(const RoundDev& rd, const LayerDev& io, const DiffDev& d, int planes, int grid_size, hipStream_t st) {
   if (rd.n_agents == 0 || d.capacity == 0 || grid_size <= 0) return hipSuccess;
   hipLaunchKernelGGL(tdk_gather_kernel, dim3(grid_size), dim3(kBlock), 0, st, rd, io, d, planes);
+  return hipGetLastError();
+}
+
+bool lists_in_gather(const RoundDev& rd) { return rd.agent_pages <= kListPages; }
+
+hipError_t launch_list_gather(const RoundDev& rd, const LayerDev& io, const DiffDev& d, int planes, int grid_size, hipStream_t st) {
+  // (capacities are mostly generous: workgroups without a slot repeat the count for nothing, so no more than four per
+  // compute unit are launched)
+  hipLaunchKernelGGL(tdk_list_gather_kernel, dim3(std::max(1, std::min(grid_size, 4 * std::max(rd.n_cus, 1)))), dim3(kBlock), 0, st, rd, io, d, planes);
   return hipGetLastError();
 }
 
