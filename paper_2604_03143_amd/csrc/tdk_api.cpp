@@ -99,6 +99,9 @@ struct tdk_round {
 
 namespace {
 
+// K and V of one page
+int64_t page_pair_bytes(const tdk_round* r) { return (int64_t)r->model.page_tokens * r->model.num_kv_heads * r->model.head_dim * 4; }
+
 // group: agents per work item; read_group: the same for the kernels that only read (equal when the caller named one)
 tdk_status upload_work(tdk_round* r, int group, int read_group) {
   std::vector<WorkItem> work, rwork;
@@ -387,7 +390,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   r->rd.interleaved = model->rope_style == TDK_ROPE_INTERLEAVED;
   r->rd.nontemporal = r->flags & TDK_TUNE_ALL;
 
-  st = upload_work(r, plan_auto_group(r->sessions), plan_auto_group(r->sessions, true));
+  st = upload_work(r, plan_auto_group(r->sessions, false, page_pair_bytes(r)), plan_auto_group(r->sessions, true, page_pair_bytes(r)));
   if (st != TDK_OK) return st;
   for (int b = 0; b < 2 && e == hipSuccess; ++b) {
     e = hipEventCreateWithFlags(&r->ev_loaded[b], hipEventDisableTiming);
@@ -444,8 +447,8 @@ tdk_status tdk_round_tune(tdk_round* r, int32_t agents_per_group, int32_t flags)
     if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
     r->flags = flags;
     r->rd.nontemporal = flags & TDK_TUNE_ALL;
-    return upload_work(r, agents_per_group ? agents_per_group : plan_auto_group(r->sessions),
-                       agents_per_group ? agents_per_group : plan_auto_group(r->sessions, true));
+    return upload_work(r, agents_per_group ? agents_per_group : plan_auto_group(r->sessions, false, page_pair_bytes(r)),
+                       agents_per_group ? agents_per_group : plan_auto_group(r->sessions, true, page_pair_bytes(r)));
   });
 }
 

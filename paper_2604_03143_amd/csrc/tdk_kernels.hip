@@ -1389,10 +1389,11 @@ __global__ __launch_bounds__(kBlock) void tdk_page_read_product_kernel(const u32
 // launch is over before an imbalance between the XCDs can build up, and the hardware's own dispatch of fresh
 // workgroups fills freed wavefront slots sooner than a looping workgroup does): two workgroups per compute unit
 // that loop over the items (see below).  `queued_kernel` / `static_kernel` are the two instantiations.
+// `half_pages`: the call writes one of the two planes only.
 // `extra` static workgroups behind the page items (decode's payload copies on small rounds); returns whether they
 // were launched (only the static form takes them).
 template <class KernelQ, class KernelS, class... Args>
-static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, KernelS static_kernel, int extra, hipStream_t st, Args... args) {
+static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, KernelS static_kernel, bool half_pages, int extra, hipStream_t st, Args... args) {
   int n = 0;
   {
     static std::mutex mu;
@@ -1421,12 +1422,18 @@ static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, Kernel
   }
   const bool ride = extra > 0 && !large && (rd.nontemporal & 1024);
   RoundDev rs = rd;
-  rs.dyn_begin = rd.n_work;
+  if (half_pages) {
+    // single-plane restore: an item of the write list holds half the bytes it was cut for, the read list's items are
+    // coarser (37 agents x 2999 tokens, 4 heads, both planes stored and restored: 140 us on the one, 130 on the other)
+    rs.work = rd.rwork;
+    rs.n_work = rd.n_rwork;
+  }
+  rs.dyn_begin = rs.n_work;
   rs.dyn_count = 0;
-  if ((rd.nontemporal & 2048) && rd.n_work >= 64) {
+  if ((rd.nontemporal & 2048) && rs.n_work >= 64) {
     // the last fifth of the items is shared (see Items::first); twice as many workgroups as items stand by for it
-    const int tail = rd.n_work / 5;
-    rs.dyn_begin = rd.n_work - tail;
+    const int tail = rs.n_work / 5;
+    rs.dyn_begin = rs.n_work - tail;
     rs.dyn_count = 2 * tail;
   }
   hipLaunchKernelGGL(static_kernel, dim3((unsigned)(rs.dyn_begin + rs.dyn_count) + (ride ? (unsigned)extra : 0u)), dim3(kBlock), 0, st, rs, args...);
@@ -1465,7 +1472,7 @@ hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t s
     with_bool(rd.seg != 0, [&](auto sg) {
       constexpr int R = decltype(rpw)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
-      launch_write_pages(rd, tdk_rerotate_kernel<R, P, I, N, G, true>, tdk_rerotate_kernel<R, P, I, N, G, false>, 0, st, io);
+      launch_write_pages(rd, tdk_rerotate_kernel<R, P, I, N, G, true>, tdk_rerotate_kernel<R, P, I, N, G, false>, false, 0, st, io);
     });
   }); }); });
   return hipGetLastError();
@@ -1515,7 +1522,7 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
       constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
       *scattered = launch_write_pages(rd, tdk_decode_kernel<R, P, I, N, M, G, true>, tdk_decode_kernel<R, P, I, N, M, G, false>,
-                                      scatter_blocks, st, io, d, scatter_blocks);
+                                      planes != 3, scatter_blocks, st, io, d, scatter_blocks);
     }); });
   }); }); });
   return hipGetLastError();

@@ -253,7 +253,7 @@ void plan_work(const std::vector<PlanSession>& sessions, int group, bool taper, 
   }
 }
 
-int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels) {
+int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels, int64_t page_bytes) {
   // Measured on MI355X: about 9 agents per work item is the best trade between re-reads of the
   // master page (one per work item, served by the XCD's L2) and the number of work items; rounds
   // too small to give ~2800 items that way are split further (a launch of one workgroup per item then runs
@@ -262,9 +262,23 @@ int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels)
   // The kernels that only read have their own list: every item re-reads its master page, which costs them more
   // than the coarser end of their launch (the same session: compare kernel 87 us with 9 agents per item, 91 with 3),
   // so they stop splitting at ~900 items.
+  //
+  // An item must also be worth its start: about 8 us of dependent reads, during which the compute unit's other two
+  // workgroups have to keep its share of the memory busy (about 64 KB in 3 us each), so an item takes at least
+  // 1.3 x 64 KB of pages (K and V of one page of one agent: page_bytes); and with fewer than 3 agents the re-reads
+  // of the master page weigh as much as the pages.  25 agents x 5000 tokens, collect: 1 KV head (8 KB pages) 23 us
+  // with 3 agents per item, 18 with 9; 2 heads, restore 41 us with 3, 31 with 7; 8 heads 112 us with 1, 100 with 3.
+  // 48 agents with 32-token pages and their own block orders, restore: 130 us with 1, 110 with 2, 105 with 3.
   const int64_t target = read_kernels ? 900 : 2800;
-  int best = 9;
-  for (int g = 9; g >= 1; --g) {
+  // A round that cannot even give every compute unit an item is cut down to single agents all the same: nothing is
+  // saturated there, and the pages of an item are written one after another (4 agents x 256 tokens, collect + restore +
+  // store: 28.4 us with 1, 30.6 with 2).
+  int64_t pairs = 0;
+  for (const auto& s : sessions) pairs += (int64_t)s.pages * (int64_t)s.agents.size();
+  const int64_t worth = std::max<int64_t>(3, (85 * 1024 + page_bytes - 1) / std::max<int64_t>(page_bytes, 1));
+  const int floor = (int)std::min<int64_t>(kMaxGroup, std::max<int64_t>(1, std::min(worth, pairs / 256)));
+  int best = std::max(9, floor);
+  for (int g = best; g >= floor; --g) {
     int64_t items = 0;
     for (const auto& s : sessions) {
       const int n = (int)s.agents.size();
