@@ -1047,58 +1047,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
   attend_diff16_body<SEGMOVED>(rd, d, at, Vs, h, rest % rd.n_agents, rest / rd.n_agents, threadIdx.x);
 }
 
-// Both passes in one launch, for rounds with identity layouts and few query rows per agent: one ramp and one drain instead of two, and the listed-pages pass (bound by HBM) streams while
-// the master pass (bound by arithmetic and LDS latency) computes.  A workgroup of the listed-pages kind = four
-// wavefronts = four KV heads of one agent's piece; the pieces past 0, most of which leave at once, come last.
-// Where the kinds run (measured with clock stamps and the hardware ids of the compute units): the device deals
-// consecutive workgroup ids to the 8 XCDs, inside an XCD to its 4 shader engines in turn, inside an engine to its
-// compute units in turn, and the two slots of a compute unit receive ids 256 apart.  With the kinds alternating
-// in groups of 8 ids every engine holds one kind only; alternating in blocks of 32 puts both kinds on every
-// engine but still never on one compute unit; blocks of 256 pair one workgroup of each kind on every compute
-// unit.  The launch takes the same time in all three (the master workgroups slow down by what the listed ones
-// gain: both wait for memory, whose latency under this launch's own 60 MB in flight is 5 to 9 us), so the
-// simplest form stays.
-struct FusedGrid {
-  int32_t n_master;      // workgroups of the master pass: heads * (sessions * chunks) * row blocks
-  int32_t row_blocks;    // blocks of 128 query rows per session and KV head
-  int32_t n_diff0;       // workgroups of the listed-pages pass per piece: agents * head_groups
-  int32_t head_groups;   // ceil(heads / 4)
-};
-
-constexpr int kFusedLds = kMasterLds > kWaves * kTile * kVsStride * 2 ? kMasterLds : kWaves * kTile * kVsStride * 2;
-
-template <bool ROWS32>    // the listed-pages kind with 32-row tiles (17 to 32 rows per agent and KV head) or 16-row tiles
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void tdk_attend_fused_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
-                                                                  const AttendDev at, const FusedGrid fg) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds[kFusedLds];
-  const int bid = blockIdx.x;
-  // ids alternate between the kinds in groups of eight while both last (consecutive ids go to different XCDs,
-  // so both kinds reach every XCD, on different shader engines), then come the master workgroups that are left,
-  // then the other kind's
-  const int groups = min(fg.n_master, fg.n_diff0) >> 3;
-  int m_id = -1, d_id = -1;
-  if (bid < 16 * groups) {
-    const int at8 = (bid >> 4) * 8 + (bid & 7);
-    if (bid & 8) d_id = at8; else m_id = at8;
-  } else {
-    const int r = bid - 16 * groups, m_left = fg.n_master - 8 * groups;
-    if (r < m_left) m_id = 8 * groups + r; else d_id = 8 * groups + (r - m_left);
-  }
-  if (m_id >= 0) {
-    const int h = m_id % rd.heads, rest = m_id / rd.heads;
-    // the row blocks of one (chunk, KV head) get ids 8 apart: same XCD, one after the other, so the second
-    // finds the tiles in that XCD's L2
-    attend_master_body<false>(rd, io, d, at, lds, h, rest / fg.row_blocks, rest % fg.row_blocks);
-  } else {
-    const int piece = d_id / fg.n_diff0, rem = d_id - piece * fg.n_diff0;
-    const int agent = rem / fg.head_groups, h = (rem - agent * fg.head_groups) * kWaves + (threadIdx.x >> 6);
-    if (h >= rd.heads) return;
-    uint16_t* Vs = reinterpret_cast<uint16_t*>(lds) + (threadIdx.x >> 6) * (kTile * kVsStride);
-    if (ROWS32) attend_diff32_body(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
-    else attend_diff16_body<false, true>(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // One agent per wavefront: attention of rounds whose agents bring enough query rows of their own (prefill, and
 // every round with per-agent block orders).  A wavefront owns 32 query rows of ONE agent and KV head and
@@ -1659,6 +1607,238 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
 }
 
 // ---------------------------------------------------------------------------------------------
+// Packed rows (identity layouts, few rows per agent): the master pass for 128 query rows of a session's agents, whatever
+// agents they belong to, with the pipelined steps of the kernel above.  Rows of one wavefront have different agents, so the
+// listed pages are masked per lane; those pages are the listed-pages pass's work.
+// Where it is used (launch_attend_fused): at most two row blocks over every tile and a chip full of lists.  250 agents,
+// ten sessions, 1 query token 132 -> 128 us, 2 tokens 181 -> 159 us.  A workgroup starts up later here (two more tiles
+// and the first scores before the loop), which one session feels (28.5 -> 29.2 us), and with three row blocks or more
+// the plain form's calls of coming tiles into L2 serve several readers (100 agents x 25600 tokens 135 -> 138 us).
+// ---------------------------------------------------------------------------------------------
+struct PackedShared {
+  uint16_t k[2][kBigTile * kKsStride];
+  uint16_t v[2][kBigTile * kVsStride];
+  uint64_t mask[kRowsPerBlock * kMaskWords];              // bit p: page p of this chunk is listed in the row's agent's diff
+};
+
+// KV head h, chunk number `sc` = session * n_chunks + chunk, row block zb
+__device__ __forceinline__ void attend_packed_body(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at,
+                                                   PackedShared& sh, int h, int sc, int zb) {
+  const int session = sc / at.n_chunks, chunk = sc - session * at.n_chunks;
+  const SessionDev sd = rd.sess[session];
+  const int tok_begin = chunk * at.chunk_tokens;
+  if (tok_begin >= sd.span || sd.n_agents == 0) return;
+  const int rows = sd.n_agents * at.n_q * at.group;
+  const int row_begin = zb * kRowsPerBlock;
+  if (row_begin >= rows) return;
+  const int T = rd.page_tokens, lg = T == 16 ? 4 : 5;
+  const int tok_end = min(sd.span, tok_begin + at.chunk_tokens);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
+
+  // staging: sixteen lanes per token row, four rows per wavefront instruction; rows past the end repeat the last one
+  // (their scores are masked)
+  const int st_tok = threadIdx.x >> 4, st_pc = threadIdx.x & 15;
+  const uint32_t row_bytes = (uint32_t)rd.heads * 256u;
+  uint32_t voff[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) voff[e] = (uint32_t)(16 * e + st_tok) * row_bytes + 16u * st_pc;
+  const char* mk = reinterpret_cast<const char*>(io.master_k) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
+  const char* mv = reinterpret_cast<const char*>(io.master_v) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
+  const int steps = (tok_end - tok_begin + kBigTile - 1) / kBigTile, last = tok_end - tok_begin - 1;
+  u32x4 kreg[4], vreg[4];
+  auto fetch = [&](const char* base, int i, u32x4 (&r)[4]) __attribute__((always_inline)) {      // (a step past the last one repeats it)
+    const int ii = min(i, steps - 1), left = last - ii * kBigTile;
+    const char* tile = base + (int64_t)ii * kBigTile * row_bytes;
+    uint32_t off[4] = {voff[0], voff[1], voff[2], voff[3]};
+    if (left < kBigTile - 1)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) off[e] = (uint32_t)min(16 * e + st_tok, left) * row_bytes + 16u * st_pc;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) r[e] = *reinterpret_cast<const u32x4*>(tile + off[e]);
+  };
+  auto put_k = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.k[buf] + (16 * e + st_tok) * kKsStride + 8 * st_pc) = kreg[e];
+  };
+  auto put_v = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.v[buf] + (16 * e + st_tok) * kVsStride + 8 * st_pc) = vreg[e];
+  };
+  fetch(mk, 0, kreg);                                     // (asked for before the page masks are looked up)
+  fetch(mv, 0, vreg);
+
+  // which pages of this chunk each row's agent lists in its diff
+  if (threadIdx.x < kRowsPerBlock) {
+    uint64_t mask[kMaskWords] = {0, 0};
+    const RowRef rr = row_ref(rd, sd, at, h, row_begin + threadIdx.x);
+    if (rr.agent >= 0) {
+      int64_t lo = d.offset[rr.agent], hi = lo + d.count[rr.agent];
+      if (lo < 0) lo = 0;
+      if (hi > d.capacity) hi = d.capacity;
+      const int pg0 = tok_begin / T, pg1 = (tok_end - 1) / T;
+      int64_t a = lo, b = hi;
+      while (a < b) {                      // first listed page >= pg0
+        const int64_t mid = (a + b) >> 1;
+        if (d.idx[mid] < pg0) a = mid + 1; else b = mid;
+      }
+      for (; a < hi; ++a) {
+        const int p = d.idx[a];
+        if (p > pg1 || p < pg0) break;
+        const int rel_p = p - pg0;
+        if (rel_p < 64) mask[0] |= (uint64_t)1 << rel_p; else mask[1] |= (uint64_t)1 << (rel_p - 64);
+      }
+    }
+    sh.mask[kMaskWords * threadIdx.x] = mask[0];
+    sh.mask[kMaskWords * threadIdx.x + 1] = mask[1];
+  }
+
+  // this lane's query row, rotated back by its agent's offset: its B operands stay in registers
+  const RowRef mine = row_ref(rd, sd, at, h, row_begin + wave * kRowsPerWave + n);
+  bf16x8 qf[8];
+  {
+    u32x4 raw[8];
+    const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + mine.out * kHeadDim);
+    const uint32_t flip = at.q_flip ? 0x80008000u : 0u;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      u32x4 v = {0, 0, 0, 0};
+      if (mine.agent >= 0) v = qp[2 * kk + hh];
+      raw[kk] = u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip};
+    }
+    turn_back32(raw, rd.tab + (size_t)(mine.agent >= 0 ? mine.agent : 0) * (2 * kHalf), rd.interleaved, hh, qf);
+  }
+  put_k(0);
+  put_v(0);
+  fetch(mk, 1, kreg);
+  put_k(1);
+  __syncthreads();
+
+  // which 16-token groups of step i the lane's agent lists (bit g: group g), read ahead of their use
+  const uint64_t* my_masks = sh.mask + kMaskWords * (wave * kRowsPerWave + n);
+  auto listed = [&](int i) __attribute__((always_inline)) {
+    const uint32_t pg = (uint32_t)min(i, steps - 1) * kBigTile >> lg;              // four pages of 16 tokens or two of 32
+    const uint32_t m = (uint32_t)(my_masks[pg >> 6] >> (pg & 63u));
+    if (T == 16) return m & 0xfu;
+    return ((m & 1u) ? 0x3u : 0u) | ((m & 2u) ? 0xcu : 0u);
+  };
+  auto mask_scores = [&](int i, uint32_t m4, f32x16 (&s)[2], float& mx) __attribute__((always_inline)) {
+    const int left = last + 1 - i * kBigTile;
+    if (!__any(m4 != 0u) && left >= kBigTile) return;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const bool off = (m4 >> (2 * t + g)) & 1u;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[t][8 * g + e] = off ? -INFINITY : s[t][8 * g + e];
+      }
+    if (left < kBigTile) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (32 * t + 8 * (e >> 2) + 4 * hh + (e & 3) >= left) s[t][e] = -INFINITY;
+    }
+    rows_max<2>(s, mx);
+  };
+  RowState st;
+  row_state_init(st);
+  f32x16 s0[2], s1[2];
+  {
+    float mx;
+    rows_scores(sh.k[0], qf, n, hh, s0);
+    rows_max<2>(s0, mx);
+    mask_scores(0, listed(0), s0, mx);
+    rows_settle(mx, at.scale, st);
+  }
+  __syncthreads();                                        // the first step replaces its K tile
+  auto step = [&](int i, f32x16 (&s)[2], f32x16 (&nx)[2]) __attribute__((always_inline)) {
+    fetch(mk, i + 2, kreg);
+    fetch(mv, i + 1, vreg);
+    const uint32_t m4 = listed(i + 1);
+    float mx;
+    rows_step(sh.k[(i + 1) & 1], sh.v[i & 1], qf, s, nx, mx, at.scale, lane, st);
+    put_k(i & 1);                                         // (nobody reads these two buffers in this step)
+    put_v((i + 1) & 1);
+    if (i + 1 < steps) {
+      mask_scores(i + 1, m4, nx, mx);
+      rows_settle(mx, at.scale, st);
+    }
+    __syncthreads();
+  };
+  for (int i = 0; i < steps; i += 2) {
+    step(i, s0, s1);
+    if (i + 1 < steps) step(i + 1, s1, s0);
+  }
+
+  const float l_tot = st.l_run + __shfl_xor(st.l_run, 32);
+  if (mine.agent >= 0) {
+    const int64_t slot = mine.out * at.n_parts + chunk;
+    float4* po = reinterpret_cast<float4*>(at.part_o + slot * kHeadDim);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        po[(32 * b + 8 * q4 + 4 * hh) >> 2] = make_float4(st.oacc[b][4 * q4], st.oacc[b][4 * q4 + 1], st.oacc[b][4 * q4 + 2], st.oacc[b][4 * q4 + 3]);
+    if (hh == 0) { at.part_m[slot] = st.m_run; at.part_l[slot] = l_tot; }
+  }
+}
+
+// Both passes in one launch, for rounds with identity layouts and few query rows per agent: one ramp and one drain instead of two, and the listed-pages pass (bound by HBM) streams while
+// the master pass (bound by arithmetic and LDS latency) computes.  A workgroup of the listed-pages kind = four
+// wavefronts = four KV heads of one agent's piece; the pieces past 0, most of which leave at once, come last.
+// Where the kinds run (measured with clock stamps and the hardware ids of the compute units): the device deals
+// consecutive workgroup ids to the 8 XCDs, inside an XCD to its 4 shader engines in turn, inside an engine to its
+// compute units in turn, and the two slots of a compute unit receive ids 256 apart.  With the kinds alternating
+// in groups of 8 ids every engine holds one kind only; alternating in blocks of 32 puts both kinds on every
+// engine but still never on one compute unit; blocks of 256 pair one workgroup of each kind on every compute
+// unit.  The launch takes the same time in all three (the master workgroups slow down by what the listed ones
+// gain: both wait for memory, whose latency under this launch's own 60 MB in flight is 5 to 9 us), so the
+// simplest form stays.
+struct FusedGrid {
+  int32_t n_master;      // workgroups of the master pass: heads * (sessions * chunks) * row blocks
+  int32_t row_blocks;    // blocks of 128 query rows per session and KV head
+  int32_t n_diff0;       // workgroups of the listed-pages pass per piece: agents * head_groups
+  int32_t head_groups;   // ceil(heads / 4)
+};
+
+static_assert(kWaves * kTile * kVsStride * 2 <= (int)sizeof(PackedShared) && kMasterLds <= (int)sizeof(PackedShared), "one allocation for all");
+
+template <bool ROWS32, bool PIPELINED>    // PIPELINED: the master kind with pipelined steps; ROWS32: the listed-pages kind with 32-row tiles (17 to 32 rows per agent and KV head) or 16-row tiles
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void tdk_attend_fused_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
+                                                                  const AttendDev at, const FusedGrid fg) {
+  constexpr int kLds = PIPELINED ? (int)sizeof(PackedShared) : kMasterLds > kWaves * kTile * kVsStride * 2 ? kMasterLds : kWaves * kTile * kVsStride * 2;
+  __shared__ __attribute__((aligned(16))) unsigned char lds[kLds];
+  const int bid = blockIdx.x;
+  // ids alternate between the kinds in groups of eight while both last (consecutive ids go to different XCDs,
+  // so both kinds reach every XCD, on different shader engines), then come the master workgroups that are left,
+  // then the other kind's
+  const int groups = min(fg.n_master, fg.n_diff0) >> 3;
+  int m_id = -1, d_id = -1;
+  if (bid < 16 * groups) {
+    const int at8 = (bid >> 4) * 8 + (bid & 7);
+    if (bid & 8) d_id = at8; else m_id = at8;
+  } else {
+    const int r = bid - 16 * groups, m_left = fg.n_master - 8 * groups;
+    if (r < m_left) m_id = 8 * groups + r; else d_id = 8 * groups + (r - m_left);
+  }
+  if (m_id >= 0) {
+    const int h = m_id % rd.heads, rest = m_id / rd.heads;
+    // the row blocks of one (chunk, KV head) get ids 8 apart: same XCD, one after the other, so the second
+    // finds the tiles in that XCD's L2
+    if (PIPELINED) attend_packed_body(rd, io, d, at, *reinterpret_cast<PackedShared*>(lds), h, rest / fg.row_blocks, rest % fg.row_blocks);
+    else attend_master_body<false>(rd, io, d, at, lds, h, rest / fg.row_blocks, rest % fg.row_blocks);
+  } else {
+    const int piece = d_id / fg.n_diff0, rem = d_id - piece * fg.n_diff0;
+    const int agent = rem / fg.head_groups, h = (rem - agent * fg.head_groups) * kWaves + (threadIdx.x >> 6);
+    if (h >= rd.heads) return;
+    uint16_t* Vs = reinterpret_cast<uint16_t*>(lds) + (threadIdx.x >> 6) * (kTile * kVsStride);
+    if (ROWS32) attend_diff32_body(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
+    else attend_diff16_body<false, true>(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // merge: out = sum_c o_c e^(m_c - M) / sum_c l_c e^(m_c - M), lse = M + log(that sum); one wavefront per row
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void tdk_attend_merge_kernel(const RoundDev rd, const DiffDev d, const AttendDev at) {
@@ -1776,8 +1956,13 @@ hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const Dif
   fg.n_diff0 = rd.n_agents * fg.head_groups;
   const int64_t blocks = (int64_t)fg.n_master + (int64_t)fg.n_diff0 * at.piece_grid;
   if (blocks == 0) return hipSuccess;
-  if (at.n_q * at.group > 16) hipLaunchKernelGGL(tdk_attend_fused_kernel<true>, dim3((unsigned)blocks), dim3(kBlock), 0, st, rd, io, d, at, fg);
-  else hipLaunchKernelGGL(tdk_attend_fused_kernel<false>, dim3((unsigned)blocks), dim3(kBlock), 0, st, rd, io, d, at, fg);
+  const bool pipelined = fg.row_blocks <= 2 && (int64_t)rd.n_agents * rd.heads > rd.n_cus;      // (see attend_packed_body)
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, rd, io, d, at, fg); };
+  if (at.n_q * at.group > 16) {
+    if (pipelined) launch(tdk_attend_fused_kernel<true, true>); else launch(tdk_attend_fused_kernel<true, false>);
+  } else {
+    if (pipelined) launch(tdk_attend_fused_kernel<false, true>); else launch(tdk_attend_fused_kernel<false, false>);
+  }
   return hipGetLastError();
 }
 

@@ -118,3 +118,18 @@ def test_empty_spans(tdo, n_q, Hq):
         assert (out == 0).all() and torch.isneginf(lse).all()
     finally:
         r.destroy()
+
+
+@pytest.mark.parametrize("T,style,span,scale,grow", [(16, 0, 63, None, False), (16, 1, 64, 1.0, True), (32, 0, 65, -0.2, False),
+                                                     (16, 0, 193, None, True), (32, 1, 700, None, False)])
+def test_packed_rows_of_many_lists(tdo, T, style, span, scale, grow):
+    """36 agents x 8 KV heads (more lists than compute units) in two sessions, 3 rows per agent and KV head: the master pass
+    with pipelined steps, at spans around a step, with listed pages and ragged ends."""
+    spec = wl.RoundSpec("rows7", 97, 1, 8, 128, T, 1.0e6, 2, 18, 1, span, 3, 200, 0.25)
+    _case(tdo, spec, 1, 24, style=style, scale=scale, grow=np.arange(36) * 5 if grow else None)
+
+
+def test_packed_rows_in_two_blocks_and_several_chunks(tdo):
+    """18 rows per agent and KV head: two blocks of 128 rows, the second not full; a span of several chunks."""
+    spec = wl.RoundSpec("rows8", 98, 1, 8, 128, 16, 1.0e6, 3, 12, 3, 500, 3, 200, 0.1)
+    _case(tdo, spec, 9, 16)
