@@ -638,12 +638,14 @@ bool attend_plan(const tdk_round* r, int32_t n_q, int32_t n_q_heads, AttendPlan&
   //   head, 49 against 52 with 20; ten sessions: 268 against 329 us with 20 rows), worse from 33 rows on (40 rows:
   //   94 against 70 us, ten sessions 575 against 460 us; 320 rows: 462 against 206 us).
   //   With per-agent block orders the packed form needs a copy of every row per segment and reloads a tile's queries
-  //   lane by lane: it is better only with few rows per agent on a chip that is full without splitting lists
-  //   (5 rows: ten sessions 237 against 465 us, but one session 75 against 62 us; 20 rows: ten sessions 647 against
-  //   506 us, one session 107 against 70 us).
+  //   lane by lane: it is better only with few rows per agent, whose 32-row tiles are mostly empty, and only where that
+  //   waste outweighs its start, from about 100 steps of 64 tokens per compute unit on, counting every agent and KV head
+  //   (5 rows: 62 steps per unit 75 packed against 62 us, 617 steps 237 against 465 us; 4 rows, 168 steps 100 against
+  //   117 us; 20 rows: 62 steps 107 against 70 us, 617 steps 647 against 506 us).
   const int64_t lists = (int64_t)r->n_agents * r->model.num_kv_heads;
+  const int64_t agent_steps = r->total_tokens / 64 * r->model.num_kv_heads;
   p.own_rows = agent_rows > 32 || r->total_master_rows == 0 || lists >= ((int64_t)1 << 27) ||
-               (r->rd.seg && (agent_rows > 16 || lists <= r->n_cus));
+               (r->rd.seg && (agent_rows > 16 || agent_steps <= 100 * (int64_t)r->n_cus));
   if (p.own_rows) {
     const int64_t per_agent = (agent_rows + 31) / 32, cus = r->n_cus;
     // Chunks of the span: workgroups of four wavefronts, two of which share a compute unit (each then takes about

@@ -45,18 +45,17 @@ def test_few_rows_with_stored_positions_moved(tdo, n_q, grow):
         _case(tdo, spec, n_q, 6, style=style, grow=grow)
 
 
-@pytest.mark.parametrize("n_agents,H,n_q,Hq,T,moved", [(3, 1, 33, 1, 16, False), (40, 8, 1, 16, 16, False), (40, 8, 1, 16, 16, True),
-                                                       (40, 8, 3, 48, 32, True), (5, 2, 12, 8, 32, True)])
-def test_borders_of_blocks_anywhere(tdo, n_agents, H, n_q, Hq, T, moved):
+@pytest.mark.parametrize("n_agents,H,n_q,Hq,T,moved,span", [(3, 1, 33, 1, 16, False, 397), (40, 8, 1, 16, 16, False, 5301), (40, 8, 1, 16, 16, True, 5301),
+                                                            (40, 8, 1, 16, 16, True, 397), (40, 8, 3, 48, 32, True, 397), (5, 2, 12, 8, 32, True, 397)])
+def test_borders_of_blocks_anywhere(tdo, n_agents, H, n_q, Hq, T, moved, span):
     """Agents whose segment borders differ from agent to agent (cuts at random tokens, the segments in random order):
-    steps end at the borders of every agent of a workgroup.  40 agents x 8 KV heads with few rows take the packed
-    form, the others one agent per wavefront."""
+    steps end at the borders of every agent of a workgroup.  40 agents x 8 KV heads with few rows over
+    5301 tokens take the packed form, the others one agent per wavefront."""
     import torch
     from paper_2604_03143_amd import tdk
     import gpu_helpers as gh
-    span = 397
     spec = wl.RoundSpec("rows5", 85, 1, H, 128, T, 1.0e6, 1, n_agents, 1, span, 300, 700, 0.25)
-    rnd = wl.make_round(spec)
+    rnd = wl.make_round(spec, perturbed_per_agent=min(spec.span_pages, 12))
     g = np.random.default_rng([85, n_agents, T])
     rnd.segments = []
     for i in range(n_agents):
@@ -90,7 +89,7 @@ def test_borders_of_blocks_anywhere(tdo, n_agents, H, n_q, Hq, T, moved):
                               tdk.attend_io(gh.up(q), n_q, Hq, scale, out, lse, ws, nbytes))
         torch.cuda.synchronize()
         ab.assert_within(out.cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64),
-                         want_o, want_l, tol_o, tol_l, what=(n_agents, H, n_q, Hq, T, moved))
+                         want_o, want_l, tol_o, tol_l, what=(n_agents, H, n_q, Hq, T, moved, span))
     finally:
         r.destroy()
 
