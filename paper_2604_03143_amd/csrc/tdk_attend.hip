@@ -1048,8 +1048,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 }
 
 // ---------------------------------------------------------------------------------------------
-// One agent per wavefront: attention of rounds whose agents bring enough query rows of their own (prefill, and
-// every round with per-agent block orders).  A wavefront owns 32 query rows of ONE agent and KV head and
+// One agent per wavefront: attention of rounds whose agents bring enough query rows of their own (prefill, and with
+// per-agent block orders also fewer rows, up to the work attend_plan names).  A wavefront owns 32 query rows of ONE agent and KV head and
 // walks the span in 64-token steps; the four wavefronts of a workgroup share the master's K and V tiles in LDS,
 // whatever agents they belong to.  Because the rows of a wavefront have one agent, everything that depends on
 // the agent is uniform: the pages its diff lists (a bit mask in LDS; most steps have none and skip the masking),
@@ -1611,11 +1611,9 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
 // agents they belong to, with the pipelined steps of the kernel above.  Rows of one wavefront have different agents, so the
 // listed pages are masked per lane; those pages are the listed-pages pass's work.
 // Where it is used (launch_attend_fused): at most two row blocks over every tile, a chip full of lists and chunks of at
-// least eight steps.  250 agents,
-// ten sessions, 1 query token 132 -> 128 us, 2 tokens 181 -> 159 us.  A workgroup starts up later here (two more tiles
-// and the first scores before the loop), which one session feels (28.5 -> 29.2 us) and spans of a few steps (207 tokens:
-// 19.5 -> 19.7 us), and with three row blocks or more
-// the plain form's calls of coming tiles into L2 serve several readers (100 agents x 25600 tokens 135 -> 138 us).
+// least eight steps.  250 agents, ten sessions, 1 query token 132 -> 128 us, 2 tokens 181 -> 159 us.  A workgroup starts
+// up later here (two more tiles and the first scores before the loop), which one session feels (28.5 -> 29.2 us) and spans
+// of a few steps (207 tokens: 19.5 -> 19.7 us), and with three row blocks or more the plain form's calls of coming tiles into L2 serve several readers (100 agents x 25600 tokens 135 -> 138 us).
 // ---------------------------------------------------------------------------------------------
 struct PackedShared {
   uint16_t k[2][kBigTile * kKsStride];
