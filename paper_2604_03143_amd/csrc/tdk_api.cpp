@@ -785,7 +785,8 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     at.scale = std::fmax(std::fabs(a->scale), 1e-30f);
     at.q_flip = std::signbit(a->scale) ? 1 : 0;
     at.max_seg = r->max_segments;
-    at.diff_seg = r->rd.seg && r->seg_moved ? r->max_segments : 1;
+    at.seg_moved = r->rd.seg && r->seg_moved ? 1 : 0;
+    at.diff_seg = at.seg_moved ? r->max_segments : 1;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const LayerDev l = layer_dev(io);
     const DiffDev d = diff_dev(in);

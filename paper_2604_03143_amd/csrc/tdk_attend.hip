@@ -495,10 +495,10 @@ __global__ __launch_bounds__(kBlock) void tdk_attend_qrot_kernel(const RoundDev 
   }
   // the queries the listed pages meet: as they are, or turned back by the distance the stored values
   // have moved since they were encoded (then one such copy per segment: diff_seg copies per row)
-  for (int k = 0; k < (at.diff_seg > 1 ? nseg : 1); ++k) {
+  for (int k = 0; k < (at.seg_moved ? nseg : 1); ++k) {
     uint16_t* dst2 = reinterpret_cast<uint16_t*>(at.qdiff) + (row * at.diff_seg + k) * kHeadDim;
     uint16_t za = (uint16_t)(src[ia] ^ flip), zb = (uint16_t)(src[ib] ^ flip);
-    if (at.diff_seg > 1) {
+    if (at.seg_moved) {
       const float* td = rd.segtab_diff + (size_t)(seg0 + k) * (2 * kHalf);   // identity tables copy exactly
       const float c2 = td[lane], s2 = td[kHalf + lane];
       if (c2 != 1.f || s2 != 0.f) {
@@ -1934,7 +1934,7 @@ hipError_t launch_attend_diff(const RoundDev& rd, const DiffDev& d, const Attend
   const int64_t blocks = (int64_t)rd.heads * rd.n_agents * at.piece_grid;
   if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)blocks);
-  if (at.diff_seg > 1) hipLaunchKernelGGL(tdk_attend_diff16_kernel<true>, grid, dim3(64), 0, st, rd, d, at);
+  if (at.seg_moved) hipLaunchKernelGGL(tdk_attend_diff16_kernel<true>, grid, dim3(64), 0, st, rd, d, at);
   else hipLaunchKernelGGL(tdk_attend_diff16_kernel<false>, grid, dim3(64), 0, st, rd, d, at);
   return hipGetLastError();
 }
@@ -1976,7 +1976,7 @@ hipError_t launch_attend_rows(const RoundDev& rd, const LayerDev& io, const Diff
   if (blocks == 0) return hipSuccess;
   if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)blocks);
-  if (rd.seg && at.diff_seg > 1) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, true>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
+  if (rd.seg && at.seg_moved) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, true>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
   else if (rd.seg) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
   else hipLaunchKernelGGL((tdk_attend_rows_kernel<false, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
   return hipGetLastError();

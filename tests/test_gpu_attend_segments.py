@@ -1,0 +1,63 @@
+"""Attention over rounds with per-agent segment lists, in the forms that block permutations do not produce: layouts of a
+single segment.  Bounds as in test_gpu_attend.py."""
+import numpy as np
+import pytest
+
+import attend_bounds as ab
+from paper_2604_03143_amd import workload as wl
+from helpers import OracleRun
+
+pytestmark = pytest.mark.gpu
+
+
+def segment_case(tdo, spec, segments, diff_pos, n_q, Hq, style=0, scale=None, perturbed=None):
+    """segments[i]: agent i's rows (first master token, position, tokens); diff_pos[i]: where each of them started when the
+    mirrors were stored."""
+    import torch
+    from paper_2604_03143_amd import tdk
+    import gpu_helpers as gh
+    rnd = wl.make_round(spec, perturbed_per_agent=perturbed)
+    rnd.segments = segments(rnd)
+    o = OracleRun(tdo, rnd, style=style)
+    o.rerotate(); o.perturb()
+    d = o.encode()
+    seg_diff = diff_pos(rnd)
+    A, n = rnd.n_agents, int(d.offset[-1])
+    assert n > 0
+    g = np.random.default_rng([spec.stream, n_q, Hq])
+    q = wl.f32_to_bf16_bits(g.standard_normal((A, n_q, Hq, 128)).astype(np.float32))
+    scale = 1.0 / np.sqrt(128.0) if scale is None else scale
+    hr = tdo.HostRound(rnd, diff_pos0=rnd.agent_pos0, segment_diff_pos=seg_diff)
+    want_o, want_l, tol_o, tol_l = ab.expected_and_bounds(tdo, o.g, hr, o.mk, o.mv, d, q, n_q, Hq, scale)
+    r = tdk.round_from_workload(rnd, style=style, diff_pos0=rnd.agent_pos0, segment_diff_pos=seg_diff)
+    try:
+        mk, mv, dq = gh.up(o.mk), gh.up(o.mv), gh.up(q)
+        cnt, off = torch.from_numpy(d.count).cuda(), torch.from_numpy(d.offset).cuda()
+        idx, pay = torch.from_numpy(d.idx[:n].copy()).cuda(), gh.up(d.payload[:n].copy())
+        ovf = torch.zeros(1, dtype=torch.int32, device="cuda")
+        nbytes = tdk.tdk_attend_workspace_bytes(r, n_q, Hq)
+        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+        out = torch.full((A, n_q, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+        lse = torch.full((A, n_q, Hq), float("nan"), dtype=torch.float32, device="cuda")
+        tdk.tdk_attend_shared(r, 0, tdk.layer_io(mk, mv, None, None, 0), tdk.diff(cnt, off, idx, pay, n, ovf),
+                              tdk.attend_io(dq, n_q, Hq, scale, out, lse, ws, nbytes))
+        torch.cuda.synchronize()
+        return ab.assert_within(out.cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64),
+                                want_o, want_l, tol_o, tol_l, what=(spec.name, n_q, Hq, style))
+    finally:
+        r.destroy()
+
+
+# rows per agent and KV head: 3 and 16 (16-row tiles for the listed pages), 18 and 40 (32-row tiles); the last round is
+# large enough for the form that packs the rows of several agents
+@pytest.mark.parametrize("n_agents,H,n_q,Hq,T,style,span", [(4, 2, 1, 6, 16, 0, 250), (5, 1, 4, 4, 32, 1, 97), (4, 2, 6, 6, 16, 1, 250),
+                                                            (3, 2, 5, 16, 32, 0, 129), (40, 8, 1, 16, 16, 0, 5301)])
+def test_one_segment_per_agent_stored_elsewhere(tdo, n_agents, H, n_q, Hq, T, style, span):
+    """Every agent's layout is one segment, stored when it began 37 + 11 i tokens earlier (one agent's did not move): the
+    listed pages meet rows turned back by that distance.  Scale 1: near one-hot weights, so that rows that are not turned
+    move the results far outside the bound."""
+    spec = wl.RoundSpec("one", 101, 1, H, 128, T, 1.0e6, 1, n_agents, 1, span, 600, 900, 0.3)
+    segments = lambda rnd: [np.array([[0, int(p), span]], np.int64) for p in rnd.agent_pos0]
+    moved = lambda rnd: [s[:, 1] - (0 if i == 1 else 37 + 11 * i) for i, s in enumerate(rnd.segments)]
+    segment_case(tdo, spec, segments, moved, n_q, Hq, style=style, scale=1.0 if span < 1000 else None,
+                 perturbed=min(spec.span_pages, 12))
