@@ -605,134 +605,25 @@ tdk_status tdk_check_layer(tdk_round* r, int32_t layer, const tdk_layer_io* io, 
   });
 }
 
-namespace {
-
-// Shape of the attention pass for a round: tokens per workgroup of the master pass, parts per query
-// row, and the layout of the caller's workspace.
-struct AttendPlan {
-  int32_t chunk_tokens = 0, n_chunks = 0, n_parts = 0, max_rows = 0, n_pieces = 1, piece_tokens = 0;
-  bool    own_rows = false;        // one agent per wavefront (tdk_attend_rows_kernel)
-  int32_t max_agents = 0;
-  int64_t rows = 0;
-  size_t o_qrot = 0, o_qdiff = 0, o_part_o = 0, o_part_m = 0, o_part_l = 0, bytes = 0;
-};
-
-bool attend_plan(const tdk_round* r, int32_t n_q, int32_t n_q_heads, AttendPlan& p) {
-  if (!r || n_q < 1 || n_q_heads < 1 || n_q_heads % r->model.num_kv_heads) return false;
-  const int32_t G = n_q_heads / r->model.num_kv_heads;
-  int64_t max_span = 0, max_agents = 0;
-  for (const auto& hs : r->sessions) {
-    if (hs.agents.empty()) continue;
-    max_span = std::max<int64_t>(max_span, hs.span);
-    max_agents = std::max<int64_t>(max_agents, (int64_t)hs.agents.size());
-  }
-  const int64_t max_rows = max_agents * n_q * G;
-  if (max_rows >= (int64_t)1 << 30) return false;
-  p.max_rows = (int32_t)max_rows;
-  p.rows = (int64_t)r->n_agents * n_q * n_q_heads;
-  p.max_agents = (int32_t)max_agents;
-  const int64_t agent_rows = (int64_t)n_q * G;
-  // Which kernels: one agent per wavefront, or the rows of a session's agents packed into one block.
-  //   Packed rows waste no place in the 32-row tiles, but their listed pages need a pass and partial results of their
-  //   own: better for few rows per agent (25 agents, one session: 28 against 49 us with 5 rows per agent and KV
-  //   head, 49 against 52 with 20; ten sessions: 268 against 329 us with 20 rows), worse from 33 rows on (40 rows:
-  //   94 against 70 us, ten sessions 575 against 460 us; 320 rows: 462 against 206 us).
-  //   With per-agent block orders the packed form needs a copy of every row per segment and reloads a tile's queries
-  //   lane by lane: it is better only with few rows per agent, whose 32-row tiles are mostly empty, and only where that
-  //   waste outweighs its start, from about 100 steps of 64 tokens per compute unit on, counting every agent and KV head
-  //   (5 rows: 62 steps per unit 75 packed against 62 us, 617 steps 237 against 465 us; 4 rows, 168 steps 100 against
-  //   117 us; 20 rows: 62 steps 107 against 70 us, 617 steps 647 against 506 us).
-  const int64_t lists = (int64_t)r->n_agents * r->model.num_kv_heads;
-  const int64_t agent_steps = r->total_tokens / 64 * r->model.num_kv_heads;
-  p.own_rows = agent_rows > 32 || r->total_master_rows == 0 || lists >= ((int64_t)1 << 27) ||
-               (r->rd.seg && (agent_rows > 16 || agent_steps <= 100 * (int64_t)r->n_cus));
-  if (p.own_rows) {
-    const int64_t per_agent = (agent_rows + 31) / 32, cus = r->n_cus;
-    // Chunks of the span: workgroups of four wavefronts, two of which share a compute unit (each then takes about
-    // 1.6 times as long).  In units of a 64-token step (about 1.2 us): a workgroup starts up in 8, a step with
-    // per-agent block orders costs 2 (query reloads at the borders), a second launch to merge costs 6 and the
-    // traffic of the partial results.  (16 query tokens, 25 agents: 1, 2, 4, 8 chunks take 104, 74, 68, 79 us without
-    // listed pages; per-agent orders, 4 tokens: 1, 4, 8, 12 chunks 252, 87, 70, 85 us.)
-    double best = -1;
-    const int k_lo = (int)std::max<int64_t>(1, (max_span + 16383) / 16384);
-    for (int k = k_lo; k < k_lo + 32; ++k) {
-      const int64_t c = std::max<int64_t>(64, ((max_span + k - 1) / k + 63) / 64 * 64);
-      if (k > k_lo && c * (k - 1) >= max_span) continue;       // the same chunks as a smaller k
-      int64_t wgs = 0;
-      for (const auto& hs : r->sessions)
-        if (!hs.agents.empty()) wgs += (((int64_t)hs.span + c - 1) / c) * (((int64_t)hs.agents.size() * per_agent + 3) / 4);
-      wgs *= r->model.num_kv_heads;
-      const double one = (double)(c / 64) * (r->rd.seg ? 2 : 1) + 8;
-      const int64_t full = wgs / (2 * cus), rest = wgs % (2 * cus);
-      const double cost = one * (1.6 * (double)full + (rest == 0 ? 0.0 : rest > cus ? 1.6 : 1.0)) +
-                          (max_span > c ? 6 + (double)p.rows * ((double)max_span / (double)c + 1) * 1024 / 6e6 : 0.0);
-      if (best < 0 || cost < best) { best = cost; p.chunk_tokens = (int32_t)c; }
-    }
-    p.n_chunks = (int32_t)((max_span + p.chunk_tokens - 1) / p.chunk_tokens);
-    p.n_pieces = 0;
-    p.piece_tokens = 512;          // (no listed-pages pass: the merge finds no pieces)
-    p.n_parts = std::max(p.n_chunks, 1);
-    size_t off = 0;
-    auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-    p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
-    p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
-    p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
-    p.bytes = std::max<size_t>(off, 256);
-    return true;
-  }
-  // Tokens per workgroup of the master pass.  A workgroup walks its chunk in steps of 64 tokens; two
-  // workgroups fit a compute unit at a time, so the pass takes about ceil(workgroups / slots) rounds of
-  // (steps per chunk + a fixed start-up cost of about two steps).  Of the chunk sizes that the 128-bit page
-  // mask per query row can cover, the one with the lowest such cost wins; ties go to the larger chunk
-  // (fewer partial results to merge).
-  const int64_t row_blocks = std::max<int64_t>(1, (max_rows + 127) / 128);
-  const int64_t slots = 2 * (int64_t)r->n_cus;
-  const int32_t max_chunk = std::min<int32_t>(128 * r->model.page_tokens, 4096);
-  // Chunks shorter than 512 tokens are not tried (unless the span is): a workgroup's start-up (page masks,
-  // query rotation, first rows) costs about as much as three steps, every chunk adds a partial result per row
-  // for the merge, and rounds small enough to consider such chunks are bounded by the listed-pages pass anyway
-  // (one session of 25 agents: 44 us with chunks of 128 tokens, 32 us with 512).
-  const int32_t min_chunk = (int32_t)std::min<int64_t>(512, (max_span + 63) / 64 * 64);
-  int32_t chunk = std::max(min_chunk, 64);
-  int64_t best = -1;
-  for (int32_t c = max_chunk; c >= std::max(min_chunk, 64); c -= 64) {
-    int64_t wgs = 0;
-    for (const auto& hs : r->sessions)
-      if (!hs.agents.empty()) wgs += ((int64_t)hs.span + c - 1) / c;
-    wgs *= r->model.num_kv_heads * row_blocks;
-    if (wgs == 0) break;
-    const int64_t cost = ((wgs + slots - 1) / slots) * (std::min<int64_t>(c, max_span + 63) / 64 + 2);
-    if (best < 0 || cost < best) { best = cost; chunk = c; }
-  }
-  p.chunk_tokens = chunk;
-  p.n_chunks = (int32_t)((max_span + chunk - 1) / chunk);
-  // the listed-pages pass: one wavefront takes a piece of an agent's list and every piece has its own partial result
-  {
-    int64_t max_pages = 0;
-    for (const auto& hs : r->sessions)
-      if (!hs.agents.empty()) max_pages = std::max<int64_t>(max_pages, hs.pages);
-    p.piece_tokens = attend_piece_tokens((int64_t)r->n_agents * r->model.num_kv_heads, r->n_cus);
-    p.n_pieces = (int32_t)std::max<int64_t>(1, (max_pages * r->model.page_tokens + p.piece_tokens - 1) / p.piece_tokens);
-  }
-  p.n_parts = p.n_chunks + p.n_pieces;
-  size_t off = 0;
-  auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-  if (r->rd.seg) {                 // copies of every query row per segment
-    p.o_qrot = place((size_t)p.rows * r->max_segments * kHeadDim * 2);
-    p.o_qdiff = place((size_t)p.rows * (r->seg_moved ? r->max_segments : 1) * kHeadDim * 2);
-  }
-  p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
-  p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
-  p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
-  p.bytes = std::max<size_t>(off, 256);
-  return true;
+// what the attention planner needs to know of a round
+static AttendShape attend_shape(const tdk_round* r) {
+  AttendShape s;
+  s.sessions = &r->sessions;
+  s.n_agents = r->n_agents;
+  s.heads = r->model.num_kv_heads;
+  s.page_tokens = r->model.page_tokens;
+  s.n_cus = r->n_cus;
+  s.seg = r->rd.seg != 0;
+  s.seg_moved = r->seg_moved;
+  s.max_segments = r->max_segments;
+  s.total_tokens = r->total_tokens;
+  s.total_master_rows = r->total_master_rows;
+  return s;
 }
-
-}  // namespace
 
 size_t tdk_attend_workspace_bytes(const tdk_round* r, int32_t n_q, int32_t n_q_heads) {
   AttendPlan p;
-  return attend_plan(r, n_q, n_q_heads, p) ? p.bytes : 0;
+  return r && attend_plan(attend_shape(r), n_q, n_q_heads, p) ? p.bytes : 0;
 }
 
 tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io, const tdk_diff* in,
@@ -747,13 +638,14 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     tdk_status st = check_diff(r, in, false);
     if (st != TDK_OK) return st;
     AttendPlan p;
-    if (!attend_plan(r, a->n_q, a->n_q_heads, p))
+    if (!attend_plan(attend_shape(r), a->n_q, a->n_q_heads, p))
       return fail(TDK_ERR_INVALID_ARG, "n_q must be >= 1 and n_q_heads a positive multiple of the KV heads");
     if (!std::isfinite(a->scale)) return fail(TDK_ERR_INVALID_ARG, "scale must be finite");
     if (p.rows == 0) return TDK_OK;
     if (!a->q || !a->out || !a->lse || !a->workspace) return fail(TDK_ERR_INVALID_ARG, "attend io holds a NULL buffer");
     if (((uintptr_t)a->q & 15) || ((uintptr_t)a->out & 15) || ((uintptr_t)a->workspace & 255))
       return fail(TDK_ERR_INVALID_ARG, "q / out must be 16-byte aligned, the workspace 256-byte aligned");
+    if (p.blocks >= kMaxBlocks) return hip_fail(hipErrorInvalidConfiguration, "attention launch larger than a grid");
     if (a->workspace_bytes < p.bytes) return fail(TDK_ERR_INVALID_ARG, "workspace smaller than tdk_attend_workspace_bytes()");
     if (r->total_master_rows > 0) {
       if (!io->master_k || !io->master_v) return fail(TDK_ERR_INVALID_ARG, "layer io holds a NULL master");
@@ -777,9 +669,7 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     at.n_parts = p.n_parts;
     at.n_pieces = p.n_pieces;
     at.piece_tokens = p.piece_tokens;
-    // most lists are far shorter than a whole session's pages: a few wavefronts per list walk its pieces in turn,
-    // instead of one launched wavefront per possible piece (nearly all of which would find nothing)
-    at.piece_grid = std::min<int32_t>(p.n_pieces, 4);
+    at.piece_grid = p.piece_grid;
     // the kernels take a positive scale: the sign travels with the query copies, and a zero scale (uniform
     // weights) becomes one so small that every scaled score rounds to zero
     at.scale = std::fmax(std::fabs(a->scale), 1e-30f);
@@ -795,7 +685,7 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
       if (p.n_chunks <= 1) return TDK_OK;
     } else if (!r->rd.seg) {
       // (master and listed pages in one launch, which also rotates the query rows itself)
-      TDK_LAUNCH(r, TDK_KERNEL_ATTEND_MASTER, s, launch_attend_fused(r->rd, l, d, at, p.max_rows, s));
+      TDK_LAUNCH(r, TDK_KERNEL_ATTEND_MASTER, s, launch_attend_fused(r->rd, l, d, at, p.fused, s));
     } else {
       TDK_LAUNCH(r, TDK_KERNEL_ATTEND_QROT, s, launch_attend_qrot(r->rd, at, s));
       TDK_LAUNCH(r, TDK_KERNEL_ATTEND_MASTER, s, launch_attend_master(r->rd, l, d, at, p.max_rows, s));

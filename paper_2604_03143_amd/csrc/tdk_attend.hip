@@ -747,7 +747,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // has).  The K rows go straight from the payload into the MFMA operand registers, the V rows through one
 // row-major tile in LDS.  32 query rows at a time.
 // ---------------------------------------------------------------------------------------------
-constexpr int kPieceTiles = 16;                // 512 listed tokens per piece at most (small rounds use shorter pieces)
 
 // Vs: this wavefront's V tile, kTile * kVsStride bf16 elements; lane: 0..63.
 __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const DiffDev& d, const AttendDev& at, uint16_t* Vs,
@@ -1795,13 +1794,6 @@ __device__ __forceinline__ void attend_packed_body(const RoundDev& rd, const Lay
 // unit.  The launch takes the same time in all three (the master workgroups slow down by what the listed ones
 // gain: both wait for memory, whose latency under this launch's own 60 MB in flight is 5 to 9 us), so the
 // simplest form stays.
-struct FusedGrid {
-  int32_t n_master;      // workgroups of the master pass: heads * (sessions * chunks) * row blocks
-  int32_t row_blocks;    // blocks of 128 query rows per session and KV head
-  int32_t n_diff0;       // workgroups of the listed-pages pass per piece: agents * head_groups
-  int32_t head_groups;   // ceil(heads / 4)
-};
-
 static_assert(kWaves * kTile * kVsStride * 2 <= (int)sizeof(PackedShared) && kMasterLds <= (int)sizeof(PackedShared), "one allocation for all");
 
 template <bool ROWS32, bool PIPELINED>    // PIPELINED: the master kind with pipelined steps; ROWS32: the listed-pages kind with 32-row tiles (17 to 32 rows per agent and KV head) or 16-row tiles
@@ -1939,21 +1931,8 @@ hipError_t launch_attend_diff(const RoundDev& rd, const DiffDev& d, const Attend
   return hipGetLastError();
 }
 
-int attend_piece_tokens(int64_t lists, int n_cus) {
-  // lists = agents x KV heads.  A piece is 512 tokens, unless the round is so small (at most one list per compute
-  // unit) that its few wavefronts would each walk ten or more tiles one after another while most
-  // of the chip idles: then 128.  (Shorter pieces in larger rounds cost more in start-up than they gain: the
-  // 100-agent long round 138 -> 162 us with pieces of 256 tokens.)
-  return (lists > n_cus ? kPieceTiles : kPieceTiles / 4) * kTile;
-}
-
 hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at,
-                               int max_rows, hipStream_t st) {
-  FusedGrid fg;
-  fg.row_blocks = (max_rows + kRowsPerBlock - 1) / kRowsPerBlock;
-  fg.n_master = rd.heads * rd.n_sessions * at.n_chunks * fg.row_blocks;
-  fg.head_groups = (rd.heads + kWaves - 1) / kWaves;
-  fg.n_diff0 = rd.n_agents * fg.head_groups;
+                               const FusedGrid& fg, hipStream_t st) {
   const int64_t blocks = (int64_t)fg.n_master + (int64_t)fg.n_diff0 * at.piece_grid;
   if (blocks == 0) return hipSuccess;
   const bool pipelined = fg.row_blocks <= 2 && (int64_t)rd.n_agents * rd.heads > rd.n_cus && at.chunk_tokens >= 512;      // (see attend_packed_body)

@@ -300,4 +300,145 @@ void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queue
   q_begin[8] = (int32_t)queued.size();
 }
 
+namespace {
+
+int attend_piece_tokens(int64_t lists, int n_cus) {
+  // lists = agents x KV heads.  A piece is 512 tokens, unless the round is so small (at most one list per compute
+  // unit) that its few wavefronts would each walk ten or more tiles one after another while most
+  // of the chip idles: then 128.  (Shorter pieces in larger rounds cost more in start-up than they gain: the
+  // 100-agent long round 138 -> 162 us with pieces of 256 tokens.)
+  return lists > n_cus ? 512 : 128;
+}
+
+size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+}  // namespace
+
+bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p) {
+  if (n_q < 1 || n_q_heads < 1 || n_q_heads % r.heads) return false;
+  const int32_t G = n_q_heads / r.heads;
+  int64_t max_span = 0, max_agents = 0;
+  for (const auto& hs : *r.sessions) {
+    if (hs.agents.empty()) continue;
+    max_span = std::max<int64_t>(max_span, hs.span);
+    max_agents = std::max<int64_t>(max_agents, (int64_t)hs.agents.size());
+  }
+  const int64_t max_rows = max_agents * n_q * G;
+  if (max_rows >= (int64_t)1 << 30) return false;
+  p.max_rows = (int32_t)max_rows;
+  p.rows = (int64_t)r.n_agents * n_q * n_q_heads;
+  const int64_t n_sessions = (int64_t)r.sessions->size();
+  auto times = [](int64_t a, int64_t b) { return a > 0 && b > INT64_MAX / a ? INT64_MAX : a * b; };
+  p.max_agents = (int32_t)max_agents;
+  const int64_t agent_rows = (int64_t)n_q * G;
+  // Which kernels: one agent per wavefront, or the rows of a session's agents packed into one block.
+  //   Packed rows waste no place in the 32-row tiles, but their listed pages need a pass and partial results of their
+  //   own: better for few rows per agent (25 agents, one session: 28 against 49 us with 5 rows per agent and KV
+  //   head, 49 against 52 with 20; ten sessions: 268 against 329 us with 20 rows), worse from 33 rows on (40 rows:
+  //   94 against 70 us, ten sessions 575 against 460 us; 320 rows: 462 against 206 us).
+  //   With per-agent block orders the packed form needs a copy of every row per segment and reloads a tile's queries
+  //   lane by lane: it is better only with few rows per agent, whose 32-row tiles are mostly empty, and only where that
+  //   waste outweighs its start, from about 100 steps of 64 tokens per compute unit on, counting every agent and KV head
+  //   (5 rows: 62 steps per unit 75 packed against 62 us, 617 steps 237 against 465 us; 4 rows, 168 steps 100 against
+  //   117 us; 20 rows: 62 steps 107 against 70 us, 617 steps 647 against 506 us).
+  const int64_t lists = (int64_t)r.n_agents * r.heads;
+  const int64_t agent_steps = r.total_tokens / 64 * r.heads;
+  p.own_rows = agent_rows > 32 || r.total_master_rows == 0 || lists >= ((int64_t)1 << 27) ||
+               (r.seg && (agent_rows > 16 || agent_steps <= 100 * (int64_t)r.n_cus));
+  if (p.own_rows) {
+    const int64_t per_agent = (agent_rows + 31) / 32, cus = r.n_cus;
+    // Chunks of the span: workgroups of four wavefronts, two of which share a compute unit (each then takes about
+    // 1.6 times as long).  In units of a 64-token step (about 1.2 us): a workgroup starts up in 8, a step with
+    // per-agent block orders costs 2 (query reloads at the borders), a second launch to merge costs 6 and the
+    // traffic of the partial results.  (16 query tokens, 25 agents: 1, 2, 4, 8 chunks take 104, 74, 68, 79 us without
+    // listed pages; per-agent orders, 4 tokens: 1, 4, 8, 12 chunks 252, 87, 70, 85 us.)
+    double best = -1;
+    const int k_lo = (int)std::max<int64_t>(1, (max_span + 16383) / 16384);
+    for (int k = k_lo; k < k_lo + 32; ++k) {
+      const int64_t c = std::max<int64_t>(64, ((max_span + k - 1) / k + 63) / 64 * 64);
+      if (k > k_lo && c * (k - 1) >= max_span) continue;       // the same chunks as a smaller k
+      int64_t wgs = 0;
+      for (const auto& hs : *r.sessions)
+        if (!hs.agents.empty()) wgs += (((int64_t)hs.span + c - 1) / c) * (((int64_t)hs.agents.size() * per_agent + 3) / 4);
+      wgs *= r.heads;
+      const double one = (double)(c / 64) * (r.seg ? 2 : 1) + 8;
+      const int64_t full = wgs / (2 * cus), rest = wgs % (2 * cus);
+      const double cost = one * (1.6 * (double)full + (rest == 0 ? 0.0 : rest > cus ? 1.6 : 1.0)) +
+                          (max_span > c ? 6 + (double)p.rows * ((double)max_span / (double)c + 1) * 1024 / 6e6 : 0.0);
+      if (best < 0 || cost < best) { best = cost; p.chunk_tokens = (int32_t)c; }
+    }
+    p.n_chunks = (int32_t)((max_span + p.chunk_tokens - 1) / p.chunk_tokens);
+    p.n_pieces = 0;
+    p.piece_tokens = 512;          // (no listed-pages pass: the merge finds no pieces)
+    p.n_parts = std::max(p.n_chunks, 1);
+    p.blocks = times(times(times(r.heads, (max_agents * per_agent + kWaves - 1) / kWaves), n_sessions), p.n_parts);
+    size_t off = 0;
+    auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
+    p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
+    p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
+    p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
+    p.bytes = std::max<size_t>(off, 256);
+    return true;
+  }
+  // Tokens per workgroup of the master pass.  A workgroup walks its chunk in steps of 64 tokens; two
+  // workgroups fit a compute unit at a time, so the pass takes about ceil(workgroups / slots) rounds of
+  // (steps per chunk + a fixed start-up cost of about two steps).  Of the chunk sizes that the 128-bit page
+  // mask per query row can cover, the one with the lowest such cost wins; ties go to the larger chunk
+  // (fewer partial results to merge).
+  const int64_t row_blocks = std::max<int64_t>(1, (max_rows + 127) / 128);
+  const int64_t slots = 2 * (int64_t)r.n_cus;
+  const int32_t max_chunk = std::min<int32_t>(128 * r.page_tokens, 4096);
+  // Chunks shorter than 512 tokens are not tried (unless the span is): a workgroup's start-up (page masks,
+  // query rotation, first rows) costs about as much as three steps, every chunk adds a partial result per row
+  // for the merge, and rounds small enough to consider such chunks are bounded by the listed-pages pass anyway
+  // (one session of 25 agents: 44 us with chunks of 128 tokens, 32 us with 512).
+  const int32_t min_chunk = (int32_t)std::min<int64_t>(512, (max_span + 63) / 64 * 64);
+  int32_t chunk = std::max(min_chunk, 64);
+  int64_t best = -1;
+  for (int32_t c = max_chunk; c >= std::max(min_chunk, 64); c -= 64) {
+    int64_t wgs = 0;
+    for (const auto& hs : *r.sessions)
+      if (!hs.agents.empty()) wgs += ((int64_t)hs.span + c - 1) / c;
+    wgs *= r.heads * row_blocks;
+    if (wgs == 0) break;
+    const int64_t cost = ((wgs + slots - 1) / slots) * (std::min<int64_t>(c, max_span + 63) / 64 + 2);
+    if (best < 0 || cost < best) { best = cost; chunk = c; }
+  }
+  p.chunk_tokens = chunk;
+  p.n_chunks = (int32_t)((max_span + chunk - 1) / chunk);
+  // the listed-pages pass: one wavefront takes a piece of an agent's list and every piece has its own partial result
+  {
+    int64_t max_pages = 0;
+    for (const auto& hs : *r.sessions)
+      if (!hs.agents.empty()) max_pages = std::max<int64_t>(max_pages, hs.pages);
+    p.piece_tokens = attend_piece_tokens((int64_t)r.n_agents * r.heads, r.n_cus);
+    p.n_pieces = (int32_t)std::max<int64_t>(1, (max_pages * r.page_tokens + p.piece_tokens - 1) / p.piece_tokens);
+  }
+  p.n_parts = p.n_chunks + p.n_pieces;
+  // Most lists are far shorter than a whole session's pages: a few wavefronts per list walk its pieces in turn,
+  // instead of one launched wavefront per possible piece (nearly all of which would find nothing).
+  p.piece_grid = std::min<int32_t>(p.n_pieces, 4);
+  // The launches, in 64 bits: the master pass has every session as wide as the widest one and as long as the longest,
+  // so rounds of very many sessions reach the limit of a grid long before their rows do.
+  const int64_t master = times(times(times(r.heads, row_blocks), n_sessions), p.n_chunks);
+  if (r.seg) {
+    p.blocks = std::max(master, times(lists, p.piece_grid));
+  } else {
+    const int64_t head_groups = (r.heads + kWaves - 1) / kWaves, diff0 = r.n_agents * head_groups;
+    p.blocks = master == INT64_MAX ? master : master + diff0 * p.piece_grid;
+    if (p.blocks < kMaxBlocks) p.fused = {(int32_t)master, (int32_t)row_blocks, (int32_t)diff0, (int32_t)head_groups};
+  }
+  size_t off = 0;
+  auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
+  if (r.seg) {                 // copies of every query row per segment
+    p.o_qrot = place((size_t)p.rows * r.max_segments * kHeadDim * 2);
+    p.o_qdiff = place((size_t)p.rows * (r.seg_moved ? r.max_segments : 1) * kHeadDim * 2);
+  }
+  p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
+  p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
+  p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
+  p.bytes = std::max<size_t>(off, 256);
+  return true;
+}
+
 }  // namespace tdk

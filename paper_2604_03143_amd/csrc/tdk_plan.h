@@ -55,4 +55,27 @@ void plan_work(const std::vector<PlanSession>& sessions, int group, bool taper, 
 void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queued, int32_t (&q_begin)[9]);
 int  plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels = false, int64_t page_bytes = 64 * 1024);   // agents per work item when the caller names none
 
+// Attention over mirrors that are never restored: what the planner needs to know of a round.
+struct AttendShape {
+  const std::vector<PlanSession>* sessions = nullptr;
+  int32_t n_agents = 0, heads = 1, page_tokens = 16, n_cus = 256, max_segments = 1;
+  bool seg = false, seg_moved = false;               // as in RoundPlan (any_segments, seg_moved)
+  int64_t total_tokens = 0, total_master_rows = 0;
+};
+
+constexpr int64_t kMaxBlocks = (int64_t)1 << 31;     // workgroups of one launch: ids are int32
+
+// Shape of the attention pass for a call: tokens per workgroup of the master pass, parts per query row, the launch, and
+// the layout of the caller's workspace.
+struct AttendPlan {
+  int32_t chunk_tokens = 0, n_chunks = 0, n_parts = 0, max_rows = 0, n_pieces = 1, piece_tokens = 0, piece_grid = 1;
+  bool    own_rows = false;        // one agent per wavefront (tdk_attend_rows_kernel)
+  int32_t max_agents = 0;
+  int64_t rows = 0;
+  int64_t blocks = 0;              // workgroups of the largest launch; the call is refused from kMaxBlocks on
+  FusedGrid fused{};               // the shared launch (identity layouts, not own_rows, blocks < kMaxBlocks)
+  size_t o_qrot = 0, o_qdiff = 0, o_part_o = 0, o_part_m = 0, o_part_l = 0, bytes = 0;
+};
+bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p);   // false: bad arguments
+
 }  // namespace tdk

@@ -48,4 +48,12 @@ struct alignas(16) PageTab {
   int32_t w;   // bit t: table t's run sat at another position when the stored diff was encoded
 };
 
+// Grid of the attention launch that holds the master pass and the listed-pages pass.
+struct FusedGrid {
+  int32_t n_master;      // workgroups of the master pass: heads * (sessions * chunks) * row blocks
+  int32_t row_blocks;    // blocks of 128 query rows per session and KV head
+  int32_t n_diff0;       // workgroups of the listed-pages pass per piece: agents * head_groups
+  int32_t head_groups;   // ceil(heads / 4)
+};
+
 }  // namespace tdk

@@ -1,0 +1,99 @@
+// Host-only driver for the attention planner (attend_plan in csrc/tdk_plan.cpp), built with AddressSanitizer and
+// UndefinedBehaviorSanitizer by tests/test_attend_plan.py.  Exit code 0 = clean.
+#include <algorithm>
+#include <cstdint>
+#include <cstdio>
+#include <string>
+#include <vector>
+
+#include "tdk_plan.h"
+
+using namespace tdk;
+
+static uint64_t rng_state = 0x2545F4914F6CDD1Dull;
+static uint32_t rnd() {                       // splitmix64, upper half
+  uint64_t z = (rng_state += 0x9E3779B97F4A7C15ull);
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  return (uint32_t)((z ^ (z >> 31)) >> 32);
+}
+static int64_t between(int64_t lo, int64_t hi) { return lo + (int64_t)(rnd() % (uint32_t)(hi - lo + 1)); }
+
+#define REQUIRE(c) do { if (!(c)) { std::fprintf(stderr, "case %d: requirement failed: %s (line %d)\n", cs, #c, __LINE__); return 1; } } while (0)
+
+struct Made {
+  std::vector<PlanSession> sessions;
+  AttendShape shape;
+  void add(int32_t span, int32_t agents) {
+    PlanSession s;
+    s.span = span;
+    s.pages = (span + shape.page_tokens - 1) / shape.page_tokens;
+    for (int32_t i = 0; i < agents; ++i) s.agents.push_back(shape.n_agents + i);
+    shape.n_agents += agents;
+    shape.total_tokens += (int64_t)span * agents;
+    shape.total_master_rows += span;
+    sessions.push_back(s);
+  }
+  const AttendShape& done() { shape.sessions = &sessions; return shape; }
+};
+
+static Made draw() {
+  Made m;
+  m.shape.heads = (int32_t)between(1, 8);
+  m.shape.page_tokens = rnd() % 2 ? 16 : 32;
+  m.shape.seg = rnd() % 2;
+  m.shape.seg_moved = m.shape.seg && rnd() % 2;
+  m.shape.max_segments = m.shape.seg ? (int32_t)between(1, 40) : 1;
+  const int n = (int)between(1, 10);
+  const int32_t agents = (int32_t)between(0, 60);
+  const int32_t span = rnd() % 4 ? (int32_t)between(1, 26000) : (int32_t)between(0, 70);
+  for (int i = 0; i < n; ++i) m.add(rnd() % 2 ? span : (int32_t)between(0, span), rnd() % 3 ? agents : (int32_t)between(0, agents));
+  return m;
+}
+
+// The launch of a plan, in 128 bits.
+static __int128 blocks_of(const AttendShape& s, const AttendPlan& p, int64_t agent_rows) {
+  const __int128 sessions = (__int128)s.sessions->size();
+  if (p.own_rows) return (__int128)s.heads * (((__int128)p.max_agents * ((agent_rows + 31) / 32) + 3) / 4) * sessions * std::max(p.n_chunks, 1);
+  const __int128 master = (__int128)s.heads * (((__int128)p.max_rows + 127) / 128) * sessions * p.n_chunks;
+  const __int128 lists = s.seg ? (__int128)s.heads * s.n_agents : (__int128)s.n_agents * ((s.heads + 3) / 4);
+  return s.seg ? std::max(master, lists * p.piece_grid) : master + lists * p.piece_grid;
+}
+
+static int check_grids() {
+  int cs = 0;
+  for (; cs < 3000; ++cs) {
+    Made m = draw();
+    const AttendShape& s = m.done();
+    const int32_t n_q = rnd() % 2 ? (int32_t)between(1, 9) : (int32_t)between(1, 200), group = (int32_t)between(1, 8);
+    AttendPlan p;
+    REQUIRE(attend_plan(s, n_q, group * s.heads, p));
+    if (s.n_agents == 0) continue;
+    REQUIRE((__int128)p.blocks == blocks_of(s, p, (int64_t)n_q * group) && p.blocks < kMaxBlocks);
+    if (!p.own_rows && !s.seg) {
+      REQUIRE((int64_t)p.fused.n_master + (int64_t)p.fused.n_diff0 * p.piece_grid == p.blocks);
+      REQUIRE(p.fused.n_master == (int64_t)s.heads * p.fused.row_blocks * (int64_t)s.sessions->size() * p.n_chunks);
+    }
+  }
+  // One wide session among very many small ones: the master pass's grid is all sessions times the widest, which does not
+  // fit 32 bits although rows, lists and pages do.  The plan says so instead of wrapping around.
+  for (int32_t group : {4, 32, 40}) {
+    Made m;
+    m.shape.heads = 8;
+    m.add(600, 8192);
+    for (int i = 1; i < 131072; ++i) m.add(16, 0);
+    const AttendShape& s = m.done();
+    AttendPlan p;
+    REQUIRE(attend_plan(s, 1, 8 * group, p));
+    REQUIRE((__int128)p.blocks == blocks_of(s, p, group));
+    REQUIRE((p.blocks >= kMaxBlocks) == (group >= 32));
+    REQUIRE(group < 32 || p.fused.n_master == 0);
+  }
+  return 0;
+}
+
+int main() {
+  if (check_grids()) return 1;
+  std::printf("attention planner: clean\n");
+  return 0;
+}
