@@ -65,6 +65,13 @@ struct RowState {
   f32x16 oacc[4];
 };
 
+// The maximum that goes with a partial sum.  A NaN score keeps a row's reference point at -infinity for as long as no step is
+// free of NaN, and the merge takes -infinity for an empty part: such a part says +infinity instead, and the row becomes NaN.
+__device__ __forceinline__ float part_max(float m_run, float l_tot) { return m_run == -INFINITY && l_tot != l_tot ? INFINITY : m_run; }
+
+// log-sum-exp of a row: -infinity for an empty one, NaN for a row with a NaN score
+__device__ __forceinline__ float row_lse(float m, float l) { return l > 0.f ? m + __logf(l) : l != l ? l : -INFINITY; }
+
 __device__ __forceinline__ void row_state_init(RowState& st) {
   st.m_run = -INFINITY;
   st.l_run = 0.f;
@@ -727,7 +734,7 @@ __device__ __forceinline__ void attend_master_body(const RoundDev& rd, const Lay
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
         po[(32 * b + 8 * q4 + 4 * hh) >> 2] = make_float4(rs.oacc[b][4 * q4], rs.oacc[b][4 * q4 + 1], rs.oacc[b][4 * q4 + 2], rs.oacc[b][4 * q4 + 3]);
-    if (hh == 0) { at.part_m[slot] = rs.m_run; at.part_l[slot] = l_tot; }
+    if (hh == 0) { at.part_m[slot] = part_max(rs.m_run, l_tot); at.part_l[slot] = l_tot; }
   }
 }
 
@@ -859,7 +866,7 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4)
           po[(32 * b + 8 * q4 + 4 * hh) >> 2] = make_float4(rs.oacc[b][4 * q4], rs.oacc[b][4 * q4 + 1], rs.oacc[b][4 * q4 + 2], rs.oacc[b][4 * q4 + 3]);
-      if (hh == 0) { at.part_m[slot] = rs.m_run; at.part_l[slot] = l_tot; }
+      if (hh == 0) { at.part_m[slot] = part_max(rs.m_run, l_tot); at.part_l[slot] = l_tot; }
     }
     wave_sync();                                 // before the next block's first tile overwrites the V tile
   }
@@ -1025,7 +1032,7 @@ __device__ __forceinline__ bool attend_diff16_piece(const RoundDev& rd, const Di
     float4* po = reinterpret_cast<float4*>(at.part_o + slot * kHeadDim);
 #pragma unroll
     for (int b = 0; b < 8; ++b) po[4 * b + g4] = make_float4(rs.oacc[b][0], rs.oacc[b][1], rs.oacc[b][2], rs.oacc[b][3]);
-    if (g4 == 0) { at.part_m[slot] = rs.m_run; at.part_l[slot] = l_tot; }
+    if (g4 == 0) { at.part_m[slot] = part_max(rs.m_run, l_tot); at.part_l[slot] = l_tot; }
   }
   return true;
 }
@@ -1590,12 +1597,12 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   float f = 1.f;
   if (rg.direct) {
     po = reinterpret_cast<float4*>(at.out + out * kHeadDim);
-    f = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    if (hh == 0) at.lse[out] = l_tot > 0.f ? st.m_run + __logf(l_tot) : -INFINITY;
+    f = l_tot > 0.f ? 1.f / l_tot : l_tot != l_tot ? l_tot : 0.f;
+    if (hh == 0) at.lse[out] = row_lse(st.m_run, l_tot);
   } else {
     const int64_t slot = out * at.n_parts + chunk;
     po = reinterpret_cast<float4*>(at.part_o + slot * kHeadDim);
-    if (hh == 0) { at.part_m[slot] = st.m_run; at.part_l[slot] = l_tot; }
+    if (hh == 0) { at.part_m[slot] = part_max(st.m_run, l_tot); at.part_l[slot] = l_tot; }
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -1779,7 +1786,7 @@ __device__ __forceinline__ void attend_packed_body(const RoundDev& rd, const Lay
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4)
         po[(32 * b + 8 * q4 + 4 * hh) >> 2] = make_float4(st.oacc[b][4 * q4], st.oacc[b][4 * q4 + 1], st.oacc[b][4 * q4 + 2], st.oacc[b][4 * q4 + 3]);
-    if (hh == 0) { at.part_m[slot] = st.m_run; at.part_l[slot] = l_tot; }
+    if (hh == 0) { at.part_m[slot] = part_max(st.m_run, l_tot); at.part_l[slot] = l_tot; }
   }
 }
 
@@ -1891,9 +1898,9 @@ __global__ __launch_bounds__(kBlock) void tdk_attend_merge_kernel(const RoundDev
   }
 #pragma unroll
   for (int sft = 32; sft > 0; sft >>= 1) L += __shfl_xor(L, sft);
-  const float inv = L > 0.f ? 1.f / L : 0.f;
+  const float inv = L > 0.f ? 1.f / L : L != L ? L : 0.f;
   reinterpret_cast<float2*>(at.out + row * kHeadDim)[lane] = make_float2(a0 * inv, a1 * inv);
-  if (lane == 0) at.lse[row] = L > 0.f ? M + __logf(L) : -INFINITY;
+  if (lane == 0) at.lse[row] = row_lse(M, L);
 }
 
 // ---------------------------------------------------------------------------------------------
