@@ -681,7 +681,7 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     const LayerDev l = layer_dev(io);
     const DiffDev d = diff_dev(in);
     if (p.own_rows) {
-      TDK_LAUNCH(r, TDK_KERNEL_ATTEND_MASTER, s, launch_attend_rows(r->rd, l, d, at, p.max_agents, s));
+      TDK_LAUNCH(r, TDK_KERNEL_ATTEND_MASTER, s, launch_attend_rows(r->rd, l, d, at, p.max_agents, p.launch_sessions, s));
       if (p.n_chunks <= 1) return TDK_OK;
     } else if (!r->rd.seg) {
       // (master and listed pages in one launch, which also rotates the query rows itself)

@@ -16,6 +16,7 @@
 // of many agents run tdk_attend_qrot_kernel, tdk_attend_master_kernel and tdk_attend_diff16_kernel one after another.
 #include "tdk_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace tdk {
@@ -1081,6 +1082,7 @@ struct RowsGrid {
   int32_t blocks;       // workgroups (four wavefronts) per (session, KV head, chunk), for the largest session
   int32_t per_agent;    // wavefronts per agent and KV head
   int32_t direct;       // the span is one chunk: write out / lse here instead of partial results
+  int32_t session0;     // first session of this launch
 };
 
 struct RowsShared {
@@ -1366,7 +1368,7 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   const int h = blockIdx.x % rd.heads, rest = blockIdx.x / rd.heads;
   const int wb = rest % rg.blocks, sc = rest / rg.blocks;
   const int n_ch = max(at.n_chunks, 1);
-  const int session = sc / n_ch, chunk = sc - session * n_ch;
+  const int s_local = sc / n_ch, chunk = sc - s_local * n_ch, session = rg.session0 + s_local;
   const SessionDev sd = rd.sess[session];
   if (wb * kWaves >= sd.n_agents * rg.per_agent) return;
   const int T = rd.page_tokens;
@@ -1953,19 +1955,24 @@ hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const Dif
 }
 
 hipError_t launch_attend_rows(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at, int max_agents,
-                              hipStream_t st) {
+                              int launch_sessions, hipStream_t st) {
   RowsGrid rg;
   rg.per_agent = (at.n_q * at.group + kRowsPerWave - 1) / kRowsPerWave;
   rg.blocks = (int)(((int64_t)max_agents * rg.per_agent + kWaves - 1) / kWaves);
   rg.direct = at.n_chunks <= 1;
-  const int64_t blocks = (int64_t)rd.heads * rg.blocks * rd.n_sessions * (at.n_chunks > 1 ? at.n_chunks : 1);
-  if (blocks == 0) return hipSuccess;
-  if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
-  const dim3 grid((unsigned)blocks);
-  if (rd.seg && at.seg_moved) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, true>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
-  else if (rd.seg) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
-  else hipLaunchKernelGGL((tdk_attend_rows_kernel<false, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
-  return hipGetLastError();
+  const int64_t per_session = (int64_t)rd.heads * rg.blocks * (at.n_chunks > 1 ? at.n_chunks : 1);
+  for (int s0 = 0; s0 < rd.n_sessions && per_session > 0; s0 += launch_sessions) {     // (nearly always one launch)
+    const int64_t blocks = per_session * std::min(launch_sessions, rd.n_sessions - s0);
+    if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
+    rg.session0 = s0;
+    const dim3 grid((unsigned)blocks);
+    if (rd.seg && at.seg_moved) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, true>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
+    else if (rd.seg) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
+    else hipLaunchKernelGGL((tdk_attend_rows_kernel<false, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_attend_merge(const RoundDev& rd, const DiffDev& d, const AttendDev& at, hipStream_t st) {

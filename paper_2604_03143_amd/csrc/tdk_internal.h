@@ -124,7 +124,7 @@ hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const Dif
                                const FusedGrid& fg, hipStream_t st);
 // one agent per wavefront (32 of its query rows); a span that is one chunk is finished here (no merge)
 hipError_t launch_attend_rows(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at, int max_agents,
-                              hipStream_t st);
+                              int launch_sessions, hipStream_t st);
 
 hipError_t launch_page_fill(u32x4* dst, const int32_t* ids, int n_pages, int page_u4, uint32_t word, hipStream_t st);
 hipError_t launch_page_read(const u32x4* src, const int32_t* ids, int n_pages, int page_u4, u32x4* sink, hipStream_t st);

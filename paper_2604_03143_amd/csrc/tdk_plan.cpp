@@ -371,7 +371,11 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     p.n_pieces = 0;
     p.piece_tokens = 512;          // (no listed-pages pass: the merge finds no pieces)
     p.n_parts = std::max(p.n_chunks, 1);
-    p.blocks = times(times(times(r.heads, (max_agents * per_agent + kWaves - 1) / kWaves), n_sessions), p.n_parts);
+    // A launch takes as many sessions as fit a grid: with four wavefronts per workgroup and short chunks it has up to 30
+    // times the workgroups of the packed form, and a round that fits that one has to fit this one too.
+    p.blocks = times(times(r.heads, (max_agents * per_agent + kWaves - 1) / kWaves), p.n_parts);
+    p.launch_sessions = (int32_t)std::min<int64_t>(std::max<int64_t>((kMaxBlocks - 1) / std::max<int64_t>(p.blocks, 1), 1), std::max<int64_t>(n_sessions, 1));
+    p.blocks = times(p.blocks, p.launch_sessions);
     size_t off = 0;
     auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));

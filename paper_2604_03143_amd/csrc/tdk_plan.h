@@ -71,6 +71,7 @@ struct AttendPlan {
   int32_t chunk_tokens = 0, n_chunks = 0, n_parts = 0, max_rows = 0, n_pieces = 1, piece_tokens = 0, piece_grid = 1;
   bool    own_rows = false;        // one agent per wavefront (tdk_attend_rows_kernel)
   int32_t max_agents = 0;
+  int32_t launch_sessions = 0;     // own_rows: sessions per launch
   int64_t rows = 0;
   int64_t blocks = 0;              // workgroups of the largest launch; the call is refused from kMaxBlocks on
   FusedGrid fused{};               // the shared launch (identity layouts, not own_rows, blocks < kMaxBlocks)

@@ -54,7 +54,7 @@ static Made draw() {
 // The launch of a plan, in 128 bits.
 static __int128 blocks_of(const AttendShape& s, const AttendPlan& p, int64_t agent_rows) {
   const __int128 sessions = (__int128)s.sessions->size();
-  if (p.own_rows) return (__int128)s.heads * (((__int128)p.max_agents * ((agent_rows + 31) / 32) + 3) / 4) * sessions * std::max(p.n_chunks, 1);
+  if (p.own_rows) return (__int128)s.heads * (((__int128)p.max_agents * ((agent_rows + 31) / 32) + 3) / 4) * p.launch_sessions * std::max(p.n_chunks, 1);
   const __int128 master = (__int128)s.heads * (((__int128)p.max_rows + 127) / 128) * sessions * p.n_chunks;
   const __int128 lists = s.seg ? (__int128)s.heads * s.n_agents : (__int128)s.n_agents * ((s.heads + 3) / 4);
   return s.seg ? std::max(master, lists * p.piece_grid) : master + lists * p.piece_grid;
@@ -70,6 +70,7 @@ static int check_grids() {
     REQUIRE(attend_plan(s, n_q, group * s.heads, p));
     if (s.n_agents == 0) continue;
     REQUIRE((__int128)p.blocks == blocks_of(s, p, (int64_t)n_q * group) && p.blocks < kMaxBlocks);
+    REQUIRE(!p.own_rows || p.launch_sessions == (int32_t)s.sessions->size());
     if (!p.own_rows && !s.seg) {
       REQUIRE((int64_t)p.fused.n_master + (int64_t)p.fused.n_diff0 * p.piece_grid == p.blocks);
       REQUIRE(p.fused.n_master == (int64_t)s.heads * p.fused.row_blocks * (int64_t)s.sessions->size() * p.n_chunks);
@@ -86,8 +87,11 @@ static int check_grids() {
     AttendPlan p;
     REQUIRE(attend_plan(s, 1, 8 * group, p));
     REQUIRE((__int128)p.blocks == blocks_of(s, p, group));
-    REQUIRE((p.blocks >= kMaxBlocks) == (group >= 32));
-    REQUIRE(group < 32 || p.fused.n_master == 0);
+    // (40 rows: a wavefront per agent, whose launch takes as many of the sessions as fit)
+    REQUIRE((p.blocks >= kMaxBlocks) == (group == 32));
+    REQUIRE(group == 4 || p.fused.n_master == 0);
+    REQUIRE(group != 40 || (p.own_rows && p.launch_sessions >= 1 && p.launch_sessions < 131072 &&
+                            (__int128)p.blocks / p.launch_sessions * (p.launch_sessions + 1) >= kMaxBlocks));
   }
   return 0;
 }
