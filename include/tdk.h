@@ -293,7 +293,9 @@ size_t tdk_attend_workspace_bytes(const tdk_round* r, int32_t n_q, int32_t n_q_h
  * paired diff as tdk_diff_encode wrote it.  All layouts: identity or per-agent segments (one rotated copy
  * of a query row per segment), diffs stored at the current or at other positions (diff_pos0 / diff_pos).
  * Master values must be finite.
- * The workspace holds partial results; a span that need not be split to fill the chip has none.
+ * The workspace holds partial results.  tdk_attend_workspace_bytes never gets smaller with n_q: what it asks for n_q
+ * query tokens serves every call on the round with fewer (a shorter call may be cut into more parts, and need more, than a
+ * longer one).
  * Allocates nothing, enqueues one to four kernels, does not synchronise.  Errors: INVALID_ARG (NULL,
  * misaligned, n_q < 1, n_q_heads not a multiple of H, scale not finite, workspace too small). */
 tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io, const tdk_diff* in,

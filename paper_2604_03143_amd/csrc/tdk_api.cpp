@@ -622,8 +622,7 @@ static AttendShape attend_shape(const tdk_round* r) {
 }
 
 size_t tdk_attend_workspace_bytes(const tdk_round* r, int32_t n_q, int32_t n_q_heads) {
-  AttendPlan p;
-  return r && attend_plan(attend_shape(r), n_q, n_q_heads, p) ? p.bytes : 0;
+  return r ? attend_workspace_bytes(attend_shape(r), n_q, n_q_heads) : 0;
 }
 
 tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io, const tdk_diff* in,

@@ -312,6 +312,15 @@ int attend_piece_tokens(int64_t lists, int n_cus) {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// the partial results of p.rows x p.n_parts, from byte `off` of the workspace on
+void place_parts(AttendPlan& p, size_t off) {
+  auto place = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
+  p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
+  p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
+  p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
+  p.bytes = std::max<size_t>(off, 256);
+}
+
 }  // namespace
 
 bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p) {
@@ -376,12 +385,7 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     p.blocks = times(times(r.heads, (max_agents * per_agent + kWaves - 1) / kWaves), p.n_parts);
     p.launch_sessions = (int32_t)std::min<int64_t>(std::max<int64_t>((kMaxBlocks - 1) / std::max<int64_t>(p.blocks, 1), 1), std::max<int64_t>(n_sessions, 1));
     p.blocks = times(p.blocks, p.launch_sessions);
-    size_t off = 0;
-    auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-    p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
-    p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
-    p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
-    p.bytes = std::max<size_t>(off, 256);
+    place_parts(p, 0);
     return true;
   }
   // Tokens per workgroup of the master pass.  A workgroup walks its chunk in steps of 64 tokens; two
@@ -433,16 +437,36 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     if (p.blocks < kMaxBlocks) p.fused = {(int32_t)master, (int32_t)row_blocks, (int32_t)diff0, (int32_t)head_groups};
   }
   size_t off = 0;
-  auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   if (r.seg) {                 // copies of every query row per segment
-    p.o_qrot = place((size_t)p.rows * r.max_segments * kHeadDim * 2);
-    p.o_qdiff = place((size_t)p.rows * (r.seg_moved ? r.max_segments : 1) * kHeadDim * 2);
+    p.o_qdiff = align_up((size_t)p.rows * r.max_segments * kHeadDim * 2, 256);
+    off = p.o_qdiff + align_up((size_t)p.rows * (r.seg_moved ? r.max_segments : 1) * kHeadDim * 2, 256);
   }
-  p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
-  p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
-  p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
-  p.bytes = std::max<size_t>(off, 256);
+  place_parts(p, off);
   return true;
+}
+
+// A short call may be cut into more parts than a long one, whose rows fill the chip by themselves, and may need more
+// memory; a program that sizes its workspace for its longest call expects it to serve the shorter ones.
+size_t attend_workspace_bytes(const AttendShape& r, int32_t n_q, int32_t n_q_heads) {
+  AttendPlan p;
+  if (!attend_plan(r, n_q, n_q_heads, p)) return 0;
+  const int64_t group = n_q_heads / r.heads;
+  size_t most = p.bytes;
+  for (int64_t n = 1; n < n_q;) {
+    AttendPlan one;
+    if (!attend_plan(r, (int32_t)n, n_q_heads, one)) return 0;
+    // Up to 32 rows per agent and KV head: every length by itself.  Beyond: the lengths with the same number of
+    // wavefronts per agent at once, since more rows add only to the cost of further parts and so never get more of them.
+    int64_t last = n;
+    if (n * group > 32) {
+      last = std::min<int64_t>(std::max<int64_t>((n * group + 31) / 32 * 32 / group, n), n_q);
+      one.rows = (int64_t)r.n_agents * last * n_q_heads;
+      place_parts(one, 0);
+    }
+    most = std::max(most, one.bytes);
+    n = last + 1;
+  }
+  return most;
 }
 
 }  // namespace tdk

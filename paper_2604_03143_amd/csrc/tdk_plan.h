@@ -78,5 +78,6 @@ struct AttendPlan {
   size_t o_qrot = 0, o_qdiff = 0, o_part_o = 0, o_part_m = 0, o_part_l = 0, bytes = 0;
 };
 bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p);   // false: bad arguments
+size_t attend_workspace_bytes(const AttendShape& r, int32_t n_q, int32_t n_q_heads);     // covers every call of up to n_q query tokens; 0: bad arguments
 
 }  // namespace tdk

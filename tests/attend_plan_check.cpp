@@ -96,8 +96,37 @@ static int check_grids() {
   return 0;
 }
 
+// A workspace sized for n_q query tokens serves every shorter call.
+static int check_workspace() {
+  int cs = 0;
+  for (; cs < 400; ++cs) {
+    Made m = draw();
+    const AttendShape& s = m.done();
+    const int32_t group = rnd() % 4 ? (int32_t)between(1, 9) : (int32_t)between(1, 48);
+    const int32_t top = (int32_t)between(1, 90);
+    size_t before = 0, need = 0;
+    for (int32_t n_q = 1; n_q <= top; ++n_q) {
+      AttendPlan p;
+      REQUIRE(attend_plan(s, n_q, group * s.heads, p));
+      need = std::max(need, p.bytes);
+      const size_t asked = attend_workspace_bytes(s, n_q, group * s.heads);
+      REQUIRE(asked >= need && asked >= before);
+      before = asked;
+    }
+  }
+  // 25 agents, 5000 tokens, 40 query heads on 8 KV heads: two query tokens need more than 64
+  Made m;
+  m.shape.heads = 8;
+  m.add(5000, 25);
+  AttendPlan two, long_call;
+  REQUIRE(attend_plan(m.done(), 2, 40, two) && attend_plan(m.done(), 64, 40, long_call));
+  REQUIRE(two.bytes > long_call.bytes && attend_workspace_bytes(m.done(), 64, 40) >= two.bytes);
+  REQUIRE(attend_workspace_bytes(m.done(), 0, 40) == 0 && attend_workspace_bytes(m.done(), 1, 41) == 0);
+  return 0;
+}
+
 int main() {
-  if (check_grids()) return 1;
+  if (check_grids() || check_workspace()) return 1;
   std::printf("attention planner: clean\n");
   return 0;
 }
