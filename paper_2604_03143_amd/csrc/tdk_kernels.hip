@@ -683,8 +683,10 @@ constexpr int kCopyBatch = 8;
 
 // Planes p0 .. p1 - 1 (0 = K, 1 = V) of one slot between pool and payload; slot_data: the payload of plane p0.  A row past
 // the span (row < 0) is zero in the payload and not written in the pool.  No branch stands around a load: a load with
-// nothing to fetch repeats one of its page.
-template <bool TO_PAYLOAD, bool NT>
+// nothing to fetch repeats one of its page.  NT: streaming stores; NTL: non-temporal loads.  (The gather's loads are always
+// ordinary ones: the next compare finds the pages it reads in the memory-side cache; 85 agents x 8914 tokens, one
+// page in 17 listed: 539 us with non-temporal loads, 528 with ordinary ones.)
+template <bool TO_PAYLOAD, bool NT, bool NTL>
 __device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io, u32x4* slot_data, int p0, int p1, const SlotShared& sh) {
   const int row_u4 = rd.heads * 16, page_u4 = rd.page_tokens * row_u4, n = (p1 - p0) * page_u4;
   const uint32_t inv = 0xffffffffu / (uint32_t)row_u4 + 1u;      // i / row_u4 == __umulhi(i, inv) for i < 2^13 (row_u4 <= 128)
@@ -700,8 +702,7 @@ __device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io
       const int64_t row = sh.row[r];
       there[j] = row >= 0;
       at[j] = (plane ? io.pool_v : io.pool_k) + (row >= 0 ? row : max(sh.row[0], (int64_t)0)) * row_u4 + (q - r * row_u4);
-      if (TO_PAYLOAD) v[j] = ld16<NT>(at[j]);
-      else v[j] = ld16<NT>(slot_data + i);
+      v[j] = ld16<NTL>(TO_PAYLOAD ? at[j] : slot_data + i);
     }
 #pragma unroll
     for (int j = 0; j < kCopyBatch; ++j) {
@@ -721,8 +722,8 @@ __device__ __forceinline__ void gather_slot(const RoundDev& rd, const LayerDev& 
                                             const SlotShared& sh) {
   const int p0 = planes == 2 ? 1 : 0, p1 = planes == 1 ? 1 : 2;
   u32x4* data = d.payload + slot * (p1 - p0) * (int64_t)(rd.page_tokens * rd.heads * 16);
-  if (rd.nontemporal & 16) copy_slot<true, true>(rd, io, data, p0, p1, sh);
-  else copy_slot<true, false>(rd, io, data, p0, p1, sh);
+  if (rd.nontemporal & 16) copy_slot<true, true, false>(rd, io, data, p0, p1, sh);
+  else copy_slot<true, false, false>(rd, io, data, p0, p1, sh);
 }
 
 __global__ __launch_bounds__(kBlock) void tdk_gather_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
@@ -868,6 +869,13 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
   const int row_u4 = rd.heads * 16;
   const int page_u4 = T * row_u4;
   const Lane L = lane_geometry<false>(rd.heads, T);
+  // Payload reads are streamed only where the payload and the masters together exceed the 256 MB memory-side cache: there
+  // they would push the masters out (250 agents, ten sessions, 94 and 297 MB of payload beside 205 MB of masters: whole restore
+  // 1040 and 1104 us with ordinary reads, 957 and 1000 streamed; 64 agents, 320 + 52 MB: 732 -> 692).  What fits is
+  // found there, if it was written or read lately, and streamed reads are slower (64 agents, 128 and 192 + 52 MB: 634 and
+  // 642 us, streamed 650 and 662; 212 agents of four sessions, 236 + 22 MB: 240 and 271).
+  const int64_t planes16 = planes == 3 ? 32 : 16;
+  const bool stream = (rd.nontemporal & 8) && (total * page_u4 + rd.master_rows * row_u4) * planes16 > (int64_t)256 << 20;
   for (int64_t slot = first; slot < total; slot += stride) {
     if (threadIdx.x == 0) sh.owner = -1;
     __syncthreads();
@@ -951,8 +959,9 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
       data += page_u4;
     }
     if (p0 < p1) {
-      if (rd.nontemporal & 8) copy_slot<false, true>(rd, io, data, p0, p1, sh);
-      else copy_slot<false, false>(rd, io, data, p0, p1, sh);
+      if (stream) copy_slot<false, true, true>(rd, io, data, p0, p1, sh);
+      else if (rd.nontemporal & 8) copy_slot<false, true, false>(rd, io, data, p0, p1, sh);
+      else copy_slot<false, false, false>(rd, io, data, p0, p1, sh);
     }
     __syncthreads();
   }
