@@ -873,9 +873,9 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
   // they would push the masters out (250 agents, ten sessions, 94 and 297 MB of payload beside 205 MB of masters: whole restore
   // 1040 and 1104 us with ordinary reads, 957 and 1000 streamed; 64 agents, 320 + 52 MB: 732 -> 692).  What fits is
   // found there, if it was written or read lately, and streamed reads are slower (64 agents, 128 and 192 + 52 MB: 634 and
-  // 642 us, streamed 650 and 662; 212 agents of four sessions, 236 + 22 MB: 240 and 271).
-  const int64_t planes16 = planes == 3 ? 32 : 16;
-  const bool stream = (rd.nontemporal & 8) && (total * page_u4 + rd.master_rows * row_u4) * planes16 > (int64_t)256 << 20;
+  // 642 us, streamed 650 and 662; 212 agents of four sessions, 236 + 22 MB: 240 and 271).  A call on one plane counts the other
+  // plane's half too: a program restores both in turn (20 agents, 52 + 133 MB a plane: 368 us, streamed 335).
+  const bool stream = (rd.nontemporal & 8) && (total * page_u4 + rd.master_rows * row_u4) * 32 > (int64_t)256 << 20;
   for (int64_t slot = first; slot < total; slot += stride) {
     if (threadIdx.x == 0) sh.owner = -1;
     __syncthreads();
