@@ -1432,10 +1432,8 @@ static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, Kernel
   const bool ride = extra > 0 && !large && (rd.nontemporal & 1024);
   RoundDev rs = rd;
   if (half_pages) {
-    // single-plane restore: an item of the write list holds half the bytes it was cut for, the read list's items are
-    // coarser (37 agents x 2999 tokens, 4 heads, both planes stored and restored: 140 us on the one, 130 on the other)
-    rs.work = rd.rwork;
-    rs.n_work = rd.n_rwork;
+    rs.work = rd.pwork;
+    rs.n_work = rd.n_pwork;
   }
   rs.dyn_begin = rs.n_work;
   rs.dyn_count = 0;

@@ -253,7 +253,7 @@ void plan_work(const std::vector<PlanSession>& sessions, int group, bool taper, 
   }
 }
 
-int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels, int64_t page_bytes) {
+int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels, int64_t page_bytes, int n_cus, int planes) {
   // Measured on MI355X: about 9 agents per work item is the best trade between re-reads of the
   // master page (one per work item, served by the XCD's L2) and the number of work items; rounds
   // too small to give ~2800 items that way are split further (a launch of one workgroup per item then runs
@@ -264,19 +264,31 @@ int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels,
   // so they stop splitting at ~900 items.
   //
   // An item must also be worth its start: about 8 us of dependent reads, during which the compute unit's other two
-  // workgroups have to keep its share of the memory busy (about 64 KB in 3 us each), so an item takes at least
-  // 1.3 x 64 KB of pages (K and V of one page of one agent: page_bytes); and with fewer than 3 agents the re-reads
-  // of the master page weigh as much as the pages.  25 agents x 5000 tokens, collect: 1 KV head (8 KB pages) 23 us
-  // with 3 agents per item, 18 with 9; 2 heads, restore 41 us with 3, 31 with 7; 8 heads 112 us with 1, 100 with 3.
-  // 48 agents with 32-token pages and their own block orders, restore: 130 us with 1, 110 with 2, 105 with 3.
+  // workgroups have to keep its share of the memory busy (about 64 KB in 3 us each).  So an item that writes takes at
+  // least 1.3 x 64 KB of pages, and with fewer than 3 agents the re-reads of the master page weigh as much as the
+  // pages.  25 agents x 5000 tokens, collect: 1 KV head (8 KB pages) 23 us with 3 agents per item, 18 with 9; 2 heads,
+  // restore 41 us with 3, 31 with 7; 8 heads 112 us with 1, 100 with 3.  48 agents with 32-token pages and their own block
+  // orders, restore: 130 us with 1, 110 with 2, 105 with 3.  Writing one plane, an item holds half the bytes and has a list of
+  // its own (37 agents x 2999 tokens, 4 heads, both planes stored and restored: 140 us with 3 agents per item, 130 with 6).
+  // Reading items are worth 3 agents at most, whatever their pages: the rows of several agents are in flight there anyway
+  // (2 heads, 1840 (agent, page) pairs, store of one plane: 12.2 us with 2, 12.4 with 3, 13.5 with 6; 1 head, 3150 pairs, check
+  // layer 16.2 with 3, 18.3 with 11; 8 heads, 1260 pairs, store 33.2 with 1, 26.3 with 3).
+  //
+  // A round too small to fill the chip with such items is cut finer: nothing is saturated there, and an item's pages are
+  // written one after another.  The line is one pair per compute unit and agent of an item; for pages above 64 KB as much
+  // more as the pages are larger for the kernels that write, for smaller pages half as much again for those that read.
+  // 8 heads, 32-token pages, collect of 532 pairs: 14.7 us with 1 agent per item, 17.3 with 2; restore of 1140 pairs: 39.9 with
+  // 1, 38.3 with 2, 42.2 with 3; store of 532 pairs 54.0 with 1, 50.0 with 2; check layer of 1180 pairs 33.2 with 1, 29.5 with 3.
+  // 16-token pages, restore of 1148 pairs: 20.9 with 1, 18.1 with 3; 1 head, 900 pairs: 8.9 with 1, 6.3 with 3; store of one
+  // plane, 702 pairs: 15.2 with 1, 16.0 with 2; four agents x 256 tokens, collect + restore + store: 28.4 with 1, 30.6 with 2.
   const int64_t target = read_kernels ? 900 : 2800;
-  // A round that cannot even give every compute unit an item is cut down to single agents all the same: nothing is
-  // saturated there, and the pages of an item are written one after another (4 agents x 256 tokens, collect + restore +
-  // store: 28.4 us with 1, 30.6 with 2).
   int64_t pairs = 0;
   for (const auto& s : sessions) pairs += (int64_t)s.pages * (int64_t)s.agents.size();
-  const int64_t worth = std::max<int64_t>(3, (85 * 1024 + page_bytes - 1) / std::max<int64_t>(page_bytes, 1));
-  const int floor = (int)std::min<int64_t>(kMaxGroup, std::max<int64_t>(1, std::min(worth, pairs / 256)));
+  const int64_t item_bytes = std::max<int64_t>(planes == 2 ? page_bytes : page_bytes / 2, 1);
+  const int64_t worth = read_kernels ? 3 : std::max<int64_t>(3, (85 * 1024 + item_bytes - 1) / item_bytes);
+  const int64_t cus = std::max(n_cus, 1), kLarge = 64 * 1024;
+  const int64_t per_agent = read_kernels ? (page_bytes > kLarge ? cus : cus * 3 / 2) : cus * std::max<int64_t>(1, page_bytes / kLarge);
+  const int floor = (int)std::min<int64_t>(kMaxGroup, std::max<int64_t>(1, std::min(worth, pairs / per_agent)));
   int best = std::max(9, floor);
   for (int g = best; g >= floor; --g) {
     int64_t items = 0;

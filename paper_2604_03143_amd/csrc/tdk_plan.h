@@ -53,7 +53,9 @@ tdk_status plan_round(const tdk_model* model, const tdk_session* sessions, int32
 // items grouped by that XCD (queue x = queued[q_begin[x] .. q_begin[x + 1])).
 void plan_work(const std::vector<PlanSession>& sessions, int group, bool taper, std::vector<WorkItem>& work);
 void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queued, int32_t (&q_begin)[9]);
-int  plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels = false, int64_t page_bytes = 64 * 1024);   // agents per work item when the caller names none
+// agents per work item when the caller names none; page_bytes: K and V of one page; planes: written by the call (2, or 1)
+int  plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels = false, int64_t page_bytes = 64 * 1024,
+                     int n_cus = 256, int planes = 2);
 
 // Attention over mirrors that are never restored: what the planner needs to know of a round.
 struct AttendShape {

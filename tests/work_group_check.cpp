@@ -1,0 +1,47 @@
+// Host-only driver for the rule that sizes the page kernels' work items (csrc/tdk_plan.cpp), built by
+// tests/test_work_groups.py.  Exit code 0 = clean.
+#include <cstdio>
+#include <vector>
+
+#include "tdk_plan.h"
+
+using namespace tdk;
+
+static std::vector<PlanSession> round_of(int sessions, int agents, int pages) {
+  std::vector<PlanSession> v;
+  for (int s = 0; s < sessions; ++s) {
+    PlanSession p;
+    p.pages = pages;
+    for (int i = 0; i < agents; ++i) p.agents.push_back(s * agents + i);
+    v.push_back(p);
+  }
+  return v;
+}
+
+#define REQUIRE(c) do { if (!(c)) { std::fprintf(stderr, "requirement failed: %s (line %d)\n", #c, __LINE__); return 1; } } while (0)
+
+int main() {
+  const auto kb = [](int heads, int page_tokens) { return (int64_t)heads * page_tokens * 512; };   // K and V of one page
+  // kernels that read: at least three agents per item, whatever the size of their pages
+  REQUIRE(plan_auto_group(round_of(2, 25, 63), true, kb(1, 16), 256) == 3);
+  REQUIRE(plan_auto_group(round_of(10, 23, 8), true, kb(2, 16), 256) == 3);
+  REQUIRE(plan_auto_group(round_of(1, 78, 9), true, kb(8, 16), 256) == 1);        // 702 pairs
+  REQUIRE(plan_auto_group(round_of(1, 78, 9), true, kb(8, 32), 256) == 2);        // the same with pages of 128 KB
+  // kernels that write, small rounds: one pair per compute unit and agent of an item, two with pages of 128 KB
+  REQUIRE(plan_auto_group(round_of(1, 133, 4), false, kb(8, 32), 256) == 1);      // 532
+  REQUIRE(plan_auto_group(round_of(10, 19, 6), false, kb(8, 32), 256) == 2);      // 1140
+  REQUIRE(plan_auto_group(round_of(10, 19, 6), false, kb(8, 32), 512) == 1);      // the same on a chip twice as wide
+  REQUIRE(plan_auto_group(round_of(10, 10, 9), false, kb(1, 16), 256) == 3);      // 900
+  // larger ones: what an item is worth, in bytes
+  REQUIRE(plan_auto_group(round_of(1, 141, 60), false, kb(1, 16), 256) == 11);
+  REQUIRE(plan_auto_group(round_of(1, 25, 313), false, kb(8, 16), 256) == 3);
+  REQUIRE(plan_auto_group(round_of(10, 25, 313), false, kb(8, 16), 256) == 9);
+  // writing one plane: items of the same worth hold twice the agents
+  REQUIRE(plan_auto_group(round_of(1, 37, 188), false, kb(4, 16), 256, 2) == 3);
+  REQUIRE(plan_auto_group(round_of(1, 37, 188), false, kb(4, 16), 256, 1) == 6);
+  REQUIRE(plan_auto_group(round_of(10, 18, 77), false, kb(8, 16), 256, 1) == 5);
+  REQUIRE(plan_auto_group(round_of(4, 11, 154), false, kb(8, 32), 256, 1) == 3);
+  REQUIRE(plan_auto_group(round_of(10, 15, 4), false, kb(8, 32), 256, 1) == 1);   // 600
+  std::printf("work groups: clean\n");
+  return 0;
+}
