@@ -1157,9 +1157,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4
 // every thread consecutive tokens, so that one scan over the workgroup serves the whole span.  (250 agents x 5000
 // tokens, under the profiler: 36 + 5 us with 4 wavefronts, keys read again in every pass and a launch of its own for the
 // masters; 21 us now; the whole check-layer call 441 -> 426 us.)
-constexpr int kSelBlock = 1024;
-constexpr int kSelWaves = kSelBlock / 64;
-constexpr int kSelKeys = 16384;
+// Spans of up to 512 tokens leave most of 16 wavefronts without work at every barrier: 4 wavefronts there (call with 144,
+// 242 and 500 tokens: 12.8, 15.4 and 21.1 us with 16, 11.8, 14.4 and 20.6 with 4; 600, 800 and 1024 tokens: 12.2, 13.9 and
+// 13.1 with 16, 12.9, 15.0 and 14.0 with 4).
+constexpr int kSelBlock = 1024, kSelKeys = 16384;
+constexpr int kSelSmall = 256, kSelShort = 512;
 
 // Master of a session: the agent with the lowest total deviation (NaN counts as +inf; ties go to the agent listed
 // first).  One wavefront; the totals were delivered by other workgroups, so they are read at device scope.
@@ -1183,15 +1185,17 @@ __device__ __forceinline__ void choose_master(const RoundDev& rd, const PlanDev&
   if (lane == 0) pl.master[session] = sd.n_agents ? best_i : -1;
 }
 
-__global__ __launch_bounds__(kSelBlock) void tdk_select_kernel(const RoundDev rd, const PlanDev pl) {
-  __shared__ uint32_t keys[kSelKeys];
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void tdk_select_kernel(const RoundDev rd, const PlanDev pl) {
+  constexpr int kSelWaves = BLOCK / 64, kKeys = BLOCK == kSelBlock ? kSelKeys : kSelShort;
+  __shared__ uint32_t keys[kKeys];
   __shared__ uint32_t hist[4][256];             // one histogram per pass: a pass costs one barrier
   __shared__ double s_sum[kSelWaves];
   __shared__ int s_a[kSelWaves], s_b[kSelWaves];
   __shared__ int s_last;
   const int a = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   if (a == 0)                                   // sessions without agents have no workgroup of their own
-    for (int s = tid; s < rd.n_sessions; s += kSelBlock)
+    for (int s = tid; s < rd.n_sessions; s += BLOCK)
       if (rd.sess[s].n_agents == 0) pl.master[s] = -1;
   if (a >= rd.n_agents) return;
   const AgentDev ad = rd.agents[a];
@@ -1199,19 +1203,19 @@ __global__ __launch_bounds__(kSelBlock) void tdk_select_kernel(const RoundDev rd
   const float* sc = pl.score + ad.score_off;
   const float min_score = pl.min_score;
   auto to_key = [&](float v) -> uint32_t { return !(v <= min_score) ? (__float_as_uint(v) & 0x7fffffffu) : 0u; };
-  auto key_of = [&](int m) -> uint32_t { return m < kSelKeys ? keys[m] : to_key(sc[m]); };
-  hist[tid >> 8][tid & 255] = 0u;
+  auto key_of = [&](int m) -> uint32_t { return m < kKeys ? keys[m] : to_key(sc[m]); };
+  for (int q = tid; q < 4 * 256; q += BLOCK) hist[q >> 8][q & 255] = 0u;
   __syncthreads();
   // total deviation, number of candidates, keys, and the first pass's histogram
   double part = 0.0;
   int cand = 0;
-  for (int m = tid; m < S; m += kSelBlock) {
+  for (int m = tid; m < S; m += BLOCK) {
     const float v = sc[m];
     const uint32_t key = to_key(v);
     part += (double)v;
     cand += key != 0u;
     if (key != 0u) atomicAdd(&hist[0][key >> 24], 1u);
-    if (m < kSelKeys) keys[m] = key;
+    if (m < kKeys) keys[m] = key;
   }
 #pragma unroll
   for (int sft = 32; sft > 0; sft >>= 1) { part += __shfl_xor(part, sft); cand += __shfl_xor(cand, sft); }
@@ -1247,7 +1251,7 @@ __global__ __launch_bounds__(kSelBlock) void tdk_select_kernel(const RoundDev rd
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = 24 - 8 * pass;
     if (pass > 0) {
-      for (int m = tid; m < S; m += kSelBlock) {
+      for (int m = tid; m < S; m += BLOCK) {
         const uint32_t key = key_of(m);
         if (key != 0u && (key & mask) == prefix) atomicAdd(&hist[pass][(key >> shift) & 255u], 1u);
       }
@@ -1280,7 +1284,7 @@ __global__ __launch_bounds__(kSelBlock) void tdk_select_kernel(const RoundDev rd
   const uint32_t tkey = prefix;
   const int need_eq = (int)need;       // how many tokens equal to the threshold key are taken (the first ones)
   // ordered compaction: thread t takes tokens [t c, (t + 1) c)
-  const int per = (S + kSelBlock - 1) / kSelBlock, m0 = min(tid * per, S), m1 = min(m0 + per, S);
+  const int per = (S + BLOCK - 1) / BLOCK, m0 = min(tid * per, S), m1 = min(m0 + per, S);
   int gt = 0, eq = 0;
   for (int m = m0; m < m1; ++m) {
     const uint32_t key = key_of(m);
@@ -1555,7 +1559,9 @@ hipError_t launch_keydiff(const RoundDev& rd, const LayerDev& io, const PlanDev&
 
 hipError_t launch_select(const RoundDev& rd, const PlanDev& pl, hipStream_t st) {
   if (rd.n_agents == 0 && rd.n_sessions == 0) return hipSuccess;
-  hipLaunchKernelGGL(tdk_select_kernel, dim3(std::max(rd.n_agents, 1)), dim3(kSelBlock), 0, st, rd, pl);
+  const dim3 grid(std::max(rd.n_agents, 1));
+  if (rd.max_span <= kSelShort) hipLaunchKernelGGL(tdk_select_kernel<kSelSmall>, grid, dim3(kSelSmall), 0, st, rd, pl);
+  else hipLaunchKernelGGL(tdk_select_kernel<kSelBlock>, grid, dim3(kSelBlock), 0, st, rd, pl);
   return hipGetLastError();
 }
 

@@ -57,3 +57,11 @@ def test_repeated_calls_on_one_round():
             assert (t[2] == 0).all() if call % 2 else torch.equal(t[1], first[1])
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("spans,ratio", [([255, 256], 0.3), ([257, 511], 1.0), ([512, 3], 0.05), ([513, 512], 0.4), ([130, 0], 0.2)])
+def test_short_spans(tdo, spans, ratio):
+    """The form with 4 wavefronts (no span above 512 tokens), at the edges of its passes and of its range."""
+    spec = wl.RoundSpec("sel5", 93, 1, 2, 128, 16, 1.0e6, 2, 2, 1, max(spans), 3, 60, 0.2)
+    run_case(tdo, wl.make_round(spec, spans=spans, agents=[2, 3]), ratio, 0.0, noise_everywhere=0.02)
+    run_case(tdo, wl.make_round(spec, spans=spans, agents=[2, 3]), ratio, 3.0e38, noise_everywhere=0.02)
