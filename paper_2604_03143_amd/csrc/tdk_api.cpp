@@ -88,6 +88,7 @@ struct tdk_round {
   int64_t total_tokens = 0;        // sum over agents of their session's span
   int32_t max_segments = 1;        // most segments any agent has (1 for identity layouts)
   bool seg_moved = false;          // a segmented agent's stored diff sits at other positions
+  bool seg_apart = false;          // and segments of one agent have moved by different distances
   bool diff_moved = false;         // some agent's stored diff sits at other positions (segmented or not)
 
   bool timing = false;
@@ -296,6 +297,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   r->total_tokens = p.total_tokens;
   r->max_segments = p.max_segments;
   r->seg_moved = p.seg_moved;
+  r->seg_apart = p.seg_apart;
   r->diff_moved = p.diff_moved;
   r->work_capacity = p.work_capacity;
   r->model = *model;
@@ -684,6 +686,7 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     at.q_flip = std::signbit(a->scale) ? 1 : 0;
     at.max_seg = r->max_segments;
     at.seg_moved = r->rd.seg && r->seg_moved ? 1 : 0;
+    at.seg_apart = at.seg_moved && r->seg_apart ? 1 : 0;
     at.diff_seg = at.seg_moved ? r->max_segments : 1;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const LayerDev l = layer_dev(io);

@@ -1256,12 +1256,14 @@ __device__ __forceinline__ void rows_step(const uint16_t* Ks, const uint16_t* Vs
 // The pages d.idx[l0 .. l1) of the agent's list, 32 tokens at a time, from the payload, through K and V tiles that
 // only this wavefront uses (kListedLds bytes).  The payload address of a listed token depends on its place in the list
 // alone, so the next tile travels to registers while this one is multiplied.  load_q(k) loads the query
-// fragments for tokens of segment k (SEGMOVED; otherwise called once with 0).
+// fragments for tokens of segment k (SEGMOVED; otherwise called once with 0).  Which segment a token belongs to is in the
+// agent's page table (`pages`, tables counted from seg_base): one read, where a search through the segments' first tokens
+// is a chain of reads per tile.
 constexpr int kListedLds = kTile * (kKsStride + kVsStride) * 2;
 
 template <bool SEGMOVED, class LoadQ>
 __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d, const AttendDev& at, const SessionDev& sd, uint16_t* lds,
-                                            int h, int seg_base, int seg_n, int64_t l0, int n_pages, int lane, bf16x8 (&qf)[8],
+                                            int h, const PageTab* pages, int seg_base, int64_t l0, int n_pages, int lane, bf16x8 (&qf)[8],
                                             LoadQ load_q, RowState& st) {
   if (n_pages <= 0) return;
   uint16_t* Ks = lds;
@@ -1285,6 +1287,7 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
   };
   fetch(0);
   if (!SEGMOVED) load_q(0);
+  int loaded = -1;                               // SEGMOVED: the segment whose turned rows qf holds
   for (int t0 = 0; t0 < n_tok; t0 += kTile) {
     wave_sync();                                 // the previous tile has been consumed
     int seg_cur = 0;
@@ -1293,8 +1296,10 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
       const int m = (p_next << lg) + ((t0 + n) & (T - 1));
       if (p_next >= 0 && p_next < sd.pages && m < sd.span) {
         ok = true;
-        if (SEGMOVED)
-          while (seg_cur + 1 < seg_n && rd.seg_src[seg_base + seg_cur + 1] <= m) ++seg_cur;
+        if (SEGMOVED) {
+          const PageTab pt = pages[p_next];
+          seg_cur = (((uint32_t)pt.z >> (m & (T - 1))) & 1u ? pt.y : pt.x) - seg_base;
+        }
       }
     }
     const uint32_t valid = (uint32_t)__ballot(ok);
@@ -1306,7 +1311,7 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
       *reinterpret_cast<u32x4*>(Vs + (4 * j + st_row) * kVsStride + 8 * st_pc) = v;
     }
     wave_sync();                                 // the tile is complete
-    if (t0 + kTile < n_tok) fetch(t0 + kTile);
+    if (!SEGMOVED && t0 + kTile < n_tok) fetch(t0 + kTile);
     f32x16 s[1];
     auto scores = [&](f32x16 (&x)[1]) __attribute__((always_inline)) {
       f32x16 y;                                  // two chains of products
@@ -1326,26 +1331,24 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
     } else {
       // tokens of several segments, stored at different distances from today's positions: scores once per
       // segment present, with the queries turned back by that distance, and every token keeps its own
-      int sid[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) sid[i] = __shfl(seg_cur, 8 * (i >> 2) + 4 * hh + (i & 3));
 #pragma unroll
       for (int i = 0; i < 16; ++i) s[0][i] = 0.f;
-      int done = -1;
-      while (true) {
-        int cand = (lane < kTile && ((valid >> lane) & 1u) && seg_cur > done) ? seg_cur : 0x7fffffff;
-#pragma unroll
-        for (int sft = 32; sft > 0; sft >>= 1) cand = min(cand, __shfl_xor(cand, sft));
-        cand = __builtin_amdgcn_readfirstlane(cand);
-        if (cand == 0x7fffffff) break;
-        load_q(cand);
+      uint32_t rest = valid;                     // tokens whose scores are still to come
+      while (rest != 0u) {
+        const int cand = __builtin_amdgcn_readlane(seg_cur, __builtin_ctz(rest));
+        const uint32_t mine = (uint32_t)__ballot(ok && seg_cur == cand);     // (lanes 32..63 repeat lanes 0..31)
+        rest &= ~mine;
+        if (cand != loaded) load_q(cand);        // (lists ascend: the segment of the last tile often goes on in this one)
+        loaded = cand;
         f32x16 x[1];
         scores(x);
+        const uint32_t ms = mine >> (4 * hh);    // score i of a lane belongs to token 8 (i / 4) + 4 hh + i % 4
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (sid[i] == cand) s[0][i] = x[0][i];
-        done = cand;
+          if ((ms >> (8 * (i >> 2) + (i & 3))) & 1u) s[0][i] = x[0][i];
       }
+      // (only now, although the rows arrive later: in flight during the loop above they cost registers that spill)
+      if (t0 + kTile < n_tok) fetch(t0 + kTile);
     }
     if (valid != 0xffffffffu) {
       const uint32_t vs = valid >> (4 * hh);     // score i of a lane belongs to token 8 (i / 4) + 4 hh + i % 4
@@ -1361,7 +1364,7 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
   wave_sync();
 }
 
-template <bool SEG, bool MOVED>   // MOVED (SEG only): some segment's stored diff sits at other positions
+template <bool SEG, bool APART>   // APART (SEG only): segments of one agent have moved by different distances since their diff was stored
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev d, const AttendDev at, const RowsGrid rg) {
   __shared__ __attribute__((aligned(16))) RowsShared sh;
@@ -1583,12 +1586,16 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   // ---- the listed pages, from the payload ----
   if (active) {
     uint16_t* lds = reinterpret_cast<uint16_t*>(&sh) + wave * (kListedLds / 2);
-    if (SEG && MOVED) {
-      rows_listed<true>(rd, d, at, sd, lds, h, seg_base, seg_n, l0, (int)(l1 - l0), lane, qf,
+    // Segments that have moved together meet the same rows, so one turn serves the whole list; only lists whose segments have
+    // moved by different distances need a turn per segment.
+    const int moved = __builtin_amdgcn_readfirstlane(rd.agents[agent].diff_rot);
+    if (SEG && APART && moved == 1) {
+      rows_listed<true>(rd, d, at, sd, lds, h, rd.pagetab + rd.agents[agent].flag_off, seg_base, l0, (int)(l1 - l0), lane, qf,
                             [&](int k) __attribute__((always_inline)) { load_q(rd.segtab_diff + (size_t)(seg_base + k) * (2 * kHalf)); }, st);
     } else {
-      rows_listed<false>(rd, d, at, sd, lds, h, seg_base, seg_n, l0, (int)(l1 - l0), lane, qf,
-                             [&](int) __attribute__((always_inline)) { load_q(!SEG && rd.agents[agent].diff_rot != 0 ? rd.tab_diff + (size_t)agent * (2 * kHalf) : nullptr); }, st);
+      const float* turn = moved == 0 ? nullptr : SEG ? rd.segtab_diff + (size_t)seg_base * (2 * kHalf) : rd.tab_diff + (size_t)agent * (2 * kHalf);
+      rows_listed<false>(rd, d, at, sd, lds, h, nullptr, 0, l0, (int)(l1 - l0), lane, qf,
+                             [&](int) __attribute__((always_inline)) { load_q(turn); }, st);
     }
   }
 
@@ -1966,7 +1973,7 @@ hipError_t launch_attend_rows(const RoundDev& rd, const LayerDev& io, const Diff
     if (blocks >= ((int64_t)1 << 31)) return hipErrorInvalidConfiguration;
     rg.session0 = s0;
     const dim3 grid((unsigned)blocks);
-    if (rd.seg && at.seg_moved) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, true>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
+    if (rd.seg && at.seg_apart) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, true>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
     else if (rd.seg) hipLaunchKernelGGL((tdk_attend_rows_kernel<true, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
     else hipLaunchKernelGGL((tdk_attend_rows_kernel<false, false>), grid, dim3(kBlock), 0, st, rd, io, d, at, rg);
     const hipError_t e = hipGetLastError();

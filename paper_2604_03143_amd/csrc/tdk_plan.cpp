@@ -103,6 +103,11 @@ tdk_status plan_round(const tdk_model* model, const tdk_session* sessions, int32
     ad.diff_rot = a.n_segments ? 0 : a.diff_pos0 != a.dst_pos0;
     for (int32_t q = 0; q < a.n_segments; ++q) ad.diff_rot |= a.segments[q].diff_pos != a.segments[q].dst_pos;
     if (ad.diff_rot) out.diff_moved = true;
+    bool together = ad.diff_rot != 0;
+    for (int32_t q = 1; q < a.n_segments; ++q)
+      together &= a.segments[q].dst_pos - a.segments[q].diff_pos == a.segments[0].dst_pos - a.segments[0].diff_pos;
+    if (together) ad.diff_rot |= 2;
+    else if (ad.diff_rot) out.seg_apart = true;
     score_off += S;
     {
       // only pages that hold shared tokens count (the hull of a permuted layout may contain others)

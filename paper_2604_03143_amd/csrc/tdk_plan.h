@@ -40,6 +40,7 @@ struct RoundPlan {
   int64_t total_tokens = 0;           // sum over agents of their session's span
   int32_t max_segments = 1;           // most segments any agent has (1 for identity layouts)
   bool seg_moved = false;             // a segmented agent's stored diff sits at other positions
+  bool seg_apart = false;             // and segments of one agent have moved by different distances
   bool diff_moved = false;            // some agent's stored diff sits at other positions (segmented or not)
   size_t work_capacity = 0;           // work items in the worst case (every agent its own group)
 };

@@ -35,7 +35,8 @@ struct AgentDev {
   int32_t session;
   int32_t flag_off;     // start of this agent's per-page flags in the flag scratch
   int32_t score_off;    // start of this agent's per-token scores (sum of the spans of earlier agents)
-  int32_t diff_rot;     // 1: payload K rows of this agent were stored at another position (re-rotate on restore)
+  int32_t diff_rot;     // bit 0: payload K rows of this agent were stored at another position (re-rotate on restore);
+                        // bit 1: and every segment of its layout has moved by the same distance
 };
 
 // Per (agent, master page) of a round with per-agent block layouts: the rotation tables of the (at most two)

@@ -1,5 +1,5 @@
 """Attention over rounds with per-agent segment lists, in the forms that block permutations do not produce: layouts of a
-single segment.  Bounds as in test_gpu_attend.py."""
+single segment, and segments that moved together or apart.  Bounds as in test_gpu_attend.py."""
 import numpy as np
 import pytest
 
@@ -61,3 +61,34 @@ def test_one_segment_per_agent_stored_elsewhere(tdo, n_agents, H, n_q, Hq, T, st
     moved = lambda rnd: [s[:, 1] - (0 if i == 1 else 37 + 11 * i) for i, s in enumerate(rnd.segments)]
     segment_case(tdo, spec, segments, moved, n_q, Hq, style=style, scale=1.0 if span < 1000 else None,
                  perturbed=min(spec.span_pages, 12))
+
+
+# rows per agent and KV head: 3 and 16 (packed form or a wavefront per agent), 20 and 40 (a wavefront per agent)
+@pytest.mark.parametrize("how", ["together", "apart", "mixed"])
+@pytest.mark.parametrize("n_q,Hq,T,style", [(1, 6, 16, 0), (4, 8, 32, 1), (5, 8, 32, 0), (10, 8, 16, 1)])
+def test_segments_moved_together_and_apart(tdo, how, n_q, Hq, T, style):
+    """Lists that run over several segments of an agent.  Together: all of an agent's segments have moved by one distance (one
+    turn serves the list); apart: by different ones, so a tile of the list meets rows turned for each; mixed: agents of both
+    kinds and one that has not moved, in one round."""
+    spec = wl.RoundSpec("seg2", 102, 1, 2, 128, T, 1.0e6, 1, 5, 1, 700, 900, 1200, 0.5)
+    g = np.random.default_rng([102, T, n_q])
+
+    def segments(rnd):
+        out = []
+        for p in rnd.agent_pos0:
+            cuts = np.unique(np.concatenate([[0], np.sort(g.choice(np.arange(1, 700 // T), 5, replace=False)) * T + int(g.integers(0, T))]))
+            lens = np.diff(np.concatenate([cuts, [700]]))
+            order = g.permutation(len(cuts))
+            dst = np.empty(len(cuts), np.int64)
+            dst[order] = int(p) + np.concatenate([[0], np.cumsum(lens[order])[:-1]])
+            out.append(np.stack([cuts, dst, lens], 1))
+        return out
+
+    def moved(rnd):
+        out = []
+        for i, s in enumerate(rnd.segments):
+            kind = {"together": 0, "apart": 1, "mixed": i % 3}[how]
+            out.append(s[:, 1] - (23 * (i + 1) if kind == 0 else 11 + 17 * np.arange(len(s)) if kind == 1 else 0))
+        return out
+
+    segment_case(tdo, spec, segments, moved, n_q, Hq, style=style, scale=1.0)
