@@ -626,6 +626,7 @@ static AttendShape attend_shape(const tdk_round* r) {
   s.n_cus = r->n_cus;
   s.seg = r->rd.seg != 0;
   s.seg_moved = r->seg_moved;
+  s.seg_apart = r->seg_apart;
   s.max_segments = r->max_segments;
   s.total_tokens = r->total_tokens;
   s.total_master_rows = r->total_master_rows;

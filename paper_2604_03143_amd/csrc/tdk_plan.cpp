@@ -329,6 +329,31 @@ int attend_piece_tokens(int64_t lists, int n_cus) {
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Own block orders, at most 32 rows per agent and KV head: a wavefront per agent, or packed rows?  The packed form needs a
+// copy of every row per segment and reloads a tile's queries lane by lane; the wavefronts of one agent walk the span with
+// 32-row tiles that are mostly empty, and their lists with them.  From 17 rows on the packed tiles are no emptier (25 agents x
+// 5000 tokens, 20 rows 107 against 69 us; 100 agents x 1500 tokens 112 against 97; ten sessions of 25 x 600 tokens 138
+// against 88).  With fewer rows the packed form wins once there are enough agents to fill the chip; what decides is the
+// work per compute unit (64-token steps over all agents and KV heads) and how many workgroups of four agents share a
+// chunk.  Measured over 21 rounds (1 to 10 sessions of 3 to 100 agents, 600 to 9000 tokens, 2 and 8 KV heads, blocks of 64 and
+// 200 tokens, 2 to 20 % of the pages listed, diffs that moved together or not), time packed / time per agent:
+//   1 row:       up to 32 steps and 3/8 of a workgroup per compute unit 1.0 .. 3.3; 61 steps 0.96, 73 steps and 25/32 0.60
+//   2 to 7 rows: up to 60 steps and 3/8                               1.01 .. 3.3; 69 steps 0.94, 110 steps 0.92
+//   8 and more:  up to 110 steps and 5/8                              0.99 .. 3.2; 138 steps and 3/4 0.74
+// Where segments of one agent have moved by different distances since the diff was stored, the lists turn rows per segment:
+// up to 28 steps and 1/8 of a workgroup 1.04 .. 2.5; 30 steps and 7/32 0.73 (1 row, a fifth of the pages listed).
+bool attend_rows_for_segments(const AttendShape& r, int64_t agent_rows) {
+  if (agent_rows > 16) return true;
+  int64_t wgs = 0;
+  for (const auto& hs : *r.sessions) wgs += ((int64_t)hs.agents.size() + kWaves - 1) / kWaves;
+  wgs *= r.heads;
+  const int64_t steps = r.total_tokens / 64 * r.heads, cus = r.n_cus;
+  if (r.seg_apart) return steps <= 28 * cus && 8 * wgs <= cus;
+  if (agent_rows == 1) return steps <= 32 * cus && 8 * wgs <= 3 * cus;
+  if (agent_rows < 8) return steps <= 60 * cus && 8 * wgs <= 3 * cus;
+  return steps <= 110 * cus && 8 * wgs <= 5 * cus;
+}
+
 // the partial results of p.rows x p.n_parts, from byte `off` of the workspace on
 void place_parts(AttendPlan& p, size_t off) {
   auto place = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
@@ -362,15 +387,9 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
   //   own: better for few rows per agent (25 agents, one session: 28 against 49 us with 5 rows per agent and KV
   //   head, 49 against 52 with 20; ten sessions: 268 against 329 us with 20 rows), worse from 33 rows on (40 rows:
   //   94 against 70 us, ten sessions 575 against 460 us; 320 rows: 462 against 206 us).
-  //   With per-agent block orders the packed form needs a copy of every row per segment and reloads a tile's queries
-  //   lane by lane: it is better only with few rows per agent, whose 32-row tiles are mostly empty, and only where that
-  //   waste outweighs its start, from about 100 steps of 64 tokens per compute unit on, counting every agent and KV head
-  //   (5 rows: 62 steps per unit 75 packed against 62 us, 617 steps 237 against 465 us; 4 rows, 168 steps 100 against
-  //   117 us; 20 rows: 62 steps 107 against 70 us, 617 steps 647 against 506 us).
   const int64_t lists = (int64_t)r.n_agents * r.heads;
-  const int64_t agent_steps = r.total_tokens / 64 * r.heads;
   p.own_rows = agent_rows > 32 || r.total_master_rows == 0 || lists >= ((int64_t)1 << 27) ||
-               (r.seg && (agent_rows > 16 || agent_steps <= 100 * (int64_t)r.n_cus));
+               (r.seg && attend_rows_for_segments(r, agent_rows));
   if (p.own_rows) {
     const int64_t per_agent = (agent_rows + 31) / 32, cus = r.n_cus;
     // Chunks of the span: workgroups of four wavefronts, two of which share a compute unit (each then takes about

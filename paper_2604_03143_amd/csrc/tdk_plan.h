@@ -62,7 +62,7 @@ int  plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels
 struct AttendShape {
   const std::vector<PlanSession>* sessions = nullptr;
   int32_t n_agents = 0, heads = 1, page_tokens = 16, n_cus = 256, max_segments = 1;
-  bool seg = false, seg_moved = false;               // as in RoundPlan (any_segments, seg_moved)
+  bool seg = false, seg_moved = false, seg_apart = false;      // as in RoundPlan (any_segments, seg_moved, seg_apart)
   int64_t total_tokens = 0, total_master_rows = 0;
 };
 

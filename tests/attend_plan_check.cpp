@@ -43,6 +43,7 @@ static Made draw() {
   m.shape.page_tokens = rnd() % 2 ? 16 : 32;
   m.shape.seg = rnd() % 2;
   m.shape.seg_moved = m.shape.seg && rnd() % 2;
+  m.shape.seg_apart = m.shape.seg_moved && rnd() % 2;
   m.shape.max_segments = m.shape.seg ? (int32_t)between(1, 40) : 1;
   const int n = (int)between(1, 10);
   const int32_t agents = (int32_t)between(0, 60);
@@ -125,8 +126,31 @@ static int check_workspace() {
   return 0;
 }
 
+// Own block orders with few rows per agent: a wavefront per agent on both sides of the rule's lines.
+static int check_segment_rule() {
+  int cs = 0;
+  auto own = [](int sessions, int agents, int span, int heads, int group, bool apart, int n_cus) {
+    Made m;
+    m.shape.heads = heads;
+    m.shape.seg = true;
+    m.shape.seg_moved = m.shape.seg_apart = apart;
+    m.shape.max_segments = 12;
+    m.shape.n_cus = n_cus;
+    for (int i = 0; i < sessions; ++i) m.add(span, agents);
+    AttendPlan p;
+    return attend_plan(m.done(), 1, group * heads, p) ? (int)p.own_rows : -1;
+  };
+  REQUIRE(own(1, 25, 2500, 8, 1, false, 256) == 1 && own(1, 25, 5000, 8, 1, false, 256) == 0 && own(1, 100, 600, 8, 1, false, 256) == 0);
+  REQUIRE(own(4, 6, 5000, 8, 5, false, 256) == 1 && own(4, 12, 3000, 8, 5, false, 256) == 0 && own(1, 100, 600, 8, 5, false, 256) == 0);
+  REQUIRE(own(1, 25, 9000, 8, 8, false, 256) == 1 && own(4, 22, 3230, 8, 8, false, 256) == 0 && own(10, 25, 600, 8, 16, false, 256) == 0);
+  REQUIRE(own(2, 8, 1500, 8, 4, true, 256) == 1 && own(1, 25, 2500, 8, 4, true, 256) == 0 && own(1, 25, 2500, 8, 4, false, 256) == 1);
+  REQUIRE(own(10, 25, 600, 8, 17, true, 256) == 1 && own(10, 25, 5000, 8, 20, false, 256) == 1);
+  REQUIRE(own(1, 25, 2500, 8, 1, false, 128) == 0 && own(1, 25, 5000, 8, 1, false, 512) == 1);
+  return 0;
+}
+
 int main() {
-  if (check_grids() || check_workspace()) return 1;
+  if (check_grids() || check_workspace() || check_segment_rule()) return 1;
   std::printf("attention planner: clean\n");
   return 0;
 }
