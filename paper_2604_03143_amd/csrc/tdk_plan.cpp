@@ -340,18 +340,23 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 //   1 row:       up to 32 steps and 3/8 of a workgroup per compute unit 1.0 .. 3.3; 61 steps 0.96, 73 steps and 25/32 0.60
 //   2 to 7 rows: up to 60 steps and 3/8                               1.01 .. 3.3; 69 steps 0.94, 110 steps 0.92
 //   8 and more:  up to 110 steps and 5/8                              0.99 .. 3.2; 138 steps and 3/4 0.74
+// Short spans of many agents leave the packed form as little to do: up to 24 steps (1 row: 12) one workgroup per compute unit is
+// still better off with a wavefront per agent (20 sessions of 4 x 300 tokens 1.21 .. 1.81, 100 agents x 300 tokens 1.36 .. 2.16; ten
+// sessions of 25 x 200 tokens, 24 steps and 35/16, 0.76).
 // Where segments of one agent have moved by different distances since the diff was stored, the lists turn rows per segment:
-// up to 28 steps and 1/8 of a workgroup 1.04 .. 2.5; 30 steps and 7/32 0.73 (1 row, a fifth of the pages listed).
+// up to 28 steps and 1/8 of a workgroup 1.04 .. 2.5, up to 8 steps and 3/8 1.10 .. 1.45; 30 steps and 7/32 0.73, 16 steps and
+// 9/16 0.88 (1 row, a fifth of the pages listed).  With 8 rows or more up to 24 steps and 1/2: 0.97 .. 1.7; 18 steps and
+// 35/64 0.88.
 bool attend_rows_for_segments(const AttendShape& r, int64_t agent_rows) {
   if (agent_rows > 16) return true;
   int64_t wgs = 0;
   for (const auto& hs : *r.sessions) wgs += ((int64_t)hs.agents.size() + kWaves - 1) / kWaves;
   wgs *= r.heads;
   const int64_t steps = r.total_tokens / 64 * r.heads, cus = r.n_cus;
-  if (r.seg_apart) return steps <= 28 * cus && 8 * wgs <= cus;
-  if (agent_rows == 1) return steps <= 32 * cus && 8 * wgs <= 3 * cus;
-  if (agent_rows < 8) return steps <= 60 * cus && 8 * wgs <= 3 * cus;
-  return steps <= 110 * cus && 8 * wgs <= 5 * cus;
+  auto within = [&](int64_t most_steps, int64_t eighths) { return steps <= most_steps * cus && 8 * wgs <= eighths * cus; };
+  if (r.seg_apart) return within(28, 1) || within(8, 3) || (agent_rows >= 8 && within(24, 4));
+  if (agent_rows == 1) return within(32, 3) || within(12, 8);
+  return within(24, 8) || (agent_rows < 8 ? within(60, 3) : within(110, 5));
 }
 
 // the partial results of p.rows x p.n_parts, from byte `off` of the workspace on

@@ -142,6 +142,9 @@ static int check_segment_rule() {
   };
   REQUIRE(own(1, 25, 2500, 8, 1, false, 256) == 1 && own(1, 25, 5000, 8, 1, false, 256) == 0 && own(1, 100, 600, 8, 1, false, 256) == 0);
   REQUIRE(own(4, 6, 5000, 8, 5, false, 256) == 1 && own(4, 12, 3000, 8, 5, false, 256) == 0 && own(1, 100, 600, 8, 5, false, 256) == 0);
+  REQUIRE(own(20, 4, 300, 8, 1, false, 256) == 1 && own(4, 22, 530, 8, 4, false, 256) == 1 && own(4, 22, 530, 8, 1, false, 256) == 0);
+  REQUIRE(own(10, 25, 200, 8, 4, false, 256) == 0 && own(10, 2, 449, 8, 1, true, 256) == 1 && own(2, 34, 483, 8, 1, true, 256) == 0);
+  REQUIRE(own(4, 12, 1000, 8, 8, true, 256) == 1 && own(4, 12, 1000, 8, 4, true, 256) == 0);
   REQUIRE(own(1, 25, 9000, 8, 8, false, 256) == 1 && own(4, 22, 3230, 8, 8, false, 256) == 0 && own(10, 25, 600, 8, 16, false, 256) == 0);
   REQUIRE(own(2, 8, 1500, 8, 4, true, 256) == 1 && own(1, 25, 2500, 8, 4, true, 256) == 0 && own(1, 25, 2500, 8, 4, false, 256) == 1);
   REQUIRE(own(10, 25, 600, 8, 17, true, 256) == 1 && own(10, 25, 5000, 8, 20, false, 256) == 1);
