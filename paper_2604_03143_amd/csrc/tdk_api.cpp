@@ -687,6 +687,7 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     at.q_flip = std::signbit(a->scale) ? 1 : 0;
     at.max_seg = r->max_segments;
     at.seg_moved = r->rd.seg && r->seg_moved ? 1 : 0;
+    at.diff_moved = r->diff_moved ? 1 : 0;
     at.seg_apart = at.seg_moved && r->seg_apart ? 1 : 0;
     at.diff_seg = at.seg_moved ? r->max_segments : 1;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);

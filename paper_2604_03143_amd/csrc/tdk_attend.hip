@@ -756,7 +756,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // row-major tile in LDS.  32 query rows at a time.
 // ---------------------------------------------------------------------------------------------
 
-// Vs: this wavefront's V tile, kTile * kVsStride bf16 elements; lane: 0..63.
+// Vs: this wavefront's V tile, kTile * kVsStride bf16 elements; lane: 0..63.  MOVED: some agent's diff sits at other positions
+template <bool MOVED>
 __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const DiffDev& d, const AttendDev& at, uint16_t* Vs,
                                                    int h, int agent, int piece, int lane) {
   const int T = rd.page_tokens;
@@ -799,7 +800,7 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
         raw[kk] = u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip};
         qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
       }
-      if (ad.diff_rot) turn_back32(raw, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, hh, qf);
+      if (MOVED && ad.diff_rot) turn_back32(raw, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, hh, qf);
     }
     RowState rs;
     row_state_init(rs);
@@ -875,10 +876,11 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
 }
 
 // the pieces z, z + piece_grid, ... of one list, until one lies past its end
+template <bool MOVED>
 __device__ __forceinline__ void attend_diff32_body(const RoundDev& rd, const DiffDev& d, const AttendDev& at, uint16_t* Vs,
                                                    int h, int agent, int piece0, int lane) {
   for (int piece = piece0; piece < at.n_pieces; piece += at.piece_grid)
-    if (!attend_diff32_piece(rd, d, at, Vs, h, agent, piece, lane)) break;
+    if (!attend_diff32_piece<MOVED>(rd, d, at, Vs, h, agent, piece, lane)) break;
 }
 
 // The same pass with 16 query rows per wavefront: used when an agent brings at most 16 rows per KV head
@@ -886,7 +888,7 @@ __device__ __forceinline__ void attend_diff32_body(const RoundDev& rd, const Dif
 
 // Vs: this wavefront's V tile, kTile * kVsStride bf16 elements (the K rows go straight from the payload into
 // the MFMA operand registers); lane: 0..63
-template <bool SEGMOVED, bool QDIRECT = false>
+template <bool SEGMOVED, bool QDIRECT, bool MOVED>
 __device__ __forceinline__ bool attend_diff16_piece(const RoundDev& rd, const DiffDev& d, const AttendDev& at, uint16_t* Vs,
                                                    int h, int agent, int piece, int lane) {
   const int T = rd.page_tokens;
@@ -923,7 +925,7 @@ __device__ __forceinline__ bool attend_diff16_piece(const RoundDev& rd, const Di
       if (row_ok) v = qp[4 * kk + g4];
       qf[kk] = __builtin_bit_cast(bf16x8, u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip});
     }
-    if (QDIRECT && ad.diff_rot) turn_back16(qf, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, g4);
+    if (QDIRECT && MOVED && ad.diff_rot) turn_back16(qf, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, g4);
   };
   if (!SEGMOVED) load_q(0);
   const int seg_base = SEGMOVED ? rd.seg_off[agent] : 0;
@@ -1039,11 +1041,11 @@ __device__ __forceinline__ bool attend_diff16_piece(const RoundDev& rd, const Di
 }
 
 // the pieces z, z + piece_grid, ... of one list, until one lies past its end
-template <bool SEGMOVED, bool QDIRECT = false>
+template <bool SEGMOVED, bool QDIRECT = false, bool MOVED = false>
 __device__ __forceinline__ void attend_diff16_body(const RoundDev& rd, const DiffDev& d, const AttendDev& at, uint16_t* Vs,
                                                    int h, int agent, int piece0, int lane) {
   for (int piece = piece0; piece < at.n_pieces; piece += at.piece_grid)
-    if (!attend_diff16_piece<SEGMOVED, QDIRECT>(rd, d, at, Vs, h, agent, piece, lane)) break;
+    if (!attend_diff16_piece<SEGMOVED, QDIRECT, MOVED>(rd, d, at, Vs, h, agent, piece, lane)) break;
 }
 
 template <bool SEGMOVED>
@@ -1812,7 +1814,9 @@ __device__ __forceinline__ void attend_packed_body(const RoundDev& rd, const Lay
 // simplest form stays.
 static_assert(kWaves * kTile * kVsStride * 2 <= (int)sizeof(PackedShared) && kMasterLds <= (int)sizeof(PackedShared), "one allocation for all");
 
-template <bool ROWS32, bool PIPELINED>    // PIPELINED: the master kind with pipelined steps; ROWS32: the listed-pages kind with 32-row tiles (17 to 32 rows per agent and KV head) or 16-row tiles
+// MOVED: some agent's diff was stored at other positions (a kernel of its own: turning rows costs registers that the 32-row
+// tiles do not have; 100 agents x 1500 tokens, 20 rows, diffs not moved: 69.6 us in one kernel for both, 67.5 in its own).
+template <bool ROWS32, bool PIPELINED, bool MOVED>    // PIPELINED: the master kind with pipelined steps; ROWS32: the listed-pages kind with 32-row tiles (17 to 32 rows per agent and KV head) or 16-row tiles
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void tdk_attend_fused_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
                                                                   const AttendDev at, const FusedGrid fg) {
   constexpr int kLds = PIPELINED ? (int)sizeof(PackedShared) : kMasterLds > kWaves * kTile * kVsStride * 2 ? kMasterLds : kWaves * kTile * kVsStride * 2;
@@ -1841,8 +1845,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     const int agent = rem / fg.head_groups, h = (rem - agent * fg.head_groups) * kWaves + (threadIdx.x >> 6);
     if (h >= rd.heads) return;
     uint16_t* Vs = reinterpret_cast<uint16_t*>(lds) + (threadIdx.x >> 6) * (kTile * kVsStride);
-    if (ROWS32) attend_diff32_body(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
-    else attend_diff16_body<false, true>(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
+    if (ROWS32) attend_diff32_body<MOVED>(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
+    else attend_diff16_body<false, true, MOVED>(rd, d, at, Vs, h, agent, piece, threadIdx.x & 63);
   }
 }
 
@@ -1952,12 +1956,11 @@ hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const Dif
   const int64_t blocks = (int64_t)fg.n_master + (int64_t)fg.n_diff0 * at.piece_grid;
   if (blocks == 0) return hipSuccess;
   const bool pipelined = fg.row_blocks <= 2 && (int64_t)rd.n_agents * rd.heads > rd.n_cus && at.chunk_tokens >= 512;      // (see attend_packed_body)
-  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, rd, io, d, at, fg); };
-  if (at.n_q * at.group > 16) {
-    if (pipelined) launch(tdk_attend_fused_kernel<true, true>); else launch(tdk_attend_fused_kernel<true, false>);
-  } else {
-    if (pipelined) launch(tdk_attend_fused_kernel<false, true>); else launch(tdk_attend_fused_kernel<false, false>);
-  }
+  auto with = [](bool b, auto f) { if (b) f(std::true_type{}); else f(std::false_type{}); };
+  with(at.n_q * at.group > 16, [&](auto rows32) { with(pipelined, [&](auto pipe) { with(at.diff_moved != 0, [&](auto moved) {
+    hipLaunchKernelGGL((tdk_attend_fused_kernel<decltype(rows32)::value, decltype(pipe)::value, decltype(moved)::value>), dim3((unsigned)blocks),
+                       dim3(kBlock), 0, st, rd, io, d, at, fg);
+  }); }); });
   return hipGetLastError();
 }
 

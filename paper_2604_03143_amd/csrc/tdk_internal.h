@@ -98,6 +98,7 @@ struct AttendDev {
   int32_t diff_seg;                  // copies of every query row in qdiff: max_seg if a segmented round's stored
                                      // diffs sit at other positions (each segment moved by its own distance), else 1
   int32_t seg_moved;                 // segmented round whose stored diffs sit at other positions (max_seg may still be 1)
+  int32_t diff_moved;                // some agent's stored diff sits at other positions (segmented or not)
   int32_t seg_apart;                 // and segments of one agent have moved by different distances
   float   scale;                     // magnitude of the caller's scale, at least 1e-30
   int32_t q_flip;                    // the caller's scale was negative: the query copies carry the sign
