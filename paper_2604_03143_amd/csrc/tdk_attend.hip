@@ -1627,10 +1627,8 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
 // Packed rows (identity layouts, few rows per agent): the master pass for 128 query rows of a session's agents, whatever
 // agents they belong to, with the pipelined steps of the kernel above.  Rows of one wavefront have different agents, so the
 // listed pages are masked per lane; those pages are the listed-pages pass's work.
-// Where it is used (launch_attend_fused): at most two row blocks over every tile, a chip full of lists and chunks of at
-// least eight steps.  250 agents, ten sessions, 1 query token 132 -> 128 us, 2 tokens 181 -> 159 us.  A workgroup starts
-// up later here (two more tiles and the first scores before the loop), which one session feels (28.5 -> 29.2 us) and spans
-// of a few steps (207 tokens: 19.5 -> 19.7 us), and with three row blocks or more the plain form's calls of coming tiles into L2 serve several readers (100 agents x 25600 tokens 135 -> 138 us).
+// Where it is used: attend_plan (at most 16 rows per agent and KV head, two row blocks over every tile, enough steps).  250
+// agents, ten sessions, 5000 tokens: 1 query token (5 rows) 111 -> 109 us in a graph, 2 tokens (10 rows) 164 -> 153.
 // ---------------------------------------------------------------------------------------------
 struct PackedShared {
   uint16_t k[2][kBigTile * kKsStride];
@@ -1952,15 +1950,17 @@ hipError_t launch_attend_diff(const RoundDev& rd, const DiffDev& d, const Attend
 }
 
 hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at,
-                               const FusedGrid& fg, hipStream_t st) {
+                               const FusedGrid& fg, bool pipelined, hipStream_t st) {
   const int64_t blocks = (int64_t)fg.n_master + (int64_t)fg.n_diff0 * at.piece_grid;
   if (blocks == 0) return hipSuccess;
-  const bool pipelined = fg.row_blocks <= 2 && (int64_t)rd.n_agents * rd.heads > rd.n_cus && at.chunk_tokens >= 512;      // (see attend_packed_body)
   auto with = [](bool b, auto f) { if (b) f(std::true_type{}); else f(std::false_type{}); };
-  with(at.n_q * at.group > 16, [&](auto rows32) { with(pipelined, [&](auto pipe) { with(at.diff_moved != 0, [&](auto moved) {
-    hipLaunchKernelGGL((tdk_attend_fused_kernel<decltype(rows32)::value, decltype(pipe)::value, decltype(moved)::value>), dim3((unsigned)blocks),
-                       dim3(kBlock), 0, st, rd, io, d, at, fg);
-  }); }); });
+  with(at.diff_moved != 0, [&](auto moved) {
+    constexpr bool M = decltype(moved)::value;
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kBlock), 0, st, rd, io, d, at, fg); };
+    if (at.n_q * at.group > 16) launch(tdk_attend_fused_kernel<true, false, M>);
+    else if (pipelined) launch(tdk_attend_fused_kernel<false, true, M>);
+    else launch(tdk_attend_fused_kernel<false, false, M>);
+  });
   return hipGetLastError();
 }
 

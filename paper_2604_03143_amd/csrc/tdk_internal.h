@@ -126,7 +126,7 @@ hipError_t launch_attend_diff(const RoundDev& rd, const DiffDev& d, const Attend
 hipError_t launch_attend_merge(const RoundDev& rd, const DiffDev& d, const AttendDev& at, hipStream_t st);
 // master pass and listed-pages pass in one launch (identity layouts, few rows per agent)
 hipError_t launch_attend_fused(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at,
-                               const FusedGrid& fg, hipStream_t st);
+                               const FusedGrid& fg, bool pipelined, hipStream_t st);
 // one agent per wavefront (32 of its query rows); a span that is one chunk is finished here (no merge)
 hipError_t launch_attend_rows(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const AttendDev& at, int max_agents,
                               int launch_sessions, hipStream_t st);

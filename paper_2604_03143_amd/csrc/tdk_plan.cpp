@@ -455,6 +455,22 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
   }
   p.chunk_tokens = chunk;
   p.n_chunks = (int32_t)((max_span + chunk - 1) / chunk);
+  // Pipelined steps in the master pass (identity layouts; tdk_attend.hip, attend_packed_body).  A workgroup starts up later there
+  // (two more tiles and the first scores before the loop), so it needs workgroups of at least 8 steps and at least 2 3/4 steps
+  // per compute unit over the whole pass; with three row blocks or more the plain form's calls of coming tiles into L2
+  // serve several readers; and 17 rows or more (32-row tiles for the listed pages) lose with many listed pages what
+  // they gain with few.  Time plain / pipelined, 1 to 16 rows, 3 and 20 % of the pages listed: ten sessions of 6 x 2000
+  // tokens (9.8 steps) 1.04 .. 1.10, four of 12 x 3000 (5.9) 1.04 .. 1.06, ten of 25 x 600 (2.9) 1.00 .. 1.10, 50 agents x 12000 (5.9)
+  // 1.01 .. 1.05; one session of 25 x 5000 (2.4) 0.99 .. 1.04, of 50 x 2000 (2.0) 0.99 .. 1.00, two of 36 x 500 (1.0) 0.96 .. 1.02, ten of
+  // 25 x 1500 with 2 heads (1.8) 0.95 .. 1.01, two of 25 x 207 (0.2) 0.92 .. 0.99; 20 rows, half of the pages listed, ten sessions of 6 x
+  // 2000 tokens 145 against 176 us.
+  {
+    int64_t steps = 0;
+    for (const auto& hs : *r.sessions)
+      if (!hs.agents.empty()) steps += ((int64_t)hs.span + 63) / 64;
+    steps *= r.heads * row_blocks;
+    p.pipelined = !r.seg && agent_rows <= 16 && row_blocks <= 2 && std::min<int64_t>(chunk, max_span) >= 512 && 4 * steps >= 11 * (int64_t)r.n_cus;
+  }
   // the listed-pages pass: one wavefront takes a piece of an agent's list and every piece has its own partial result
   {
     int64_t max_pages = 0;

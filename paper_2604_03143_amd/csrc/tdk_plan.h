@@ -73,6 +73,7 @@ constexpr int64_t kMaxBlocks = (int64_t)1 << 31;     // workgroups of one launch
 struct AttendPlan {
   int32_t chunk_tokens = 0, n_chunks = 0, n_parts = 0, max_rows = 0, n_pieces = 1, piece_tokens = 0, piece_grid = 1;
   bool    own_rows = false;        // one agent per wavefront (tdk_attend_rows_kernel)
+  bool    pipelined = false;       // the shared launch's master pass with pipelined steps
   int32_t max_agents = 0;
   int32_t launch_sessions = 0;     // own_rows: sessions per launch
   int64_t rows = 0;

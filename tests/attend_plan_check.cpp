@@ -152,8 +152,30 @@ static int check_segment_rule() {
   return 0;
 }
 
+// Pipelined steps on both sides of their lines; the span a workgroup really walks counts, not the chunk it could.
+static int check_pipelined_rule() {
+  int cs = 0;
+  auto pipe = [](int sessions, int agents, int span, int heads, int group, bool seg = false) {
+    Made m;
+    m.shape.heads = heads;
+    m.shape.seg = seg;
+    for (int i = 0; i < sessions; ++i) m.add(span, agents);
+    AttendPlan p;
+    return attend_plan(m.done(), 1, group * heads, p) ? (int)(p.pipelined && !p.own_rows) : -1;
+  };
+  REQUIRE(pipe(10, 25, 5000, 8, 5) == 1 && pipe(10, 25, 600, 8, 1) == 1 && pipe(1, 50, 12000, 8, 2) == 1 && pipe(10, 12, 5000, 2, 5) == 1);
+  REQUIRE(pipe(1, 25, 5000, 8, 5) == 0 && pipe(1, 50, 2000, 8, 5) == 0 && pipe(1, 40, 5000, 8, 1) == 0);     // too few steps
+  REQUIRE(pipe(10, 25, 207, 8, 5) == 0 && pipe(100, 4, 511, 8, 5) == 0 && pipe(100, 4, 512, 8, 5) == 1);       // short spans
+  REQUIRE(pipe(10, 6, 2000, 8, 16) == 1 && pipe(10, 6, 2000, 8, 17) == 0 && pipe(10, 25, 5000, 8, 11) == 0);      // 32-row tiles; three row blocks
+  REQUIRE(pipe(10, 25, 5000, 8, 5, true) == 0);
+  // the rounds of the GPU tests of that form
+  REQUIRE(pipe(10, 4, 513, 8, 3) == 1 && pipe(10, 4, 575, 8, 3) == 1 && pipe(10, 4, 577, 8, 3) == 1 && pipe(10, 4, 640, 8, 3) == 1);
+  REQUIRE(pipe(2, 12, 5301, 8, 16) == 1);
+  return 0;
+}
+
 int main() {
-  if (check_grids() || check_workspace() || check_segment_rule()) return 1;
+  if (check_grids() || check_workspace() || check_segment_rule() || check_pipelined_rule()) return 1;
   std::printf("attention planner: clean\n");
   return 0;
 }

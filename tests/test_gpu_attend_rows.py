@@ -132,3 +132,18 @@ def test_packed_rows_in_two_blocks_and_several_chunks(tdo):
     """18 rows per agent and KV head: two blocks of 128 rows, the second not full; a span of several chunks."""
     spec = wl.RoundSpec("rows8", 98, 1, 8, 128, 16, 1.0e6, 3, 12, 3, 500, 3, 200, 0.1)
     _case(tdo, spec, 9, 16)
+
+
+@pytest.mark.parametrize("T,style,span,scale,grow", [(16, 0, 513, None, False), (16, 1, 575, 1.0, True), (32, 0, 577, -0.2, False),
+                                                     (32, 1, 640, None, True)])
+def test_pipelined_steps_around_their_ends(tdo, T, style, span, scale, grow):
+    """Ten sessions of four agents x 8 KV heads, spans of 9 and 10 steps: the master pass with pipelined steps (the planner's
+    own test pins that these rounds take it), at odd and even numbers of steps and ragged ends, with listed pages."""
+    spec = wl.RoundSpec("rows9", 99, 1, 8, 128, T, 1.0e6, 10, 4, 1, span, 3, 200, 0.2)
+    _case(tdo, spec, 1, 24, style=style, scale=scale, grow=np.arange(40) * 5 if grow else None)
+
+
+def test_pipelined_steps_in_two_blocks_and_several_chunks(tdo):
+    """16 rows per agent and KV head: two blocks of 128 rows, the second half full; spans of several chunks."""
+    spec = wl.RoundSpec("rows10", 100, 1, 8, 128, 16, 1.0e6, 2, 12, 1, 5301, 3, 200, 0.05)
+    _case(tdo, spec, 2, 64)
