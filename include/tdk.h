@@ -133,8 +133,7 @@ size_t     tdk_scratch_bytes(const tdk_round* r);       /* device bytes the roun
  * through L2 and written back early instead of lingering as dirty lines that the next kernel has to
  * flush); the default was measured best for the whole rerotate / decode / encode sequence.
  * Synchronises the device (the work list it replaces may still be in use).  Results never depend on
- * these settings.  The page kernels of models with 1, 2 or 4 KV heads stream whatever the first three NT flags say
- * (several rows share an access there, in that one form). */
+ * these settings. */
 #define TDK_TUNE_NT_REROTATE_STORES 1
 #define TDK_TUNE_NT_DECODE_STORES   2
 #define TDK_TUNE_NT_COMPARE_LOADS   4

@@ -1468,10 +1468,6 @@ template <class F> static void with_rows(const RoundDev& rd, F f) {
     default: f(ic<4>{}, std::true_type{}); break;
   }
 }
-// the cache policy as a type: packed rows are always streamed (one instantiation each)
-template <class P, class F> static void with_policy(P, bool nt, F f) {
-  if constexpr (P::value) { f(std::true_type{}); } else { if (nt) f(std::true_type{}); else f(std::false_type{}); }
-}
 template <class F> static void with_bool(bool b, F f) { if (b) f(std::true_type{}); else f(std::false_type{}); }
 template <class F> static void with_planes(int planes, F f) {
   if (planes == 1) f(ic<1>{}); else if (planes == 2) f(ic<2>{}); else f(ic<3>{});
@@ -1479,7 +1475,7 @@ template <class F> static void with_planes(int planes, F f) {
 
 hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
-  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_policy(pack, (rd.nontemporal & 1) != 0, [&](auto nt) {
+  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 1) != 0, [&](auto nt) {
     with_bool(rd.seg != 0, [&](auto sg) {
       constexpr int R = decltype(rpw)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
@@ -1492,7 +1488,7 @@ hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t s
 hipError_t launch_flag(const RoundDev& rd, const LayerDev& io, float eps, int planes, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
   with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_planes(planes, [&](auto pm) {
-    with_bool(rd.seg != 0, [&](auto sg) { with_policy(pack, (rd.nontemporal & 4) != 0, [&](auto ntl) {
+    with_bool(rd.seg != 0, [&](auto sg) { with_bool((rd.nontemporal & 4) != 0, [&](auto ntl) {
       hipLaunchKernelGGL((tdk_flag_kernel<decltype(rpw)::value, decltype(pack)::value, decltype(il)::value, decltype(pm)::value, decltype(sg)::value,
                                           decltype(ntl)::value>), dim3(rd.n_rwork), dim3(kBlock), 0, st, rd, io, eps);
     }); });
@@ -1528,7 +1524,7 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
   *scattered = false;
   if (rd.n_work == 0) return hipSuccess;
   if (rd.n_agents == 0 || d.capacity == 0) scatter_blocks = 0;
-  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_policy(pack, (rd.nontemporal & 2) != 0, [&](auto nt) {
+  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 2) != 0, [&](auto nt) {
     with_planes(planes, [&](auto pm) { with_bool(rd.seg != 0, [&](auto sg) {
       constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
@@ -1549,7 +1545,7 @@ hipError_t launch_scatter(const RoundDev& rd, const LayerDev& io, const DiffDev&
 hipError_t launch_keydiff(const RoundDev& rd, const LayerDev& io, const PlanDev& pl, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
   with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool(rd.seg != 0, [&](auto sg) {
-    with_policy(pack, (rd.nontemporal & 4) != 0, [&](auto ntl) {
+    with_bool((rd.nontemporal & 4) != 0, [&](auto ntl) {
       hipLaunchKernelGGL((tdk_keydiff_kernel<decltype(rpw)::value, decltype(pack)::value, decltype(il)::value, decltype(sg)::value, decltype(ntl)::value>),
                          dim3(rd.n_rwork), dim3(kBlock), 0, st, rd, io, pl);
     });
