@@ -25,8 +25,9 @@ extern "C" {
 #define TDK_KERNEL_SELECT   7
 #define TDK_KERNEL_MASTER   8    /* the choice of the masters: part of TDK_KERNEL_SELECT's launch, no launches of its own */
 #define TDK_KERNEL_ATTEND_QROT   9
-#define TDK_KERNEL_ATTEND_MASTER 10   /* also the launch that holds the master and the listed-pages pass together */
-#define TDK_KERNEL_ATTEND_DIFF   11   /* (no launches of its own when that shared launch is used)                  */
+#define TDK_KERNEL_ATTEND_MASTER 10   /* also the launches that hold the master and the listed-pages pass together
+                                         (tdk_attend_fused_kernel, tdk_attend_rows_kernel) */
+#define TDK_KERNEL_ATTEND_DIFF   11   /* (no launches of its own when one of those is used) */
 #define TDK_KERNEL_ATTEND_MERGE  12
 #define TDK_KERNEL_KINDS    13
 tdk_status tdk_timing_enable(tdk_round* r, int32_t on);

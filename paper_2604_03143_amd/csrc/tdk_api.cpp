@@ -259,7 +259,7 @@ const char* tdk_kernel_name(int32_t kernel) {
     case TDK_KERNEL_MASTER: return "tdk_select_kernel";
     case TDK_KERNEL_ATTEND_QROT: return "tdk_attend_qrot_kernel";
     case TDK_KERNEL_ATTEND_MASTER: return "tdk_attend_master_kernel";
-    case TDK_KERNEL_ATTEND_DIFF: return "tdk_attend_diff_kernel";
+    case TDK_KERNEL_ATTEND_DIFF: return "tdk_attend_diff16_kernel";
     case TDK_KERNEL_ATTEND_MERGE: return "tdk_attend_merge_kernel";
   }
   return "";

@@ -753,7 +753,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // listed tokens and has its own partial result, so there is nothing to combine inside the kernel; workgroups
 // whose piece lies past the end of the agent's list leave at once (the merge knows how many pieces an agent
 // has).  The K rows go straight from the payload into the MFMA operand registers, the V rows through one
-// row-major tile in LDS.  32 query rows at a time.
+// row-major tile in LDS.  This form: 17 to 32 query rows per agent and KV head.
 // ---------------------------------------------------------------------------------------------
 
 // Vs: this wavefront's V tile, kTile * kVsStride bf16 elements; lane: 0..63.  MOVED: some agent's diff sits at other positions
@@ -781,96 +781,92 @@ __device__ __forceinline__ bool attend_diff32_piece(const RoundDev& rd, const Di
   auto tok_off = [&](int tk) { return (uint32_t)(tk / T) * 2u * page_u + (uint32_t)(tk % T) * row_u + (uint32_t)(h * kHeadDim); };
   const int st_row = lane >> 4, st_pc = lane & 15;
 
-  for (int r0 = 0; r0 < per_agent; r0 += kRowsPerWave) {
-    // this lane's query row of the block
-    const int rem = r0 + n;
-    const bool row_ok = rem < per_agent;
-    const int qi = row_ok ? rem / at.group : 0, g = row_ok ? rem - qi * at.group : 0;
-    const int64_t out = ((int64_t)agent * at.n_q + qi) * at.n_q_heads + h * at.group + g;
-    bf16x8 qf[8];
+  // this lane's query row (at most 32 per agent and KV head: one block)
+  const bool row_ok = n < per_agent;
+  const int qi = row_ok ? n / at.group : 0, g = row_ok ? n - qi * at.group : 0;
+  const int64_t out = ((int64_t)agent * at.n_q + qi) * at.n_q_heads + h * at.group + g;
+  bf16x8 qf[8];
+  {
+    // the listed pages meet the caller's rows as they are, or turned back by the distance the stored values have moved
+    const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim);
+    const uint32_t flip = at.q_flip ? 0x80008000u : 0u;
+    u32x4 raw[8];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      u32x4 v = {0, 0, 0, 0};
+      if (row_ok) v = qp[2 * kk + hh];
+      raw[kk] = u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip};
+      qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
+    }
+    if (MOVED && ad.diff_rot) turn_back32(raw, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, hh, qf);
+  }
+  RowState rs;
+  row_state_init(rs);
+  // The next tile travels from the payload to registers while the current one is multiplied.  K: lane
+  // (n, hh) loads what it multiplies, elements 16 kk + 8 hh .. + 7 of the row of token n.  V: sixteen lanes
+  // per 256-byte row, four rows per instruction.  The payload address of a listed token depends on its place
+  // in the list alone, so the rows are requested together with the page number; what the page number decides
+  // (does the token lie inside the span, which segment holds it) is settled when the tile is used.
+  u32x4 kreg[8], vreg[8];
+  int p_next = -1;                             // master page of token lane % 32 of the fetched tile (-1: no such token)
+  auto fetch = [&](int tile) {
+    const int t = tile * kTile + n;
+    const bool there = t < n_tok;
+    p_next = there ? d.idx[lo + t / T] : -1;
+    const u32x4 z = {0, 0, 0, 0};
+    const uint32_t tile_off = (uint32_t)tile * tile_u;
+    const uint32_t off = tile_off + tok_off(n) + 8u * hh;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      kreg[kk] = z;
+      if (there) kreg[kk] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(apay + off + 16 * kk));
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      vreg[j] = z;
+      if (tile * kTile + 4 * j + st_row < n_tok)
+        vreg[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(apay + tile_off + tok_off(4 * j + st_row) + page_u + 8u * st_pc));
+    }
+  };
+  fetch(tile_begin);
+  for (int tile = tile_begin; tile < tile_end; ++tile) {
+    wave_sync();                               // the previous tile has been consumed
+    // bit t of valid: token t of the tile exists and lies inside the span (lanes 32..63 repeat lanes 0..31)
+    bool ok = false;
     {
-      // the listed pages meet the caller's rows as they are, or turned back by the distance the stored values have moved
-      const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim);
-      const uint32_t flip = at.q_flip ? 0x80008000u : 0u;
-      u32x4 raw[8];
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        u32x4 v = {0, 0, 0, 0};
-        if (row_ok) v = qp[2 * kk + hh];
-        raw[kk] = u32x4{v.x ^ flip, v.y ^ flip, v.z ^ flip, v.w ^ flip};
-        qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
-      }
-      if (MOVED && ad.diff_rot) turn_back32(raw, rd.tab_diff + (size_t)agent * (2 * kHalf), rd.interleaved, hh, qf);
+      const int rr = (tile * kTile + n) % T, p = p_next;
+      ok = p >= 0 && p < sd.pages && p * T + rr < sd.span;
     }
-    RowState rs;
-    row_state_init(rs);
-    // The next tile travels from the payload to registers while the current one is multiplied.  K: lane
-    // (n, hh) loads what it multiplies, elements 16 kk + 8 hh .. + 7 of the row of token n.  V: sixteen lanes
-    // per 256-byte row, four rows per instruction.  The payload address of a listed token depends on its place
-    // in the list alone, so the rows are requested together with the page number; what the page number decides
-    // (does the token lie inside the span, which segment holds it) is settled when the tile is used.
-    u32x4 kreg[8], vreg[8];
-    int p_next = -1;                             // master page of token lane % 32 of the fetched tile (-1: no such token)
-    auto fetch = [&](int tile) {
-      const int t = tile * kTile + n;
-      const bool there = t < n_tok;
-      p_next = there ? d.idx[lo + t / T] : -1;
+    const uint32_t valid = (uint32_t)__ballot(ok);
+    if (valid != 0xffffffffu) {                // rows of tokens that do not count are staged as zeros
       const u32x4 z = {0, 0, 0, 0};
-      const uint32_t tile_off = (uint32_t)tile * tile_u;
-      const uint32_t off = tile_off + tok_off(n) + 8u * hh;
 #pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        kreg[kk] = z;
-        if (there) kreg[kk] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(apay + off + 16 * kk));
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        vreg[j] = z;
-        if (tile * kTile + 4 * j + st_row < n_tok)
-          vreg[j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(apay + tile_off + tok_off(4 * j + st_row) + page_u + 8u * st_pc));
-      }
-    };
-    fetch(tile_begin);
-    for (int tile = tile_begin; tile < tile_end; ++tile) {
-      wave_sync();                               // the previous tile has been consumed
-      // bit t of valid: token t of the tile exists and lies inside the span (lanes 32..63 repeat lanes 0..31)
-      bool ok = false;
-      {
-        const int rr = (tile * kTile + n) % T, p = p_next;
-        ok = p >= 0 && p < sd.pages && p * T + rr < sd.span;
-      }
-      const uint32_t valid = (uint32_t)__ballot(ok);
-      if (valid != 0xffffffffu) {                // rows of tokens that do not count are staged as zeros
-        const u32x4 z = {0, 0, 0, 0};
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (!((valid >> (4 * j + st_row)) & 1u)) vreg[j] = z;     // (their scores are switched off below)
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) *reinterpret_cast<u32x4*>(Vs + (4 * j + st_row) * kVsStride + 8 * st_pc) = vreg[j];
-      f32x16 sacc;
-      scores32(kreg, qf, sacc);
-      wave_sync();                               // the V tile is complete
-      if (tile + 1 < tile_end) fetch(tile + 1);  // the K registers are free: the scores are taken
-      // score i of a lane belongs to token 8 (i / 4) + 4 hh + i % 4: four nibbles of `valid`
-      const uint32_t vs = valid >> (4 * hh);
-      uint32_t live = (vs & 0xfu) | ((vs >> 4) & 0xf0u) | ((vs >> 8) & 0xf00u) | ((vs >> 12) & 0xf000u);
-      if (!row_ok) live = 0;
-      softmax_pv32(Vs, sacc, at.scale, live, lane, rs);
+      for (int j = 0; j < 8; ++j)
+        if (!((valid >> (4 * j + st_row)) & 1u)) vreg[j] = z;     // (their scores are switched off below)
     }
-    // this piece's partial result for the block's rows: lane (n, hh) holds elements 32 b + 8 q + 4 hh + (0..3) of row n
-    const float l_tot = rs.l_run + __shfl_xor(rs.l_run, 32);
-    if (row_ok) {
-      const int64_t slot = out * at.n_parts + at.n_chunks + piece;
-      float4* po = reinterpret_cast<float4*>(at.part_o + slot * kHeadDim);
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
+    for (int j = 0; j < 8; ++j) *reinterpret_cast<u32x4*>(Vs + (4 * j + st_row) * kVsStride + 8 * st_pc) = vreg[j];
+    f32x16 sacc;
+    scores32(kreg, qf, sacc);
+    wave_sync();                               // the V tile is complete
+    if (tile + 1 < tile_end) fetch(tile + 1);  // the K registers are free: the scores are taken
+    // score i of a lane belongs to token 8 (i / 4) + 4 hh + i % 4: four nibbles of `valid`
+    const uint32_t vs = valid >> (4 * hh);
+    uint32_t live = (vs & 0xfu) | ((vs >> 4) & 0xf0u) | ((vs >> 8) & 0xf00u) | ((vs >> 12) & 0xf000u);
+    if (!row_ok) live = 0;
+    softmax_pv32(Vs, sacc, at.scale, live, lane, rs);
+  }
+  // this piece's partial result: lane (n, hh) holds elements 32 b + 8 q + 4 hh + (0..3) of row n
+  const float l_tot = rs.l_run + __shfl_xor(rs.l_run, 32);
+  if (row_ok) {
+    const int64_t slot = out * at.n_parts + at.n_chunks + piece;
+    float4* po = reinterpret_cast<float4*>(at.part_o + slot * kHeadDim);
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4)
-          po[(32 * b + 8 * q4 + 4 * hh) >> 2] = make_float4(rs.oacc[b][4 * q4], rs.oacc[b][4 * q4 + 1], rs.oacc[b][4 * q4 + 2], rs.oacc[b][4 * q4 + 3]);
-      if (hh == 0) { at.part_m[slot] = part_max(rs.m_run, l_tot); at.part_l[slot] = l_tot; }
-    }
-    wave_sync();                                 // before the next block's first tile overwrites the V tile
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        po[(32 * b + 8 * q4 + 4 * hh) >> 2] = make_float4(rs.oacc[b][4 * q4], rs.oacc[b][4 * q4 + 1], rs.oacc[b][4 * q4 + 2], rs.oacc[b][4 * q4 + 3]);
+    if (hh == 0) { at.part_m[slot] = part_max(rs.m_run, l_tot); at.part_l[slot] = l_tot; }
   }
   return true;
 }

@@ -22,3 +22,9 @@ def kernels():
 def test_few_heads_have_both_cache_policies(kernels, form):
     """TDK_TUNE_NT_* choose the policy for models with 1, 2 or 4 KV heads too (several rows per access)."""
     assert form.format("true") in kernels and form.format("false") in kernels
+
+
+def test_timed_kernels_have_the_names_they_are_given(kernels):
+    names = {k.split("<")[0] for k in kernels}
+    for kind in range(tdk.KERNEL_KINDS):
+        assert tdk.tdk_kernel_name(kind) in names, kind
