@@ -394,6 +394,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   r->rd.seg_src = any_segments ? reinterpret_cast<const int32_t*>(base + o_seg_src) : nullptr;
   r->rd.n_agents = n_agents;
   r->rd.master_rows = r->total_master_rows;
+  r->rd.diff_moved = r->diff_moved ? 1 : 0;
   r->rd.max_span = 0;
   for (const auto& hs : r->sessions) if (!hs.agents.empty()) r->rd.max_span = std::max(r->rd.max_span, hs.span);
   r->rd.n_sessions = n_sessions;

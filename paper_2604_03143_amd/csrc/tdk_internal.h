@@ -46,6 +46,7 @@ struct RoundDev {
   int32_t nontemporal;
   int32_t seg;               // 1: rowmap / pagetab / segtab describe the layout
   int32_t max_span;          // longest span of a session with agents
+  int32_t diff_moved;        // some agent's stored diff sits at other positions: its K rows are turned on restore
   int64_t master_rows;       // rows of master_k / master_v (all sessions)
 };
 

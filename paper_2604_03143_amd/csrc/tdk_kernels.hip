@@ -683,9 +683,9 @@ constexpr int kCopyBatch = 8;
 
 // Planes p0 .. p1 - 1 (0 = K, 1 = V) of one slot between pool and payload; slot_data: the payload of plane p0.  A row past
 // the span (row < 0) is zero in the payload and not written in the pool.  No branch stands around a load: a load with
-// nothing to fetch repeats one of its page.  NT: streaming stores; NTL: non-temporal loads.  (The gather's loads are always
-// ordinary ones: the next compare finds the pages it reads in the memory-side cache; 85 agents x 8914 tokens, one
-// page in 17 listed: 539 us with non-temporal loads, 528 with ordinary ones.)
+// nothing to fetch repeats one of its page.  NT: streaming stores; NTL: non-temporal loads.  (The gather streams both:
+// with caches that change from call to call a store of 180 agents x 2166 tokens, one page in ten listed, took 277 us with
+// ordinary loads and 263 streamed; 30 agents x 2000, one in five, 69 and 70.)
 template <bool TO_PAYLOAD, bool NT, bool NTL>
 __device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io, u32x4* slot_data, int p0, int p1, const SlotShared& sh) {
   const int row_u4 = rd.heads * 16, page_u4 = rd.page_tokens * row_u4, n = (p1 - p0) * page_u4;
@@ -722,7 +722,7 @@ __device__ __forceinline__ void gather_slot(const RoundDev& rd, const LayerDev& 
                                             const SlotShared& sh) {
   const int p0 = planes == 2 ? 1 : 0, p1 = planes == 1 ? 1 : 2;
   u32x4* data = d.payload + slot * (p1 - p0) * (int64_t)(rd.page_tokens * rd.heads * 16);
-  if (rd.nontemporal & 16) copy_slot<true, true, false>(rd, io, data, p0, p1, sh);
+  if (rd.nontemporal & 16) copy_slot<true, true, true>(rd, io, data, p0, p1, sh);
   else copy_slot<true, false, false>(rd, io, data, p0, p1, sh);
 }
 
@@ -869,13 +869,16 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
   const int row_u4 = rd.heads * 16;
   const int page_u4 = T * row_u4;
   const Lane L = lane_geometry<false>(rd.heads, T);
-  // Payload reads are streamed only where the payload and the masters together exceed the 256 MB memory-side cache: there
-  // they would push the masters out (250 agents, ten sessions, 94 and 297 MB of payload beside 205 MB of masters: whole restore
-  // 1040 and 1104 us with ordinary reads, 957 and 1000 streamed; 64 agents, 320 + 52 MB: 732 -> 692).  What fits is
-  // found there, if it was written or read lately, and streamed reads are slower (64 agents, 128 and 192 + 52 MB: 634 and
-  // 642 us, streamed 650 and 662; 212 agents of four sessions, 236 + 22 MB: 240 and 271).  A call on one plane counts the other
-  // plane's half too: a program restores both in turn (20 agents, 52 + 133 MB a plane: 368 us, streamed 335).
-  const bool stream = (rd.nontemporal & 8) && (total * page_u4 + rd.master_rows * row_u4) * 32 > (int64_t)256 << 20;
+  // Payload reads are streamed where the call's inputs are too many to be found in the 256 MB memory-side cache by the time
+  // they are read: there ordinary reads find nothing and push the masters out, which are read more than once.  What the call
+  // leaves in that cache is counted: payload and masters, and for moved diffs the K rows once more, whose stores are
+  // ordinary ones.  Measured with inputs that change from call to call, ordinary -> streamed: 20, 41, 61 MB 43.6 -> 48.6,
+  // 82.4 -> 88.0, 121 -> 127 us; 73 MB 150 -> 155; 84 MB 125 -> 122; 92 MB 96.7 -> 101; 94 MB 297 -> 282; 102 MB 218 -> 209;
+  // 133 MB 155 -> 146; 184 MB 205 -> 193; 306 MB 293 -> 266; moved diffs 55 MB 70.4 -> 74.8, 75 MB 91.3 -> 93.4, 83 MB
+  // 110 -> 105 and 107 -> 102.  (One set of inputs over and over stays with ordinary reads up to 256 MB: 180 MB 634 us, streamed
+  // 650.)  A call on one plane counts both: a program restores them in turn.
+  const int64_t u4s = total * page_u4 * (rd.diff_moved ? 3 : 2) + rd.master_rows * row_u4 * 2;
+  const bool stream = (rd.nontemporal & 8) && u4s * 16 > (int64_t)80 << 20;
   for (int64_t slot = first; slot < total; slot += stride) {
     if (threadIdx.x == 0) sh.owner = -1;
     __syncthreads();

@@ -1,6 +1,6 @@
 """Payload copies of the restore in their two load policies: ordinary reads, and streamed reads where payload and masters
-exceed the memory-side cache (256 MB).  The round is a little larger than that, so the policy is the streamed one; with the
-streaming of the copies switched off it is the ordinary one.  The pools must be the same, bit for bit, and hold the payload
+exceed 80 MB.  The round is larger than that, so the policy is the streamed one; with the streaming of the copies switched
+off it is the ordinary one.  The pools must be the same, bit for bit, and hold the payload
 in the listed rows."""
 import numpy as np
 import pytest
@@ -27,7 +27,7 @@ def test_streamed_and_ordinary_reads(T, moved):
         tables.append(bt)
     pages = -(-span // T)
     lists = [np.sort(g.choice(pages, size=listed, replace=False)).astype(np.int32) for _ in range(agents)]
-    assert (span * 2 + agents * listed * T * 2) * H * D * 2 > 256 << 20
+    assert (span * 2 + agents * listed * T * 2) * H * D * 2 > 80 << 20
     r = tdk.tdk_round_create(tdk.model(1, H, D, T, 1.0e6, tdk.ROPE_HALF), [span], [0], [0] * agents, pos0, tables, pos0 - moved, None, None)
     try:
         bits = lambda *shape: torch.randint(0, 0x7000, shape, dtype=torch.int16, device="cuda")
