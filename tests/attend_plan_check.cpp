@@ -148,6 +148,7 @@ static int check_segment_rule() {
   REQUIRE(own(1, 25, 9000, 8, 8, false, 256) == 1 && own(4, 22, 3230, 8, 8, false, 256) == 0 && own(10, 25, 600, 8, 16, false, 256) == 0);
   REQUIRE(own(2, 8, 1500, 8, 4, true, 256) == 1 && own(1, 25, 2500, 8, 4, true, 256) == 0 && own(1, 25, 2500, 8, 4, false, 256) == 1);
   REQUIRE(own(10, 25, 600, 8, 17, true, 256) == 1 && own(10, 25, 5000, 8, 20, false, 256) == 1);
+  REQUIRE(own(1, 40, 900, 8, 3, true, 256) == 0 && own(1, 5, 700, 2, 3, true, 256) == 1);      // the rounds of the GPU tests
   REQUIRE(own(1, 25, 2500, 8, 1, false, 128) == 0 && own(1, 25, 5000, 8, 1, false, 512) == 1);
   return 0;
 }

@@ -122,8 +122,8 @@ def test_empty_spans(tdo, n_q, Hq):
 @pytest.mark.parametrize("T,style,span,scale,grow", [(16, 0, 63, None, False), (16, 1, 64, 1.0, True), (32, 0, 65, -0.2, False),
                                                      (16, 0, 193, None, True), (32, 1, 700, None, False)])
 def test_packed_rows_of_many_lists(tdo, T, style, span, scale, grow):
-    """36 agents x 8 KV heads (more lists than compute units) in two sessions, 3 rows per agent and KV head: the master pass
-    with pipelined steps, at spans around a step, with listed pages and ragged ends."""
+    """36 agents x 8 KV heads (more lists than compute units) in two sessions, 3 rows per agent and KV head: the packed
+    master pass at spans around a step, too short for pipelined steps, with listed pages and ragged ends."""
     spec = wl.RoundSpec("rows7", 97, 1, 8, 128, T, 1.0e6, 2, 18, 1, span, 3, 200, 0.25)
     _case(tdo, spec, 1, 24, style=style, scale=scale, grow=np.arange(36) * 5 if grow else None)
 

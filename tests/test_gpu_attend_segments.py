@@ -63,7 +63,28 @@ def test_one_segment_per_agent_stored_elsewhere(tdo, n_agents, H, n_q, Hq, T, st
                  perturbed=min(spec.span_pages, 12))
 
 
-# rows per agent and KV head: 3 and 16 (packed form or a wavefront per agent), 20 and 40 (a wavefront per agent)
+def random_segments(rnd, span, T, g):
+    """Six segments per agent, cut at random tokens, in random order."""
+    out = []
+    for p in rnd.agent_pos0:
+        cuts = np.unique(np.concatenate([[0], np.sort(g.choice(np.arange(1, span // T), 5, replace=False)) * T + int(g.integers(0, T))]))
+        lens = np.diff(np.concatenate([cuts, [span]]))
+        order = g.permutation(len(cuts))
+        dst = np.empty(len(cuts), np.int64)
+        dst[order] = int(p) + np.concatenate([[0], np.cumsum(lens[order])[:-1]])
+        out.append(np.stack([cuts, dst, lens], 1))
+    return out
+
+
+def moved_by(rnd, how):
+    out = []
+    for i, s in enumerate(rnd.segments):
+        kind = {"together": 0, "apart": 1, "mixed": i % 3}[how]
+        out.append(s[:, 1] - (23 * (i % 7 + 1) if kind == 0 else 11 + 17 * np.arange(len(s)) if kind == 1 else 0))
+    return out
+
+
+# a wavefront per agent: 3, 16, 20 and 40 rows per agent and KV head
 @pytest.mark.parametrize("how", ["together", "apart", "mixed"])
 @pytest.mark.parametrize("n_q,Hq,T,style", [(1, 6, 16, 0), (4, 8, 32, 1), (5, 8, 32, 0), (10, 8, 16, 1)])
 def test_segments_moved_together_and_apart(tdo, how, n_q, Hq, T, style):
@@ -72,23 +93,13 @@ def test_segments_moved_together_and_apart(tdo, how, n_q, Hq, T, style):
     kinds and one that has not moved, in one round."""
     spec = wl.RoundSpec("seg2", 102, 1, 2, 128, T, 1.0e6, 1, 5, 1, 700, 900, 1200, 0.5)
     g = np.random.default_rng([102, T, n_q])
+    segment_case(tdo, spec, lambda rnd: random_segments(rnd, 700, T, g), lambda rnd: moved_by(rnd, how), n_q, Hq, style=style, scale=1.0)
 
-    def segments(rnd):
-        out = []
-        for p in rnd.agent_pos0:
-            cuts = np.unique(np.concatenate([[0], np.sort(g.choice(np.arange(1, 700 // T), 5, replace=False)) * T + int(g.integers(0, T))]))
-            lens = np.diff(np.concatenate([cuts, [700]]))
-            order = g.permutation(len(cuts))
-            dst = np.empty(len(cuts), np.int64)
-            dst[order] = int(p) + np.concatenate([[0], np.cumsum(lens[order])[:-1]])
-            out.append(np.stack([cuts, dst, lens], 1))
-        return out
 
-    def moved(rnd):
-        out = []
-        for i, s in enumerate(rnd.segments):
-            kind = {"together": 0, "apart": 1, "mixed": i % 3}[how]
-            out.append(s[:, 1] - (23 * (i + 1) if kind == 0 else 11 + 17 * np.arange(len(s)) if kind == 1 else 0))
-        return out
-
-    segment_case(tdo, spec, segments, moved, n_q, Hq, style=style, scale=1.0)
+@pytest.mark.parametrize("how", ["apart", "mixed"])
+def test_packed_rows_with_half_of_the_pages_listed(tdo, how):
+    """The same with 40 agents x 8 KV heads and 3 rows per agent, a round that packs the rows of several agents: the lists go
+    to the 16-row pass, with the rows turned for every segment."""
+    spec = wl.RoundSpec("seg3", 103, 1, 8, 128, 16, 1.0e6, 1, 40, 1, 900, 900, 1200, 0.5)
+    g = np.random.default_rng([103])
+    segment_case(tdo, spec, lambda rnd: random_segments(rnd, 900, 16, g), lambda rnd: moved_by(rnd, how), 1, 24, scale=1.0)
