@@ -677,7 +677,7 @@ __device__ __forceinline__ int64_t slot_row(const RoundDev& rd, const AgentDev& 
 
 // 16-byte accesses per thread in flight in gather / scatter: a K and a V page are 16 accesses per thread, so a slot is
 // two round trips to memory (with 4 in flight, and a branch around each, it was four: payload copies of 64 agents x 12800
-// tokens with a tenth of the pages listed 141 -> 137 us, the whole restore 735 -> 692; 48 agents with moved mirrors and
+// tokens with a tenth of the pages listed 141 -> 137 us, with streamed reads; 48 agents with moved mirrors and
 // their own block orders, whose K rows are turned four at a time now instead of one, 148 -> 124 us).
 constexpr int kCopyBatch = 8;
 
