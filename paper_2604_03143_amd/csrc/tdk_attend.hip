@@ -419,31 +419,26 @@ __device__ __forceinline__ void turn_back16(bf16x8 (&qf)[4], const float* tab, b
   }
 }
 
-// Loads a query row's B operands for the 32-row tiles: fragment kk of a lane holds elements 16 kk + 8 hh .. + 7.
-// tab != NULL turns the row back by that rotation.  All lanes of the wavefront use the same table; it goes through
-// lds_tab (128 floats of this wavefront), so that the fragments are turned one pair at a time with few registers.
-// A negative scale's sign travels with the rows.
-__device__ __forceinline__ void load_queries(const AttendDev& at, bool interleaved, int64_t out, bool on, const float* tab, float* lds_tab,
-                                             int lane, bf16x8 (&qf)[8]) {
-  const int hh = lane >> 5;
+// A query row as it is, in the order of the B operands for the 32-row tiles: fragment kk of a lane holds elements
+// 16 kk + 8 hh .. + 7.  A negative scale's sign travels with the rows.
+__device__ __forceinline__ void raw_queries(const AttendDev& at, int64_t out, bool on, int lane, u32x4 (&raw)[8]) {
   const uint32_t flip = at.q_flip ? 0x80008000u : 0u;
-  float2 t2 = make_float2(1.f, 0.f);
-  if (tab) t2 = reinterpret_cast<const float2*>(tab)[lane];
-  u32x4 raw[8];
   const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim);
   const uint32_t keep = on ? 0xffffffffu : 0u;             // (a row that does not exist reads another and is zero)
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk) {
-    const u32x4 v = qp[2 * kk + hh];
+    const u32x4 v = qp[2 * kk + (lane >> 5)];
     raw[kk] = u32x4{(v.x ^ flip) & keep, (v.y ^ flip) & keep, (v.z ^ flip) & keep, (v.w ^ flip) & keep};
   }
-  if (!tab) {
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
-    return;
-  }
+}
+
+// Those rows turned back by the rotation whose table the wavefront's lanes hold (entries 2 lane and 2 lane + 1 of its
+// 128); it goes through lds_tab (128 floats of this wavefront), so that the fragments are turned one pair at a time
+// with few registers.
+__device__ __forceinline__ void turn_queries(const u32x4 (&raw)[8], bool interleaved, float2 tab, float* lds_tab, int lane, bf16x8 (&qf)[8]) {
+  const int hh = lane >> 5;
   wave_sync();                                           // an earlier table has been used
-  reinterpret_cast<float2*>(lds_tab)[lane] = t2;
+  reinterpret_cast<float2*>(lds_tab)[lane] = tab;
   wave_sync();
   if (!interleaved) {
 #pragma unroll
@@ -472,6 +467,35 @@ __device__ __forceinline__ void load_queries(const AttendDev& at, bool interleav
       if (kk & 1) __builtin_amdgcn_sched_barrier(0);
     }
   }
+}
+
+// Both: tab != NULL turns the rows back by that rotation, the same for all lanes of the wavefront.
+__device__ __forceinline__ void load_queries(const AttendDev& at, bool interleaved, int64_t out, bool on, const float* tab, float* lds_tab,
+                                             int lane, bf16x8 (&qf)[8]) {
+  float2 t2 = make_float2(1.f, 0.f);
+  if (tab) t2 = reinterpret_cast<const float2*>(tab)[lane];
+  u32x4 raw[8];
+  raw_queries(at, out, on, lane, raw);
+  if (tab) {
+    turn_queries(raw, interleaved, t2, lds_tab, lane, qf);
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
+  }
+}
+
+// A wavefront's search in an ascending list: how many of the n entries from v on are smaller than x (64 probes a round).
+__device__ __forceinline__ int count_below(const int32_t* v, int n, int x, int lane) {
+  int at = 0;
+  while (n > 64) {
+    const int stride = (n + 63) >> 6, i = lane * stride;
+    const int c = __popcll(__ballot(i < n && v[at + i] < x));
+    if (c == 0) return at;
+    const int skip = (c - 1) * stride + 1;
+    at += skip;
+    n = min(stride - 1, n - skip);
+  }
+  return at + __popcll(__ballot(lane < n && v[at + lane] < x));
 }
 
 }  // namespace
@@ -1058,23 +1082,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // walks the span in 64-token steps; the four wavefronts of a workgroup share the master's K and V tiles in LDS,
 // whatever agents they belong to.  Because the rows of a wavefront have one agent, everything that depends on
 // the agent is uniform: the pages its diff lists (a bit mask in LDS; most steps have none and skip the masking),
-// the segment of its layout (one reload of the query fragments per border).  The same wavefront then adds the
+// the segment of its layout (one reload of the query fragments per border; the steps run over the borders, and the
+// scores of the tokens behind one are taken again).  The same wavefront then adds the
 // listed pages from the payload to the same accumulators, so a span that is not split needs no partial results
 // and no merge.
 // The steps are software-pipelined: the score products of step i + 1 stand beside the exponentials of step i
 // in one basic block (the matrix cores and the vector units then work at the same time within a wavefront),
 // the K and V tiles are double-buffered with one barrier per step, and the rows of the tiles after that travel
-// to registers meanwhile.
+// from memory straight to LDS meanwhile (through registers and LDS writes 204 to 217 us against 198 at the size below).
 // What bounds it (25 agents x 64 query tokens x 40 heads over 5000 tokens, 2 wavefronts per SIMD, counters): matrix
-// cores busy 46 %, vector units 42 %, LDS 47 % of the time, about 1 us per wavefront and step; no single pipe is
-// full, the rest is waiting between dependent stages (score products, maxima, exponentials, second products) and at the
-// barrier.  64 rows per wavefront (half the LDS bytes per product, one wavefront per SIMD) measured the same.
+// cores, vector units and LDS are each busy a little under half of the time, about 1 us per wavefront and step; no
+// single pipe is full, the rest is waiting between dependent stages (score products, maxima, exponentials, second
+// products) and at the barrier.  64 rows per wavefront (half the LDS bytes per product, one wavefront per SIMD) measured
+// the same.
 // Measured against rows of all agents in one block plus separate listed-pages and merge launches: 64 query tokens
-// per agent 462 -> 206 us, 16 tokens 140 -> 93 us, 8 tokens 94 -> 70 us.
+// per agent 462 -> 206 us, 16 tokens 140 -> 93 us, 8 tokens 94 -> 70 us.  Per-agent orders of blocks of 200 tokens, steps
+// that ended at every border, a chain of reads to find a chunk's first segment and page, tiles through registers -> now:
+// 25 agents x 5000 tokens, 20 rows 70 -> 54 us; 129 x 4307, 35 rows 502 -> 375; blocks of 64, 151 x 937, 80 rows 105 -> 81.
 // ---------------------------------------------------------------------------------------------
 constexpr int kRowsMaskWords = 32;                        // 32-bit words of a wavefront's page mask
 constexpr int kRowsMaxPages = 32 * kRowsMaskWords;        // pages per chunk
-constexpr int kRowsMaxTokens = 16 * kRowsMaxPages;        // tokens per chunk
 
 struct RowsGrid {
   int32_t blocks;       // workgroups (four wavefronts) per (session, KV head, chunk), for the largest session
@@ -1083,14 +1110,58 @@ struct RowsGrid {
   int32_t session0;     // first session of this launch
 };
 
+// The tiles of these kernels: rows of 256 bytes without padding, as the loads that write LDS directly leave them (a wavefront
+// instruction fills 1 KB: four rows), with the 16-byte pieces of a row exchanged so that the reads spread over the banks:
+// piece c of K row r stands at place c ^ (r % 16) (the score operands of 16 rows fall on all 64 banks), piece c of
+// V row r at c ^ 4 (r % 4) (the 64-byte parts of four rows that a transposing read meets do).
+constexpr int kStepTile = kBigTile * kHeadDim * 2;        // bytes of one K or V tile of a step
+__device__ __forceinline__ int k_place(int r, int c) { return r * (kHeadDim * 2) + 16 * (c ^ (r & 15)); }
+__device__ __forceinline__ int v_place(int r, int c) { return r * (kHeadDim * 2) + 16 * (c ^ (4 * (r & 3))); }
+
+// 16 bytes per lane from memory straight into LDS: lane l's piece goes to byte lds + 16 l.  base and lds are the same for
+// all lanes.  The instruction writes no register; the compiler does not see that it is in flight: landed() waits for it,
+// before the barrier that hands the tile over.  (The builtin makes every later LDS read of the kernel wait for the
+// tile, also reads of the other buffer.)  The wait states: M0 before its use, and base, which a vector instruction may
+// have written just before.  (M0 has no other use in these kernels.)
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
+}
+__device__ __forceinline__ void landed() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ uint32_t lds_byte(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p; }
+
+// One thread's share of the loads of a step's tile: thread t brings piece t % 16 of rows t / 16, 16 + t / 16, ...
+struct StepLoader {
+  uint32_t row_bytes, k_off, v_off;      // distance of two tokens in memory; this thread's places in the first 16 rows
+  int st_tok, st_pc;
+  uint32_t lds_wave;                     // where this wavefront's four rows of every sixteen go
+  __device__ __forceinline__ StepLoader(int heads) {
+    st_tok = threadIdx.x >> 4;
+    st_pc = threadIdx.x & 15;
+    row_bytes = (uint32_t)heads * (kHeadDim * 2);
+    k_off = (uint32_t)st_tok * row_bytes + 16u * (st_pc ^ (st_tok & 15));
+    v_off = (uint32_t)st_tok * row_bytes + 16u * (st_pc ^ (4 * (st_tok & 3)));
+    lds_wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * 1024u;
+  }
+  // rows 0 .. 63 from `tile` on into the LDS tile at byte `lds`; rows behind `last` repeat that one
+  __device__ __forceinline__ void load(const char* tile, int last, uint32_t first, uint32_t lds) const {
+    if (last >= kBigTile - 1) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) load_to_lds(tile + (size_t)(16 * e) * row_bytes, first, lds + 4096u * e + lds_wave);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        load_to_lds(tile, first - (uint32_t)st_tok * row_bytes + (uint32_t)min(16 * e + st_tok, last) * row_bytes, lds + 4096u * e + lds_wave);
+    }
+  }
+};
+
 struct RowsShared {
-  uint16_t k[2][kBigTile * kKsStride];
-  uint16_t v[2][kBigTile * kVsStride];
-  uint32_t border[kRowsMaxTokens / 32];                   // bit t: a segment of some agent begins at token t of the chunk
+  unsigned char k[2][kStepTile];
+  unsigned char v[2][kStepTile];
   float tab[kWaves][2 * kHalf];                           // rotation table of the query rows being loaded
   uint32_t mask[kWaves][kRowsMaskWords];                  // bit p: page p of the chunk is listed in the wavefront's agent's diff
 };
-static_assert(kWaves * kTile * (kKsStride + kVsStride) * 2 <= sizeof(RowsShared::k) + sizeof(RowsShared::v),
+static_assert(kWaves * 2 * kTile * kHeadDim * 2 <= sizeof(RowsShared::k) + sizeof(RowsShared::v),
               "the listed pages' tiles reuse the memory of the master's");
 
 // maximum of a value over the lane pair (n, n + 32)
@@ -1125,14 +1196,26 @@ __device__ __forceinline__ void rows_settle(float mx, float scale, RowState& st)
   }
 }
 
+// The operands of the two products, from tiles of rows of 256 bytes.  Score product: elements 16 kk + 8 hh .. + 7 of row n
+// of the 32 rows from `Ks` on.  Second product: see pv_tr; tokens 16 kk .. + 15, elements 32 q .. + 31.
+__device__ __forceinline__ bf16x8 k_operand(const unsigned char* Ks, int kk, int n, int hh) {
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(Ks + (k_place(n, hh) ^ (32 * kk))));
+}
+__device__ __forceinline__ bf16x8 v_operand(const unsigned char* Vs, int kk, int q, int lane) {
+  const int i16 = lane & 15, blk = lane >> 4;
+  const unsigned char* p = Vs + (v_place(4 * (blk >> 1) + (i16 >> 2), 2 * (blk & 1)) ^ (64 * q)) + 8 * (i16 & 3);
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + (16 * kk) * (kHeadDim * 2)));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + (16 * kk + 8) * (kHeadDim * 2)));
+  const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+  return __builtin_bit_cast(bf16x8, u32x4{l2.x, l2.y, h2.x, h2.y});
+}
+
 // NT tiles of 32 tokens: weights from the settled scores, sums, and O^T += V^T P^T (see pv_tr for the operands).
 template <int NT>
-__device__ __forceinline__ void rows_weights_pv(const uint16_t* Vs, const f32x16 (&s)[NT], float scale, int lane, RowState& st) {
+__device__ __forceinline__ void rows_weights_pv(const unsigned char* Vs, const f32x16 (&s)[NT], float scale, int lane, RowState& st) {
   constexpr float kLog2e = 1.4426950408889634f;
   const float c2 = scale * kLog2e;
   const float m2 = -(st.m_run == -INFINITY ? 0.f : st.m_run) * kLog2e;
-  const int i16 = lane & 15, blk = lane >> 4;
-  const uint16_t* base = Vs + (4 * (blk >> 1) + (i16 >> 2)) * kVsStride + 16 * (blk & 1) + 4 * (i16 & 3);
 #pragma unroll
   for (int kk = 0; kk < 2 * NT; ++kk) {
     float p[8];
@@ -1147,16 +1230,12 @@ __device__ __forceinline__ void rows_weights_pv(const uint16_t* Vs, const f32x16
     const bf16x8 pb = __builtin_bit_cast(bf16x8, w);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + (16 * kk) * kVsStride + 32 * q));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(base + (16 * kk + 8) * kVsStride + 32 * q));
-      const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-      const bf16x8 va = __builtin_bit_cast(bf16x8, u32x4{l2.x, l2.y, h2.x, h2.y});
-      st.oacc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb, st.oacc[q], 0, 0, 0);
+      st.oacc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(Vs, kk, q, lane), pb, st.oacc[q], 0, 0, 0);
     }
   }
 }
 
-__device__ __forceinline__ void rows_scores(const uint16_t* Ks, const bf16x8 (&qf)[8], int n, int hh, f32x16 (&s)[2]) {
+__device__ __forceinline__ void rows_scores(const unsigned char* Ks, const bf16x8 (&qf)[8], int n, int hh, f32x16 (&s)[2]) {
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -1164,10 +1243,8 @@ __device__ __forceinline__ void rows_scores(const uint16_t* Ks, const bf16x8 (&q
 #pragma unroll
   for (int kk = 0; kk < 8; ++kk)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(Ks + (kTile * t + n) * kKsStride + 16 * kk + 8 * hh));
-      s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], s[t], 0, 0, 0);
-    }
+    for (int t = 0; t < 2; ++t)
+      s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(Ks + t * (kStepTile / 2), kk, n, hh), qf[kk], s[t], 0, 0, 0);
 }
 
 // One pipelined step: the score products of the next step's K tile (16 operands of 32 tokens x 16 elements), the
@@ -1177,24 +1254,15 @@ __device__ __forceinline__ void rows_scores(const uint16_t* Ks, const bf16x8 (&q
 // operand four slots ahead, and a few weights (scale and reference point in one fma, exp2, sum, packing), spread so
 // that a slot's vector work takes about as long as its products; the maxima of the new scores stand in the last
 // slots.  nx: the raw scores of the next step, mx: their maxima; s is used up.
-__device__ __forceinline__ void rows_step(const uint16_t* Ks, const uint16_t* Vs, const bf16x8 (&qf)[8], f32x16 (&s)[2],
+__device__ __forceinline__ void rows_step(const unsigned char* Ks, const unsigned char* Vs, const bf16x8 (&qf)[8], f32x16 (&s)[2],
                                           f32x16 (&nx)[2], float& mx, float scale, int lane, RowState& st) {
   constexpr float kLog2e = 1.4426950408889634f;
-  constexpr int kAhead = 4;
-  const int n = lane & 31, hh = lane >> 5, i16 = lane & 15, blk = lane >> 4;
+  constexpr int kAhead = 4;                                 // (6 and 8 measured the same)
+  const int n = lane & 31, hh = lane >> 5;
   const float c2 = scale * kLog2e;
   const float m2 = -(st.m_run == -INFINITY ? 0.f : st.m_run) * kLog2e;
-  const uint16_t* kb = Ks + n * kKsStride + 8 * hh;
-  const uint16_t* vb = Vs + (4 * (blk >> 1) + (i16 >> 2)) * kVsStride + 16 * (blk & 1) + 4 * (i16 & 3);
-  auto k_op = [&](int j) {
-    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kb + (j & 1) * kTile * kKsStride + 16 * (j >> 1)));
-  };
-  auto v_op = [&](int j) {
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vb + 16 * (j >> 2) * kVsStride + 32 * (j & 3)));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vb + (16 * (j >> 2) + 8) * kVsStride + 32 * (j & 3)));
-    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
-    return __builtin_bit_cast(bf16x8, u32x4{l2.x, l2.y, h2.x, h2.y});
-  };
+  auto k_op = [&](int j) { return k_operand(Ks + (j & 1) * (kStepTile / 2), j >> 1, n, hh); };
+  auto v_op = [&](int j) { return v_operand(Vs, j >> 2, j & 3, lane); };
   // weight number w, in the order the second products need them: 16 tokens at a time
   uint32_t pw[4][4];
   auto weight = [&](int w) {
@@ -1257,15 +1325,15 @@ __device__ __forceinline__ void rows_step(const uint16_t* Ks, const uint16_t* Vs
 // fragments for tokens of segment k (SEGMOVED; otherwise called once with 0).  Which segment a token belongs to is in the
 // agent's page table (`pages`, tables counted from seg_base): one read, where a search through the segments' first tokens
 // is a chain of reads per tile.
-constexpr int kListedLds = kTile * (kKsStride + kVsStride) * 2;
+constexpr int kListedLds = 2 * kTile * kHeadDim * 2;
 
 template <bool SEGMOVED, class LoadQ>
-__device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d, const AttendDev& at, const SessionDev& sd, uint16_t* lds,
+__device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d, const AttendDev& at, const SessionDev& sd, unsigned char* lds,
                                             int h, const PageTab* pages, int seg_base, int64_t l0, int n_pages, int lane, bf16x8 (&qf)[8],
                                             LoadQ load_q, RowState& st) {
   if (n_pages <= 0) return;
-  uint16_t* Ks = lds;
-  uint16_t* Vs = lds + kTile * kKsStride;
+  unsigned char* Ks = lds;
+  unsigned char* Vs = lds + kTile * kHeadDim * 2;
   const int T = rd.page_tokens, lg = T == 16 ? 4 : 5, n = lane & 31, hh = lane >> 5, st_row = lane >> 4, st_pc = lane & 15;
   const int n_tok = n_pages * T;
   // (offsets inside the chunk's part of the payload fit 32 bits: at most 2 x 1024 pages of 64 KB or less)
@@ -1305,8 +1373,8 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
     for (int j = 0; j < 8; ++j) {
       u32x4 v = vreg[j];
       if (!((valid >> (4 * j + st_row)) & 1u)) v = u32x4{0, 0, 0, 0};      // rows of tokens that do not count
-      *reinterpret_cast<u32x4*>(Ks + (4 * j + st_row) * kKsStride + 8 * st_pc) = kreg[j];
-      *reinterpret_cast<u32x4*>(Vs + (4 * j + st_row) * kVsStride + 8 * st_pc) = v;
+      *reinterpret_cast<u32x4*>(Ks + k_place(4 * j + st_row, st_pc)) = kreg[j];
+      *reinterpret_cast<u32x4*>(Vs + v_place(4 * j + st_row, st_pc)) = v;
     }
     wave_sync();                                 // the tile is complete
     if (!SEGMOVED && t0 + kTile < n_tok) fetch(t0 + kTile);
@@ -1317,7 +1385,7 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
       for (int i = 0; i < 16; ++i) { x[0][i] = 0.f; y[i] = 0.f; }
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(Ks + n * kKsStride + 16 * kk + 8 * hh));
+        const bf16x8 a = k_operand(Ks, kk, n, hh);
         if (kk & 1) y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], y, 0, 0, 0);
         else x[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], x[0], 0, 0, 0);
       }
@@ -1408,81 +1476,42 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     int64_t lo = d.offset[agent], hi = lo + d.count[agent];
     if (lo < 0) lo = 0;
     if (hi > d.capacity) hi = d.capacity;
-    auto first_at = [&](int page) {                     // first entry >= page
-      int64_t a = lo, b = hi;
-      while (a < b) {
-        const int64_t mid = (a + b) >> 1;
-        if (d.idx[mid] < page) a = mid + 1; else b = mid;
-      }
-      return a;
-    };
-    l0 = first_at(pg0);
-    l1 = first_at((tok_end - 1) / T + 1);
-    if (l1 - l0 > kRowsMaxPages) l1 = l0 + kRowsMaxPages;                      // (a list this round did not produce)
+    const int32_t* list = d.idx + lo;
+    const int len = hi > lo ? (int)min<int64_t>(hi - lo, 1 << 30) : 0, pg1 = (tok_end - 1) / T + 1;
+    const int first = lane < len ? list[lane] : 0x7fffffff;
     if (lane < kRowsMaskWords) sh.mask[wave][lane] = 0u;
+    int i0, i1;
+    if (len <= 64) {
+      i0 = __popcll(__ballot(first < pg0));
+      i1 = __popcll(__ballot(first < pg1));
+    } else {
+      i0 = count_below(list, len, pg0, lane);
+      i1 = count_below(list, len, pg1, lane);
+    }
+    i1 = max(min(i1, i0 + kRowsMaxPages), i0);                                 // (a list this round did not produce)
+    l0 = lo + i0;
+    l1 = lo + i1;
     wave_sync();
-    for (int64_t a = l0 + lane; a < l1; a += 64) {
-      const int rel = d.idx[a] - pg0;
+    for (int i = i0 + lane; i < i1; i += 64) {
+      const int rel = list[i] - pg0;
       if (rel >= 0 && rel < kRowsMaxPages) atomicOr(&sh.mask[wave][rel >> 5], 1u << (rel & 31));
     }
     wave_sync();
   }
 
   // ---- the master's tokens ----
-  const int st_tok = threadIdx.x >> 4, st_pc = threadIdx.x & 15;
   const int lg = T == 16 ? 4 : 5;
-  const uint32_t row_bytes = (uint32_t)rd.heads * 256u;
-  uint32_t voff[4];                                      // this thread's four rows of a whole tile
-#pragma unroll
-  for (int e = 0; e < 4; ++e) voff[e] = (uint32_t)(16 * e + st_tok) * row_bytes + 16u * st_pc;
-  u32x4 kreg[4], vreg[4];
-  auto put_k = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.k[buf] + (16 * e + st_tok) * kKsStride + 8 * st_pc) = kreg[e];
+  const StepLoader ld(rd.heads);
+  const char* mk = reinterpret_cast<const char*>(io.master_k) + (sd.master_row0 + tok_begin) * (int64_t)ld.row_bytes + h * 256;
+  const char* mv = reinterpret_cast<const char*>(io.master_v) + (sd.master_row0 + tok_begin) * (int64_t)ld.row_bytes + h * 256;
+  // the tile of the step that begins at token p (rows behind the chunk repeat its last token; their scores are masked)
+  auto fetch_k = [&](int p, int buf) __attribute__((always_inline)) {
+    const int at_tok = min(p, tok_end - 1);
+    ld.load(mk + (int64_t)(at_tok - tok_begin) * ld.row_bytes, tok_end - 1 - at_tok, ld.k_off, lds_byte(sh.k[buf]));
   };
-  auto put_v = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.v[buf] + (16 * e + st_tok) * kVsStride + 8 * st_pc) = vreg[e];
-  };
-  // A step takes 64 tokens, or, with per-agent block orders, fewer: up to the next place where some wavefront of the
-  // workgroup enters another segment (agents of one session mostly have their borders in the same places), so
-  // that a step always lies in one segment of every agent.  Those places are the bits of sh.border.
-  if (SEG) {
-    for (int i = threadIdx.x; i < kRowsMaxTokens / 32; i += kBlock) sh.border[i] = 0u;
-    __syncthreads();
-    if (active)
-      for (int k = lane + 1; k < seg_n; k += 64) {
-        const int rel = rd.seg_src[seg_base + k] - tok_begin;
-        if (rel > 0 && rel < tok_end - tok_begin) atomicOr(&sh.border[rel >> 5], 1u << (rel & 31));
-      }
-    __syncthreads();
-  }
-  auto step_end = [&](int p) __attribute__((always_inline)) {            // where the step that begins at token p ends
-    int len = kBigTile;
-    if (SEG) {
-      const int rel = p + 1 - tok_begin, w = rel >> 5;
-      uint32_t x[3];
-#pragma unroll
-      for (int q = 0; q < 3; ++q) x[q] = __builtin_amdgcn_readfirstlane(sh.border[min(w + q, kRowsMaxTokens / 32 - 1)]);
-      const uint64_t lo = ((uint64_t)x[1] << 32) | x[0], hi = x[2];
-      const uint64_t window = rel & 31 ? (lo >> (rel & 31)) | (hi << (64 - (rel & 31))) : lo;           // bit q: a border at p + 1 + q
-      if (window) len = min(kBigTile, __builtin_ctzll(window) + 1);
-    }
-    return min(p + len, tok_end);
-  };
-  const char* mk = reinterpret_cast<const char*>(io.master_k) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
-  const char* mv = reinterpret_cast<const char*>(io.master_v) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
-  // the tile of the step that begins at token p (rows behind the step belong to others or repeat the last token of
-  // the chunk; their scores are masked)
-  auto fetch = [&](const char* base, int p, u32x4 (&r)[4]) __attribute__((always_inline)) {
-    const int at_tok = min(p, tok_end - 1), left = tok_end - 1 - at_tok;
-    const char* tile = base + (int64_t)(at_tok - tok_begin) * row_bytes;
-    uint32_t off[4] = {voff[0], voff[1], voff[2], voff[3]};
-    if (left < kBigTile - 1)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) off[e] = (uint32_t)min(16 * e + st_tok, left) * row_bytes + 16u * st_pc;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = *reinterpret_cast<const u32x4*>(tile + off[e]);
+  auto fetch_v = [&](int p, int buf) __attribute__((always_inline)) {
+    const int at_tok = min(p, tok_end - 1);
+    ld.load(mv + (int64_t)(at_tok - tok_begin) * ld.row_bytes, tok_end - 1 - at_tok, ld.v_off, lds_byte(sh.v[buf]));
   };
   // the two words of the page mask that hold a step's pages (read early, used by mask_scores)
   auto mask_words = [&](int p) __attribute__((always_inline)) {
@@ -1512,56 +1541,102 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     }
     rows_max<2>(s, mx);
   };
-  // this wavefront's segment at token p, and its query fragments
-  int seg_next = 0;                                      // where the next segment begins (0: nothing loaded yet)
-  auto enter = [&](int p) __attribute__((always_inline)) {
-    if (p < seg_next) return;
-    auto src = [&](int k) __attribute__((always_inline)) { return k < seg_n ? __builtin_amdgcn_readfirstlane(rd.seg_src[seg_base + k]) : 0x7fffffff; };
-    while (src(seg_k + 1) <= p) ++seg_k;
-    seg_next = src(seg_k + 1);
-    load_q(rd.segtab + (size_t)(seg_base + seg_k) * (2 * kHalf));
+  // Per-agent block orders: where a segment begins the rows are read again and turned by that segment's table.  The first tokens
+  // of 64 segments stand in the lanes (`src`), from segment `win` on, so that finding the segment of a token is a vote;
+  // the next segment's table is asked for when this one's has been used.
+  int win = 0, src = 0, seg_next = 0x7fffffff;           // seg_next: where the next segment begins
+  float2 seg_tab = make_float2(1.f, 0.f);                // the table that is asked for: segment seg_k
+  auto window = [&](int k0) __attribute__((always_inline)) {
+    win = k0;
+    src = k0 + lane < seg_n ? rd.seg_src[seg_base + k0 + lane] : 0x7fffffff;
+  };
+  auto table = [&](int k) __attribute__((always_inline)) {
+    seg_k = k;
+    seg_tab = reinterpret_cast<const float2*>(rd.segtab + (size_t)(seg_base + min(k, seg_n - 1)) * (2 * kHalf))[lane];
+  };
+  auto enter = [&](int p) __attribute__((always_inline)) {                // the segment of token p, p not before the current one
+    int c = __popcll(__ballot(src <= p));
+    while (c == 64) { window(win + 63); c = __popcll(__ballot(src <= p)); }
+    seg_next = __builtin_amdgcn_readlane(src, c);
+    u32x4 raw[8];
+    raw_queries(at, out, row_ok, lane, raw);
+    if (seg_k != win + c - 1) table(win + c - 1);
+    turn_queries(raw, rd.interleaved, seg_tab, sh.tab[wave], lane, qf);
+    table(seg_k + 1);
+  };
+  // The scores of the step [p, end) were taken with the rows of the segment of its first token: those of the tokens of
+  // further segments are taken again, for the 32-token tiles that have some.  Leaves the rows of the segment of `end`.
+  // (With steps that end at every border instead, blocks of 200 tokens took four steps per block.)
+  auto follow = [&](const unsigned char* Ks, int p, int end, f32x16 (&s)[2], float& mx) __attribute__((always_inline)) {
+    bool again = false;
+    while (seg_next <= end && seg_next < tok_end) {
+      const int b = seg_next - p;                        // the first token of the step that belongs to the next segment
+      enter(seg_next);
+      if (b >= kBigTile) break;
+      again = true;
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        if (b >= kTile * (t + 1)) continue;
+        f32x16 x;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) x[i] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(Ks + t * (kStepTile / 2), kk, ln & 31, ln >> 5), qf[kk], x, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[t][e] = kTile * t + 8 * (e >> 2) + 4 * (ln >> 5) + (e & 3) >= b ? x[e] : s[t][e];
+      }
+    }
+    if (again) rows_max<2>(s, mx);
   };
   if (tok_end > tok_begin) {
     f32x16 s0[2], s1[2];
-    // starts of the next step, of the one after it and of the third
-    int p1 = tok_begin, p2 = step_end(p1), p3 = step_end(p2);
-    fetch(mk, p1, kreg);
-    fetch(mv, p1, vreg);
-    put_k(0);
-    put_v(0);
-    fetch(mk, p2, kreg);
+    // starts of this step and of the next one
+    int p1 = tok_begin, p2 = min(p1 + kBigTile, tok_end);
+    fetch_k(p1, 0);
+    fetch_v(p1, 0);
+    fetch_k(p2, 1);
     if (active) {
-      if (SEG) enter(p1);
-      else load_q(rd.tab + (size_t)agent * (2 * kHalf));
+      if (SEG) {
+        window(0);
+        seg_k = -1;
+        enter(p1);
+      } else {
+        load_q(rd.tab + (size_t)agent * (2 * kHalf));
+      }
     }
-    put_k(1);
+    landed();
     __syncthreads();
     if (active) {
       float mx;
       rows_scores(sh.k[0], qf, n, hh, s0);
       rows_max<2>(s0, mx);
+      if (SEG) follow(sh.k[0], p1, p2, s0, mx);
       mask_scores(p1, p2, mask_words(p1), s0, mx);
       rows_settle(mx, at.scale, st);
     }
     __syncthreads();                                     // the first step replaces its K tile
     // the weights and second products of the step whose scores are s (buffers `odd`), and the scores of the next one
     auto step = [&](int odd, f32x16 (&s)[2], f32x16 (&nx)[2]) __attribute__((always_inline)) {
-      if (SEG && active && p2 < tok_end) enter(p2);
-      fetch(mk, p3, kreg);                               // the tiles after that travel to registers meanwhile
-      fetch(mv, p2, vreg);
+      const int p3 = min(p2 + kBigTile, tok_end);
+      fetch_k(p3, odd);                                  // the tiles after that travel to LDS meanwhile (nobody reads
+      fetch_v(p2, odd ^ 1);                              // these two buffers in this step)
       uint2 words = make_uint2(0u, 0u);
       float mx;
       if (active) {
         words = mask_words(p2);
-        rows_step(sh.k[odd ^ 1], sh.v[odd], qf, s, nx, mx, at.scale, lane, st);      // (past the last step: scores that are not used)
+        int ln = lane;
+        if (SEG) asm volatile("" : "+v"(ln));            // (the places in the tiles are worked out again: kept from step to step they spill)
+        rows_step(sh.k[odd ^ 1], sh.v[odd], qf, s, nx, mx, at.scale, ln, st);        // (past the last step: scores that are not used)
       }
-      put_k(odd);                                        // (nobody reads these two buffers in this step)
-      put_v(odd ^ 1);
       if (active && p2 < tok_end) {
+        if (SEG) follow(sh.k[odd ^ 1], p2, p3, nx, mx);
         mask_scores(p2, p3, words, nx, mx);
         rows_settle(mx, at.scale, st);
       }
-      p1 = p2; p2 = p3; p3 = step_end(p3);
+      p1 = p2; p2 = p3;
+      landed();
       __syncthreads();
     };
     if (SEG) {
@@ -1583,7 +1658,7 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
 
   // ---- the listed pages, from the payload ----
   if (active) {
-    uint16_t* lds = reinterpret_cast<uint16_t*>(&sh) + wave * (kListedLds / 2);
+    unsigned char* lds = sh.k[0] + wave * kListedLds;
     // Segments that have moved together meet the same rows, so one turn serves the whole list; only lists whose segments have
     // moved by different distances need a turn per segment.
     const int moved = __builtin_amdgcn_readfirstlane(rd.agents[agent].diff_rot);
@@ -1627,8 +1702,8 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
 // agents, ten sessions, 5000 tokens: 1 query token (5 rows) 111 -> 109 us in a graph, 2 tokens (10 rows) 164 -> 153.
 // ---------------------------------------------------------------------------------------------
 struct PackedShared {
-  uint16_t k[2][kBigTile * kKsStride];
-  uint16_t v[2][kBigTile * kVsStride];
+  unsigned char k[2][kStepTile];
+  unsigned char v[2][kStepTile];
   uint64_t mask[kRowsPerBlock * kMaskWords];              // bit p: page p of this chunk is listed in the row's agent's diff
 };
 
@@ -1646,37 +1721,22 @@ __device__ __forceinline__ void attend_packed_body(const RoundDev& rd, const Lay
   const int tok_end = min(sd.span, tok_begin + at.chunk_tokens);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
 
-  // staging: sixteen lanes per token row, four rows per wavefront instruction; rows past the end repeat the last one
-  // (their scores are masked)
-  const int st_tok = threadIdx.x >> 4, st_pc = threadIdx.x & 15;
-  const uint32_t row_bytes = (uint32_t)rd.heads * 256u;
-  uint32_t voff[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) voff[e] = (uint32_t)(16 * e + st_tok) * row_bytes + 16u * st_pc;
-  const char* mk = reinterpret_cast<const char*>(io.master_k) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
-  const char* mv = reinterpret_cast<const char*>(io.master_v) + (sd.master_row0 + tok_begin) * (int64_t)row_bytes + h * 256;
+  // rows past the end repeat the last one (their scores are masked), a step past the last one repeats it
+  const StepLoader ld(rd.heads);
+  const char* mk = reinterpret_cast<const char*>(io.master_k) + (sd.master_row0 + tok_begin) * (int64_t)ld.row_bytes + h * 256;
+  const char* mv = reinterpret_cast<const char*>(io.master_v) + (sd.master_row0 + tok_begin) * (int64_t)ld.row_bytes + h * 256;
   const int steps = (tok_end - tok_begin + kBigTile - 1) / kBigTile, last = tok_end - tok_begin - 1;
-  u32x4 kreg[4], vreg[4];
-  auto fetch = [&](const char* base, int i, u32x4 (&r)[4]) __attribute__((always_inline)) {      // (a step past the last one repeats it)
-    const int ii = min(i, steps - 1), left = last - ii * kBigTile;
-    const char* tile = base + (int64_t)ii * kBigTile * row_bytes;
-    uint32_t off[4] = {voff[0], voff[1], voff[2], voff[3]};
-    if (left < kBigTile - 1)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) off[e] = (uint32_t)min(16 * e + st_tok, left) * row_bytes + 16u * st_pc;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) r[e] = *reinterpret_cast<const u32x4*>(tile + off[e]);
+  auto fetch_k = [&](int i, int buf) __attribute__((always_inline)) {
+    const int t0 = min(i, steps - 1) * kBigTile;
+    ld.load(mk + (int64_t)t0 * ld.row_bytes, last - t0, ld.k_off, lds_byte(sh.k[buf]));
   };
-  auto put_k = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.k[buf] + (16 * e + st_tok) * kKsStride + 8 * st_pc) = kreg[e];
+  auto fetch_v = [&](int i, int buf) __attribute__((always_inline)) {
+    const int t0 = min(i, steps - 1) * kBigTile;
+    ld.load(mv + (int64_t)t0 * ld.row_bytes, last - t0, ld.v_off, lds_byte(sh.v[buf]));
   };
-  auto put_v = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) *reinterpret_cast<u32x4*>(sh.v[buf] + (16 * e + st_tok) * kVsStride + 8 * st_pc) = vreg[e];
-  };
-  fetch(mk, 0, kreg);                                     // (asked for before the page masks are looked up)
-  fetch(mv, 0, vreg);
+  fetch_k(0, 0);                                          // (asked for before the page masks are looked up)
+  fetch_v(0, 0);
+  fetch_k(1, 1);
 
   // which pages of this chunk each row's agent lists in its diff
   if (threadIdx.x < kRowsPerBlock) {
@@ -1718,10 +1778,7 @@ __device__ __forceinline__ void attend_packed_body(const RoundDev& rd, const Lay
     }
     turn_back32(raw, rd.tab + (size_t)(mine.agent >= 0 ? mine.agent : 0) * (2 * kHalf), rd.interleaved, hh, qf);
   }
-  put_k(0);
-  put_v(0);
-  fetch(mk, 1, kreg);
-  put_k(1);
+  landed();
   __syncthreads();
 
   // which 16-token groups of step i the lane's agent lists (bit g: group g), read ahead of their use
@@ -1764,17 +1821,16 @@ __device__ __forceinline__ void attend_packed_body(const RoundDev& rd, const Lay
   }
   __syncthreads();                                        // the first step replaces its K tile
   auto step = [&](int i, f32x16 (&s)[2], f32x16 (&nx)[2]) __attribute__((always_inline)) {
-    fetch(mk, i + 2, kreg);
-    fetch(mv, i + 1, vreg);
+    fetch_k(i + 2, i & 1);                                // (nobody reads these two buffers in this step)
+    fetch_v(i + 1, (i + 1) & 1);
     const uint32_t m4 = listed(i + 1);
     float mx;
     rows_step(sh.k[(i + 1) & 1], sh.v[i & 1], qf, s, nx, mx, at.scale, lane, st);
-    put_k(i & 1);                                         // (nobody reads these two buffers in this step)
-    put_v((i + 1) & 1);
     if (i + 1 < steps) {
       mask_scores(i + 1, m4, nx, mx);
       rows_settle(mx, at.scale, st);
     }
+    landed();
     __syncthreads();
   };
   for (int i = 0; i < steps; i += 2) {

@@ -103,3 +103,24 @@ def test_packed_rows_with_half_of_the_pages_listed(tdo, how):
     spec = wl.RoundSpec("seg3", 103, 1, 8, 128, 16, 1.0e6, 1, 40, 1, 900, 900, 1200, 0.5)
     g = np.random.default_rng([103])
     segment_case(tdo, spec, lambda rnd: random_segments(rnd, 900, 16, g), lambda rnd: moved_by(rnd, how), 1, 24, scale=1.0)
+
+
+@pytest.mark.parametrize("n_q,Hq,T,span,how", [(5, 8, 16, 1400, "together"), (10, 8, 16, 1337, "mixed"), (5, 8, 32, 2600, "apart")])
+def test_more_segments_than_a_wavefront_has_lanes(tdo, n_q, Hq, T, span, how):
+    """A border in every page, at a random token: up to five segments meet a 64-token step, an agent has more than 64 of them
+    and, with nine pages in ten listed, a list of more than 64 pages."""
+    spec = wl.RoundSpec("seg4", 104, 1, 2, 128, T, 1.0e6, 1, 3, 1, span, 900, 1200, 0.9)
+    g = np.random.default_rng([104, T])
+
+    def segments(rnd):
+        out = []
+        for p in rnd.agent_pos0:
+            cuts = np.concatenate([[0], np.arange(1, span // T) * T + g.integers(0, T, span // T - 1)])
+            lens = np.diff(np.concatenate([cuts, [span]]))
+            order = g.permutation(len(cuts))
+            dst = np.empty(len(cuts), np.int64)
+            dst[order] = int(p) + np.concatenate([[0], np.cumsum(lens[order])[:-1]])
+            out.append(np.stack([cuts, dst, lens], 1))
+        return out
+
+    segment_case(tdo, spec, segments, lambda rnd: [np.maximum(m, 0) for m in moved_by(rnd, how)], n_q, Hq, scale=1.0)
