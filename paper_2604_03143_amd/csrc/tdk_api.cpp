@@ -307,8 +307,10 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   const size_t work_cap = p.work_capacity;
   const int64_t flag_off = p.total_pages;
   const auto& sess_dev = p.sess;
-  const auto& agent_dev = p.agents;
   const auto& order = p.order;
+  std::vector<AgentDev> agent_dev = p.agents;      // in the caller's order, then once more grouped by session
+  agent_dev.reserve(2 * order.size());
+  for (const int32_t a : order) agent_dev.push_back(p.agents[a]);
   const auto& bt = p.bt;
   const auto& tab = p.tab;
   const auto& tab_diff = p.tab_diff;
@@ -377,6 +379,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   r->rd.pwork = reinterpret_cast<const WorkItem*>(base + o_pwork);
   r->rd.sess = reinterpret_cast<const SessionDev*>(base + o_sess);
   r->rd.agents = reinterpret_cast<const AgentDev*>(base + o_agents);
+  r->rd.oagents = r->rd.agents + n_agents;
   r->rd.order = reinterpret_cast<const int32_t*>(base + o_order);
   r->rd.bt = reinterpret_cast<const int32_t*>(base + o_bt);
   r->rd.tab = reinterpret_cast<const float*>(base + o_tab);

@@ -15,6 +15,7 @@ struct RoundDev {
   const WorkItem*   qwork;   // the same items grouped by that XCD: the queues of a queued launch
   const SessionDev* sess;
   const AgentDev*   agents;
+  const AgentDev*   oagents; // the agents' descriptors grouped by session: oagents[i] = agents[order[i]]
   const int32_t*    order;   // agent ids grouped by session
   const int32_t*    bt;      // block-table slices, concatenated
   const float*      tab;     // [n_agents][2][64]: cos then sin of the agent's delta

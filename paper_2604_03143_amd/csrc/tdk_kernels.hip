@@ -95,8 +95,7 @@ struct GroupShared {
   int32_t pg0[kMaxGroup];             // physical page holding the master page's first token
   int32_t pg1[kMaxGroup];             // the next logical page's physical page (or -1)
   int32_t off[kMaxGroup];             // row of the first token inside pg0
-  int32_t aux[kMaxGroup];             // flag kernel: OR of the waves; decode: payload slot or -1
-  int32_t agent[kMaxGroup];
+  int32_t aux[kMaxGroup];             // flag kernel: OR of the waves; decode: 1 if the page is listed
 };
 
 // The same for rounds with per-agent block layouts: a master page can meet two segments of an agent
@@ -106,14 +105,13 @@ struct GroupSharedSeg {
   int32_t  row[kMaxGroup][32];       // pool row of each row of the page
   uint32_t sel[kMaxGroup];           // bit r set: row r uses the second table
   int32_t  aux[kMaxGroup];
-  int32_t  agent[kMaxGroup];
 };
 
 __device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& w, const int T, GroupSharedSeg& sh) {
   const int tid = threadIdx.x;
   for (int i = tid; i < w.ag_count * 64; i += kBlock) {
     const int g = i >> 6, which = (i >> 5) & 1, q = i & 31;
-    const AgentDev ad = rd.agents[rd.order[w.ag_begin + g]];
+    const AgentDev ad = rd.oagents[w.ag_begin + g];
     const PageTab pt = rd.pagetab[ad.flag_off + w.page];
     const int t = which ? pt.y : pt.x;
     reinterpret_cast<float4*>(sh.tab[g][which])[q] =
@@ -122,15 +120,12 @@ __device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& 
   const SessionDev sd = rd.sess[w.session];
   for (int i = tid; i < w.ag_count * T; i += kBlock) {
     const int g = T == 16 ? i >> 4 : i >> 5, r = i & (T - 1);
-    const AgentDev ad = rd.agents[rd.order[w.ag_begin + g]];
+    const AgentDev ad = rd.oagents[w.ag_begin + g];
     const int m = w.page * T + r;
     sh.row[g][r] = m < sd.span ? rd.rowmap[ad.score_off + m] : 0;
   }
   if (tid < w.ag_count) {
-    const int a = rd.order[w.ag_begin + tid];
-    sh.sel[tid] = (uint32_t)rd.pagetab[rd.agents[a].flag_off + w.page].z;
-    sh.aux[tid] = 0;
-    sh.agent[tid] = a;
+    sh.sel[tid] = (uint32_t)rd.pagetab[rd.oagents[w.ag_begin + tid].flag_off + w.page].z;
   }
 }
 
@@ -143,15 +138,12 @@ __device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& 
         reinterpret_cast<const float4*>(rd.tab + (size_t)a * (2 * kHalf))[q];
   }
   if (tid < w.ag_count) {
-    const int a = rd.order[w.ag_begin + tid];
-    const AgentDev ad = rd.agents[a];
+    const AgentDev ad = rd.oagents[w.ag_begin + tid];
     const int a0 = ad.pos0 + w.page * T;
     const int lp = (T == 16 ? a0 >> 4 : a0 >> 5) - ad.lp_first;       // (positions are not negative)
     sh.pg0[tid] = rd.bt[ad.bt_off + lp];
     sh.pg1[tid] = (lp + 1 < ad.bt_len) ? rd.bt[ad.bt_off + lp + 1] : -1;
     sh.off[tid] = a0 & (T - 1);
-    sh.aux[tid] = 0;
-    sh.agent[tid] = a;
   }
 }
 
@@ -503,6 +495,7 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
   stamp_begin(rd, item);
   const WorkItem w = rd.rwork[item];
   stage_group(rd, w, T, sh);
+  if (threadIdx.x < w.ag_count) sh.aux[threadIdx.x] = 0;
   MasterRows<RPW> M;
   load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
   bool special[RPW];
@@ -562,8 +555,7 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
   }
   lds_barrier();
   if (threadIdx.x < w.ag_count) {
-    const AgentDev ad = rd.agents[sh.agent[threadIdx.x]];
-    rd.flags[ad.flag_off + w.page] = (uint8_t)sh.aux[threadIdx.x];
+    rd.flags[rd.oagents[w.ag_begin + threadIdx.x].flag_off + w.page] = (uint8_t)sh.aux[threadIdx.x];
   }
   stamp_end(rd, item);
 }
@@ -977,6 +969,39 @@ __global__ __launch_bounds__(kBlock) void tdk_scatter_kernel(const RoundDev rd, 
   scatter_slots<IL>(rd, io, d, planes, ss, blockIdx.x, gridDim.x);
 }
 
+// Skip-or-correct decision of a work item: listed[g] = 1 where the item's page is in the index list of agent g of its group.
+// All threads of the workgroup take part, 64 lanes per agent in groups of up to four, 32 in groups of up to eight and so on:
+// each round of reads divides what is left of a list by that number.  One agent per thread halves it, and every read is a memory
+// latency in front of the item's first store: 37 agents x 2999 tokens, 4 heads, one plane after the other 127.5 -> 125.6 us,
+// 4 x 12 agents x 3001 tokens with moved diffs and own orders 104.2 -> 101.9, 13 agents x 19322 tokens, 4 heads 292 -> 275.
+__device__ __forceinline__ void find_listed(const RoundDev& rd, const DiffDev& d, const WorkItem& w, int32_t* listed) {
+  const int lg = w.ag_count <= 4 ? 6 : w.ag_count <= 8 ? 5 : w.ag_count <= 16 ? 4 : 3;      // kMaxGroup << 3 == kBlock
+  const int g = threadIdx.x >> lg, lanes = 1 << lg, l = threadIdx.x & (lanes - 1), shift = threadIdx.x & 63 & ~(lanes - 1);
+  const uint64_t mine = (lanes == 64 ? ~0ull : (1ull << lanes) - 1ull) << shift;
+  const int32_t* v = d.idx;
+  int n = 0;
+  if (g < w.ag_count) {
+    const int a = rd.order[w.ag_begin + g];
+    int64_t lo = d.offset[a];
+    int64_t hi = lo + d.count[a];
+    if (lo < 0) lo = 0;
+    if (hi > d.capacity) hi = d.capacity;
+    v += lo;
+    n = hi > lo ? (int)min<int64_t>(hi - lo, 1 << 30) : 0;
+  }
+  bool found = false;
+  while (__any(n > 0)) {
+    const int stride = (n + lanes - 1) >> lg, i = l * stride;
+    const int x = i < n ? v[i] : 0x7fffffff;
+    const uint64_t below = __ballot(x < w.page) & mine;
+    found |= (__ballot(x == w.page) & mine) != 0;
+    const int c = __popcll(below), skip = c ? (c - 1) * stride + 1 : n;
+    v += skip;
+    n = found ? 0 : max(min(stride - 1, n - skip), 0);
+  }
+  if (l == 0 && g < w.ag_count) listed[g] = found;
+}
+
 template <int RPW, bool PACK, bool IL, bool NT, int PM, bool SEG, bool Q>
 __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
                                                             const int n_scatter) {
@@ -1005,26 +1030,11 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
     stage_group(rd, w, T, sh);
     MasterRows<RPW> M;
     load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
-    if (threadIdx.x < w.ag_count) {
-      // skip-or-correct decision per block: is this page in the agent's index list?
-      const int a = rd.order[w.ag_begin + threadIdx.x];
-      int64_t lo = d.offset[a];
-      int64_t hi = lo + d.count[a];
-      if (lo < 0) lo = 0;
-      if (hi > d.capacity) hi = d.capacity;
-      int64_t slot = -1;
-      while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        const int v = d.idx[mid];
-        if (v == w.page) { slot = mid; break; }
-        if (v < w.page) lo = mid + 1; else hi = mid;
-      }
-      sh.aux[threadIdx.x] = (int32_t)slot;
-    }
+    find_listed(rd, d, w, sh.aux);
     lds_barrier();
     items.prefetch(rd);
     for (int g = 0; g < w.ag_count; ++g) {
-      if (sh.aux[g] >= 0) continue;   // listed in the diff: the scatter kernel writes this page
+      if (sh.aux[g] != 0) continue;   // listed in the diff: the scatter kernel writes this page
       float c[8], s[8];
       if (DOK && !SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
 #pragma unroll
@@ -1100,7 +1110,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4
   stage_group(rd, w, T, sh);
   MasterRows<RPW> M;
   load_master<RPW, PACK, false>(rd, io, w, T, L, M);
-  if (threadIdx.x < w.ag_count) sh.aux[threadIdx.x] = rd.agents[sh.agent[threadIdx.x]].score_off;   // (own entry of sh.agent)
+  if (threadIdx.x < w.ag_count) sh.aux[threadIdx.x] = rd.oagents[w.ag_begin + threadIdx.x].score_off;
   lds_barrier();
   // Rolling requests: row k of the next agent is asked for as soon as row k of this one has been used, into the
   // registers that just became free, so a wavefront keeps its eight 16-byte loads per lane in flight all the
