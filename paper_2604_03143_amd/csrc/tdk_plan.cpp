@@ -401,12 +401,19 @@ double packed_segments_us(const AttendShape& r, const AttendLoad& l, double list
 
 // A wavefront per agent; `parts` of 1 or less: no merge.  A workgroup walks its part of the lists after its steps.  Two workgroups
 // share a compute unit: the launch lasts partly in proportion to its workgroups and partly in whole rounds of them.
-double rows_us(const AttendShape& r, const AttendLoad& l) {
+// More than 32 rows and the master's order: workgroups find the tiles of others in L2, and partial results are many.  There the
+// estimate is an older one, in steps of 1.2 us: a workgroup starts up in 8, two that share a unit take 1.6 times as long, the
+// merge costs 6 and its traffic (16 query tokens, 25 agents: 1, 2, 4, 8 chunks take 104, 74, 68, 79 us without listed pages; with
+// the constants for few rows 12 agents x 2496 tokens x 320 rows would be cut in two, 57 -> 73 us).
+double rows_us(const AttendShape& r, const AttendLoad& l, int64_t agent_rows) {
   const double tiles = kListedShare * l.steps * 2;
   const double full = std::floor(l.wgs / 2 + 1e-9), rest = l.wgs - 2 * full;
   auto rounds = [&](double two) { return full * two + (rest < 1e-9 ? 0.0 : rest > 1 ? two : 1.0); };
   double us, merge;
-  if (!r.seg) {
+  if (!r.seg && agent_rows > 32) {
+    us = 1.2 * (8 + l.steps) * rounds(1.6);
+    merge = 1.2 * (6 + l.rows * (l.parts + 1) * 1024e3 / 6e6);
+  } else if (!r.seg) {
     us = (8.9 + 1.34 * l.steps + 1.46 * tiles) * (0.65 * std::max(1.0, 0.755 + 0.31 * l.wgs) + 0.35 * rounds(1.32)) + 0.57 * listed_us(r);
     merge = 3.3 + 0.154 * l.parts + 0.223 * l.rows * l.parts;
   } else {            // (apart: the lists turn their rows per segment)
@@ -486,7 +493,7 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
   auto try_own = [&](int64_t c) {
     int64_t chunks, wgs;
     count(c, chunks, wgs);
-    const double us = rows_us(r, load(c, chunks, wgs));
+    const double us = rows_us(r, load(c, chunks, wgs), agent_rows);
     if (own_best < 0 || us < own_best) { own_best = us; own_chunk = c; }
   };
   // Which kernels: one agent per wavefront, or the rows of a session's agents packed into one block.  Packed rows waste no
@@ -534,7 +541,7 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
       p.own_rows = own_best >= 0 && own_best < best;
     }
   } else {
-    for_chunks(max_span, 64, longest_own, try_own);
+    for_chunks(max_span, agent_rows > 32 && !r.seg ? std::max<int64_t>(64, max_span / 32) : 64, longest_own, try_own);
   }
   if (p.own_rows) {
     p.pipelined = false;
