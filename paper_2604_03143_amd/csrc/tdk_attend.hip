@@ -1927,12 +1927,30 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 
 // ---------------------------------------------------------------------------------------------
 // merge: out = sum_c o_c e^(m_c - M) / sum_c l_c e^(m_c - M), lse = M + log(that sum); one wavefront per row
+// A chain of small reads: what the row's agent lists decides which parts exist.  So the first eight chunks' rows and all
+// maxima and sums (up to 64 parts) are asked for before that is known, and what does not exist gets no weight.  A
+// half-wavefront takes every other part, 16 bytes per lane.  2 x 8 agents x 1113 tokens, 4 rows 14.2 -> 13.1 us with
+// its launch, 6 x 608 tokens, own orders 17.7 -> 16.6, 250 agents x 5000 tokens 137.7 -> 137.5.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void tdk_attend_merge_kernel(const RoundDev rd, const DiffDev d, const AttendDev at) {
   const int64_t row = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
   const int64_t n_rows = (int64_t)rd.n_agents * at.n_q * at.n_q_heads;
   if (row >= n_rows) return;
-  const int lane = threadIdx.x & 63;
+  constexpr int kFirst = 8;
+  const int lane = threadIdx.x & 63, half = lane >> 5, n = lane & 31;
+  const int64_t base = row * at.n_parts;
+  const float4* part = reinterpret_cast<const float4*>(at.part_o + base * kHeadDim) + n;
+  const int early = min(at.n_chunks, kFirst);
+  f32x4a v[kFirst / 2];
+  auto ask = [&](int j, int slot, bool there) {
+    v[j] = f32x4a{0.f, 0.f, 0.f, 0.f};
+    if (there) v[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x4a*>(part + (int64_t)slot * (kHeadDim / 4)));
+  };
+  float m0 = -INFINITY, l0 = 0.f;
+  if (lane < at.n_parts) { m0 = at.part_m[base + lane]; l0 = at.part_l[base + lane]; }
+#pragma unroll
+  for (int j = 0; j < kFirst / 2; ++j) ask(j, 2 * j + half, 2 * j + half < early);
+
   const int agent = (int)(row / ((int64_t)at.n_q * at.n_q_heads));
   const int span = rd.sess[rd.agents[agent].session].span;
   const int chunks = (span + at.chunk_tokens - 1) / at.chunk_tokens;
@@ -1945,49 +1963,58 @@ __global__ __launch_bounds__(kBlock) void tdk_attend_merge_kernel(const RoundDev
     const int64_t n_tok = hi > lo ? (hi - lo) * rd.page_tokens : 0;
     pieces = (int)min<int64_t>((n_tok + at.piece_tokens - 1) / at.piece_tokens, at.n_pieces);   // (a count beyond the session's pages)
   }
-  const int used = chunks + pieces;
-  const int64_t base = row * at.n_parts;
-  auto part_of = [&](int c) { return c < chunks ? c : at.n_chunks + (c - chunks); };
-  // a lane per part for the maxima and the weights, then a lane per output element
-  float M = -INFINITY;
-  for (int c0 = 0; c0 < used; c0 += 64) {
-    const int c = c0 + lane;
-    if (c < used) M = fmaxf(M, at.part_m[base + part_of(c)]);
-  }
+  auto exists = [&](int slot) { return slot < chunks || (slot >= at.n_chunks && slot < at.n_chunks + pieces); };
+  // a lane per part for the maxima and the weights
+  float M = exists(lane) ? m0 : -INFINITY;
+  for (int c = lane + 64; c < at.n_chunks + pieces; c += 64)
+    if (exists(c)) M = fmaxf(M, at.part_m[base + c]);
 #pragma unroll
   for (int sft = 32; sft > 0; sft >>= 1) M = fmaxf(M, __shfl_xor(M, sft));
-  // lane l keeps output elements 2 l and 2 l + 1; the parts' rows are requested eight at a time, before any is used
-  float L = 0.f, a0 = 0.f, a1 = 0.f;
-  for (int c0 = 0; c0 < used; c0 += 64) {
-    const int c = c0 + lane;
+  // lane n of a half keeps output elements 4 n .. 4 n + 3
+  float L = 0.f, a[4] = {0.f, 0.f, 0.f, 0.f};
+  auto weight = [&](int slot, float m, float l) {
     float w = 0.f;
-    if (c < used) {
-      const float m = at.part_m[base + part_of(c)];
-      if (m != -INFINITY) { w = __expf(m - M); L = __builtin_fmaf(at.part_l[base + part_of(c)], w, L); }
-    }
-    const int cnt = min(64, used - c0);
-    for (int j0 = 0; j0 < cnt; j0 += 8) {
-      f32x2a v[8];
+    if (exists(slot) && m != -INFINITY) { w = __expf(m - M); L = __builtin_fmaf(l, w, L); }
+    return w;
+  };
+  auto add = [&](int j, float w) {                       // (a part that does not exist or is empty has weight 0; its row was never written)
+    if (w != 0.f)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        v[j] = f32x2a{0.f, 0.f};
-        if (j0 + j < cnt)
-          v[j] = __builtin_nontemporal_load(reinterpret_cast<const f32x2a*>(at.part_o + (base + part_of(c0 + j0 + j)) * kHeadDim) + lane);
-      }
+      for (int e = 0; e < 4; ++e) a[e] = __builtin_fmaf(v[j][e], w, a[e]);
+  };
+  float w = weight(lane, m0, l0);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const float wj = __shfl(w, (j0 + j) & 63);           // 0 for a part that does not exist or is empty
-        if (j0 + j < cnt && wj != 0.f) {                     // (an empty part's row was never written)
-          a0 = __builtin_fmaf(v[j].x, wj, a0);
-          a1 = __builtin_fmaf(v[j].y, wj, a1);
-        }
+  for (int j = 0; j < kFirst / 2; ++j) {
+    const float wj = __shfl(w, 2 * j + half);
+    if (2 * j + half < early) add(j, wj);
+  }
+  // the other parts, eight at a time: chunks from `early` on, then pieces
+  const int more = max(chunks - early, 0), rest = more + pieces;
+  int w_of = 0;                                          // the weights in the lanes are those of slots 64 w_of ..
+  for (int r0 = 0; r0 < rest; r0 += kFirst) {
+    auto slot_of = [&](int r) { return r < more ? early + r : at.n_chunks + (r - more); };
+#pragma unroll
+    for (int j = 0; j < kFirst / 2; ++j) ask(j, slot_of(r0 + 2 * j + half), r0 + 2 * j + half < rest);
+#pragma unroll
+    for (int k = 0; k < kFirst; ++k) {
+      const int r = r0 + k;
+      if (r >= rest) break;
+      const int slot = slot_of(r);
+      if ((slot >> 6) != w_of) {                         // (slots ascend: each group of 64 is weighed once)
+        w_of = slot >> 6;
+        const int c = 64 * w_of + lane;
+        w = exists(c) ? weight(c, at.part_m[base + c], at.part_l[base + c]) : 0.f;
       }
+      const float wk = __shfl(w, slot & 63);
+      if (half == (k & 1)) add(k >> 1, wk);
     }
   }
 #pragma unroll
   for (int sft = 32; sft > 0; sft >>= 1) L += __shfl_xor(L, sft);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) a[e] += __shfl_xor(a[e], 32);
   const float inv = L > 0.f ? 1.f / L : L != L ? L : 0.f;
-  reinterpret_cast<float2*>(at.out + row * kHeadDim)[lane] = make_float2(a0 * inv, a1 * inv);
+  if (half == 0) reinterpret_cast<float4*>(at.out + row * kHeadDim)[n] = make_float4(a[0] * inv, a[1] * inv, a[2] * inv, a[3] * inv);
   if (lane == 0) at.lse[row] = row_lse(M, L);
 }
 

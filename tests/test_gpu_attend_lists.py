@@ -16,3 +16,11 @@ def test_lists_and_rows_of_every_length(tdo, T, n_q, span, frac):
     """One query head per KV head: 2, 3, 4 and 5 wavefronts per agent, five agents."""
     spec = wl.RoundSpec("lists1", 111, 1, 1, 128, T, 1.0e6, 1, 5, 1, span, 3, 200, frac)
     _case(tdo, spec, n_q, 1, perturb=frac > 0)
+
+
+@pytest.mark.parametrize("span,n_q,Hq,H,frac", [(500, 1, 8, 2, 0.3), (900, 1, 8, 2, 0.9), (2600, 1, 20, 1, 0.5), (6000, 1, 4, 1, 0.7), (6000, 1, 4, 1, 0.0)])
+def test_many_parts_are_merged(tdo, span, n_q, Hq, H, frac):
+    """Spans cut into few and many chunks and lists into few and many pieces: 8 to 32 chunks and up to 47 pieces, so that the
+    parts of a row fall into one or several groups of 64 and most slots between them do not exist."""
+    spec = wl.RoundSpec("lists2", 112, 1, H, 128, 16, 1.0e6, 1, 3, 1, span, 3, 200, frac)
+    _case(tdo, spec, n_q, Hq, perturb=frac > 0)
