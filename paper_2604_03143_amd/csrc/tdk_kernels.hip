@@ -1222,13 +1222,23 @@ __global__ __launch_bounds__(BLOCK) void tdk_select_kernel(const RoundDev rd, co
   // total deviation, number of candidates, keys, and the first pass's histogram
   double part = 0.0;
   int cand = 0;
-  for (int m = tid; m < S; m += BLOCK) {
-    const float v = sc[m];
-    const uint32_t key = to_key(v);
-    part += (double)v;
-    cand += key != 0u;
-    if (key != 0u) atomicAdd(&hist[0][key >> 24], 1u);
-    if (m < kKeys) keys[m] = key;
+  // (eight scores per thread in flight: one after the other they are five memory latencies at 5000 tokens; 4 x 3 agents x
+  // 5776 tokens, 2 heads, 23.0 -> 22.2 us for the call, 21 x 8773 41.0 -> 39.7)
+  constexpr int kAhead = 8;
+  for (int m0 = tid; m0 < S; m0 += kAhead * BLOCK) {
+    float v[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) v[q] = sc[min(m0 + q * BLOCK, S - 1)];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int m = m0 + q * BLOCK;
+      if (m >= S) break;
+      const uint32_t key = to_key(v[q]);
+      part += (double)v[q];
+      cand += key != 0u;
+      if (key != 0u) atomicAdd(&hist[0][key >> 24], 1u);
+      if (m < kKeys) keys[m] = key;
+    }
   }
 #pragma unroll
   for (int sft = 32; sft > 0; sft >>= 1) { part += __shfl_xor(part, sft); cand += __shfl_xor(cand, sft); }
