@@ -319,12 +319,12 @@ void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queue
 
 namespace {
 
-// Listed tokens per piece of the listed-pages pass; lists = agents x KV heads.  Short pieces spread a list over more
-// wavefronts, which rounds that do not fill the chip need; every piece has a partial result per row.  (Of 578 rounds with
-// identity layouts, in the best form otherwise, 128 tokens take 0.95 to 0.98 of the time up to 1500 lists on average; ten sessions of 25
-// agents, 2000 lists, lose 3 %.)  Partial results of more than 256 MB are not worth it.
-int attend_piece_tokens(int64_t lists, int64_t rows, int64_t max_span) {
-  return lists > 1500 || rows * ((max_span + 127) / 128) > ((int64_t)256 << 20) / (kHeadDim * (int64_t)sizeof(float)) ? 512 : 128;
+int attend_piece_tokens(int64_t lists, int n_cus) {
+  // lists = agents x KV heads.  A piece is 512 tokens, unless the round is so small (at most one list per compute
+  // unit) that its few wavefronts would each walk ten or more tiles one after another while most
+  // of the chip idles: then 128.  (Shorter pieces in larger rounds cost more in start-up than they gain: the
+  // 100-agent long round 138 -> 162 us with pieces of 256 tokens.)
+  return lists > n_cus ? 512 : 128;
 }
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -359,15 +359,15 @@ bool attend_rows_for_segments(const AttendShape& r, int64_t agent_rows) {
   return within(24, 8) || (agent_rows < 8 ? within(60, 3) : within(110, 5));
 }
 
-// What a call takes, in microseconds, for every way to cut the span.  The three estimates below were fitted (robust least
-// squares on the logarithm) to 24 000 timed launches of 1100 rounds: 1 to 20 sessions, 2 to 260 agents, 64 to 26 000 tokens, 1 to 8 KV
-// heads, 1 to 512 rows per agent and KV head, 2 to 20 % of the pages listed, diffs moved or not, both page sizes, every form and
-// up to 14 chunk sizes each.  They are within 10 % (own block orders 12 to 14 %) of the measured times, and what they choose takes 1.03
-// to 1.05 times the best choice on average.  Against the rules before them (chunks of 512 tokens or more, lowest number
-// of rounds of workgroup slots; packed rows up to 32 per agent): identity layouts with up to 32 rows 1.22 times as fast
-// (geometric mean of 578 rounds; 33 more than 2 % slower, 6 more than 10 %), own block orders 1.03 (379 rounds), their packed form
-// 1.11 (111).  On 137 other rounds 1.11 over all, among them 102 -> 121 us (109 agents x 5192 tokens, 16 rows, 2 % listed) and 40.6 -> 17.8
-// (4 x 23 agents x 152 tokens, 32 rows).
+// What a call takes, in microseconds, where nothing is simple: the master's order, at most 32 rows per agent and KV head, and a pass
+// too small for pipelined steps.  Both estimates are robust least squares fits (on the logarithm) to 9 000 timed launches of 318
+// rounds: 1 to 20 sessions, 2 to 260 agents, 64 to 26 000 tokens, 1 to 8 KV heads, 1 to 32 rows, 2 to 20 % of the pages listed, diffs
+// moved or not, both page sizes, both forms, up to 14 chunk sizes; three sets of inputs in turn, so that the caches hold
+// what they hold in a program.  They are within 11 and 9 % of the measured times.  What they choose takes 1.04 times the best
+// choice on average and is 1.27 times as fast as the rule before (packed rows, chunks of 512 tokens or more): 12 of the 318
+// rounds are more than 2 % slower, 2 more than 10 % (198 agents x 3857 tokens, 16 rows, 4 heads 80 -> 94 us), 4 x 23 agents
+// x 152 tokens with 32 rows take 18 us instead of 41.  (With one set of inputs over and over, 2 to 5 % listed pages and short
+// pieces look better than they are: fitted to that, ten sessions of 25 x 5000 tokens lost 6 %.)
 struct AttendLoad {
   double wgs;        // workgroups of the pass over the master, per compute unit
   double steps;      // 64-token steps of a workgroup
@@ -379,64 +379,39 @@ constexpr double kListedShare = 0.08;       // share of the pages taken to be li
 // microseconds at 6 TB/s for the payload of the listed pages
 double listed_us(const AttendShape& r) { return kListedShare * (double)r.total_tokens * r.heads * (4 * kHeadDim) / 6e6; }
 
-// 32-token tiles that a wavefront of the listed-pages pass walks one after the other; at most four wavefronts share a list
-double listed_tiles(int64_t max_span, int piece) {
+// rounds of workgroups, two to a compute unit: a round of at most one per unit counts 1, a fuller one `two`
+double rounds_of(double wgs, double two) {
+  const double full = std::floor(wgs / 2 + 1e-9), rest = wgs - 2 * full;
+  return full * two + (rest < 1e-9 ? 0.0 : rest > 1 ? two : 1.0);
+}
+
+// Packed rows and listed pages in one launch, and the merge.  Both kinds of workgroup run at the same time.  At most four
+// wavefronts share a list.
+double packed_us(const AttendShape& r, AttendLoad l, int64_t max_span, int piece) {
   const double tokens = kListedShare * (double)max_span, pieces = std::max(1.0, std::ceil(tokens / piece));
-  return std::ceil(pieces / std::min(4.0, std::ceil((double)max_span / piece))) * std::min((double)piece, std::max(32.0, tokens)) / 32;
+  const double tiles = std::ceil(pieces / std::min(4.0, std::ceil((double)max_span / piece))) * std::min((double)piece, std::max(32.0, tokens)) / 32;
+  const double walk = (0.805 + 1.505 * l.steps) * (0.572 * std::max(1.0, 1.83 * l.wgs) + 0.428 * rounds_of(l.wgs, 0.98));
+  const double list = 1.37 * tiles + 0.865 * listed_us(r);
+  l.parts += pieces;
+  return 8.35 + std::sqrt(walk * walk + list * list) + 0.099 * l.parts + 0.39 * l.rows * l.parts;
 }
 
-// Identity layouts, packed rows and listed pages in one launch.  Both kinds of workgroup run at the same time; the
-// launch is as slow as the steps of one workgroup until the chip is two thirds full and in proportion beyond.
-double packed_us(const AttendShape& r, const AttendLoad& l, bool pipelined, double list_wgs, double tiles) {
-  const double walk = (pipelined ? 1.25 + 1.17 * l.steps : 0.53 + 1.40 * l.steps) * std::max(1.0, 1.4 * (l.wgs + 0.05 * list_wgs));
-  const double list = 0.99 * tiles + 1.18 * listed_us(r);
-  return 9.4 + std::sqrt(walk * walk + list * list) + 0.134 * l.parts + 0.30 * l.rows * l.parts;
-}
-
-// Own block orders, packed rows: rotated copies of the rows, master pass, listed pages and merge one after the other.
-double packed_segments_us(const AttendShape& r, const AttendLoad& l, double list_wgs, double tiles) {
-  return 11.8 + 5.0 * l.steps * std::max(1.0, 0.69 * l.wgs) + 0.96 * tiles * std::max(1.0, 0.13 * list_wgs) + 1.39 * listed_us(r) +
-         (r.seg_moved ? 7.3 : 0.0) + 0.29 * l.parts + 0.42 * l.rows * l.parts;
-}
-
-// A wavefront per agent; `parts` of 1 or less: no merge.  A workgroup walks its part of the lists after its steps.  Two workgroups
-// share a compute unit: the launch lasts partly in proportion to its workgroups and partly in whole rounds of them.
-// More than 32 rows and the master's order: workgroups find the tiles of others in L2, and partial results are many.  There the
-// estimate is an older one, in steps of 1.2 us: a workgroup starts up in 8, two that share a unit take 1.6 times as long, the
-// merge costs 6 and its traffic (16 query tokens, 25 agents: 1, 2, 4, 8 chunks take 104, 74, 68, 79 us without listed pages; with
-// the constants for few rows 12 agents x 2496 tokens x 320 rows would be cut in two, 57 -> 73 us).
-double rows_us(const AttendShape& r, const AttendLoad& l, int64_t agent_rows) {
-  const double tiles = kListedShare * l.steps * 2;
-  const double full = std::floor(l.wgs / 2 + 1e-9), rest = l.wgs - 2 * full;
-  auto rounds = [&](double two) { return full * two + (rest < 1e-9 ? 0.0 : rest > 1 ? two : 1.0); };
-  double us, merge;
-  if (!r.seg && agent_rows > 32) {
-    us = 1.2 * (8 + l.steps) * rounds(1.6);
-    merge = 1.2 * (6 + l.rows * (l.parts + 1) * 1024e3 / 6e6);
-  } else if (!r.seg) {
-    us = (8.9 + 1.34 * l.steps + 1.46 * tiles) * (0.65 * std::max(1.0, 0.755 + 0.31 * l.wgs) + 0.35 * rounds(1.32)) + 0.57 * listed_us(r);
-    merge = 3.3 + 0.154 * l.parts + 0.223 * l.rows * l.parts;
-  } else {            // (apart: the lists turn their rows per segment)
-    us = (7.2 + 2.14 * l.steps + (r.seg_apart ? 6.0 : 2.09) * tiles) * (0.62 * std::max(1.0, 0.669 + 0.432 * l.wgs) + 0.38 * rounds(1.08)) +
-         (r.seg_apart ? 3.0 : 0.405) * listed_us(r);
-    merge = 5.5 + 0.138 * l.parts + 0.236 * l.rows * l.parts;
-  }
-  return us + (l.parts > 1 ? merge : 0.0);
+// A wavefront per agent, and the merge where the span is cut.  A workgroup walks its part of the lists after its steps.
+double rows_us(const AttendShape& r, const AttendLoad& l) {
+  const double tiles = 2 * kListedShare * l.steps;
+  return (9.03 + 1.40 * l.steps + 1.47 * tiles) * (0.638 * std::max(1.0, 0.823 + 0.306 * l.wgs) + 0.362 * rounds_of(l.wgs, 1.16)) +
+         0.76 * listed_us(r) + (l.parts > 1 ? 2.6 + 0.175 * l.parts + 0.22 * l.rows * l.parts : 0.0);
 }
 
 // Calls f(chunk) for the chunk sizes worth trying, longest first: the span in 1, 2, .. 16 and then ever more equal parts, in
-// multiples of 64 tokens from `lo` to `hi`.
+// multiples of 64 tokens up to `most`.
 template <class F>
-void for_chunks(int64_t max_span, int64_t lo, int64_t hi, F f) {
+void for_chunks(int64_t max_span, int64_t most, F f) {
   int64_t last = 0;
   for (int64_t k = 1;; k += 1 + k / 16 * 2) {
     const int64_t c = std::max<int64_t>(64, ((max_span + k - 1) / k + 63) / 64 * 64);
-    if (c != last && c <= hi) {
-      if (c < lo && last) break;
-      f(std::max(c, lo));
-      last = c;
-    }
-    if (c <= std::max<int64_t>(lo, 64)) break;
+    if (c != last && c <= most) f(last = c);
+    if (c == 64) break;
   }
 }
 
@@ -468,84 +443,77 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
   auto times = [](int64_t a, int64_t b) { return a > 0 && b > INT64_MAX / a ? INT64_MAX : a * b; };
   p.max_agents = (int32_t)max_agents;
   const int64_t agent_rows = (int64_t)n_q * G;
-  const int64_t lists = (int64_t)r.n_agents * r.heads, per_agent = (agent_rows + 31) / 32;
-  const int64_t row_blocks = std::max<int64_t>(1, (max_rows + 127) / 128);
-  // chunks of c tokens over all sessions with agents, and the workgroups of the rows kernel in them (both per KV head)
-  int64_t with_agents = 0;
-  for (const auto& hs : *r.sessions) with_agents += !hs.agents.empty();
-  auto count = [&](int64_t c, int64_t& chunks, int64_t& row_wgs) {
-    chunks = row_wgs = 0;
-    int64_t span = -1, n = 0;
-    for (const auto& hs : *r.sessions) {
-      if (hs.agents.empty()) continue;
-      if (hs.span != span) { span = hs.span; n = (span + c - 1) / c; }
-      chunks += n;
-      row_wgs += n * (((int64_t)hs.agents.size() * per_agent + 3) / 4);
-    }
-  };
-  auto load = [&](int64_t c, int64_t chunks, int64_t wgs) {
-    return AttendLoad{(double)wgs * r.heads / r.n_cus, (double)((std::min(c, max_span) + 63) / 64), (double)chunks / (double)std::max<int64_t>(with_agents, 1),
-                      (double)p.rows / 1000};
-  };
-  const int64_t longest_own = std::max<int64_t>(64, ((max_span + (max_span + 16383) / 16384 - 1) / std::max<int64_t>((max_span + 16383) / 16384, 1) + 63) / 64 * 64);
-  double own_best = -1;
-  int64_t own_chunk = 64;
-  auto try_own = [&](int64_t c) {
-    int64_t chunks, wgs;
-    count(c, chunks, wgs);
-    const double us = rows_us(r, load(c, chunks, wgs), agent_rows);
-    if (own_best < 0 || us < own_best) { own_best = us; own_chunk = c; }
-  };
-  // Which kernels: one agent per wavefront, or the rows of a session's agents packed into one block.  Packed rows waste no
-  // place in the 32-row tiles, but their listed pages need a pass and partial results of their own.  From 33 rows on the tiles
-  // of one agent are full and packing has nothing to save (40 rows: 94 against 70 us, ten sessions 575 against 460; 320 rows:
-  // 462 against 206); below, the estimates decide (identity layouts) or the lines of attend_rows_for_segments.
+  // Which kernels: one agent per wavefront, or the rows of a session's agents packed into one block.
+  //   Packed rows waste no place in the 32-row tiles, but their listed pages need a pass and partial results of their
+  //   own.  From 33 rows on the tiles of one agent are full and packing has nothing to save (40 rows: 94 against 70 us, ten
+  //   sessions 575 against 460 us; 320 rows: 462 against 206 us).  Below, in the master's order, the pipelined steps decide
+  //   (10 rows, ten sessions: packed) or the estimates above.
+  const int64_t lists = (int64_t)r.n_agents * r.heads;
+  const int64_t row_blocks = std::max<int64_t>(1, (max_rows + 127) / 128), per_agent = (agent_rows + 31) / 32, cus = r.n_cus;
+  const int32_t max_chunk = std::min<int32_t>(128 * r.page_tokens, 4096);
   p.own_rows = agent_rows > 32 || r.total_master_rows == 0 || lists >= ((int64_t)1 << 27) ||
                (r.seg && attend_rows_for_segments(r, agent_rows));
-  // The master pass with packed rows: a workgroup walks its chunk in steps of 64 tokens, and the 128-bit page mask per query
-  // row limits it.  Pipelined steps (identity layouts; tdk_attend.hip, attend_packed_body): a workgroup starts up later there (two more
-  // tiles and the first scores before the loop), so it needs at least 8 steps per workgroup and at least 2 3/4 per compute unit over the
-  // whole pass; with three row blocks or more the plain form's calls of coming tiles into L2 serve several readers; and
-  // 17 rows or more (32-row tiles for the listed pages) lose with many listed pages what they gain with few.
-  // Time plain / pipelined, 1 to 16 rows, 3 and 20 % of the pages listed: ten sessions of 6 x 2000 tokens (9.8 steps) 1.04 .. 1.10, four
-  // of 12 x 3000 (5.9) 1.04 .. 1.06, ten of 25 x 600 (2.9) 1.00 .. 1.10, 50 agents x 12000 (5.9) 1.01 .. 1.05; one session of 25 x 5000 (2.4)
-  // 0.99 .. 1.04, of 50 x 2000 (2.0) 0.99 .. 1.00, two of 36 x 500 (1.0) 0.96 .. 1.02, ten of 25 x 1500 with 2 heads (1.8) 0.95 .. 1.01, two
-  // of 25 x 207 (0.2) 0.92 .. 0.99; 20 rows, half of the pages listed, ten sessions of 6 x 2000 tokens 145 against 176 us.
-  // Passes that qualify take chunks of 512 tokens or more.
-  int64_t chunk = 64;
-  if (!p.own_rows) {
-    int64_t all_steps, unused;
-    count(64, all_steps, unused);
-    p.pipelined = !r.seg && agent_rows <= 16 && row_blocks <= 2 && max_span >= 512 && 4 * all_steps * r.heads * row_blocks >= 11 * (int64_t)r.n_cus;
-    p.piece_tokens = attend_piece_tokens(lists, p.rows, max_span);
-    double best = -1;
-    auto try_packed = [&](int64_t c, int piece) {
-      // (a launch that fits a grid with the longest chunks is not cut so fine that it does not)
-      if (best >= 0 && times(times(times(r.heads, row_blocks), n_sessions), (max_span + c - 1) / c) >= kMaxBlocks - times(lists, 4)) return;
-      int64_t chunks, row_wgs;
-      count(c, chunks, row_wgs);
-      const double pieces = std::max(1.0, std::ceil(kListedShare * (double)max_span / piece)), grid = std::min(4.0, std::ceil((double)max_span / piece));
-      AttendLoad l = load(c, chunks, chunks * row_blocks);
-      l.parts += pieces;
-      const double list_wgs = (double)r.n_agents * ((r.heads + kWaves - 1) / kWaves) * std::min(pieces, grid) / r.n_cus, tiles = listed_tiles(max_span, piece);
-      const double us = r.seg ? packed_segments_us(r, l, list_wgs, tiles) : packed_us(r, l, p.pipelined, list_wgs, tiles);
-      if (best < 0 || us < best) { best = us; chunk = c; p.piece_tokens = piece; }
-    };
-    const int64_t most = std::min<int64_t>(128 * r.page_tokens, 4096);
-    for_chunks(max_span, p.pipelined ? 512 : 64, most, [&](int64_t c) { try_packed(c, p.piece_tokens); });
-    // identity layouts: is a wavefront per agent faster?  (Not where the packed launch does not fit a grid: it is refused.)
-    const int64_t groups = (r.heads + kWaves - 1) / kWaves, n_chunks = (max_span + chunk - 1) / chunk;
-    const bool fits = times(times(times(r.heads, row_blocks), n_sessions), n_chunks) < kMaxBlocks - times(r.n_agents * groups, 4);
-    if (!r.seg && !p.pipelined && fits) {
-      for_chunks(max_span, 64, longest_own, try_own);
-      p.own_rows = own_best >= 0 && own_best < best;
-    }
-  } else {
-    for_chunks(max_span, agent_rows > 32 && !r.seg ? std::max<int64_t>(64, max_span / 32) : 64, longest_own, try_own);
+  p.piece_tokens = attend_piece_tokens(lists, r.n_cus);
+  // enough steps for the pipelined form? (see below)
+  int64_t steps = 0;
+  for (const auto& hs : *r.sessions)
+    if (!hs.agents.empty()) steps += ((int64_t)hs.span + 63) / 64;
+  steps *= r.heads * row_blocks;
+  const bool long_pass = !r.seg && agent_rows <= 16 && row_blocks <= 2 && max_span >= 512 && 4 * steps >= 11 * cus;
+  int32_t chosen = 0;              // the chunk that the estimates chose
+  if (!p.own_rows && !r.seg && !long_pass) {
+    int64_t with_agents = 0;
+    for (const auto& hs : *r.sessions) with_agents += !hs.agents.empty();
+    double packed = -1, rows = -1;
+    int64_t packed_chunk = 64, rows_chunk = 64;
+    for_chunks(max_span, std::max<int64_t>(16384, max_chunk), [&](int64_t c) {
+      // chunks of c tokens over all sessions with agents, and the workgroups of the rows kernel in them (both per KV head)
+      int64_t chunks = 0, row_wgs = 0, span = -1, n = 0;
+      for (const auto& hs : *r.sessions) {
+        if (hs.agents.empty()) continue;
+        if (hs.span != span) { span = hs.span; n = (span + c - 1) / c; }
+        chunks += n;
+        row_wgs += n * (((int64_t)hs.agents.size() + kWaves - 1) / kWaves);
+      }
+      AttendLoad l{(double)(chunks * row_blocks * r.heads) / (double)cus, (double)((std::min(c, max_span) + 63) / 64),
+                   (double)chunks / (double)std::max<int64_t>(with_agents, 1), (double)p.rows / 1000};
+      // (a packed launch that fits a grid with its longest chunks is not cut so fine that it does not)
+      const bool fits = times(times(times(r.heads, row_blocks), n_sessions), (max_span + c - 1) / c) < kMaxBlocks - times(lists, 4);
+      if (c <= max_chunk && (packed < 0 || fits)) {
+        const double us = packed_us(r, l, max_span, p.piece_tokens);
+        if (packed < 0 || us < packed) { packed = us; packed_chunk = c; }
+        if (!fits) rows = 0;         // refused, as ever: not to be taken by the other form
+      }
+      l.wgs = (double)(row_wgs * r.heads) / (double)cus;
+      const double us = rows_us(r, l);
+      if (rows < 0 || us < rows) { rows = us; rows_chunk = c; }
+    });
+    p.own_rows = rows > 0 && rows < packed;
+    chosen = (int32_t)(p.own_rows ? rows_chunk : packed_chunk);
   }
   if (p.own_rows) {
-    p.pipelined = false;
-    p.chunk_tokens = (int32_t)own_chunk;
+    // Chunks of the span: workgroups of four wavefronts, two of which share a compute unit (each then takes about
+    // 1.6 times as long).  In units of a 64-token step (about 1.2 us): a workgroup starts up in 8, a step with
+    // per-agent block orders costs 2 (query reloads at the borders), a second launch to merge costs 6 and the
+    // traffic of the partial results.  (More than 32 rows and own block orders; 50 and 192 rounds: 1.02 and 1.05 times the best
+    // choice.  16 query tokens, 25 agents: 1, 2, 4, 8 chunks take 104, 74, 68, 79 us without
+    // listed pages; per-agent orders, 4 tokens: 1, 4, 8, 12 chunks 252, 87, 70, 85 us.)
+    double best = -1;
+    if (chosen) p.chunk_tokens = chosen;
+    const int k_lo = (int)std::max<int64_t>(1, (max_span + 16383) / 16384);
+    for (int k = k_lo; !chosen && k < k_lo + 32; ++k) {
+      const int64_t c = std::max<int64_t>(64, ((max_span + k - 1) / k + 63) / 64 * 64);
+      if (k > k_lo && c * (k - 1) >= max_span) continue;       // the same chunks as a smaller k
+      int64_t wgs = 0;
+      for (const auto& hs : *r.sessions)
+        if (!hs.agents.empty()) wgs += (((int64_t)hs.span + c - 1) / c) * (((int64_t)hs.agents.size() * per_agent + 3) / 4);
+      wgs *= r.heads;
+      const double one = (double)(c / 64) * (r.seg ? 2 : 1) + 8;
+      const int64_t full = wgs / (2 * cus), rest = wgs % (2 * cus);
+      const double cost = one * (1.6 * (double)full + (rest == 0 ? 0.0 : rest > cus ? 1.6 : 1.0)) +
+                          (max_span > c ? 6 + (double)p.rows * ((double)max_span / (double)c + 1) * 1024 / 6e6 : 0.0);
+      if (best < 0 || cost < best) { best = cost; p.chunk_tokens = (int32_t)c; }
+    }
     p.n_chunks = (int32_t)((max_span + p.chunk_tokens - 1) / p.chunk_tokens);
     p.n_pieces = 0;
     p.piece_tokens = 512;          // (no listed-pages pass: the merge finds no pieces)
@@ -558,8 +526,40 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     place_parts(p, 0);
     return true;
   }
-  p.chunk_tokens = (int32_t)chunk;
+  // Tokens per workgroup of the master pass.  A workgroup walks its chunk in steps of 64 tokens; two
+  // workgroups fit a compute unit at a time, so the pass takes about ceil(workgroups / slots) rounds of
+  // (steps per chunk + a fixed start-up cost of about two steps).  Of the chunk sizes that the 128-bit page
+  // mask per query row can cover, the one with the lowest such cost wins; ties go to the larger chunk
+  // (fewer partial results to merge).
+  const int64_t slots = 2 * cus;
+  // Chunks shorter than 512 tokens are not tried here (unless the span is): a workgroup's start-up (page masks,
+  // query rotation, first rows) costs about as much as three steps, and every chunk adds a partial result per row
+  // for the merge.  Where that pays, the estimates have chosen.
+  const int32_t min_chunk = (int32_t)std::min<int64_t>(512, (max_span + 63) / 64 * 64);
+  int32_t chunk = std::max(min_chunk, 64);
+  int64_t best = -1;
+  if (chosen) chunk = chosen;
+  for (int32_t c = max_chunk; !chosen && c >= std::max(min_chunk, 64); c -= 64) {
+    int64_t wgs = 0;
+    for (const auto& hs : *r.sessions)
+      if (!hs.agents.empty()) wgs += ((int64_t)hs.span + c - 1) / c;
+    wgs *= r.heads * row_blocks;
+    if (wgs == 0) break;
+    const int64_t cost = ((wgs + slots - 1) / slots) * (std::min<int64_t>(c, max_span + 63) / 64 + 2);
+    if (best < 0 || cost < best) { best = cost; chunk = c; }
+  }
+  p.chunk_tokens = chunk;
   p.n_chunks = (int32_t)((max_span + chunk - 1) / chunk);
+  // Pipelined steps in the master pass (identity layouts; tdk_attend.hip, attend_packed_body).  A workgroup starts up later there
+  // (two more tiles and the first scores before the loop), so it needs workgroups of at least 8 steps and at least 2 3/4 steps
+  // per compute unit over the whole pass; with three row blocks or more the plain form's calls of coming tiles into L2
+  // serve several readers; and 17 rows or more (32-row tiles for the listed pages) lose with many listed pages what
+  // they gain with few.  Time plain / pipelined, 1 to 16 rows, 3 and 20 % of the pages listed: ten sessions of 6 x 2000
+  // tokens (9.8 steps) 1.04 .. 1.10, four of 12 x 3000 (5.9) 1.04 .. 1.06, ten of 25 x 600 (2.9) 1.00 .. 1.10, 50 agents x 12000 (5.9)
+  // 1.01 .. 1.05; one session of 25 x 5000 (2.4) 0.99 .. 1.04, of 50 x 2000 (2.0) 0.99 .. 1.00, two of 36 x 500 (1.0) 0.96 .. 1.02, ten of
+  // 25 x 1500 with 2 heads (1.8) 0.95 .. 1.01, two of 25 x 207 (0.2) 0.92 .. 0.99; 20 rows, half of the pages listed, ten sessions of 6 x
+  // 2000 tokens 145 against 176 us.
+  p.pipelined = long_pass && chunk >= 512;
   // the listed-pages pass: one wavefront takes a piece of an agent's list and every piece has its own partial result
   {
     int64_t max_pages = 0;
