@@ -677,12 +677,14 @@ constexpr int kCopyBatch = 8;
 // the span (row < 0) is zero in the payload and not written in the pool.  No branch stands around a load: a load with
 // nothing to fetch repeats one of its page.  NT: streaming stores; NTL: non-temporal loads.  (The gather streams both:
 // with caches that change from call to call a store of 180 agents x 2166 tokens, one page in ten listed, took 277 us with
-// ordinary loads and 263 streamed; 30 agents x 2000, one in five, 69 and 70.)
+// ordinary loads and 263 streamed; 30 agents x 2000, one in five, 69 and 70.)  share: this workgroup's part of the slot, of 1 << lg_shares.
 template <bool TO_PAYLOAD, bool NT, bool NTL>
-__device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io, u32x4* slot_data, int p0, int p1, const SlotShared& sh) {
-  const int row_u4 = rd.heads * 16, page_u4 = rd.page_tokens * row_u4, n = (p1 - p0) * page_u4;
+__device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io, u32x4* slot_data, int p0, int p1, const SlotShared& sh,
+                                          int share = 0, int lg_shares = 0) {
+  const int row_u4 = rd.heads * 16, page_u4 = rd.page_tokens * row_u4, all = (p1 - p0) * page_u4;
+  const int n = (all * (share + 1)) >> lg_shares;
   const uint32_t inv = 0xffffffffu / (uint32_t)row_u4 + 1u;      // i / row_u4 == __umulhi(i, inv) for i < 2^13 (row_u4 <= 128)
-  for (int i0 = threadIdx.x; i0 < n; i0 += kBlock * kCopyBatch) {
+  for (int i0 = ((all * share) >> lg_shares) + threadIdx.x; i0 < n; i0 += kBlock * kCopyBatch) {
     u32x4 v[kCopyBatch];
     u32x4* at[kCopyBatch];
     bool there[kCopyBatch];
@@ -709,13 +711,18 @@ __device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io
   }
 }
 
+// batches of accesses in a slot (copy_slot)
+__device__ __host__ __forceinline__ int slot_batches(const RoundDev& rd, int planes) {
+  return (planes == 3 ? 2 : 1) * rd.page_tokens * rd.heads * 16 / (kBlock * kCopyBatch);
+}
+
 // planes: bit 0 = K, bit 1 = V; a slot holds the selected planes back to back
 __device__ __forceinline__ void gather_slot(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const int planes, int64_t slot,
-                                            const SlotShared& sh) {
+                                            const SlotShared& sh, int share = 0, int lg_shares = 0) {
   const int p0 = planes == 2 ? 1 : 0, p1 = planes == 1 ? 1 : 2;
   u32x4* data = d.payload + slot * (p1 - p0) * (int64_t)(rd.page_tokens * rd.heads * 16);
-  if (rd.nontemporal & 16) copy_slot<true, true, true>(rd, io, data, p0, p1, sh);
-  else copy_slot<true, false, false>(rd, io, data, p0, p1, sh);
+  if (rd.nontemporal & 16) copy_slot<true, true, true>(rd, io, data, p0, p1, sh, share, lg_shares);
+  else copy_slot<true, false, false>(rd, io, data, p0, p1, sh, share, lg_shares);
 }
 
 __global__ __launch_bounds__(kBlock) void tdk_gather_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
@@ -798,11 +805,16 @@ __global__ __launch_bounds__(kBlock) void tdk_list_gather_kernel(const RoundDev 
     }
     if (tid == 0) { d.offset[A] = total; d.overflow[0] = total > d.capacity ? 1 : 0; }
   }
-  const int64_t slots = min((int64_t)total, d.capacity);
-  for (int64_t slot = blockIdx.x; slot < slots; slot += gridDim.x) {
+  const int slots = (int)min((int64_t)total, d.capacity);
+  // Few slots are shared out further, down to one batch of accesses per thread: a workgroup's batches are round trips to memory one
+  // after the other (4 agents x 256 tokens, the whole collect, restore and store 27.3 -> 25.5 us).
+  int lg_shares = 0;
+  while ((2 << lg_shares) <= slot_batches(rd, planes) && (int64_t)slots << (lg_shares + 1) <= gridDim.x) ++lg_shares;
+  for (int unit = blockIdx.x; unit < slots << lg_shares; unit += gridDim.x) {
+    const int slot = unit >> lg_shares, share = unit & ((1 << lg_shares) - 1);
     // the slot-th listed page: one thread holds its flag
     if (slot >= before && slot < before + own) {
-      int k = (int)slot - before, found = -1;
+      int k = slot - before, found = -1;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -825,9 +837,9 @@ __global__ __launch_bounds__(kBlock) void tdk_list_gather_kernel(const RoundDev 
     }
     __syncthreads();
     if (tid < rd.page_tokens) sh.row[tid] = slot_row(rd, rd.agents[sh.owner], sh.page, tid);
-    if (tid == 0) d.idx[slot] = sh.page;
+    if (tid == 0 && share == 0) d.idx[slot] = sh.page;
     __syncthreads();
-    gather_slot(rd, io, d, planes, slot, sh);
+    gather_slot(rd, io, d, planes, slot, sh, share, lg_shares);
     __syncthreads();
   }
 }
@@ -1536,7 +1548,8 @@ bool lists_in_gather(const RoundDev& rd) { return rd.agent_pages <= kListPages; 
 hipError_t launch_list_gather(const RoundDev& rd, const LayerDev& io, const DiffDev& d, int planes, int grid_size, hipStream_t st) {
   // (capacities are mostly generous: workgroups without a slot repeat the count for nothing, so no more than four per
   // compute unit are launched)
-  hipLaunchKernelGGL(tdk_list_gather_kernel, dim3(std::max(1, std::min(grid_size, 4 * std::max(rd.n_cus, 1)))), dim3(kBlock), 0, st, rd, io, d, planes);
+  const int64_t blocks = (int64_t)grid_size * std::max(1, slot_batches(rd, planes));
+  hipLaunchKernelGGL(tdk_list_gather_kernel, dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>(blocks, 4 * std::max(rd.n_cus, 1)))), dim3(kBlock), 0, st, rd, io, d, planes);
   return hipGetLastError();
 }
 
