@@ -1263,22 +1263,29 @@ __device__ __forceinline__ void rows_step(const unsigned char* Ks, const unsigne
   const float m2 = -(st.m_run == -INFINITY ? 0.f : st.m_run) * kLog2e;
   auto k_op = [&](int j) { return k_operand(Ks + (j & 1) * (kStepTile / 2), j >> 1, n, hh); };
   auto v_op = [&](int j) { return v_operand(Vs, j >> 2, j & 3, lane); };
+  constexpr int kWeights = 32;
   // weight number w, in the order the second products need them: 16 tokens at a time
   uint32_t pw[4][4];
+  // in three stages, each a slot after the one before: a chain of scaling, exponential, sum and packing inside one slot
+  // is longer than its product and holds up the next one (12 agents x 2496 tokens x 320 rows 67.6 -> 64.8 us)
+  auto tile = [](int w) { return w / 16; };
+  auto elem = [](int w) { return 8 * ((w / 8) & 1) + w % 8; };
   auto weight = [&](int w) {
-    const int kk = w / 8, j = w % 8, t = kk >> 1, e = 8 * (kk & 1) + j;
-    s[t][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e], c2, m2));
-    st.l_run += s[t][e];
-    if (j & 1) pw[kk][j >> 1] = pack2(s[t][e - 1], s[t][e]);
+    if (w + 2 < kWeights) s[tile(w + 2)][elem(w + 2)] = __builtin_fmaf(s[tile(w + 2)][elem(w + 2)], c2, m2);
+    if (w + 1 < kWeights) s[tile(w + 1)][elem(w + 1)] = __builtin_amdgcn_exp2f(s[tile(w + 1)][elem(w + 1)]);
+    st.l_run += s[tile(w)][elem(w)];
+    if (w & 1) pw[w / 8][(w % 8) >> 1] = pack2(s[tile(w - 1)][elem(w - 1)], s[tile(w)][elem(w)]);
   };
   // weights before the first product (while its operands arrive), per slot of the first and of the second products;
   // the eight weights of 16 tokens must stand before the four slots that use them
-  constexpr int kWeights = 32, kPre = 4, kFirst = 1, kSecond = 2;
+  constexpr int kPre = 4, kFirst = 1, kSecond = 2;
   static_assert(kPre + 16 * kFirst >= 8 && kPre + 16 * kFirst + 4 * kSecond >= 16 && kPre + 16 * kFirst + 8 * kSecond >= 24 &&
                 kPre + 16 * kFirst + 12 * kSecond >= 32, "weights stand before their products");
   bf16x8 ka[kAhead], va[kAhead];
 #pragma unroll
   for (int j = 0; j < kAhead; ++j) ka[j] = k_op(j);
+  s[tile(0)][elem(0)] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[tile(0)][elem(0)], c2, m2));
+  s[tile(1)][elem(1)] = __builtin_fmaf(s[tile(1)][elem(1)], c2, m2);
 #pragma unroll
   for (int w = 0; w < kPre; ++w) weight(w);
   __builtin_amdgcn_sched_barrier(0);
