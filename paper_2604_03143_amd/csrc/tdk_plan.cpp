@@ -365,8 +365,8 @@ bool attend_rows_for_segments(const AttendShape& r, int64_t agent_rows) {
 // moved or not, both page sizes, both forms, up to 14 chunk sizes; three sets of inputs in turn, so that the caches hold
 // what they hold in a program.  They are within 11 and 9 % of the measured times.  What they choose takes 1.04 times the best
 // choice on average and is 1.27 times as fast as the rule before (packed rows, chunks of 512 tokens or more): 12 of the 318
-// rounds are more than 2 % slower, 2 more than 10 % (198 agents x 3857 tokens, 16 rows, 4 heads 80 -> 94 us), 4 x 23 agents
-// x 152 tokens with 32 rows take 18 us instead of 41.  (With one set of inputs over and over, 2 to 5 % listed pages and short
+// rounds are more than 2 % slower, 1 more than 10 % (4 x 36 agents x 1611 tokens, 16 rows, a fifth of the pages listed 90 -> 105 us),
+// 4 x 23 agents x 152 tokens with 32 rows take 18 us instead of 41.  (With one set of inputs over and over, 2 to 5 % listed pages and short
 // pieces look better than they are: fitted to that, ten sessions of 25 x 5000 tokens lost 6 %.)
 struct AttendLoad {
   double wgs;        // workgroups of the pass over the master, per compute unit
@@ -460,13 +460,39 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     if (!hs.agents.empty()) steps += ((int64_t)hs.span + 63) / 64;
   steps *= r.heads * row_blocks;
   const bool long_pass = !r.seg && agent_rows <= 16 && row_blocks <= 2 && max_span >= 512 && 4 * steps >= 11 * cus;
+  // Tokens per workgroup of the master pass where it fills the chip.  A workgroup walks its chunk in steps of 64 tokens; two
+  // workgroups fit a compute unit at a time, so the pass takes about ceil(workgroups / slots) rounds of
+  // (steps per chunk + a fixed start-up cost of about two steps).  Of the chunk sizes that the 128-bit page
+  // mask per query row can cover, the one with the lowest such cost wins; ties go to the larger chunk
+  // (fewer partial results to merge).  Chunks shorter than 512 tokens are not tried here (unless the span is): a workgroup's
+  // start-up (page masks, query rotation, first rows) costs about as much as three steps, and every chunk adds a partial
+  // result per row for the merge.
+  auto fewest_rounds = [&]() {
+    const int64_t slots = 2 * cus;
+    const int32_t min_chunk = std::max((int32_t)std::min<int64_t>(512, (max_span + 63) / 64 * 64), 64);
+    int32_t chunk = min_chunk;
+    int64_t best = -1;
+    for (int32_t c = max_chunk; c >= min_chunk; c -= 64) {
+      int64_t wgs = 0;
+      for (const auto& hs : *r.sessions)
+        if (!hs.agents.empty()) wgs += ((int64_t)hs.span + c - 1) / c;
+      wgs *= r.heads * row_blocks;
+      if (wgs == 0) break;
+      const int64_t cost = ((wgs + slots - 1) / slots) * (std::min<int64_t>(c, max_span + 63) / 64 + 2);
+      if (best < 0 || cost < best) { best = cost; chunk = c; }
+    }
+    return chunk;
+  };
   int32_t chosen = 0;              // the chunk that the estimates chose
   if (!p.own_rows && !r.seg && !long_pass) {
     int64_t with_agents = 0;
     for (const auto& hs : *r.sessions) with_agents += !hs.agents.empty();
     double packed = -1, rows = -1;
     int64_t packed_chunk = 64, rows_chunk = 64;
-    for_chunks(max_span, std::max<int64_t>(16384, max_chunk), [&](int64_t c) {
+    // From three steps per compute unit on the packed form has nothing to gain from other chunks (1.01 times as fast on 62 such
+    // rounds, 101 -> 122 us on one), the wavefront per agent 1.3 times.
+    const int64_t only = steps >= 3 * cus ? fewest_rounds() : 0;
+    auto consider = [&](int64_t c, bool in_packed, bool in_rows) {
       // chunks of c tokens over all sessions with agents, and the workgroups of the rows kernel in them (both per KV head)
       int64_t chunks = 0, row_wgs = 0, span = -1, n = 0;
       for (const auto& hs : *r.sessions) {
@@ -479,15 +505,17 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
                    (double)chunks / (double)std::max<int64_t>(with_agents, 1), (double)p.rows / 1000};
       // (a packed launch that fits a grid with its longest chunks is not cut so fine that it does not)
       const bool fits = times(times(times(r.heads, row_blocks), n_sessions), (max_span + c - 1) / c) < kMaxBlocks - times(lists, 4);
-      if (c <= max_chunk && (packed < 0 || fits)) {
+      if (in_packed && (packed < 0 || fits)) {
         const double us = packed_us(r, l, max_span, p.piece_tokens);
         if (packed < 0 || us < packed) { packed = us; packed_chunk = c; }
         if (!fits) rows = 0;         // refused, as ever: not to be taken by the other form
       }
       l.wgs = (double)(row_wgs * r.heads) / (double)cus;
-      const double us = rows_us(r, l);
-      if (rows < 0 || us < rows) { rows = us; rows_chunk = c; }
-    });
+      const double us = in_rows ? rows_us(r, l) : 0;
+      if (in_rows && (rows < 0 || us < rows)) { rows = us; rows_chunk = c; }
+    };
+    if (only) consider(only, true, false);
+    for_chunks(max_span, 16384, [&](int64_t c) { consider(c, !only && c <= max_chunk, true); });
     p.own_rows = rows > 0 && rows < packed;
     chosen = (int32_t)(p.own_rows ? rows_chunk : packed_chunk);
   }
@@ -526,28 +554,7 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     place_parts(p, 0);
     return true;
   }
-  // Tokens per workgroup of the master pass.  A workgroup walks its chunk in steps of 64 tokens; two
-  // workgroups fit a compute unit at a time, so the pass takes about ceil(workgroups / slots) rounds of
-  // (steps per chunk + a fixed start-up cost of about two steps).  Of the chunk sizes that the 128-bit page
-  // mask per query row can cover, the one with the lowest such cost wins; ties go to the larger chunk
-  // (fewer partial results to merge).
-  const int64_t slots = 2 * cus;
-  // Chunks shorter than 512 tokens are not tried here (unless the span is): a workgroup's start-up (page masks,
-  // query rotation, first rows) costs about as much as three steps, and every chunk adds a partial result per row
-  // for the merge.  Where that pays, the estimates have chosen.
-  const int32_t min_chunk = (int32_t)std::min<int64_t>(512, (max_span + 63) / 64 * 64);
-  int32_t chunk = std::max(min_chunk, 64);
-  int64_t best = -1;
-  if (chosen) chunk = chosen;
-  for (int32_t c = max_chunk; !chosen && c >= std::max(min_chunk, 64); c -= 64) {
-    int64_t wgs = 0;
-    for (const auto& hs : *r.sessions)
-      if (!hs.agents.empty()) wgs += ((int64_t)hs.span + c - 1) / c;
-    wgs *= r.heads * row_blocks;
-    if (wgs == 0) break;
-    const int64_t cost = ((wgs + slots - 1) / slots) * (std::min<int64_t>(c, max_span + 63) / 64 + 2);
-    if (best < 0 || cost < best) { best = cost; chunk = c; }
-  }
+  const int32_t chunk = chosen ? chosen : fewest_rounds();
   p.chunk_tokens = chunk;
   p.n_chunks = (int32_t)((max_span + chunk - 1) / chunk);
   // Pipelined steps in the master pass (identity layouts; tdk_attend.hip, attend_packed_body).  A workgroup starts up later there
