@@ -1091,14 +1091,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // the K and V tiles are double-buffered with one barrier per step, and the rows of the tiles after that travel
 // from memory straight to LDS meanwhile (through registers and LDS writes 204 to 217 us against 198 at the size below).
 // What bounds it (25 agents x 64 query tokens x 40 heads over 5000 tokens, 2 wavefronts per SIMD, counters): matrix
-// cores, vector units and LDS are each busy a little under half of the time, about 1 us per wavefront and step; no
+// cores, vector units and LDS are each busy about half of the time, 1.8 us per step of both wavefronts of a SIMD; no
 // single pipe is full, the rest is waiting between dependent stages (score products, maxima, exponentials, second
 // products) and at the barrier.  64 rows per wavefront (half the LDS bytes per product, one wavefront per SIMD) measured
 // the same.
 // Measured against rows of all agents in one block plus separate listed-pages and merge launches: 64 query tokens
-// per agent 462 -> 206 us, 16 tokens 140 -> 93 us, 8 tokens 94 -> 70 us.  Per-agent orders of blocks of 200 tokens, steps
+// per agent 462 -> 206 us (193 now), 16 tokens 140 -> 93 us, 8 tokens 94 -> 70 us.  Per-agent orders of blocks of 200 tokens, steps
 // that ended at every border, a chain of reads to find a chunk's first segment and page, tiles through registers -> now:
-// 25 agents x 5000 tokens, 20 rows 70 -> 54 us; 129 x 4307, 35 rows 502 -> 375; blocks of 64, 151 x 937, 80 rows 105 -> 81.
+// 25 agents x 5000 tokens, 20 rows 70 -> 54 us (48 now); 129 x 4307, 35 rows 502 -> 375; blocks of 64, 151 x 937, 80 rows 105 -> 81.
 // ---------------------------------------------------------------------------------------------
 constexpr int kRowsMaskWords = 32;                        // 32-bit words of a wavefront's page mask
 constexpr int kRowsMaxPages = 32 * kRowsMaskWords;        // pages per chunk
