@@ -80,3 +80,12 @@ def test_sessions_of_unequal_size_and_heads_that_do_not_divide(tdo):
     for H, T in ((3, 16), (5, 32), (7, 16)):
         spec = wl.RoundSpec("lst4", 96, 2, H, 128, T, 1.0e6, 1, 2, 1, 100, 3, 150, 0.3)
         run_pipeline(tdo, wl.make_round(spec, spans=[100, 1, 0, 333], agents=[2, 3, 2, 4]))
+
+
+@pytest.mark.parametrize("H,T", [(8, 16), (8, 32), (7, 16), (6, 32), (5, 32), (4, 32), (3, 16)])
+@pytest.mark.parametrize("agents,listed", [(1, 1), (3, 1), (7, 3), (40, 3)])
+def test_few_slots_are_shared_out(tdo, H, T, agents, listed):
+    """One to 120 listed pages, fewer than there are workgroups: a slot of 2 to 16 batches of accesses is copied by 1 to 8 of them,
+    when it is stored and when it is restored."""
+    spec = wl.RoundSpec("lst5", 97, 1, H, 128, T, 1.0e6, 1, agents, 1, 4 * T + 3, 0, 40, 0.0)
+    run_pipeline(tdo, wl.make_round(spec, perturbed_per_agent=listed))
