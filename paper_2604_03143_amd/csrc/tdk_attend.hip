@@ -1122,7 +1122,8 @@ __device__ __forceinline__ int v_place(int r, int c) { return r * (kHeadDim * 2)
 // all lanes.  The instruction writes no register; the compiler does not see that it is in flight: landed() waits for it,
 // before the barrier that hands the tile over.  (The builtin makes every later LDS read of the kernel wait for the
 // tile, also reads of the other buffer.)  The wait states: M0 before its use, and base, which a vector instruction may
-// have written just before.  (M0 has no other use in these kernels.)
+// have written just before.  (M0 has no other use in these kernels, which a test of the assembly pins: the
+// compiler reserves M0 and does not take it in the list of registers that a statement overwrites.)
 __device__ __forceinline__ void load_to_lds(const void* base, uint32_t off, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(off), "s"(base) : "memory");
 }
