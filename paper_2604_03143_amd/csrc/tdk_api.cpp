@@ -653,7 +653,7 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     tdk_status st = check_diff(r, in, false);
     if (st != TDK_OK) return st;
     AttendPlan p;
-    if (!attend_plan(attend_shape(r), a->n_q, a->n_q_heads, p))
+    if (!attend_plan(attend_shape(r), a->n_q, a->n_q_heads, p, a->workspace_bytes))
       return fail(TDK_ERR_INVALID_ARG, "n_q must be >= 1 and n_q_heads a positive multiple of the KV heads");
     if (!std::isfinite(a->scale)) return fail(TDK_ERR_INVALID_ARG, "scale must be finite");
     if (p.rows == 0) return TDK_OK;

@@ -415,23 +415,30 @@ void for_chunks(int64_t max_span, int64_t most, F f) {
   }
 }
 
+// bytes of the workspace with the partial results of rows x n_parts
+size_t with_parts(size_t off, int64_t rows, int64_t n_parts) {
+  const size_t n = (size_t)rows * n_parts;
+  return std::max<size_t>(align_up(off + n * kHeadDim * sizeof(float), 256) + 2 * align_up(n * sizeof(float), 256), 256);
+}
+
 // the partial results of p.rows x p.n_parts, from byte `off` of the workspace on
 void place_parts(AttendPlan& p, size_t off) {
-  auto place = [&](size_t bytes) { const size_t o = off; off = align_up(off + bytes, 256); return o; };
-  p.o_part_o = place((size_t)p.rows * p.n_parts * kHeadDim * sizeof(float));
-  p.o_part_m = place((size_t)p.rows * p.n_parts * sizeof(float));
-  p.o_part_l = place((size_t)p.rows * p.n_parts * sizeof(float));
-  p.bytes = std::max<size_t>(off, 256);
+  const size_t n = (size_t)p.rows * p.n_parts;
+  p.o_part_o = off;
+  p.o_part_m = align_up(off + n * kHeadDim * sizeof(float), 256);
+  p.o_part_l = p.o_part_m + align_up(n * sizeof(float), 256);
+  p.bytes = with_parts(off, p.rows, p.n_parts);
 }
 
 }  // namespace
 
-bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p) {
+bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p, size_t workspace) {
   if (n_q < 1 || n_q_heads < 1 || n_q_heads % r.heads) return false;
   const int32_t G = n_q_heads / r.heads;
-  int64_t max_span = 0, max_agents = 0;
+  int64_t max_span = 0, max_agents = 0, max_pages = 0;
   for (const auto& hs : *r.sessions) {
     if (hs.agents.empty()) continue;
+    max_pages = std::max<int64_t>(max_pages, hs.pages);
     max_span = std::max<int64_t>(max_span, hs.span);
     max_agents = std::max<int64_t>(max_agents, (int64_t)hs.agents.size());
   }
@@ -453,7 +460,9 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
   const int32_t max_chunk = std::min<int32_t>(128 * r.page_tokens, 4096);
   p.own_rows = agent_rows > 32 || r.total_master_rows == 0 || lists >= ((int64_t)1 << 27) ||
                (r.seg && attend_rows_for_segments(r, agent_rows));
+  // the packed form's listed-pages pass: one wavefront takes a piece of an agent's list and every piece has its own partial result
   p.piece_tokens = attend_piece_tokens(lists, r.n_cus);
+  p.n_pieces = (int32_t)std::max<int64_t>(1, (max_pages * r.page_tokens + p.piece_tokens - 1) / p.piece_tokens);
   // enough steps for the pipelined form? (see below)
   int64_t steps = 0;
   for (const auto& hs : *r.sessions)
@@ -488,6 +497,7 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     int64_t with_agents = 0;
     for (const auto& hs : *r.sessions) with_agents += !hs.agents.empty();
     double packed = -1, rows = -1;
+    bool longest = true, refused = false;
     int64_t packed_chunk = 64, rows_chunk = 64;
     // From three steps per compute unit on the packed form has nothing to gain from other chunks (1.01 times as fast on 62 such
     // rounds, 101 -> 122 us on one), the wavefront per agent 1.3 times.
@@ -503,12 +513,18 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
       }
       AttendLoad l{(double)(chunks * row_blocks * r.heads) / (double)cus, (double)((std::min(c, max_span) + 63) / 64),
                    (double)chunks / (double)std::max<int64_t>(with_agents, 1), (double)p.rows / 1000};
-      // (a packed launch that fits a grid with its longest chunks is not cut so fine that it does not)
-      const bool fits = times(times(times(r.heads, row_blocks), n_sessions), (max_span + c - 1) / c) < kMaxBlocks - times(lists, 4);
+      // (a packed launch that fits a grid with its longest chunks is not cut so fine that it does not; one that does not is
+      // refused, as ever: not to be taken by the other form)
+      const int64_t n_chunks = (max_span + c - 1) / c;
+      const bool fits = times(times(times(r.heads, row_blocks), n_sessions), n_chunks) < kMaxBlocks - times(lists, 4);
+      if (in_packed && longest && !fits) refused = true;
+      longest = longest && !in_packed;
+      // the partial results have to fit the workspace that the call brings
+      in_packed = in_packed && with_parts(0, p.rows, n_chunks + p.n_pieces) <= workspace;
+      in_rows = in_rows && with_parts(0, p.rows, n_chunks) <= workspace;
       if (in_packed && (packed < 0 || fits)) {
         const double us = packed_us(r, l, max_span, p.piece_tokens);
         if (packed < 0 || us < packed) { packed = us; packed_chunk = c; }
-        if (!fits) rows = 0;         // refused, as ever: not to be taken by the other form
       }
       l.wgs = (double)(row_wgs * r.heads) / (double)cus;
       const double us = in_rows ? rows_us(r, l) : 0;
@@ -516,8 +532,10 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     };
     if (only) consider(only, true, false);
     for_chunks(max_span, 16384, [&](int64_t c) { consider(c, !only && c <= max_chunk, true); });
-    p.own_rows = rows > 0 && rows < packed;
-    chosen = (int32_t)(p.own_rows ? rows_chunk : packed_chunk);
+    if (packed < 0) consider(fewest_rounds(), true, false);
+    // (neither fits: the cut that needs least, for the caller to compare)
+    p.own_rows = !refused && rows > 0 && (packed < 0 || rows < packed);
+    if (p.own_rows || packed >= 0) chosen = (int32_t)(p.own_rows ? rows_chunk : packed_chunk);
   }
   if (p.own_rows) {
     // Chunks of the span: workgroups of four wavefronts, two of which share a compute unit (each then takes about
@@ -567,13 +585,6 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
   // 25 x 1500 with 2 heads (1.8) 0.95 .. 1.01, two of 25 x 207 (0.2) 0.92 .. 0.99; 20 rows, half of the pages listed, ten sessions of 6 x
   // 2000 tokens 145 against 176 us.
   p.pipelined = long_pass && chunk >= 512;
-  // the listed-pages pass: one wavefront takes a piece of an agent's list and every piece has its own partial result
-  {
-    int64_t max_pages = 0;
-    for (const auto& hs : *r.sessions)
-      if (!hs.agents.empty()) max_pages = std::max<int64_t>(max_pages, hs.pages);
-    p.n_pieces = (int32_t)std::max<int64_t>(1, (max_pages * r.page_tokens + p.piece_tokens - 1) / p.piece_tokens);
-  }
   p.n_parts = p.n_chunks + p.n_pieces;
   // Most lists are far shorter than a whole session's pages: a few wavefronts per list walk its pieces in turn,
   // instead of one launched wavefront per possible piece (nearly all of which would find nothing).

@@ -81,7 +81,9 @@ struct AttendPlan {
   FusedGrid fused{};               // the shared launch (identity layouts, not own_rows, blocks < kMaxBlocks)
   size_t o_qrot = 0, o_qdiff = 0, o_part_o = 0, o_part_m = 0, o_part_l = 0, bytes = 0;
 };
-bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p);   // false: bad arguments
+// workspace: bytes that the call brings.  Where the estimates choose the cut, they choose among those that fit; a plan that needs more
+// says so in `bytes`.  false: bad arguments
+bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p, size_t workspace = SIZE_MAX);
 size_t attend_workspace_bytes(const AttendShape& r, int32_t n_q, int32_t n_q_heads);     // covers every call of up to n_q query tokens; 0: bad arguments
 
 }  // namespace tdk

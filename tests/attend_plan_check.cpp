@@ -126,6 +126,49 @@ static int check_workspace() {
   return 0;
 }
 
+// A call that brings less than the plan of its own choice takes is cut coarser: down to what chunks of 512 tokens and more take
+// it is served, whatever the estimates prefer.
+static int check_small_workspace() {
+  int cs = 0, cut = 0;
+  for (; cs < 3000; ++cs) {
+    Made m;
+    if (cs % 3 == 0) {
+      m = draw();
+    } else {                     // short spans in the master's order
+      m.shape.heads = 1 << between(0, 3);
+      m.shape.page_tokens = rnd() % 2 ? 16 : 32;
+      for (int i = (int)between(1, 4); i > 0; --i) m.add((int32_t)between(1, 2500), (int32_t)between(1, 40));
+    }
+    const AttendShape& s = m.done();
+    const int32_t heads = s.heads * (int32_t)between(1, 9), n_q = (int32_t)between(1, 6);
+    AttendPlan free_choice, least, p;
+    REQUIRE(attend_plan(s, n_q, heads, free_choice) && attend_plan(s, n_q, heads, least, 0));
+    if (s.n_agents == 0) continue;
+    // exactly what the free choice takes changes nothing
+    REQUIRE(attend_plan(s, n_q, heads, p, free_choice.bytes) && p.own_rows == free_choice.own_rows && p.chunk_tokens == free_choice.chunk_tokens);
+    if (least.bytes >= free_choice.bytes) continue;
+    ++cut;
+    for (size_t bytes : {least.bytes, least.bytes + (free_choice.bytes - least.bytes) / 3, free_choice.bytes - 1}) {
+      REQUIRE(attend_plan(s, n_q, heads, p, bytes));
+      REQUIRE(p.bytes <= bytes && p.n_parts <= free_choice.n_parts);
+      REQUIRE((__int128)p.blocks == blocks_of(s, p, (int64_t)n_q * (heads / s.heads)) && p.blocks < kMaxBlocks);
+      REQUIRE(!p.own_rows || p.chunk_tokens <= 16384);
+      REQUIRE(p.own_rows || p.chunk_tokens <= std::min(128 * s.page_tokens, 4096));
+    }
+  }
+  REQUIRE(cut > 400);
+  // 22 agents x 2 x 493 tokens, one row: chunks of 64 tokens by choice, one chunk and four pieces where that is what fits
+  Made m;
+  m.shape.heads = 8;
+  m.add(493, 22);
+  m.add(493, 22);
+  AttendPlan p;
+  const size_t one_chunk = 352 * (1 + 4) * 520;
+  REQUIRE(attend_plan(m.done(), 1, 8, p) && p.bytes > one_chunk);
+  REQUIRE(attend_plan(m.done(), 1, 8, p, one_chunk + 512) && p.bytes <= one_chunk + 512);
+  return 0;
+}
+
 // Own block orders with few rows per agent: a wavefront per agent on both sides of the rule's lines.
 static int check_segment_rule() {
   int cs = 0;
@@ -176,7 +219,7 @@ static int check_pipelined_rule() {
 }
 
 int main() {
-  if (check_grids() || check_workspace() || check_segment_rule() || check_pipelined_rule()) return 1;
+  if (check_grids() || check_workspace() || check_small_workspace() || check_segment_rule() || check_pipelined_rule()) return 1;
   std::printf("attention planner: clean\n");
   return 0;
 }

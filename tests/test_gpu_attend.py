@@ -14,7 +14,7 @@ from helpers import OracleRun
 pytestmark = pytest.mark.gpu
 
 
-def _case(tdo, spec, n_q, Hq, style=0, grow=None, seed=3, scale=None, perturb=True):
+def _case(tdo, spec, n_q, Hq, style=0, grow=None, seed=3, scale=None, perturb=True, ws_bytes=None):
     import torch
     from paper_2604_03143_amd import tdk
     import gpu_helpers as gh
@@ -46,6 +46,9 @@ def _case(tdo, spec, n_q, Hq, style=0, grow=None, seed=3, scale=None, perturb=Tr
         io = tdk.layer_io(mk, mv, None, None, 0)
         nbytes = tdk.tdk_attend_workspace_bytes(r, n_q, Hq)
         assert nbytes > 0
+        if ws_bytes is not None:
+            assert ws_bytes < nbytes
+            nbytes = ws_bytes
         ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
         ws.fill_(0xFF)                                   # NaN patterns: stale workspace must not leak into results
         out = torch.full((rnd.n_agents, n_q, Hq, spec.head_dim), float("nan"), dtype=torch.float32, device="cuda")
@@ -54,6 +57,7 @@ def _case(tdo, spec, n_q, Hq, style=0, grow=None, seed=3, scale=None, perturb=Tr
         tdk.tdk_attend_shared(r, 0, io, dd, a, torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         got_o, got_l = out.cpu().numpy().astype(np.float64), lse.cpu().numpy().astype(np.float64)
+        assert (ws[nbytes:] == 0xFF).all()
     finally:
         r.destroy()
     return ab.assert_within(got_o, got_l, want_o, want_l, tol_o, tol_l, what=(spec.name, n_q, Hq, scale))
@@ -206,6 +210,15 @@ def test_own_block_order_and_mirrors_stored_under_another_order(tdo, T, style, b
                          want_o, want_l, tol_o, tol_l, what=(T, style, block_tokens, n_q, sharp))
     finally:
         r.destroy()
+
+
+@pytest.mark.parametrize("agents,span,n_q,Hq", [(6, 493, 1, 8), (3, 1500, 2, 24)])
+def test_workspace_for_longer_chunks_than_the_planner_likes(tdo, agents, span, n_q, Hq):
+    """A workspace that holds the results of 512-token chunks and of the pieces of 128 listed tokens, and no more: small rounds
+    would be cut into chunks of 64 tokens, which need several times that.  The call is served and stays inside."""
+    spec = wl.RoundSpec("att11", 71, 1, 8, 128, 16, 1.0e6, 2, agents, 1, span, 5, 900, 0.2)
+    rows, parts = 2 * agents * n_q * Hq, -(-span // 512) + -(-span // 128)
+    _case(tdo, spec, n_q, Hq, ws_bytes=rows * parts * 520 + 512)
 
 
 def test_argument_errors(tdo):
