@@ -681,6 +681,7 @@ tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io
     at.group = a->n_q_heads / r->model.num_kv_heads;
     at.chunk_tokens = p.chunk_tokens;
     at.n_chunks = p.n_chunks;
+    at.all_chunks = p.all_chunks;
     at.n_parts = p.n_parts;
     at.n_pieces = p.n_pieces;
     at.piece_tokens = p.piece_tokens;

@@ -92,6 +92,7 @@ struct AttendDev {
   int32_t n_q, n_q_heads, group;     // group = query heads per KV head
   int32_t chunk_tokens;              // master tokens per workgroup of the master pass (multiple of 32 and of T)
   int32_t n_chunks;                  // chunks of the longest span
+  int32_t all_chunks;                // chunks that every session with agents and a span has
   int32_t n_parts;                   // n_chunks + n_pieces: the chunks' partial results, then those of the listed pages
   int32_t n_pieces;                  // partial results of the listed-pages pass per query row
   int32_t piece_tokens;              // listed tokens per piece

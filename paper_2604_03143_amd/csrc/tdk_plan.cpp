@@ -430,6 +430,13 @@ void place_parts(AttendPlan& p, size_t off) {
   p.bytes = with_parts(off, p.rows, p.n_parts);
 }
 
+int32_t chunks_of_all(const AttendShape& r, const AttendPlan& p) {
+  int64_t least = p.n_chunks;
+  for (const auto& hs : *r.sessions)
+    if (!hs.agents.empty() && hs.span > 0) least = std::min(least, ((int64_t)hs.span + p.chunk_tokens - 1) / p.chunk_tokens);
+  return (int32_t)least;
+}
+
 }  // namespace
 
 bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPlan& p, size_t workspace) {
@@ -561,6 +568,7 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
       if (best < 0 || cost < best) { best = cost; p.chunk_tokens = (int32_t)c; }
     }
     p.n_chunks = (int32_t)((max_span + p.chunk_tokens - 1) / p.chunk_tokens);
+    p.all_chunks = chunks_of_all(r, p);
     p.n_pieces = 0;
     p.piece_tokens = 512;          // (no listed-pages pass: the merge finds no pieces)
     p.n_parts = std::max(p.n_chunks, 1);
@@ -575,6 +583,7 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
   const int32_t chunk = chosen ? chosen : fewest_rounds();
   p.chunk_tokens = chunk;
   p.n_chunks = (int32_t)((max_span + chunk - 1) / chunk);
+  p.all_chunks = chunks_of_all(r, p);
   // Pipelined steps in the master pass (identity layouts; tdk_attend.hip, attend_packed_body).  A workgroup starts up later there
   // (two more tiles and the first scores before the loop), so it needs workgroups of at least 8 steps and at least 2 3/4 steps
   // per compute unit over the whole pass; with three row blocks or more the plain form's calls of coming tiles into L2

@@ -71,6 +71,7 @@ constexpr int64_t kMaxBlocks = (int64_t)1 << 31;     // workgroups of one launch
 // Shape of the attention pass for a call: tokens per workgroup of the master pass, parts per query row, the launch, and
 // the layout of the caller's workspace.
 struct AttendPlan {
+  int32_t all_chunks = 0;          // chunks that every session with agents and a span has
   int32_t chunk_tokens = 0, n_chunks = 0, n_parts = 0, max_rows = 0, n_pieces = 1, piece_tokens = 0, piece_grid = 1;
   bool    own_rows = false;        // one agent per wavefront (tdk_attend_rows_kernel)
   bool    pipelined = false;       // the shared launch's master pass with pipelined steps

@@ -72,6 +72,9 @@ static int check_grids() {
     if (s.n_agents == 0) continue;
     REQUIRE((__int128)p.blocks == blocks_of(s, p, (int64_t)n_q * group) && p.blocks < kMaxBlocks);
     REQUIRE(!p.own_rows || p.launch_sessions == (int32_t)s.sessions->size());
+    // what the merge reads before it knows a row's session exists in every session (but for empty spans, whose rows have no part)
+    for (const auto& hs : m.sessions) REQUIRE(hs.agents.empty() || hs.span == 0 || (int64_t)(p.all_chunks - 1) * p.chunk_tokens < hs.span);
+    REQUIRE(p.all_chunks <= p.n_chunks);
     if (!p.own_rows && !s.seg) {
       REQUIRE((int64_t)p.fused.n_master + (int64_t)p.fused.n_diff0 * p.piece_grid == p.blocks);
       REQUIRE(p.fused.n_master == (int64_t)s.heads * p.fused.row_blocks * (int64_t)s.sessions->size() * p.n_chunks);
