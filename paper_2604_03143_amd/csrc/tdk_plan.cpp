@@ -363,18 +363,29 @@ bool attend_rows_for_segments(const AttendShape& r, int64_t agent_rows) {
 // too small for pipelined steps.  Both estimates are robust least squares fits (on the logarithm) to 9 000 timed launches of 318
 // rounds: 1 to 20 sessions, 2 to 260 agents, 64 to 26 000 tokens, 1 to 8 KV heads, 1 to 32 rows, 2 to 20 % of the pages listed, diffs
 // moved or not, both page sizes, both forms, up to 14 chunk sizes; three sets of inputs in turn, so that the caches hold
-// what they hold in a program.  They are within 11 and 9 % of the measured times.  What they choose takes 1.04 times the best
-// choice on average and is 1.27 times as fast as the rule before (packed rows, chunks of 512 tokens or more): 12 of the 318
-// rounds are more than 2 % slower, 1 more than 10 % (4 x 36 agents x 1611 tokens, 16 rows, a fifth of the pages listed 90 -> 105 us),
-// 4 x 23 agents x 152 tokens with 32 rows take 18 us instead of 41.  (With one set of inputs over and over, 2 to 5 % listed pages and short
-// pieces look better than they are: fitted to that, ten sessions of 25 x 5000 tokens lost 6 %.)
+// what they hold in a program.  They are within 11 and 9 % of the measured times.  (With one set of inputs over and over, 2 to 5 %
+// listed pages and short pieces look better than they are: fitted to that, ten sessions of 25 x 5000 tokens lost 6 %.)
+// What they miss is a step: up to one workgroup per compute unit the packed launch runs alone there, beyond it some share one (100
+// agents x 2500 tokens, 1 row: 56 and 200 workgroups 31 us, 64 and 200 36; 16 x 5000: 128 and 128 22.8, 160 and 128 28.7).  So
+// launches beyond it count a tenth more, and the cut that needs no estimate (packed rows, chunks of 512 tokens or more) stays unless
+// another promises 3 %.
+// Measured over 820 rounds that the fit has not seen, 2 to 20 % listed, every form and cut: 1.28 times as fast as that cut, 1.033
+// times the best choice.  18 of them are more than 5 % slower than it, 3 more than 10 % (25, 5 and one of 1.40 without the two rules
+// above): 20 sessions x 2 agents x 420 tokens, 2 rows 22 -> 28 us, 123 agents x 3289 tokens, 16 rows, a fifth listed 120 -> 140, 22
+// agents x 13329 tokens, 2 heads, 5 rows 29 -> 32.  4 x 23 agents x 152 tokens with 32 rows take 18 us instead of 41.  No page, half
+// or all of them listed (the assumed share is far off there), 120 rounds: 1.25 times as fast, 3 more than 10 % slower (2 x 43 agents x
+// 557 tokens, 5 rows, half listed 37 -> 49 us; of another 90 rounds 37 agents x 1080 tokens, 8 rows, all listed 55 -> 79).
 struct AttendLoad {
   double wgs;        // workgroups of the pass over the master, per compute unit
   double steps;      // 64-token steps of a workgroup
   double parts;      // partial results per row, on average
   double rows;       // query rows, in thousands
+  double listed;     // workgroups of the packed form that walk listed pages, per compute unit
 };
 constexpr double kListedShare = 0.08;       // share of the pages taken to be listed (the lists are on the device)
+
+// pieces of a list, with that share of the pages listed
+double pieces_of(int64_t max_span, int piece) { return std::max(1.0, std::ceil(kListedShare * (double)max_span / piece)); }
 
 // microseconds at 6 TB/s for the payload of the listed pages
 double listed_us(const AttendShape& r) { return kListedShare * (double)r.total_tokens * r.heads * (4 * kHeadDim) / 6e6; }
@@ -388,10 +399,11 @@ double rounds_of(double wgs, double two) {
 // Packed rows and listed pages in one launch, and the merge.  Both kinds of workgroup run at the same time.  At most four
 // wavefronts share a list.
 double packed_us(const AttendShape& r, AttendLoad l, int64_t max_span, int piece) {
-  const double tokens = kListedShare * (double)max_span, pieces = std::max(1.0, std::ceil(tokens / piece));
+  const double tokens = kListedShare * (double)max_span, pieces = pieces_of(max_span, piece);
   const double tiles = std::ceil(pieces / std::min(4.0, std::ceil((double)max_span / piece))) * std::min((double)piece, std::max(32.0, tokens)) / 32;
-  const double walk = (0.805 + 1.505 * l.steps) * (0.572 * std::max(1.0, 1.83 * l.wgs) + 0.428 * rounds_of(l.wgs, 0.98));
-  const double list = 1.37 * tiles + 0.865 * listed_us(r);
+  double walk = (0.805 + 1.505 * l.steps) * (0.572 * std::max(1.0, 1.83 * l.wgs) + 0.428 * rounds_of(l.wgs, 0.98));
+  double list = 1.37 * tiles + 0.865 * listed_us(r);
+  if (l.wgs + l.listed > 1) { walk *= 1.1; list *= 1.1; }
   l.parts += pieces;
   return 8.35 + std::sqrt(walk * walk + list * list) + 0.099 * l.parts + 0.39 * l.rows * l.parts;
 }
@@ -504,12 +516,15 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     int64_t with_agents = 0;
     for (const auto& hs : *r.sessions) with_agents += !hs.agents.empty();
     double packed = -1, rows = -1;
-    bool longest = true, refused = false;
+    bool first = true, refused = false;
     int64_t packed_chunk = 64, rows_chunk = 64;
     // From three steps per compute unit on the packed form has nothing to gain from other chunks (1.01 times as fast on 62 such
     // rounds, 101 -> 122 us on one), the wavefront per agent 1.3 times.
-    const int64_t only = steps >= 3 * cus ? fewest_rounds() : 0;
-    auto consider = [&](int64_t c, bool in_packed, bool in_rows) {
+    const bool only = steps >= 3 * cus;
+    // workgroups that walk lists: a piece of four KV heads each, at most four per list
+    const double walk_lists = (double)(r.n_agents * (int64_t)((r.heads + kWaves - 1) / kWaves)) *
+                              std::min({4.0, (double)p.n_pieces, pieces_of(max_span, p.piece_tokens)}) / (double)cus;
+    auto consider = [&](int64_t c, bool in_packed, bool in_rows, double bonus = 1) {
       // chunks of c tokens over all sessions with agents, and the workgroups of the rows kernel in them (both per KV head)
       int64_t chunks = 0, row_wgs = 0, span = -1, n = 0;
       for (const auto& hs : *r.sessions) {
@@ -519,27 +534,26 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
         row_wgs += n * (((int64_t)hs.agents.size() + kWaves - 1) / kWaves);
       }
       AttendLoad l{(double)(chunks * row_blocks * r.heads) / (double)cus, (double)((std::min(c, max_span) + 63) / 64),
-                   (double)chunks / (double)std::max<int64_t>(with_agents, 1), (double)p.rows / 1000};
-      // (a packed launch that fits a grid with its longest chunks is not cut so fine that it does not; one that does not is
-      // refused, as ever: not to be taken by the other form)
+                   (double)chunks / (double)std::max<int64_t>(with_agents, 1), (double)p.rows / 1000, walk_lists};
+      // (a packed launch that fits a grid with the first cut tried is not cut so fine that it does not; one that does not is refused,
+      // as ever: not to be taken by the other form)
       const int64_t n_chunks = (max_span + c - 1) / c;
       const bool fits = times(times(times(r.heads, row_blocks), n_sessions), n_chunks) < kMaxBlocks - times(lists, 4);
-      if (in_packed && longest && !fits) refused = true;
-      longest = longest && !in_packed;
+      if (in_packed && first && !fits) refused = true;
+      first = first && !in_packed;
       // the partial results have to fit the workspace that the call brings
       in_packed = in_packed && with_parts(0, p.rows, n_chunks + p.n_pieces) <= workspace;
       in_rows = in_rows && with_parts(0, p.rows, n_chunks) <= workspace;
       if (in_packed && (packed < 0 || fits)) {
-        const double us = packed_us(r, l, max_span, p.piece_tokens);
+        const double us = bonus * packed_us(r, l, max_span, p.piece_tokens);
         if (packed < 0 || us < packed) { packed = us; packed_chunk = c; }
       }
       l.wgs = (double)(row_wgs * r.heads) / (double)cus;
       const double us = in_rows ? rows_us(r, l) : 0;
       if (in_rows && (rows < 0 || us < rows)) { rows = us; rows_chunk = c; }
     };
-    if (only) consider(only, true, false);
+    consider(fewest_rounds(), true, false, 0.97);
     for_chunks(max_span, 16384, [&](int64_t c) { consider(c, !only && c <= max_chunk, true); });
-    if (packed < 0) consider(fewest_rounds(), true, false);
     // (neither fits: the cut that needs least, for the caller to compare)
     p.own_rows = !refused && rows > 0 && (packed < 0 || rows < packed);
     if (p.own_rows || packed >= 0) chosen = (int32_t)(p.own_rows ? rows_chunk : packed_chunk);

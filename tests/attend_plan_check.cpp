@@ -221,8 +221,27 @@ static int check_pipelined_rule() {
   return 0;
 }
 
+// The master's order with few rows and a pass too short for pipelined steps: what the estimates choose.
+static int check_estimates() {
+  int cs = 0;
+  auto plan = [](int sessions, int agents, int span, int heads, int group) {
+    Made m;
+    m.shape.heads = heads;
+    for (int i = 0; i < sessions; ++i) m.add(span, agents);
+    AttendPlan p;
+    attend_plan(m.done(), 1, group * heads, p);
+    return p;
+  };
+  // the packed launch stays within one workgroup per compute unit where that is near: 200 and 128 of them walk lists
+  AttendPlan p = plan(1, 100, 2500, 8, 1);
+  REQUIRE(!p.own_rows && p.fused.n_master <= 56);
+  p = plan(1, 16, 5000, 8, 1);
+  REQUIRE(!p.own_rows && p.fused.n_master <= 128 && p.fused.n_master > 96);
+  return 0;
+}
+
 int main() {
-  if (check_grids() || check_workspace() || check_small_workspace() || check_segment_rule() || check_pipelined_rule()) return 1;
+  if (check_grids() || check_workspace() || check_small_workspace() || check_segment_rule() || check_pipelined_rule() || check_estimates()) return 1;
   std::printf("attention planner: clean\n");
   return 0;
 }
