@@ -14,6 +14,7 @@
 //   - a row of 1, 2 or 4 KV heads fills only part of a wavefront that way, so several rows of the page share each
 //     instruction then (PACK: as many as fill it, see Lane).
 #include "tdk_internal.h"
+#include "tdk_plan.h"
 
 #include <algorithm>
 #include <map>
@@ -716,6 +717,9 @@ __device__ __host__ __forceinline__ int slot_batches(const RoundDev& rd, int pla
   return (planes == 3 ? 2 : 1) * rd.page_tokens * rd.heads * 16 / (kBlock * kCopyBatch);
 }
 
+// does a restore share its slots out? (scatter_slots)
+__device__ __host__ __forceinline__ bool slots_shared(const RoundDev& rd) { return !rd.diff_moved; }
+
 // planes: bit 0 = K, bit 1 = V; a slot holds the selected planes back to back
 __device__ __forceinline__ void gather_slot(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const int planes, int64_t slot,
                                             const SlotShared& sh, int share = 0, int lg_shares = 0) {
@@ -887,7 +891,7 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
   // collect, restore and store 25.5 -> 25.1 us, restore of 4 x 8 agents x 2306 tokens 66.0 -> 64.8.  (With divisions in place of
   // the shifts small calls on one plane lost 1 to 3 %.)
   int lg_shares = 0;
-  if (!rd.diff_moved)
+  if (slots_shared(rd))
     while ((2 << lg_shares) <= slot_batches(rd, planes) && total << (lg_shares + 1) <= stride) ++lg_shares;
   for (int64_t unit = first; unit < total << lg_shares; unit += stride) {
     const int64_t slot = unit >> lg_shares;
@@ -1553,15 +1557,10 @@ hipError_t launch_gather(const RoundDev& rd, const LayerDev& io, const DiffDev& 
 
 bool lists_in_gather(const RoundDev& rd) { return rd.agent_pages <= kListPages; }
 
-// workgroups for so many slots: more than one per slot while they leave places on the chip
-static int share_grid(const RoundDev& rd, int planes, int slots) {
-  return (int)std::max<int64_t>(slots, std::min<int64_t>((int64_t)slots * std::max(1, slot_batches(rd, planes)), 4 * std::max(rd.n_cus, 1)));
-}
-
 hipError_t launch_list_gather(const RoundDev& rd, const LayerDev& io, const DiffDev& d, int planes, int grid_size, hipStream_t st) {
   // (capacities are mostly generous: workgroups without a slot repeat the count for nothing, so no more than four per
   // compute unit are launched)
-  const int blocks = std::min(share_grid(rd, planes, grid_size), 4 * std::max(rd.n_cus, 1));
+  const int blocks = std::min(plan_copy_workgroups(grid_size, slot_batches(rd, planes), true, rd.n_cus), 4 * std::max(rd.n_cus, 1));
   hipLaunchKernelGGL(tdk_list_gather_kernel, dim3((unsigned)std::max(1, blocks)), dim3(kBlock), 0, st, rd, io, d, planes);
   return hipGetLastError();
 }
@@ -1573,7 +1572,7 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
   *scattered = false;
   if (rd.n_work == 0) return hipSuccess;
   if (rd.n_agents == 0 || d.capacity == 0) scatter_blocks = 0;
-  scatter_blocks = share_grid(rd, planes, scatter_blocks);
+  scatter_blocks = plan_copy_workgroups(scatter_blocks, slot_batches(rd, planes), slots_shared(rd), rd.n_cus);
   with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 2) != 0, [&](auto nt) {
     with_planes(planes, [&](auto pm) { with_bool(rd.seg != 0, [&](auto sg) {
       constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;

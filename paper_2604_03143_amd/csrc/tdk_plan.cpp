@@ -307,6 +307,11 @@ int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels,
   return best;
 }
 
+int plan_copy_workgroups(int slots, int batches, bool shared, int n_cus) {
+  if (!shared) return slots;
+  return (int)std::max<int64_t>(slots, std::min<int64_t>((int64_t)slots * std::max(1, batches), 4 * std::max(n_cus, 1)));
+}
+
 void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queued, int32_t (&q_begin)[9]) {
   queued.clear();
   queued.reserve(work.size());

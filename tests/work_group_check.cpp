@@ -42,6 +42,10 @@ int main() {
   REQUIRE(plan_auto_group(round_of(10, 18, 77), false, kb(8, 16), 256, 1) == 5);
   REQUIRE(plan_auto_group(round_of(4, 11, 154), false, kb(8, 32), 256, 1) == 3);
   REQUIRE(plan_auto_group(round_of(10, 15, 4), false, kb(8, 32), 256, 1) == 1);   // 600
+  // listed pages' copies: shared out while places are left; one workgroup per slot where the kernel does not share
+  REQUIRE(plan_copy_workgroups(10, 4, true, 256) == 40 && plan_copy_workgroups(350, 4, true, 256) == 1024);
+  REQUIRE(plan_copy_workgroups(350, 4, false, 256) == 350 && plan_copy_workgroups(5000, 4, true, 256) == 5000);
+  REQUIRE(plan_copy_workgroups(7, 0, true, 256) == 7 && plan_copy_workgroups(0, 4, true, 256) == 0);
   std::printf("work groups: clean\n");
   return 0;
 }
