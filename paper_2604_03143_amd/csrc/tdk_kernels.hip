@@ -1560,7 +1560,7 @@ bool lists_in_gather(const RoundDev& rd) { return rd.agent_pages <= kListPages; 
 hipError_t launch_list_gather(const RoundDev& rd, const LayerDev& io, const DiffDev& d, int planes, int grid_size, hipStream_t st) {
   // (capacities are mostly generous: workgroups without a slot repeat the count for nothing, so no more than four per
   // compute unit are launched)
-  const int blocks = std::min(plan_copy_workgroups(grid_size, slot_batches(rd, planes), true, rd.n_cus), 4 * std::max(rd.n_cus, 1));
+  const int blocks = std::min(plan_copy_workgroups(grid_size, slot_batches(rd, planes), rd.n_cus, 1 << 30), 4 * std::max(rd.n_cus, 1));
   hipLaunchKernelGGL(tdk_list_gather_kernel, dim3((unsigned)std::max(1, blocks)), dim3(kBlock), 0, st, rd, io, d, planes);
   return hipGetLastError();
 }
@@ -1572,7 +1572,13 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
   *scattered = false;
   if (rd.n_work == 0) return hipSuccess;
   if (rd.n_agents == 0 || d.capacity == 0) scatter_blocks = 0;
-  scatter_blocks = plan_copy_workgroups(scatter_blocks, slot_batches(rd, planes), slots_shared(rd), rd.n_cus);
+  if (slots_shared(rd)) {
+    // (three workgroups of the kernels for both planes fit a compute unit; the page items are launched with those that stand by for the
+    // last fifth.  Of the kernels for one plane more fit, and no limit showed: 60 agents x 700 tokens, pages of 32, stored and restored
+    // one plane at a time 109.7 us, 111.9 with a limit of four.)
+    const int left = planes == 3 ? 3 * rd.n_cus - rd.n_work - rd.n_work / 5 : -1;
+    scatter_blocks = plan_copy_workgroups(scatter_blocks, slot_batches(rd, planes), rd.n_cus, left);
+  }
   with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 2) != 0, [&](auto nt) {
     with_planes(planes, [&](auto pm) { with_bool(rd.seg != 0, [&](auto sg) {
       constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;

@@ -307,9 +307,14 @@ int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels,
   return best;
 }
 
-int plan_copy_workgroups(int slots, int batches, bool shared, int n_cus) {
-  if (!shared) return slots;
-  return (int)std::max<int64_t>(slots, std::min<int64_t>((int64_t)slots * std::max(1, batches), 4 * std::max(n_cus, 1)));
+int plan_copy_workgroups(int slots, int batches, int n_cus, int left) {
+  // Slots of two batches have little to gain: where one workgroup per slot fits beside the others, the further ones must fit too, or
+  // some wait until the first leave (restores with a fifth listed, 60 agents x 300 tokens, 16 x 1000 and 8 x 1000: 19.7, 18.6 and 12.0
+  // us with one per slot, 21.1, 19.5 and 12.7 beyond the chip).  Where even one per slot does not fit, more are no loss (100 x 200, 23.8
+  // -> 23.3, 25 x 1000 28.3 -> 27.5), nor with four batches (16 x 1000, pages of 32 tokens: 24.3 with one per slot, 23.6 within the
+  // chip, 21.0 beyond it).
+  const int64_t most = batches <= 2 && slots <= left ? left : 4 * (int64_t)std::max(n_cus, 1);
+  return (int)std::max<int64_t>(slots, std::min<int64_t>((int64_t)slots * std::max(1, batches), most));
 }
 
 void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queued, int32_t (&q_begin)[9]) {

@@ -57,9 +57,9 @@ void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queue
 // agents per work item when the caller names none; page_bytes: K and V of one page; planes: written by the call (2, or 1)
 int  plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels = false, int64_t page_bytes = 64 * 1024,
                      int n_cus = 256, int planes = 2);
-// workgroups that copy listed pages, for at most so many slots: more than one per slot (`shared`: the kernel shares them out, down to
-// one of its batches of accesses per thread) while they leave places on the chip
-int  plan_copy_workgroups(int slots, int batches, bool shared, int n_cus);
+// Workgroups that copy listed pages, for at most so many slots: more than one per slot where the kernel shares them out, down to one of
+// its batches of accesses per thread.  left: places on the chip that the launch's other workgroups leave
+int  plan_copy_workgroups(int slots, int batches, int n_cus, int left);
 
 // Attention over mirrors that are never restored: what the planner needs to know of a round.
 struct AttendShape {

@@ -42,10 +42,15 @@ int main() {
   REQUIRE(plan_auto_group(round_of(10, 18, 77), false, kb(8, 16), 256, 1) == 5);
   REQUIRE(plan_auto_group(round_of(4, 11, 154), false, kb(8, 32), 256, 1) == 3);
   REQUIRE(plan_auto_group(round_of(10, 15, 4), false, kb(8, 32), 256, 1) == 1);   // 600
-  // listed pages' copies: shared out while places are left; one workgroup per slot where the kernel does not share
-  REQUIRE(plan_copy_workgroups(10, 4, true, 256) == 40 && plan_copy_workgroups(350, 4, true, 256) == 1024);
-  REQUIRE(plan_copy_workgroups(350, 4, false, 256) == 350 && plan_copy_workgroups(5000, 4, true, 256) == 5000);
-  REQUIRE(plan_copy_workgroups(7, 0, true, 256) == 7 && plan_copy_workgroups(0, 4, true, 256) == 0);
+  // listed pages' copies: shared out while places are left
+  const int all = 1 << 30;
+  REQUIRE(plan_copy_workgroups(10, 4, 256, all) == 40 && plan_copy_workgroups(10, 2, 256, all) == 20 && plan_copy_workgroups(5000, 4, 256, all) == 5000);
+  REQUIRE(plan_copy_workgroups(7, 0, 256, all) == 7 && plan_copy_workgroups(0, 4, 256, all) == 0);
+  // beside page items, two batches: not beyond the chip where one per slot fits, as far as four per unit where it does not
+  REQUIRE(plan_copy_workgroups(308, 2, 256, 312) == 312 && plan_copy_workgroups(138, 2, 256, 164) == 164 && plan_copy_workgroups(28, 2, 256, 164) == 56);
+  REQUIRE(plan_copy_workgroups(383, 2, 256, 238) == 766 && plan_copy_workgroups(800, 2, 256, -700) == 1024 && plan_copy_workgroups(1500, 2, 256, -700) == 1500);
+  // four batches
+  REQUIRE(plan_copy_workgroups(350, 4, 256, 400) == 1024 && plan_copy_workgroups(96, 4, 256, 100) == 384);
   std::printf("work groups: clean\n");
   return 0;
 }
