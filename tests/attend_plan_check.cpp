@@ -224,9 +224,10 @@ static int check_pipelined_rule() {
 // The master's order with few rows and a pass too short for pipelined steps: what the estimates choose.
 static int check_estimates() {
   int cs = 0;
-  auto plan = [](int sessions, int agents, int span, int heads, int group) {
+  auto plan = [](int sessions, int agents, int span, int heads, int group, int page_tokens = 16) {
     Made m;
     m.shape.heads = heads;
+    m.shape.page_tokens = page_tokens;
     for (int i = 0; i < sessions; ++i) m.add(span, agents);
     AttendPlan p;
     attend_plan(m.done(), 1, group * heads, p);
@@ -237,6 +238,24 @@ static int check_estimates() {
   REQUIRE(!p.own_rows && p.fused.n_master <= 56);
   p = plan(1, 16, 5000, 8, 1);
   REQUIRE(!p.own_rows && p.fused.n_master <= 128 && p.fused.n_master > 96);
+  // the rounds of the GPU tests, with both page sizes: form and tokens per chunk (sessions, agents, span, heads, rows per agent and KV
+  // head)
+  auto is = [&](bool own_rows, int sessions, int agents, int span, int heads, int group, int chunk) {
+    for (int page_tokens : {16, 32}) {
+      const AttendPlan q = plan(sessions, agents, span, heads, group, page_tokens);
+      if (q.own_rows != own_rows || q.pipelined || std::min(q.chunk_tokens, (span + 63) / 64 * 64) != chunk) return false;
+    }
+    return true;
+  };
+  auto packed = [&](int sessions, int agents, int span, int heads, int group, int chunk) { return is(false, sessions, agents, span, heads, group, chunk); };
+  auto rows = [&](int sessions, int agents, int span, int heads, int group, int chunk) { return is(true, sessions, agents, span, heads, group, chunk); };
+  REQUIRE(packed(1, 2, 1100, 1, 8, 128) && packed(1, 2, 1100, 1, 18, 128) && packed(10, 2, 900, 2, 16, 192) && packed(1, 25, 900, 1, 32, 192));
+  REQUIRE(packed(6, 2, 577, 8, 16, 256) && packed(6, 2, 577, 8, 18, 256) && packed(4, 18, 1100, 8, 2, 384) && packed(20, 2, 389, 8, 1, 448));
+  REQUIRE(packed(2, 18, 193, 8, 3, 64) && packed(2, 18, 700, 8, 3, 128) && packed(3, 12, 1500, 8, 18, 512) && packed(2, 18, 600, 8, 3, 128));
+  REQUIRE(packed(1, 4, 225, 2, 3, 64) && packed(1, 4, 225, 2, 18, 64));
+  REQUIRE(rows(1, 2, 33, 1, 5, 64) && rows(20, 2, 65, 8, 1, 128) && rows(20, 2, 129, 8, 1, 192) && rows(20, 3, 193, 8, 1, 256));
+  REQUIRE(rows(20, 3, 450, 8, 1, 256) && rows(20, 3, 2000, 1, 1, 192) && rows(10, 3, 1500, 1, 16, 128) && rows(1, 2, 2000, 8, 20, 128));
+  REQUIRE(rows(2, 18, 63, 8, 3, 64) && rows(2, 18, 65, 8, 3, 128));
   return 0;
 }
 

@@ -107,13 +107,14 @@ def test_every_page_listed(tdo, n_q, Hq):
 
 def test_long_span_with_chunks_above_512_tokens(tdo):
     """Four sessions of 10280 tokens on 8 KV heads: on a 256-CU device the planner gives every workgroup of the
-    master pass 704 tokens = 44 pages (more than one 64-bit word of a row's page mask)."""
+    master pass 704 tokens = 44 pages, in pipelined steps.  (Chunks of more than the 64 pages of one word of a row's page mask: the
+    longest round of test_gpu_fullsize.py.)"""
     spec = wl.RoundSpec("att7", 67, 1, 8, 128, 16, 1.0e6, 4, 3, 40, 257, 5, 900, 0.1)
     _case(tdo, spec, 1, 8)
 
 
-# (the last two: 48 and 40 rows per agent and KV head, past the shared launch: the three kernels one after another,
-#  the listed-pages pass walking its pieces once per block of 32 rows)
+# (the last two: 48 and 40 rows per agent and KV head, past the shared launch: two wavefronts per agent, which walk the lists
+#  themselves)
 @pytest.mark.parametrize("H,Hq,T,style,n_q", [(4, 28, 16, 0, 3), (8, 8, 32, 0, 2), (2, 4, 16, 1, 5), (1, 7, 16, 0, 1),
                                                (2, 8, 16, 0, 12), (1, 5, 32, 1, 8)])
 def test_head_counts_page_sizes_styles_and_several_query_tokens(tdo, H, Hq, T, style, n_q):

@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 NAN, INF = np.uint16(0x7FC0), np.uint16(0x7F80)
 
 # (sessions, agents, H, n_q, Hq, span, own block orders, stored elsewhere).  Packed rows with 16- and 32-row tiles for the
-# listed pages, the pipelined pass (36 agents x 8 KV heads), a wavefront per agent in one chunk and in several; the same
-# with own block orders.
+# listed pages, more lists than compute units (36 agents x 8 KV heads), a wavefront per agent in one chunk and in several; the same
+# with own block orders; the pipelined pass (ten sessions), with diffs stored here and elsewhere.
 FORMS = [(1, 3, 2, 1, 6, 150, 0, 0), (1, 3, 2, 6, 6, 150, 0, 0), (2, 18, 8, 1, 24, 600, 0, 0), (1, 3, 2, 17, 4, 60, 0, 0),
-         (1, 2, 2, 17, 4, 2600, 0, 1), (1, 3, 2, 1, 6, 150, 40, 1), (1, 3, 2, 17, 4, 150, 40, 0), (1, 3, 2, 17, 4, 900, 100, 1)]
+         (1, 2, 2, 17, 4, 2600, 0, 1), (1, 3, 2, 1, 6, 150, 40, 1), (1, 3, 2, 17, 4, 150, 40, 0), (1, 3, 2, 17, 4, 900, 100, 1),
+         (10, 4, 8, 1, 24, 577, 0, 0), (10, 4, 8, 1, 24, 640, 0, 1)]
 
 
 @pytest.mark.parametrize("form", FORMS)

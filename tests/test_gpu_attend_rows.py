@@ -1,6 +1,8 @@
-"""The attention kernel that gives every wavefront one agent's query rows (more than 32 rows per agent and KV head, or
-per-agent block orders), at the sizes where its tiles end: rows around multiples of 32 and of a workgroup's 128, spans
-around multiples of a 64-token step and of a chunk, lists around a 32-token tile.  Bounds as in test_gpu_attend.py."""
+"""The attention kernel that gives every wavefront one agent's query rows (more than 32 rows per agent and KV head, per-agent block
+orders, and calls with fewer rows that the planner gives it), at the sizes where its tiles end: rows around multiples of 32 and
+of a workgroup's 128, spans around multiples of a 64-token step and of a chunk, lists around a 32-token tile.  Then the packed form
+in the master's order, plain and with pipelined steps.  Which of them a round with few rows takes, and in which chunks, is pinned by
+attend_plan_check.cpp.  Bounds as in test_gpu_attend.py."""
 import numpy as np
 import pytest
 
@@ -38,8 +40,8 @@ def test_span_cut_into_chunks(tdo, frac, spans):
 @pytest.mark.parametrize("n_q", [1, 6])
 @pytest.mark.parametrize("grow", [None, (0, 16, 7, 250)])
 def test_few_rows_with_stored_positions_moved(tdo, n_q, grow):
-    """Identity layouts with at most 32 rows per agent keep the shared launch, also when the stored diffs have moved
-    (3 and 18 rows per agent and KV head: 16-row and 32-row tiles for the listed pages)."""
+    """Identity layouts in the shared launch, in chunks of one step, also when the stored diffs have moved (3 and 18 rows per agent
+    and KV head: 16-row and 32-row tiles for the listed pages)."""
     for style in (0, 1):
         spec = wl.RoundSpec("rows4", 84, 1, 2, 128, 16, 1.0e6, 1, 4, 3, 75, 3, 300, 0.4)
         _case(tdo, spec, n_q, 6, style=style, grow=grow)
@@ -48,8 +50,8 @@ def test_few_rows_with_stored_positions_moved(tdo, n_q, grow):
 @pytest.mark.parametrize("n_agents,H,n_q,Hq,T,moved,span", [(3, 1, 33, 1, 16, False, 397), (40, 8, 1, 16, 16, False, 5301), (40, 8, 1, 16, 16, True, 5301),
                                                             (40, 8, 1, 16, 16, True, 397), (40, 8, 3, 48, 32, True, 397), (5, 2, 12, 8, 32, True, 397)])
 def test_borders_of_blocks_anywhere(tdo, n_agents, H, n_q, Hq, T, moved, span):
-    """Agents whose segment borders differ from agent to agent (cuts at random tokens, the segments in random order):
-    steps end at the borders of every agent of a workgroup.  40 agents x 8 KV heads with few rows over
+    """Agents whose segment borders differ from agent to agent (cuts at random tokens, the segments in random order): steps run
+    over the borders, and the scores of the tokens behind one are taken again.  40 agents x 8 KV heads with few rows over
     5301 tokens take the packed form, the others one agent per wavefront."""
     import torch
     from paper_2604_03143_amd import tdk
@@ -122,10 +124,38 @@ def test_empty_spans(tdo, n_q, Hq):
 @pytest.mark.parametrize("T,style,span,scale,grow", [(16, 0, 63, None, False), (16, 1, 64, 1.0, True), (32, 0, 65, -0.2, False),
                                                      (16, 0, 193, None, True), (32, 1, 700, None, False)])
 def test_packed_rows_of_many_lists(tdo, T, style, span, scale, grow):
-    """36 agents x 8 KV heads (more lists than compute units) in two sessions, 3 rows per agent and KV head: the packed
-    master pass at spans around a step, too short for pipelined steps, with listed pages and ragged ends."""
+    """36 agents x 8 KV heads (more lists than compute units) in two sessions, 3 rows per agent and KV head, with listed pages and
+    ragged ends: spans of 63 to 65 tokens with a wavefront per agent, 193 and 700 in the packed form in chunks of one and two steps,
+    too short for pipelined steps."""
     spec = wl.RoundSpec("rows7", 97, 1, 8, 128, T, 1.0e6, 2, 18, 1, span, 3, 200, 0.25)
     _case(tdo, spec, 1, 24, style=style, scale=scale, grow=np.arange(36) * 5 if grow else None)
+
+
+# (sessions, agents, KV heads, rows per agent and KV head, span): chunks of 2, 3, 4, 6 and 7 steps, odd and even, the last chunk with a
+# ragged step, with one token in it, or (389 tokens) the only one
+@pytest.mark.parametrize("T,style,shape,scale,moved", [
+    (16, 0, (1, 2, 1, 8, 1100), None, False), (32, 1, (1, 2, 1, 18, 1100), None, True), (16, 1, (10, 2, 2, 16, 900), -0.2, True),
+    (32, 0, (1, 25, 1, 32, 900), None, False), (16, 0, (1, 25, 1, 32, 900), 1.0, True), (32, 0, (6, 2, 8, 16, 577), None, True),
+    (16, 1, (6, 2, 8, 18, 577), None, False), (32, 1, (6, 2, 8, 18, 577), 1.0, True), (16, 0, (4, 18, 8, 2, 1100), None, True),
+    (32, 0, (20, 2, 8, 1, 389), None, False)])
+def test_packed_rows_in_chunks_of_several_steps(tdo, T, style, shape, scale, moved):
+    """The plain packed form's loop over its steps: tiles replaced while others are read, page masks past the first step, ragged
+    ends; 16- and 32-row tiles for the listed pages, stored here or elsewhere."""
+    sessions, agents, H, rows, span = shape
+    spec = wl.RoundSpec("rows11", 101, 1, H, 128, T, 1.0e6, sessions, agents, 1, span, 3, 200, 0.2)
+    _case(tdo, spec, 1, rows * H, style=style, scale=scale, grow=np.arange(sessions * agents) * 5 if moved else None)
+
+
+# (as above) the same with a wavefront per agent: one chunk of 1, 2, 3 and 4 steps, and several chunks
+@pytest.mark.parametrize("T,style,shape,scale,moved", [
+    (16, 0, (1, 2, 1, 5, 33), None, False), (32, 0, (20, 2, 8, 1, 65), None, True), (16, 1, (20, 2, 8, 1, 129), 1.0, False),
+    (32, 1, (20, 3, 8, 1, 193), None, True), (16, 0, (20, 3, 8, 1, 450), None, True), (32, 0, (20, 3, 1, 1, 2000), None, False),
+    (16, 1, (10, 3, 1, 16, 1500), -0.2, True), (32, 1, (1, 2, 8, 20, 2000), None, True)])
+def test_few_rows_with_a_wavefront_per_agent(tdo, T, style, shape, scale, moved):
+    """1 to 20 rows per agent and KV head: tiles that are mostly empty, one chunk written straight to the result, several merged."""
+    sessions, agents, H, rows, span = shape
+    spec = wl.RoundSpec("rows12", 102, 1, H, 128, T, 1.0e6, sessions, agents, 1, span, 3, 200, 0.2)
+    _case(tdo, spec, 1, rows * H, style=style, scale=scale, grow=np.arange(sessions * agents) * 5 if moved else None)
 
 
 def test_packed_rows_in_two_blocks_and_several_chunks(tdo):

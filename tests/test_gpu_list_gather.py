@@ -85,7 +85,8 @@ def test_sessions_of_unequal_size_and_heads_that_do_not_divide(tdo):
 @pytest.mark.parametrize("H,T", [(8, 16), (8, 32), (7, 16), (6, 32), (5, 32), (4, 32), (3, 16)])
 @pytest.mark.parametrize("agents,listed", [(1, 1), (3, 1), (7, 3), (40, 3)])
 def test_few_slots_are_shared_out(tdo, H, T, agents, listed):
-    """One to 120 listed pages, fewer than there are workgroups: a slot of 2 to 16 batches of accesses is copied by 1 to 8 of them,
+    """One to 120 listed pages, fewer than there are workgroups: a slot of two or three whole batches of accesses (8 heads and 16
+    tokens, 4 to 6 and 32) is copied by up to two of them, one of four (8 and 32) by up to four, a smaller one (3 and 7 and 16) by one,
     when it is stored and when it is restored."""
     spec = wl.RoundSpec("lst5", 97, 1, H, 128, T, 1.0e6, 1, agents, 1, 4 * T + 3, 0, 40, 0.0)
     run_pipeline(tdo, wl.make_round(spec, perturbed_per_agent=listed))
