@@ -1700,7 +1700,10 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
 
   // Lane (n, hh) holds elements 32 q + 8 j + 4 hh + (0..3) of row n.  They go out by way of LDS, so that a store instruction
   // writes whole rows (straight from the registers it writes 32 bytes of each of 32 rows; 2 x 79 agents x 90 tokens, 640 rows,
-  // 0.4 GB of results: 244.8 -> 233.5 us).  Piece c of row r (16 bytes) stands at place c ^ r.
+  // 0.4 GB of results: 244.8 -> 233.5 us).  Piece c of row r (16 bytes) stands at place c ^ r.  With 33 to 63 rows per agent, whose
+  // second wavefront is mostly empty, the way through LDS is longer than what the stores gain (ten sessions of 5 agents x 73 tokens, 33
+  // rows 15.4 against 15.0 us, 25 agents x 64 tokens, 40 rows 11.9 against 11.7; 64 rows 16.6 against 16.8, 32 rows 17.9 against 18.1;
+  // own block orders the same or slower).
   if (!active) return;
   const float l_tot = st.l_run + __shfl_xor(st.l_run, 32);
   float f = 1.f;
@@ -1712,6 +1715,18 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     at.part_m[slot] = part_max(st.m_run, l_tot);
     at.part_l[slot] = l_tot;
   }
+  float* to = rg.direct ? at.out : at.part_o + (int64_t)chunk * kHeadDim;
+  const int64_t pitch = (int64_t)kHeadDim * (rg.direct ? 1 : at.n_parts);
+  if (!SEG && per_agent_rows > kRowsPerWave && per_agent_rows < 2 * kRowsPerWave) {
+    float4* po = reinterpret_cast<float4*>(to + out * pitch) + hh;
+    if (row_ok)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          po[8 * q + 2 * j] = make_float4(st.oacc[q][4 * j] * f, st.oacc[q][4 * j + 1] * f, st.oacc[q][4 * j + 2] * f, st.oacc[q][4 * j + 3] * f);
+    return;
+  }
   float4* rows = reinterpret_cast<float4*>(sh.k[0] + wave * kListedLds);
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -1720,8 +1735,6 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
       rows[32 * n + ((8 * q + 2 * j + hh) ^ n)] = make_float4(st.oacc[q][4 * j] * f, st.oacc[q][4 * j + 1] * f,
                                                              st.oacc[q][4 * j + 2] * f, st.oacc[q][4 * j + 3] * f);
   wave_sync();
-  float* to = rg.direct ? at.out : at.part_o + (int64_t)chunk * kHeadDim;
-  const int64_t pitch = (int64_t)kHeadDim * (rg.direct ? 1 : at.n_parts);
   const int there = min(kRowsPerWave, per_agent_rows - r0);
   for (int r8 = 0; r8 < there; r8 += 8)
 #pragma unroll
