@@ -380,11 +380,11 @@ bool attend_rows_for_segments(const AttendShape& r, int64_t agent_rows) {
 // launches beyond it count a tenth more, and the cut that needs no estimate (packed rows, chunks of 512 tokens or more) stays unless
 // another promises 3 %.
 // Measured over 820 rounds that the fit has not seen, 2 to 20 % listed, every form and cut: 1.28 times as fast as that cut, 1.033
-// times the best choice.  18 of them are more than 5 % slower than it, 3 more than 10 % (25, 5 and one of 1.40 without the two rules
-// above): 20 sessions x 2 agents x 420 tokens, 2 rows 22 -> 28 us, 123 agents x 3289 tokens, 16 rows, a fifth listed 120 -> 140, 22
-// agents x 13329 tokens, 2 heads, 5 rows 29 -> 32.  4 x 23 agents x 152 tokens with 32 rows take 18 us instead of 41.  No page, half
-// or all of them listed (the assumed share is far off there), 120 rounds: 1.25 times as fast, 3 more than 10 % slower (2 x 43 agents x
-// 557 tokens, 5 rows, half listed 37 -> 49 us; of another 90 rounds 37 agents x 1080 tokens, 8 rows, all listed 55 -> 79).
+// times the best choice.  16 of them are more than 5 % slower than it, 2 more than 10 % (25, 5 and one of 1.40 with the estimates
+// alone): 20 sessions x 2 agents x 420 tokens, 2 rows 22 -> 28 us, 22 agents x 13329 tokens, 2 heads, 5 rows 29 -> 32.  4 x 23 agents x
+// 152 tokens with 32 rows take 18 us instead of 41.  71 rounds of 20 to 150 steps per compute unit: 1.34 times as fast, none slower.
+// No page, half or all of them listed (the assumed share is far off there), 120 rounds: 1.25 times as fast, 3 more than 10 % slower (2 x
+// 43 agents x 557 tokens, 5 rows, half listed 37 -> 49 us; of another 90 rounds 37 agents x 1080 tokens, 8 rows, all listed 55 -> 79).
 struct AttendLoad {
   double wgs;        // workgroups of the pass over the master, per compute unit
   double steps;      // 64-token steps of a workgroup
@@ -534,6 +534,12 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
     // workgroups that walk lists: a piece of four KV heads each, at most four per list
     const double walk_lists = (double)(r.n_agents * (int64_t)((r.heads + kWaves - 1) / kWaves)) *
                               std::min({4.0, (double)p.n_pieces, pieces_of(max_span, p.piece_tokens)}) / (double)cus;
+    // The fit has few large passes, and estimates the wavefront per agent too fast there.  With 8 to 16 rows (half of every tile is
+    // empty), three steps per compute unit and 2500 tokens or more it won nothing in 17 rounds (time per agent / packed 0.99 .. 1.41,
+    // estimated 0.77 .. 1.2), with shorter spans it won 16 of 19 (0.55 .. 0.93): there it counts twice, and is taken where nothing else
+    // fits the workspace.  From 64 steps on a promise of less than 15 % does not count (ten sessions of 25 x 5000 tokens, 20 rows 266
+    // against 291 us).
+    const double doubtful = only && agent_rows <= 16 && max_span >= 2500 ? 2 : 1;
     auto consider = [&](int64_t c, bool in_packed, bool in_rows, double bonus = 1) {
       // chunks of c tokens over all sessions with agents, and the workgroups of the rows kernel in them (both per KV head)
       int64_t chunks = 0, row_wgs = 0, span = -1, n = 0;
@@ -559,10 +565,10 @@ bool attend_plan(const AttendShape& r, int32_t n_q, int32_t n_q_heads, AttendPla
         if (packed < 0 || us < packed) { packed = us; packed_chunk = c; }
       }
       l.wgs = (double)(row_wgs * r.heads) / (double)cus;
-      const double us = in_rows ? rows_us(r, l) : 0;
+      const double us = in_rows ? doubtful * rows_us(r, l) : 0;
       if (in_rows && (rows < 0 || us < rows)) { rows = us; rows_chunk = c; }
     };
-    consider(fewest_rounds(), true, false, 0.97);
+    consider(fewest_rounds(), true, false, steps >= 64 * cus ? 0.85 : 0.97);
     for_chunks(max_span, 16384, [&](int64_t c) { consider(c, !only && c <= max_chunk, true); });
     // (neither fits: the cut that needs least, for the caller to compare)
     p.own_rows = !refused && rows > 0 && (packed < 0 || rows < packed);

@@ -238,6 +238,9 @@ static int check_estimates() {
   REQUIRE(!p.own_rows && p.fused.n_master <= 56);
   p = plan(1, 16, 5000, 8, 1);
   REQUIRE(!p.own_rows && p.fused.n_master <= 128 && p.fused.n_master > 96);
+  // large passes: up to 16 rows packed from 2500 tokens on; from 64 steps per compute unit on packed unless much is promised
+  REQUIRE(!plan(1, 123, 3289, 8, 16, 32).own_rows && !plan(4, 69, 2550, 8, 16).own_rows && plan(4, 52, 2054, 8, 16, 32).own_rows);
+  REQUIRE(!plan(10, 25, 5000, 8, 20).own_rows && plan(10, 25, 5000, 8, 25).own_rows && plan(10, 13, 3466, 8, 20).own_rows);
   // the rounds of the GPU tests, with both page sizes: form and tokens per chunk (sessions, agents, span, heads, rows per agent and KV
   // head)
   auto is = [&](bool own_rows, int sessions, int agents, int span, int heads, int group, int chunk) {
