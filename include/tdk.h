@@ -294,8 +294,8 @@ size_t tdk_attend_workspace_bytes(const tdk_round* r, int32_t n_q, int32_t n_q_h
  * Master values must be finite.
  * The workspace holds partial results.  tdk_attend_workspace_bytes never gets smaller with n_q: what it asks for n_q
  * query tokens serves every call on the round with fewer (a shorter call may be cut into more parts, and need more, than a
- * longer one).  A call that brings less is cut into fewer parts, as long as parts of 512 tokens or more fit: slower, and rounded
- * at other places; below that it is refused.
+ * longer one).  A call with few query rows in the master's order that brings less is cut into fewer parts, as long as parts of 512
+ * tokens or more fit: slower, and rounded at other places.  Other calls, and those with less, are refused.
  * Allocates nothing, enqueues one to four kernels, does not synchronise.  Errors: INVALID_ARG (NULL,
  * misaligned, n_q < 1, n_q_heads not a multiple of H, scale not finite, workspace too small). */
 tdk_status tdk_attend_shared(tdk_round* r, int32_t layer, const tdk_layer_io* io, const tdk_diff* in,

@@ -1077,8 +1077,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 }
 
 // ---------------------------------------------------------------------------------------------
-// One agent per wavefront: attention of rounds whose agents bring enough query rows of their own (prefill, and with
-// per-agent block orders also fewer rows, up to the work attend_plan names).  A wavefront owns 32 query rows of ONE agent and KV head and
+// One agent per wavefront: attention of rounds whose agents bring enough query rows of their own (prefill), and calls with fewer rows
+// that attend_plan gives it (short spans, per-agent block orders).  A wavefront owns 32 query rows of ONE agent and KV head and
 // walks the span in 64-token steps; the four wavefronts of a workgroup share the master's K and V tiles in LDS,
 // whatever agents they belong to.  Because the rows of a wavefront have one agent, everything that depends on
 // the agent is uniform: the pages its diff lists (a bit mask in LDS; most steps have none and skip the masking),
@@ -1091,12 +1091,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 // the K and V tiles are double-buffered with one barrier per step, and the rows of the tiles after that travel
 // from memory straight to LDS meanwhile (through registers and LDS writes 204 to 217 us against 198 at the size below).
 // What bounds it (25 agents x 64 query tokens x 40 heads over 5000 tokens, 2 wavefronts per SIMD, counters): matrix
-// cores, vector units and LDS are each busy about half of the time, 1.8 us per step of both wavefronts of a SIMD; no
+// cores are busy 43 % of the time, vector units 47, LDS with operand reads 25, 1.8 us per step of both wavefronts of a SIMD; no
 // single pipe is full, the rest is waiting between dependent stages (score products, maxima, exponentials, second
 // products) and at the barrier.  64 rows per wavefront (half the LDS bytes per product, one wavefront per SIMD) measured
 // the same.
 // Measured against rows of all agents in one block plus separate listed-pages and merge launches: 64 query tokens
-// per agent 462 -> 206 us (193 now), 16 tokens 140 -> 93 us, 8 tokens 94 -> 70 us.  Per-agent orders of blocks of 200 tokens, steps
+// per agent 462 -> 206 us (187 now), 16 tokens 140 -> 93 us, 8 tokens 94 -> 70 us.  Per-agent orders of blocks of 200 tokens, steps
 // that ended at every border, a chain of reads to find a chunk's first segment and page, tiles through registers -> now:
 // 25 agents x 5000 tokens, 20 rows 70 -> 54 us (48 now); 129 x 4307, 35 rows 502 -> 375; blocks of 64, 151 x 937, 80 rows 105 -> 81.
 // ---------------------------------------------------------------------------------------------
@@ -1957,7 +1957,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
 // many as every session has (reading eight of all sessions: one of 5000 and nine of 300 tokens, 25 agents each, 45.9 us instead of
 // 41.9), and all maxima and sums (up to 64 parts) are asked for before that is known; what does not exist gets no weight.  A
 // half-wavefront takes every other part, 16 bytes per lane.  2 x 8 agents x 1113 tokens, 4 rows 14.2 -> 13.1 us with
-// its launch, 6 x 608 tokens, own orders 17.7 -> 16.6, 250 agents x 5000 tokens 137.7 -> 137.5.
+// its launch, 6 x 608 tokens, own orders 17.7 -> 16.6, the 10 000 rows of 250 agents x 5000 tokens 12 us as before.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void tdk_attend_merge_kernel(const RoundDev rd, const DiffDev d, const AttendDev at) {
   const int64_t row = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
