@@ -68,6 +68,8 @@ struct tdk_round {
   int device = -1;
   int32_t n_cus = 256;             // compute units of that device
   std::vector<HostSession> sessions;
+  std::vector<int32_t> order;      // agent ids grouped by session
+  std::vector<AgentDev> agents;    // descriptors in the caller's order
   int32_t n_agents = 0;
   int64_t max_phys_page = -1;      // largest page number any shared span maps to
   int64_t total_pages = 0;         // sum over agents of their session's page count
@@ -77,7 +79,8 @@ struct tdk_round {
 
   void*  blob = nullptr;           // one device allocation for everything below
   size_t blob_bytes = 0;
-  size_t work_capacity = 0;        // WorkItems the work region can hold
+  size_t work_capacity = 0;        // items that a work list can have
+  ItemDev* work_region = nullptr;  // the four lists, one behind the other
   RoundDev rd{};
 
   // ping-pong restore: one "loaded" and one "free" event per staging buffer, one "done" per call
@@ -114,17 +117,19 @@ tdk_status upload_work(tdk_round* r, int named) {
   if (work.size() > r->work_capacity || rwork.size() > r->work_capacity || pwork.size() > r->work_capacity) return fail(TDK_ERR_INVALID_ARG, "work list larger than reserved");
   std::vector<WorkItem> queued;
   plan_queues(work, queued, r->rd.q_begin);
-  if (!work.empty()) {
-    hipError_t e = hipMemcpy(const_cast<WorkItem*>(r->rd.work), work.data(), work.size() * sizeof(WorkItem),
-                             hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(const_cast<WorkItem*>(r->rd.qwork), queued.data(), queued.size() * sizeof(WorkItem),
-                                       hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(const_cast<WorkItem*>(r->rd.rwork), rwork.data(), rwork.size() * sizeof(WorkItem),
-                                       hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(const_cast<WorkItem*>(r->rd.pwork), pwork.data(), pwork.size() * sizeof(WorkItem),
-                                       hipMemcpyHostToDevice);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpy(work list)");
+  // the four lists one behind the other, in one upload
+  std::vector<ItemDev> items;
+  const ItemDev* at[4];
+  const std::vector<WorkItem>* lists[4] = {&work, &queued, &rwork, &pwork};
+  for (int k = 0; k < 4; ++k) {
+    at[k] = r->work_region + items.size();
+    plan_items(r->sessions, r->order, r->agents, r->model.page_tokens, *lists[k], items);
   }
+  if (!items.empty()) {
+    const hipError_t e = hipMemcpy(r->work_region, items.data(), items.size() * sizeof(ItemDev), hipMemcpyHostToDevice);
+    if (e != hipSuccess) return hip_fail(e, "hipMemcpy(work lists)");
+  }
+  r->rd.work = at[0]; r->rd.qwork = at[1]; r->rd.rwork = at[2]; r->rd.pwork = at[3];
   r->rd.n_work = (int32_t)work.size();
   r->rd.n_rwork = (int32_t)rwork.size();
   r->rd.n_pwork = (int32_t)pwork.size();
@@ -289,6 +294,8 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
     if (ps != TDK_OK) return fail(ps, err);
   }
   r->sessions = p.sessions;
+  r->order = p.order;
+  r->agents = p.agents;
   r->max_phys_page = p.max_phys_page;
   r->total_pages = p.total_pages;
   r->rd.agent_pages = p.total_pages;
@@ -324,10 +331,8 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   // ---- device memory: one allocation ----
   size_t off = 0;
   auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-  const size_t o_work = place(work_cap * sizeof(WorkItem));
-  const size_t o_qwork = place(work_cap * sizeof(WorkItem));
-  const size_t o_rwork = place(work_cap * sizeof(WorkItem));
-  const size_t o_pwork = place(work_cap * sizeof(WorkItem));
+  const size_t o_work = place(4 * work_cap * sizeof(ItemDev));
+  const size_t o_places = place(any_segments ? 0 : (size_t)flag_off * sizeof(PlaceDev));
   const size_t o_sess = place(sess_dev.size() * sizeof(SessionDev));
   const size_t o_agents = place(agent_dev.size() * sizeof(AgentDev));
   const size_t o_order = place(order.size() * sizeof(int32_t));
@@ -354,34 +359,36 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   e = hipMalloc(&r->blob, r->blob_bytes);
   if (e != hipSuccess) { return e == hipErrorOutOfMemory ? fail(TDK_ERR_NOMEM, "device allocation failed") : hip_fail(e, "hipMalloc"); }
   char* base = static_cast<char*>(r->blob);
-  auto up = [&](size_t o, const void* src, size_t bytes) -> hipError_t {
-    return bytes ? hipMemcpy(base + o, src, bytes, hipMemcpyHostToDevice) : hipSuccess;
+  // the tables from o_sess to o_flags go up in one piece (a dozen blocking copies of a few KB take longer than the rest of the call)
+  std::vector<char> tables(o_flags - o_sess);
+  auto put = [&](size_t o, const auto& v) {
+    if (!v.empty()) std::memcpy(tables.data() + (o - o_sess), v.data(), v.size() * sizeof(v[0]));
   };
-  e = up(o_sess, sess_dev.data(), sess_dev.size() * sizeof(SessionDev));
-  if (e == hipSuccess) e = up(o_agents, agent_dev.data(), agent_dev.size() * sizeof(AgentDev));
-  if (e == hipSuccess) e = up(o_order, order.data(), order.size() * sizeof(int32_t));
-  if (e == hipSuccess) e = up(o_bt, bt.data(), bt.size() * sizeof(int32_t));
-  if (e == hipSuccess) e = up(o_tab, tab.data(), tab.size() * sizeof(float));
-  if (e == hipSuccess) e = up(o_tab_diff, tab_diff.data(), tab_diff.size() * sizeof(float));
-  if (e == hipSuccess && any_segments) e = up(o_rowmap, rowmap.data(), rowmap.size() * sizeof(int32_t));
-  if (e == hipSuccess && any_segments) e = up(o_pagetab, pagetab.data(), pagetab.size() * sizeof(PageTab));
-  if (e == hipSuccess && any_segments) e = up(o_segtab, segtab.data(), segtab.size() * sizeof(float));
-  if (e == hipSuccess && any_segments) e = up(o_segtab_diff, segtab_diff.data(), segtab_diff.size() * sizeof(float));
-  if (e == hipSuccess && any_segments) e = up(o_seg_off, seg_off.data(), seg_off.size() * sizeof(int32_t));
-  if (e == hipSuccess && any_segments) e = up(o_seg_src, seg_src.data(), seg_src.size() * sizeof(int32_t));
-  if (e == hipSuccess && flag_off) e = hipMemset(base + o_flags, 0, (size_t)flag_off);
-  if (e == hipSuccess) e = hipMemset(base + o_qstate, 0, o_tickets - o_qstate + (size_t)n_sessions * sizeof(int32_t));   // and the tickets behind it
+  put(o_sess, sess_dev);
+  put(o_agents, agent_dev);
+  put(o_order, order);
+  put(o_bt, bt);
+  put(o_tab, tab);
+  put(o_tab_diff, tab_diff);
+  if (any_segments) {
+    put(o_rowmap, rowmap);
+    put(o_pagetab, pagetab);
+    put(o_segtab, segtab);
+    put(o_segtab_diff, segtab_diff);
+    put(o_seg_off, seg_off);
+    put(o_seg_src, seg_src);
+  }
+  if (!tables.empty()) e = hipMemcpy(base + o_sess, tables.data(), tables.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = hipMemset(base + o_flags, 0, o_tickets - o_flags + (size_t)n_sessions * sizeof(int32_t));   // flags, queue state, tickets
   if (e != hipSuccess) return hip_fail(e, "upload of round descriptors");
 
-  r->rd.work = reinterpret_cast<const WorkItem*>(base + o_work);
-  r->rd.qwork = reinterpret_cast<const WorkItem*>(base + o_qwork);
-  r->rd.rwork = reinterpret_cast<const WorkItem*>(base + o_rwork);
-  r->rd.pwork = reinterpret_cast<const WorkItem*>(base + o_pwork);
+  r->work_region = reinterpret_cast<ItemDev*>(base + o_work);
   r->rd.sess = reinterpret_cast<const SessionDev*>(base + o_sess);
   r->rd.agents = reinterpret_cast<const AgentDev*>(base + o_agents);
   r->rd.oagents = r->rd.agents + n_agents;
   r->rd.order = reinterpret_cast<const int32_t*>(base + o_order);
   r->rd.bt = reinterpret_cast<const int32_t*>(base + o_bt);
+  r->rd.places = any_segments ? nullptr : reinterpret_cast<const PlaceDev*>(base + o_places);
   r->rd.tab = reinterpret_cast<const float*>(base + o_tab);
   r->rd.tab_diff = reinterpret_cast<const float*>(base + o_tab_diff);
   r->rd.flags = reinterpret_cast<uint8_t*>(base + o_flags);
@@ -406,6 +413,11 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   r->rd.interleaved = model->rope_style == TDK_ROPE_INTERLEAVED;
   r->rd.nontemporal = r->flags & TDK_TUNE_ALL;
 
+  // (before the work lists, whose blocking copy on the same stream waits for it)
+  if (!any_segments && flag_off) {
+    e = launch_places(r->rd, reinterpret_cast<PlaceDev*>(base + o_places), nullptr);
+    if (e != hipSuccess) return hip_fail(e, "places of the pages");
+  }
   st = upload_work(r, 0);
   if (st != TDK_OK) return st;
   for (int b = 0; b < 2 && e == hipSuccess; ++b) {

@@ -11,13 +11,14 @@ namespace tdk {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // one 16-byte access
 struct RoundDev {
-  const WorkItem*   work;    // one item per workgroup of a static launch: item i runs on XCD i % 8
-  const WorkItem*   qwork;   // the same items grouped by that XCD: the queues of a queued launch
+  const ItemDev*    work;    // one item per workgroup of a static launch: item i runs on XCD i % 8
+  const ItemDev*    qwork;   // the same items grouped by that XCD: the queues of a queued launch
   const SessionDev* sess;
   const AgentDev*   agents;
   const AgentDev*   oagents; // the agents' descriptors grouped by session: oagents[i] = agents[order[i]]
   const int32_t*    order;   // agent ids grouped by session
   const int32_t*    bt;      // block-table slices, concatenated
+  const PlaceDev*   places;  // [agent_pages]: where each page of each agent lies (identity layouts; else NULL)
   const float*      tab;     // [n_agents][2][64]: cos then sin of the agent's delta
   const float*      tab_diff;  // [n_agents][2][64]: same for dst_pos0 - diff_pos0 (payload re-rotation)
   // general block layouts (some agent has its own order of the shared blocks); all NULL otherwise
@@ -33,9 +34,9 @@ struct RoundDev {
   int32_t*          q_state; // [16] work queues: [0..7] next item of each XCD's queue, [8] workgroups that have left, [12] next item of a static launch's shared tail; all zero between launches
   int32_t*          tickets; // [n_sessions] totals delivered so far in a check-layer call; zero between calls
   int64_t           agent_pages;           // sum over agents of their session's page count: the length of a page-kernel launch
-  const WorkItem*   rwork;                 // the work list of the kernels that only read (compare, key difference): it may be coarser
+  const ItemDev*    rwork;                 // the work list of the kernels that only read (compare, key difference): it may be coarser
   int32_t           n_rwork;
-  const WorkItem*   pwork;                 // the work list of static launches that write one plane only (an item holds half the bytes)
+  const ItemDev*    pwork;                 // the work list of static launches that write one plane only (an item holds half the bytes)
   int32_t           n_pwork;
   int32_t           dyn_begin, dyn_count;  // static launches of the write kernels: workgroups [dyn_begin, dyn_begin + dyn_count) take the items from dyn_begin on in the order they start (set per launch; dyn_begin = n_work, dyn_count = 0: none)
   int32_t           q_begin[9];  // XCD x's queue is work[q_begin[x] .. q_begin[x + 1])
@@ -108,6 +109,7 @@ struct AttendDev {
 };
 
 // launchers (tdk_kernels.hip); each enqueues exactly one kernel
+hipError_t launch_places(const RoundDev& rd, PlaceDev* places, hipStream_t st);
 hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t st);
 hipError_t launch_flag(const RoundDev& rd, const LayerDev& io, float eps, int planes, hipStream_t st);
 hipError_t launch_compact(const RoundDev& rd, const DiffDev& d, hipStream_t st);

@@ -93,9 +93,9 @@ __device__ __forceinline__ u32x4 ld16(const u32x4* p) {
 
 struct GroupShared {
   float   tab[kMaxGroup][2 * kHalf];  // cos[64], sin[64] of each agent of the group
-  int32_t pg0[kMaxGroup];             // physical page holding the master page's first token
-  int32_t pg1[kMaxGroup];             // the next logical page's physical page (or -1)
-  int32_t off[kMaxGroup];             // row of the first token inside pg0
+  int64_t b0[kMaxGroup];              // byte of row 0 of the page in a pool plane, for the rows on its first physical page
+  int64_t b1[kMaxGroup];              // the same for the rows on the next one (where row 0 would lie)
+  int32_t cut[kMaxGroup];             // first row on the next one
   int32_t aux[kMaxGroup];             // flag kernel: OR of the waves; decode: 1 if the page is listed
 };
 
@@ -108,43 +108,99 @@ struct GroupSharedSeg {
   int32_t  aux[kMaxGroup];
 };
 
-__device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& w, const int T, GroupSharedSeg& sh) {
-  const int tid = threadIdx.x;
-  for (int i = tid; i < w.ag_count * 64; i += kBlock) {
-    const int g = i >> 6, which = (i >> 5) & 1, q = i & 31;
-    const AgentDev ad = rd.oagents[w.ag_begin + g];
-    const PageTab pt = rd.pagetab[ad.flag_off + w.page];
-    const int t = which ? pt.y : pt.x;
-    reinterpret_cast<float4*>(sh.tab[g][which])[q] =
-        reinterpret_cast<const float4*>(rd.segtab + (size_t)t * (2 * kHalf))[q];
+// Descriptors that no kernel writes, at an address that is the same for the whole workgroup: one scalar read.
+template <class T>
+__device__ __forceinline__ T scalar_read(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "read in words");
+  const auto* q = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p;
+  T v;
+  uint32_t w[sizeof(T) / 4];
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(T) / 4); ++k) w[k] = q[k];
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
+}
+
+// A work item in scalar registers.
+struct Item {
+  ItemDev d;
+  __device__ __forceinline__ Item(const ItemDev* list, int item) : d(scalar_read(list + __builtin_amdgcn_readfirstlane(item))) {}
+  __device__ __forceinline__ int count() const { return d.counts & 255; }
+  __device__ __forceinline__ int rows() const { return d.counts >> 8; }
+  // agent g of the group; its (agent, page) pair; its (agent, token) pair of the page's first token
+  __device__ __forceinline__ int agent(const RoundDev& rd, int g) const { return d.agent0 >= 0 ? d.agent0 + g : rd.order[d.order0 + g]; }
+  __device__ __forceinline__ int flat(const RoundDev& rd, int g) const { return d.agent0 >= 0 ? d.flat0 + g * d.pages : rd.oagents[d.order0 + g].flag_off + d.page; }
+  __device__ __forceinline__ int score(const RoundDev& rd, int g) const {
+    return d.agent0 >= 0 ? d.score0 + g * d.span : rd.oagents[d.order0 + g].score_off + d.page * rd.page_tokens;
   }
-  const SessionDev sd = rd.sess[w.session];
-  for (int i = tid; i < w.ag_count * T; i += kBlock) {
-    const int g = T == 16 ? i >> 4 : i >> 5, r = i & (T - 1);
-    const AgentDev ad = rd.oagents[w.ag_begin + g];
-    const int m = w.page * T + r;
-    sh.row[g][r] = m < sd.span ? rd.rowmap[ad.score_off + m] : 0;
-  }
-  if (tid < w.ag_count) {
-    sh.sel[tid] = (uint32_t)rd.pagetab[rd.oagents[w.ag_begin + tid].flag_off + w.page].z;
+};
+
+// A group is staged in two steps, so that its reads and those of the master page are in flight together: what an item's first store
+// waits for is the item (one scalar read), then everything else at once.  (One after the other, as branches around the loads make
+// the compiler wait, it was nine vector reads; a read that no cache holds takes 0.65 us on an idle chip and 2 to 4 on a busy one: 25 agents
+// x 5000 tokens, collect, restore and store 301.4 -> 297.9 us; 37 x 2999, 4 heads, one plane after the other 123.7 -> 121.5; 48 agents
+// with own orders and 32-token pages, restore 104 -> 102; drawn rounds up to 1.08 times.)
+struct AskedGroup { u32x4 place; float4 tab[2]; };
+
+__device__ __forceinline__ void ask_group(const RoundDev& rd, const Item& it, const int, const GroupShared&, AskedGroup& a) {
+  const int tid = threadIdx.x, n = it.count() - 1, q = tid & 31;
+  a.place = reinterpret_cast<const u32x4*>(rd.places)[it.flat(rd, min(tid, n))];
+  const float4* tab = reinterpret_cast<const float4*>(rd.tab);
+  a.tab[0] = tab[(size_t)it.agent(rd, min(tid >> 5, n)) * (kHalf / 2) + q];
+  a.tab[1] = a.tab[0];
+  if (n >= 8) a.tab[1] = tab[(size_t)it.agent(rd, min(8 + (tid >> 5), n)) * (kHalf / 2) + q];
+}
+
+__device__ __forceinline__ void put_group(const RoundDev& rd, const Item& it, const int T, GroupShared& sh, const AskedGroup& a) {
+  const int tid = threadIdx.x, n = it.count(), q = tid & 31, g = tid >> 5;
+  if (g < n) reinterpret_cast<float4*>(sh.tab[g])[q] = a.tab[0];
+  if (g + 8 < n) reinterpret_cast<float4*>(sh.tab[g + 8])[q] = a.tab[1];
+  for (int g2 = g + 16; g2 < n; g2 += 8)
+    reinterpret_cast<float4*>(sh.tab[g2])[q] = reinterpret_cast<const float4*>(rd.tab)[(size_t)it.agent(rd, g2) * (kHalf / 2) + q];
+  if (tid < n) {
+    const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
+    const int off = (int)a.place[2];
+    sh.b0[tid] = ((int64_t)(int32_t)a.place[0] * T + off) * row_bytes;
+    sh.b1[tid] = ((int64_t)(int32_t)a.place[1] * T + off - T) * row_bytes;
+    sh.cut[tid] = T - off;
   }
 }
 
-__device__ __forceinline__ void stage_group(const RoundDev& rd, const WorkItem& w, const int T, GroupShared& sh) {
-  const int tid = threadIdx.x;
-  for (int i = tid; i < w.ag_count * 32; i += kBlock) {
-    const int g = i >> 5, q = i & 31;
-    const int a = rd.order[w.ag_begin + g];
-    reinterpret_cast<float4*>(sh.tab[g])[q] =
-        reinterpret_cast<const float4*>(rd.tab + (size_t)a * (2 * kHalf))[q];
+struct AskedGroupSeg { u32x4 pt; int32_t row, sel; };
+
+__device__ __forceinline__ void ask_group(const RoundDev& rd, const Item& it, const int T, const GroupSharedSeg&, AskedGroupSeg& a) {
+  const int tid = threadIdx.x, n = it.count() - 1, lg = T == 16 ? 4 : 5;
+  a.pt = reinterpret_cast<const u32x4*>(rd.pagetab)[it.flat(rd, min(tid >> 6, n))];
+  a.sel = rd.pagetab[it.flat(rd, min(tid, n))].z;
+  a.row = rd.rowmap[it.score(rd, min(tid >> lg, n)) + min(tid & (T - 1), it.rows() - 1)];
+}
+
+__device__ __forceinline__ void put_group(const RoundDev& rd, const Item& it, const int T, GroupSharedSeg& sh, const AskedGroupSeg& a) {
+  const int tid = threadIdx.x, n = it.count(), lg = T == 16 ? 4 : 5, which = (tid >> 5) & 1, q = tid & 31;
+  const float4* tab = reinterpret_cast<const float4*>(rd.segtab);
+  u32x4 pt = a.pt;
+  for (int g = tid >> 6; g < n; g += kBlock / 64) {
+    if (g >= kBlock / 64) pt = reinterpret_cast<const u32x4*>(rd.pagetab)[it.flat(rd, g)];
+    reinterpret_cast<float4*>(sh.tab[g][which])[q] = tab[(size_t)(which ? pt[1] : pt[0]) * (kHalf / 2) + q];
   }
-  if (tid < w.ag_count) {
-    const AgentDev ad = rd.oagents[w.ag_begin + tid];
-    const int a0 = ad.pos0 + w.page * T;
-    const int lp = (T == 16 ? a0 >> 4 : a0 >> 5) - ad.lp_first;       // (positions are not negative)
-    sh.pg0[tid] = rd.bt[ad.bt_off + lp];
-    sh.pg1[tid] = (lp + 1 < ad.bt_len) ? rd.bt[ad.bt_off + lp + 1] : -1;
-    sh.off[tid] = a0 & (T - 1);
+  int32_t row = a.row;
+  for (int i = tid; i < n << lg; i += kBlock) {
+    if (i >= kBlock) row = rd.rowmap[it.score(rd, i >> lg) + min(i & (T - 1), it.rows() - 1)];
+    sh.row[i >> lg][i & (T - 1)] = row;            // (a row past the span repeats the last one; nobody uses it)
+  }
+  if (tid < n) sh.sel[tid] = (uint32_t)a.sel;
+}
+
+template <bool SEG> using Shared = std::conditional_t<SEG, GroupSharedSeg, GroupShared>;
+template <bool SEG> using Asked = std::conditional_t<SEG, AskedGroupSeg, AskedGroup>;
+
+// Where each page of each agent lies: a workgroup per agent, once per round.
+__global__ __launch_bounds__(kBlock) void tdk_places_kernel(const RoundDev rd, PlaceDev* __restrict__ places) {
+  const AgentDev ad = rd.agents[blockIdx.x];
+  const int T = rd.page_tokens, lg = T == 16 ? 4 : 5, pages = rd.sess[ad.session].pages;
+  for (int p = threadIdx.x; p < pages; p += kBlock) {
+    const int a0 = ad.pos0 + p * T, lp = (a0 >> lg) - ad.lp_first;       // (positions are not negative)
+    places[ad.flag_off + p] = PlaceDev{rd.bt[ad.bt_off + lp], lp + 1 < ad.bt_len ? rd.bt[ad.bt_off + lp + 1] : -1, a0 & (T - 1), 0};
   }
 }
 
@@ -231,47 +287,50 @@ struct MasterRows {
   template <bool PACK> __device__ __forceinline__ bool v1ok(const Lane& L, int k) const { return PACK ? L.v1ok && v1in[k] : L.v1ok; }
 };
 
+// No branch stands around a load: a row or a chunk that does not exist reads another one of the page, and is not used.
 template <int RPW, bool PACK, bool LOADV = true, bool LOADK = true>
-__device__ __forceinline__ void load_master(const RoundDev& rd, const LayerDev& io, const WorkItem& w, const int T,
+__device__ __forceinline__ void load_master(const RoundDev& rd, const LayerDev& io, const Item& it, const int T,
                                             const Lane& L, MasterRows<RPW>& M) {
-  const SessionDev sd = rd.sess[w.session];
-  const int64_t row_u4 = (int64_t)rd.heads * 16;
+  const int rows = it.rows();
+  const uint32_t row_u4 = (uint32_t)rd.heads * 16u;
+  const u32x4* mk = io.master_k + it.d.row0 * row_u4;
+  const u32x4* mv = io.master_v + it.d.row0 * row_u4;
+  const uint32_t klo = L.kok ? L.klo : L.jb, v0 = L.v0ok ? L.v0 : 0, v1 = L.v1ok ? L.v1 : 0;
 #pragma unroll
   for (int k = 0; k < RPW; ++k) {
-    const int m = w.page * T + group_row<PACK>(k, rd.heads, T);
-    M.valid[k] = m < sd.span;
-    if (PACK) { M.kin[k] = m + L.rk < sd.span; M.v0in[k] = m + L.rv0 < sd.span; M.v1in[k] = m + L.rv1 < sd.span; }
+    const int r = group_row<PACK>(k, rd.heads, T);
+    M.valid[k] = r < rows;
+    if (PACK) { M.kin[k] = r + L.rk < rows; M.v0in[k] = r + L.rv0 < rows; M.v1in[k] = r + L.rv1 < rows; }
     const u32x4 z = {0, 0, 0, 0};
     M.kl[k] = z; M.kh[k] = z; M.v0[k] = z; M.v1[k] = z;
-    if (M.valid[k]) {
-      const u32x4* rk = io.master_k + (sd.master_row0 + m + (PACK ? L.rk : 0)) * row_u4;
-      const u32x4* rv0 = io.master_v + (sd.master_row0 + m + (PACK ? L.rv0 : 0)) * row_u4;
-      const u32x4* rv1 = PACK ? io.master_v + (sd.master_row0 + m + L.rv1) * row_u4 : rv0;
-      if (LOADK && M.template kok<PACK>(L, k)) { M.kl[k] = rk[L.klo]; M.kh[k] = rk[L.khi]; }
-      if (LOADV && M.template v0ok<PACK>(L, k)) M.v0[k] = rv0[L.v0];
-      if (LOADV && M.template v1ok<PACK>(L, k)) M.v1[k] = rv1[L.v1];
+    const uint32_t rk = min(PACK ? r + L.rk : r, rows - 1) * row_u4;
+    if (LOADK) { M.kl[k] = mk[rk + klo]; M.kh[k] = mk[rk + klo + 8]; }
+    if (LOADV) {
+      M.v0[k] = mv[(PACK ? min(r + L.rv0, rows - 1) * row_u4 : rk) + v0];
+      M.v1[k] = mv[(PACK ? min(r + L.rv1, rows - 1) * row_u4 : rk) + v1];
     }
   }
 }
 
-__device__ __forceinline__ int64_t dest_row(const GroupSharedSeg& sh, int, int g, int r) { return sh.row[g][r]; }
-
-// physical pool row of row r (0..T-1) of the master page for agent g of the group
-__device__ __forceinline__ int64_t dest_row(const GroupShared& sh, int T, int g, int r) {
-  const int q = sh.off[g] + r;
-  const int pg = q < T ? sh.pg0[g] : sh.pg1[g];
-  return (int64_t)pg * T + (q & (T - 1));
+// byte of row r (0..T-1) of the master page in a pool plane, for agent g of the group
+__device__ __forceinline__ int64_t dest_row(const GroupSharedSeg& sh, uint32_t row_bytes, int g, int r) { return (int64_t)sh.row[g][r] * row_bytes; }
+__device__ __forceinline__ int64_t dest_row(const GroupShared& sh, uint32_t row_bytes, int g, int r) {
+  return (r < sh.cut[g] ? sh.b0[g] : sh.b1[g]) + (uint32_t)r * row_bytes;
 }
 
-// pool offsets (16-byte units) of a row group's chunks: one row for all lanes, or (PACK) each chunk's own
+// where a row group's rows lie: one row for all lanes, or (PACK) each chunk's own
 struct Dest { int64_t k, v0, v1; };
-template <bool PACK, class Shared>
-__device__ __forceinline__ Dest dest_of(const Shared& sh, int T, int g, int r, const Lane& L, int64_t row_u4) {
+template <bool PACK, class Sh>
+__device__ __forceinline__ Dest dest_of(const Sh& sh, uint32_t row_bytes, int g, int r, const Lane& L) {
   Dest d;
-  d.k = dest_row(sh, T, g, PACK ? r + L.rk : r) * row_u4;
-  d.v0 = PACK ? dest_row(sh, T, g, r + L.rv0) * row_u4 : d.k;
-  d.v1 = PACK ? dest_row(sh, T, g, r + L.rv1) * row_u4 : d.k;
+  d.k = dest_row(sh, row_bytes, g, PACK ? r + L.rk : r);
+  d.v0 = PACK ? dest_row(sh, row_bytes, g, r + L.rv0) : d.k;
+  d.v1 = PACK ? dest_row(sh, row_bytes, g, r + L.rv1) : d.k;
   return d;
+}
+// chunk c of the row at that byte
+template <class P> __device__ __forceinline__ P* chunk_at(P* pool, int64_t row, int c) {
+  return reinterpret_cast<P*>(reinterpret_cast<std::conditional_t<std::is_const_v<P>, const char, char>*>(pool) + row) + c;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -389,7 +448,7 @@ struct Items {
     if (!queued) return -1;
     return publish(s_item);
   }
-  __device__ __forceinline__ const WorkItem& at(const RoundDev& rd, int item) const { return queued ? rd.qwork[item] : rd.work[item]; }
+  __device__ __forceinline__ const ItemDev* list(const RoundDev& rd) const { return queued ? rd.qwork : rd.work; }
   __device__ __forceinline__ void leave(const RoundDev& rd) {
     if (queued) if (threadIdx.x == 0) {
       const int gone = atomicAdd(&rd.q_state[8], 1);
@@ -406,24 +465,26 @@ struct Items {
 template <int RPW, bool PACK, bool IL, bool NT, bool SEG, bool Q>
 __global__ __launch_bounds__(kBlock) void tdk_rerotate_kernel(const RoundDev rd, const LayerDev io) {
   const int T = PACK ? rd.page_tokens : RPW * kWaves;
-  __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
+  __shared__ Shared<SEG> sh;
   __shared__ int s_item;
   const Lane L = lane_geometry<PACK>(rd.heads, T);
   if (rd.nontemporal & 32) sweep_masters(rd, io, true, true);
-  const int64_t row_u4 = (int64_t)rd.heads * 16;
+  const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
   u32x4* pk = io.pool_k;
   u32x4* pv = io.pool_v;
   Items<Q> items;
   for (int item = items.first(rd, &s_item); item >= 0; item = items.next(rd, &s_item)) {
     stamp_begin(rd, item);
-    const WorkItem w = items.at(rd, item);
-    stage_group(rd, w, T, sh);
+    const Item w(items.list(rd), item);
+    Asked<SEG> asked;
+    ask_group(rd, w, T, sh, asked);
     MasterRows<RPW> M;
     load_master<RPW, PACK>(rd, io, w, T, L, M);
+    put_group(rd, w, T, sh, asked);
     lds_barrier();
     items.prefetch(rd);
     stamp_mid(rd, item, 2);
-    for (int g = 0; g < w.ag_count; ++g) {
+    for (int g = 0; g < w.count(); ++g) {
       if (g == 1) stamp_mid(rd, item, 3);
       float c[8], s[8];
       if (!SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
@@ -431,16 +492,16 @@ __global__ __launch_bounds__(kBlock) void tdk_rerotate_kernel(const RoundDev rd,
       for (int k = 0; k < RPW; ++k) {
         if (!M.valid[k]) continue;
         const int r = group_row<PACK>(k, rd.heads, T);
-        const Dest to = dest_of<PACK>(sh, T, g, r, L, row_u4);
+        const Dest to = dest_of<PACK>(sh, row_bytes, g, r, L);
         if (M.template kok<PACK>(L, k)) {
           if (SEG) load_tab<IL>(sh, g, PACK ? r + L.rk : r, L.jb, c, s);
           u32x4 olo, ohi;
           rotate16<IL>(M.kl[k], M.kh[k], c, s, olo, ohi);
-          st16<NT>(pk + to.k + L.klo, olo);
-          st16<NT>(pk + to.k + L.khi, ohi);
+          st16<NT>(chunk_at(pk, to.k, L.klo), olo);
+          st16<NT>(chunk_at(pk, to.k, L.khi), ohi);
         }
-        if (M.template v0ok<PACK>(L, k)) st16<NT>(pv + to.v0 + L.v0, M.v0[k]);
-        if (M.template v1ok<PACK>(L, k)) st16<NT>(pv + to.v1 + L.v1, M.v1[k]);
+        if (M.template v0ok<PACK>(L, k)) st16<NT>(chunk_at(pv, to.v0, L.v0), M.v0[k]);
+        if (M.template v1ok<PACK>(L, k)) st16<NT>(chunk_at(pv, to.v1, L.v1), M.v1[k]);
       }
     }
     stamp_end(rd, item);
@@ -487,47 +548,50 @@ template <int RPW, bool PACK, bool IL, int PM, bool SEG, bool NTL>
 __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, const LayerDev io, const float eps) {
   const int T = PACK ? rd.page_tokens : RPW * kWaves;
   constexpr bool DOK = (PM & 1) != 0, DOV = (PM & 2) != 0;
-  __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
+  __shared__ Shared<SEG> sh;
   const Lane L = lane_geometry<PACK>(rd.heads, T);
-  const int64_t row_u4 = (int64_t)rd.heads * 16;
+  const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
   const u32x4* pk = io.pool_k;
   const u32x4* pv = io.pool_v;
   const int item = blockIdx.x;
   stamp_begin(rd, item);
-  const WorkItem w = rd.rwork[item];
-  stage_group(rd, w, T, sh);
-  if (threadIdx.x < w.ag_count) sh.aux[threadIdx.x] = 0;
+  const Item w(rd.rwork, item);
+  const int count = w.count();
+  Asked<SEG> asked;
+  ask_group(rd, w, T, sh, asked);
   MasterRows<RPW> M;
   load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
-  bool special[RPW];
-#pragma unroll
-  for (int k = 0; k < RPW; ++k)
-    special[k] = ((int)chunk_special(M.kl[k]) | (int)chunk_special(M.kh[k]) | (int)chunk_special(M.v0[k]) | (int)chunk_special(M.v1[k])) != 0;
+  put_group(rd, w, T, sh, asked);
+  if ((int)threadIdx.x < count) sh.aux[threadIdx.x] = 0;
   lds_barrier();
   // Rolling requests (see tdk_keydiff_kernel): the rows of the next agent are asked for as the rows of this one
   // are used up; no branch stands around a load, a request with nothing to fetch reads the first row of the
   // master page and its result is ignored.
-  const int64_t first_row = (rd.sess[w.session].master_row0 + (int64_t)w.page * T) * row_u4;
+  const int64_t first_row = w.d.row0 * ((int64_t)rd.heads * 16);
   const u32x4* idle_k = DOK ? io.master_k + first_row + L.jb : nullptr;
   const u32x4* idle_v = DOV ? io.master_v + first_row + (threadIdx.x & 15) : nullptr;
   const u32x4 z = {0, 0, 0, 0};
   u32x4 akl[RPW], akh[RPW], av0[RPW], av1[RPW];
   auto request = [&](int g, int k) {
-    const Dest at = dest_of<PACK>(sh, T, max(min(g, w.ag_count - 1), 0), group_row<PACK>(k, rd.heads, T), L, row_u4);
-    const bool ok = g < w.ag_count && M.valid[k];
+    const Dest at = dest_of<PACK>(sh, row_bytes, min(g, count - 1), group_row<PACK>(k, rd.heads, T), L);
+    const bool ok = g < count && M.valid[k];
     akl[k] = z; akh[k] = z; av0[k] = z; av1[k] = z;
     if (DOK) {
-      akl[k] = ld16<NTL>(ok && M.template kok<PACK>(L, k) ? pk + at.k + L.klo : idle_k);
-      akh[k] = ld16<NTL>(ok && M.template kok<PACK>(L, k) ? pk + at.k + L.khi : idle_k + 8);
+      akl[k] = ld16<NTL>(ok && M.template kok<PACK>(L, k) ? chunk_at(pk, at.k, L.klo) : idle_k);
+      akh[k] = ld16<NTL>(ok && M.template kok<PACK>(L, k) ? chunk_at(pk, at.k, L.khi) : idle_k + 8);
     }
     if (DOV) {
-      av0[k] = ld16<NTL>(ok && M.template v0ok<PACK>(L, k) ? pv + at.v0 + L.v0 : idle_v);
-      av1[k] = ld16<NTL>(ok && M.template v1ok<PACK>(L, k) ? pv + at.v1 + L.v1 : idle_v);
+      av0[k] = ld16<NTL>(ok && M.template v0ok<PACK>(L, k) ? chunk_at(pv, at.v0, L.v0) : idle_v);
+      av1[k] = ld16<NTL>(ok && M.template v1ok<PACK>(L, k) ? chunk_at(pv, at.v1, L.v1) : idle_v);
     }
   };
 #pragma unroll
   for (int k = 0; k < RPW; ++k) { request(0, k); __builtin_amdgcn_sched_barrier(0); }   // in the order the loop uses them
-  for (int g = 0; g < w.ag_count; ++g) {
+  bool special[RPW];
+#pragma unroll
+  for (int k = 0; k < RPW; ++k)
+    special[k] = ((int)chunk_special(M.kl[k]) | (int)chunk_special(M.kh[k]) | (int)chunk_special(M.v0[k]) | (int)chunk_special(M.v1[k])) != 0;
+  for (int g = 0; g < count; ++g) {
     float c[8], s[8];
     if (DOK && !SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
     bool differs = false;
@@ -555,9 +619,7 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
     if (__any(differs) && (threadIdx.x & 63) == 0) atomicOr(&sh.aux[g], 1);
   }
   lds_barrier();
-  if (threadIdx.x < w.ag_count) {
-    rd.flags[rd.oagents[w.ag_begin + threadIdx.x].flag_off + w.page] = (uint8_t)sh.aux[threadIdx.x];
-  }
+  if ((int)threadIdx.x < count) rd.flags[w.flat(rd, threadIdx.x)] = (uint8_t)sh.aux[threadIdx.x];
   stamp_end(rd, item);
 }
 
@@ -998,14 +1060,14 @@ __global__ __launch_bounds__(kBlock) void tdk_scatter_kernel(const RoundDev rd, 
 // each round of reads divides what is left of a list by that number.  One agent per thread halves it, and every read is a memory
 // latency in front of the item's first store: 37 agents x 2999 tokens, 4 heads, one plane after the other 127.5 -> 125.6 us,
 // 4 x 12 agents x 3001 tokens with moved diffs and own orders 104.2 -> 101.9, 13 agents x 19322 tokens, 4 heads 292 -> 275.
-__device__ __forceinline__ void find_listed(const RoundDev& rd, const DiffDev& d, const WorkItem& w, int32_t* listed) {
-  const int lg = w.ag_count <= 4 ? 6 : w.ag_count <= 8 ? 5 : w.ag_count <= 16 ? 4 : 3;      // kMaxGroup << 3 == kBlock
+__device__ __forceinline__ void find_listed(const RoundDev& rd, const DiffDev& d, const Item& w, int32_t* listed) {
+  const int count = w.count(), page = w.d.page, lg = count <= 4 ? 6 : count <= 8 ? 5 : count <= 16 ? 4 : 3;      // kMaxGroup << 3 == kBlock
   const int g = threadIdx.x >> lg, lanes = 1 << lg, l = threadIdx.x & (lanes - 1), shift = threadIdx.x & 63 & ~(lanes - 1);
   const uint64_t mine = (lanes == 64 ? ~0ull : (1ull << lanes) - 1ull) << shift;
   const int32_t* v = d.idx;
   int n = 0;
-  if (g < w.ag_count) {
-    const int a = rd.order[w.ag_begin + g];
+  if (g < count) {
+    const int a = w.agent(rd, g);
     int64_t lo = d.offset[a];
     int64_t hi = lo + d.count[a];
     if (lo < 0) lo = 0;
@@ -1017,20 +1079,20 @@ __device__ __forceinline__ void find_listed(const RoundDev& rd, const DiffDev& d
   while (__any(n > 0)) {
     const int stride = (n + lanes - 1) >> lg, i = l * stride;
     const int x = i < n ? v[i] : 0x7fffffff;
-    const uint64_t below = __ballot(x < w.page) & mine;
-    found |= (__ballot(x == w.page) & mine) != 0;
+    const uint64_t below = __ballot(x < page) & mine;
+    found |= (__ballot(x == page) & mine) != 0;
     const int c = __popcll(below), skip = c ? (c - 1) * stride + 1 : n;
     v += skip;
     n = found ? 0 : max(min(stride - 1, n - skip), 0);
   }
-  if (l == 0 && g < w.ag_count) listed[g] = found;
+  if (l == 0 && g < count) listed[g] = found;
 }
 
 template <int RPW, bool PACK, bool IL, bool NT, int PM, bool SEG, bool Q>
 __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
                                                             const int n_scatter) {
   const int T = PACK ? rd.page_tokens : RPW * kWaves;
-  __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
+  __shared__ Shared<SEG> sh;
   __shared__ int s_item;
   constexpr bool DOK = (PM & 1) != 0, DOV = (PM & 2) != 0;
   if (!Q && (int)blockIdx.x >= rd.dyn_begin + rd.dyn_count) {
@@ -1044,20 +1106,22 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
   }
   const Lane L = lane_geometry<PACK>(rd.heads, T);
   if (rd.nontemporal & 64) sweep_masters(rd, io, DOK, DOV);
-  const int64_t row_u4 = (int64_t)rd.heads * 16;
+  const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
   u32x4* pk = io.pool_k;
   u32x4* pv = io.pool_v;
   Items<Q> items;
   for (int item = items.first(rd, &s_item); item >= 0; item = items.next(rd, &s_item)) {
     stamp_begin(rd, item);
-    const WorkItem w = items.at(rd, item);
-    stage_group(rd, w, T, sh);
+    const Item w(items.list(rd), item);
+    Asked<SEG> asked;
+    ask_group(rd, w, T, sh, asked);
     MasterRows<RPW> M;
     load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
     find_listed(rd, d, w, sh.aux);
+    put_group(rd, w, T, sh, asked);
     lds_barrier();
     items.prefetch(rd);
-    for (int g = 0; g < w.ag_count; ++g) {
+    for (int g = 0; g < w.count(); ++g) {
       if (sh.aux[g] != 0) continue;   // listed in the diff: the scatter kernel writes this page
       float c[8], s[8];
       if (DOK && !SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
@@ -1065,16 +1129,16 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
       for (int k = 0; k < RPW; ++k) {
         if (!M.valid[k]) continue;
         const int r = group_row<PACK>(k, rd.heads, T);
-        const Dest to = dest_of<PACK>(sh, T, g, r, L, row_u4);
+        const Dest to = dest_of<PACK>(sh, row_bytes, g, r, L);
         if (DOK && M.template kok<PACK>(L, k)) {
           if (SEG) load_tab<IL>(sh, g, PACK ? r + L.rk : r, L.jb, c, s);
           u32x4 olo, ohi;
           rotate16<IL>(M.kl[k], M.kh[k], c, s, olo, ohi);
-          st16<NT>(pk + to.k + L.klo, olo);
-          st16<NT>(pk + to.k + L.khi, ohi);
+          st16<NT>(chunk_at(pk, to.k, L.klo), olo);
+          st16<NT>(chunk_at(pk, to.k, L.khi), ohi);
         }
-        if (DOV && M.template v0ok<PACK>(L, k)) st16<NT>(pv + to.v0 + L.v0, M.v0[k]);
-        if (DOV && M.template v1ok<PACK>(L, k)) st16<NT>(pv + to.v1 + L.v1, M.v1[k]);
+        if (DOV && M.template v0ok<PACK>(L, k)) st16<NT>(chunk_at(pv, to.v0, L.v0), M.v0[k]);
+        if (DOV && M.template v1ok<PACK>(L, k)) st16<NT>(chunk_at(pv, to.v1, L.v1), M.v1[k]);
       }
     }
     stamp_end(rd, item);
@@ -1125,16 +1189,19 @@ __device__ __forceinline__ float row_sum_to_last_lane(float v, int width) {
 template <int RPW, bool PACK, bool IL, bool SEG, bool NTL>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4 ? 3 : 1))) void tdk_keydiff_kernel(const RoundDev rd, const LayerDev io, const PlanDev pl) {
   const int T = PACK ? rd.page_tokens : RPW * kWaves;
-  __shared__ std::conditional_t<SEG, GroupSharedSeg, GroupShared> sh;
+  __shared__ Shared<SEG> sh;
   __shared__ float s_score[kMaxGroup][PACK ? 32 : RPW * kWaves];
   const Lane L = lane_geometry<PACK>(rd.heads, T);
-  const int64_t row_u4 = (int64_t)rd.heads * 16;
+  const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
   const u32x4* pk = io.pool_k;
-  const WorkItem w = rd.rwork[blockIdx.x];
-  stage_group(rd, w, T, sh);
+  const Item w(rd.rwork, blockIdx.x);
+  const int count = w.count();
+  Asked<SEG> asked;
+  ask_group(rd, w, T, sh, asked);
   MasterRows<RPW> M;
   load_master<RPW, PACK, false>(rd, io, w, T, L, M);
-  if (threadIdx.x < w.ag_count) sh.aux[threadIdx.x] = rd.oagents[w.ag_begin + threadIdx.x].score_off;
+  put_group(rd, w, T, sh, asked);
+  if ((int)threadIdx.x < count) sh.aux[threadIdx.x] = w.score(rd, threadIdx.x);
   lds_barrier();
   // Rolling requests: row k of the next agent is asked for as soon as row k of this one has been used, into the
   // registers that just became free, so a wavefront keeps its eight 16-byte loads per lane in flight all the
@@ -1142,18 +1209,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4
   // that has nothing to fetch (a row past the span, a lane past the heads, the agent after the last) reads the
   // first row of the master page instead, and its result is not used; with straight-line code the compiler
   // counts the outstanding loads exactly and waits for the oldest pair only.
-  const u32x4* idle = io.master_k + (rd.sess[w.session].master_row0 + (int64_t)w.page * T) * row_u4 + L.jb;
+  const u32x4* idle = io.master_k + w.d.row0 * ((int64_t)rd.heads * 16) + L.jb;
   u32x4 akl[RPW], akh[RPW];
   auto request = [&](int g, int k) {
-    const int64_t base = dest_row(sh, T, max(min(g, w.ag_count - 1), 0), group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0)) * row_u4;
-    const bool ok = g < w.ag_count && M.valid[k] && M.template kok<PACK>(L, k);
-    const u32x4* lo = ok ? pk + base + L.klo : idle;
-    const u32x4* hi = ok ? pk + base + L.khi : idle + 8;
+    const int64_t base = dest_row(sh, row_bytes, min(g, count - 1), group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0));
+    const bool ok = g < count && M.valid[k] && M.template kok<PACK>(L, k);
+    const u32x4* lo = ok ? chunk_at(pk, base, L.klo) : idle;
+    const u32x4* hi = ok ? chunk_at(pk, base, L.khi) : idle + 8;
     akl[k] = ld16<NTL>(lo); akh[k] = ld16<NTL>(hi);
   };
 #pragma unroll
   for (int k = 0; k < RPW; ++k) { request(0, k); __builtin_amdgcn_sched_barrier(0); }   // in the order the loop uses them
-  for (int g = 0; g < w.ag_count; ++g) {
+  for (int g = 0; g < count; ++g) {
     float c[8], s[8];
     if (!SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
 #pragma unroll
@@ -1176,10 +1243,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4
     }
   }
   lds_barrier();
-  const int rows = min(T, rd.sess[w.session].span - w.page * T);
-  for (int i = threadIdx.x; i < w.ag_count * T; i += kBlock) {
+  const int rows = w.rows();
+  for (int i = threadIdx.x; i < count * T; i += kBlock) {
     const int g = T == 16 ? i >> 4 : i >> 5, r = i & (T - 1);
-    if (r < rows) pl.score[sh.aux[g] + w.page * T + r] = s_score[g][r];
+    if (r < rows) pl.score[sh.aux[g] + r] = s_score[g][r];
   }
 }
 
@@ -1518,6 +1585,12 @@ template <class F> static void with_rows(const RoundDev& rd, F f) {
 template <class F> static void with_bool(bool b, F f) { if (b) f(std::true_type{}); else f(std::false_type{}); }
 template <class F> static void with_planes(int planes, F f) {
   if (planes == 1) f(ic<1>{}); else if (planes == 2) f(ic<2>{}); else f(ic<3>{});
+}
+
+hipError_t launch_places(const RoundDev& rd, PlaceDev* places, hipStream_t st) {
+  if (rd.n_agents == 0) return hipSuccess;
+  hipLaunchKernelGGL(tdk_places_kernel, dim3((unsigned)rd.n_agents), dim3(kBlock), 0, st, rd, places);
+  return hipGetLastError();
 }
 
 hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t st) {

@@ -258,6 +258,28 @@ void plan_work(const std::vector<PlanSession>& sessions, int group, bool taper, 
   }
 }
 
+void plan_items(const std::vector<PlanSession>& sessions, const std::vector<int32_t>& order, const std::vector<AgentDev>& agents, int page_tokens,
+                const std::vector<WorkItem>& work, std::vector<ItemDev>& items) {
+  items.reserve(items.size() + work.size());
+  for (const WorkItem& w : work) {
+    const PlanSession& s = sessions[(size_t)w.session];
+    const int32_t first = order[(size_t)w.ag_begin], m0 = w.page * page_tokens;
+    bool consecutive = true;
+    for (int32_t g = 1; g < w.ag_count; ++g) consecutive = consecutive && order[(size_t)(w.ag_begin + g)] == first + g;
+    ItemDev it{};
+    it.row0 = s.master_row0 + m0;
+    it.page = w.page;
+    it.counts = w.ag_count | std::min(page_tokens, s.span - m0) << 8;
+    it.agent0 = consecutive ? first : -1;
+    it.order0 = w.ag_begin;
+    it.flat0 = agents[(size_t)first].flag_off + w.page;
+    it.pages = s.pages;
+    it.score0 = agents[(size_t)first].score_off + m0;
+    it.span = s.span;
+    items.push_back(it);
+  }
+}
+
 int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels, int64_t page_bytes, int n_cus, int planes) {
   // Measured on MI355X: about 9 agents per work item is the best trade between re-reads of the
   // master page (one per work item, served by the XCD's L2) and the number of work items; rounds

@@ -54,6 +54,9 @@ tdk_status plan_round(const tdk_model* model, const tdk_session* sessions, int32
 // items grouped by that XCD (queue x = queued[q_begin[x] .. q_begin[x + 1])).
 void plan_work(const std::vector<PlanSession>& sessions, int group, bool taper, std::vector<WorkItem>& work);
 void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queued, int32_t (&q_begin)[9]);
+// A work list as the kernels read it, added to `items`.  order: agent ids grouped by session; agents: their descriptors, in the caller's order
+void plan_items(const std::vector<PlanSession>& sessions, const std::vector<int32_t>& order, const std::vector<AgentDev>& agents, int page_tokens,
+                const std::vector<WorkItem>& work, std::vector<ItemDev>& items);
 // agents per work item when the caller names none; page_bytes: K and V of one page; planes: written by the call (2, or 1)
 int  plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels = false, int64_t page_bytes = 64 * 1024,
                      int n_cus = 256, int planes = 2);

@@ -19,6 +19,29 @@ struct WorkItem {
   int32_t ag_count;    // 1..kMaxGroup
 };
 
+// The same as the page kernels read it: one scalar read gives everything that the item's first accesses depend on.  A chain through
+// the item, its session and its agents to the block table is five reads deep, and each of them is a memory latency.
+struct alignas(16) ItemDev {
+  int64_t row0;        // the page's first row in master_k / master_v
+  int32_t page;        // master page number
+  int32_t counts;      // agents of the group, and from bit 8 on the page's rows inside the span
+  int32_t agent0;      // id of the first agent where the group's agents have consecutive ids, else -1
+  int32_t order0;      // the group's place in RoundDev::order
+  int32_t flat0;       // the first agent's (agent, page) pair, agents in descriptor order; the next agent's is `pages` later
+  int32_t pages;       // pages of the session
+  int32_t score0;      // the first agent's (agent, token) pair of the page's first token; the next agent's is `span` later
+  int32_t span;        // tokens of the session
+  int32_t pad[2];
+};
+
+// Where a master page lies in an agent's pool (identity layouts).
+struct alignas(16) PlaceDev {
+  int32_t pg0;         // physical page of its first token
+  int32_t pg1;         // the next logical page's physical page, -1 past the block table
+  int32_t off;         // row of the first token in pg0
+  int32_t pad;
+};
+
 struct SessionDev {
   int64_t master_row0;  // first row of this session in master_k / master_v
   int32_t span;         // S
