@@ -18,7 +18,6 @@ struct RoundDev {
   const AgentDev*   oagents; // the agents' descriptors grouped by session: oagents[i] = agents[order[i]]
   const int32_t*    order;   // agent ids grouped by session
   const int32_t*    bt;      // block-table slices, concatenated
-  const PlaceDev*   places;  // [agent_pages]: where each page of each agent lies (identity layouts; else NULL)
   const float*      tab;     // [n_agents][2][64]: cos then sin of the agent's delta
   const float*      tab_diff;  // [n_agents][2][64]: same for dst_pos0 - diff_pos0 (payload re-rotation)
   // general block layouts (some agent has its own order of the shared blocks); all NULL otherwise
@@ -50,6 +49,7 @@ struct RoundDev {
   int32_t max_span;          // longest span of a session with agents
   int32_t diff_moved;        // some agent's stored diff sits at other positions: its K rows are turned on restore
   int64_t master_rows;       // rows of master_k / master_v (all sessions)
+  const PlaceDev*   places;  // [agent_pages]: where each page of each agent lies (identity layouts; else NULL)
 };
 
 struct LayerDev {

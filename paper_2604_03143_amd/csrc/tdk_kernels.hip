@@ -93,8 +93,8 @@ __device__ __forceinline__ u32x4 ld16(const u32x4* p) {
 
 struct GroupShared {
   float   tab[kMaxGroup][2 * kHalf];  // cos[64], sin[64] of each agent of the group
-  int64_t b0[kMaxGroup];              // byte of row 0 of the page in a pool plane, for the rows on its first physical page
-  int64_t b1[kMaxGroup];              // the same for the rows on the next one (where row 0 would lie)
+  longlong2 b[kMaxGroup];             // byte of row 0 of the page in a pool plane: for the rows on its first physical page, and for
+                                      // those on the next one (where row 0 would lie)
   int32_t cut[kMaxGroup];             // first row on the next one
   int32_t aux[kMaxGroup];             // flag kernel: OR of the waves; decode: 1 if the page is listed
 };
@@ -142,32 +142,37 @@ struct Item {
 // with own orders and 32-token pages, restore 104 -> 102; drawn rounds up to 1.08 times.)
 struct AskedGroup { u32x4 place; float4 tab[2]; };
 
+// Wavefronts of a page kernel's workgroup: eight with two rows of every page each where that is faster (wide_reads, wide_writes), else four.
+__device__ __host__ constexpr int waves_of(int rpw, bool pack) { return !pack && rpw == 2 ? 2 * kWaves : kWaves; }
+
+template <int W>
 __device__ __forceinline__ void ask_group(const RoundDev& rd, const Item& it, const int, const GroupShared&, AskedGroup& a) {
   const int tid = threadIdx.x, n = it.count() - 1, q = tid & 31;
   a.place = reinterpret_cast<const u32x4*>(rd.places)[it.flat(rd, min(tid, n))];
   const float4* tab = reinterpret_cast<const float4*>(rd.tab);
   a.tab[0] = tab[(size_t)it.agent(rd, min(tid >> 5, n)) * (kHalf / 2) + q];
   a.tab[1] = a.tab[0];
-  if (n >= 8) a.tab[1] = tab[(size_t)it.agent(rd, min(8 + (tid >> 5), n)) * (kHalf / 2) + q];
+  if (n >= 2 * W) a.tab[1] = tab[(size_t)it.agent(rd, min(2 * W + (tid >> 5), n)) * (kHalf / 2) + q];
 }
 
+template <int W>
 __device__ __forceinline__ void put_group(const RoundDev& rd, const Item& it, const int T, GroupShared& sh, const AskedGroup& a) {
   const int tid = threadIdx.x, n = it.count(), q = tid & 31, g = tid >> 5;
   if (g < n) reinterpret_cast<float4*>(sh.tab[g])[q] = a.tab[0];
-  if (g + 8 < n) reinterpret_cast<float4*>(sh.tab[g + 8])[q] = a.tab[1];
-  for (int g2 = g + 16; g2 < n; g2 += 8)
+  if (g + 2 * W < n) reinterpret_cast<float4*>(sh.tab[g + 2 * W])[q] = a.tab[1];
+  for (int g2 = g + 4 * W; g2 < n; g2 += 2 * W)
     reinterpret_cast<float4*>(sh.tab[g2])[q] = reinterpret_cast<const float4*>(rd.tab)[(size_t)it.agent(rd, g2) * (kHalf / 2) + q];
   if (tid < n) {
     const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
     const int off = (int)a.place[2];
-    sh.b0[tid] = ((int64_t)(int32_t)a.place[0] * T + off) * row_bytes;
-    sh.b1[tid] = ((int64_t)(int32_t)a.place[1] * T + off - T) * row_bytes;
+    sh.b[tid] = make_longlong2(((int64_t)(int32_t)a.place[0] * T + off) * row_bytes, ((int64_t)(int32_t)a.place[1] * T + off - T) * row_bytes);
     sh.cut[tid] = T - off;
   }
 }
 
 struct AskedGroupSeg { u32x4 pt; int32_t row, sel; };
 
+template <int W>
 __device__ __forceinline__ void ask_group(const RoundDev& rd, const Item& it, const int T, const GroupSharedSeg&, AskedGroupSeg& a) {
   const int tid = threadIdx.x, n = it.count() - 1, lg = T == 16 ? 4 : 5;
   a.pt = reinterpret_cast<const u32x4*>(rd.pagetab)[it.flat(rd, min(tid >> 6, n))];
@@ -175,17 +180,18 @@ __device__ __forceinline__ void ask_group(const RoundDev& rd, const Item& it, co
   a.row = rd.rowmap[it.score(rd, min(tid >> lg, n)) + min(tid & (T - 1), it.rows() - 1)];
 }
 
+template <int W>
 __device__ __forceinline__ void put_group(const RoundDev& rd, const Item& it, const int T, GroupSharedSeg& sh, const AskedGroupSeg& a) {
   const int tid = threadIdx.x, n = it.count(), lg = T == 16 ? 4 : 5, which = (tid >> 5) & 1, q = tid & 31;
   const float4* tab = reinterpret_cast<const float4*>(rd.segtab);
   u32x4 pt = a.pt;
-  for (int g = tid >> 6; g < n; g += kBlock / 64) {
-    if (g >= kBlock / 64) pt = reinterpret_cast<const u32x4*>(rd.pagetab)[it.flat(rd, g)];
+  for (int g = tid >> 6; g < n; g += W) {
+    if (g >= W) pt = reinterpret_cast<const u32x4*>(rd.pagetab)[it.flat(rd, g)];
     reinterpret_cast<float4*>(sh.tab[g][which])[q] = tab[(size_t)(which ? pt[1] : pt[0]) * (kHalf / 2) + q];
   }
   int32_t row = a.row;
-  for (int i = tid; i < n << lg; i += kBlock) {
-    if (i >= kBlock) row = rd.rowmap[it.score(rd, i >> lg) + min(i & (T - 1), it.rows() - 1)];
+  for (int i = tid; i < n << lg; i += 64 * W) {
+    if (i >= 64 * W) row = rd.rowmap[it.score(rd, i >> lg) + min(i & (T - 1), it.rows() - 1)];
     sh.row[i >> lg][i & (T - 1)] = row;            // (a row past the span repeats the last one; nobody uses it)
   }
   if (tid < n) sh.sel[tid] = (uint32_t)a.sel;
@@ -250,10 +256,10 @@ __device__ __forceinline__ Lane lane_geometry(int H, int T) {
 }
 
 // The k-th group of rows of a wavefront: the first row of the page it covers.
-template <bool PACK>
+template <bool PACK, int W = kWaves>
 __device__ __forceinline__ int group_row(int k, int H, int T) {
   const int wave = threadIdx.x >> 6;
-  return PACK ? (wave + kWaves * k) * rows_per_access(H, T) : wave + kWaves * k;
+  return PACK ? (wave + kWaves * k) * rows_per_access(H, T) : wave + W * k;
 }
 
 __device__ __forceinline__ const float* tab_of(const GroupShared& sh, int g, int) { return sh.tab[g]; }
@@ -291,6 +297,7 @@ struct MasterRows {
 template <int RPW, bool PACK, bool LOADV = true, bool LOADK = true>
 __device__ __forceinline__ void load_master(const RoundDev& rd, const LayerDev& io, const Item& it, const int T,
                                             const Lane& L, MasterRows<RPW>& M) {
+  constexpr int W = waves_of(RPW, PACK);
   const int rows = it.rows();
   const uint32_t row_u4 = (uint32_t)rd.heads * 16u;
   const u32x4* mk = io.master_k + it.d.row0 * row_u4;
@@ -298,7 +305,7 @@ __device__ __forceinline__ void load_master(const RoundDev& rd, const LayerDev& 
   const uint32_t klo = L.kok ? L.klo : L.jb, v0 = L.v0ok ? L.v0 : 0, v1 = L.v1ok ? L.v1 : 0;
 #pragma unroll
   for (int k = 0; k < RPW; ++k) {
-    const int r = group_row<PACK>(k, rd.heads, T);
+    const int r = group_row<PACK, W>(k, rd.heads, T);
     M.valid[k] = r < rows;
     if (PACK) { M.kin[k] = r + L.rk < rows; M.v0in[k] = r + L.rv0 < rows; M.v1in[k] = r + L.rv1 < rows; }
     const u32x4 z = {0, 0, 0, 0};
@@ -312,20 +319,39 @@ __device__ __forceinline__ void load_master(const RoundDev& rd, const LayerDev& 
   }
 }
 
-// byte of row r (0..T-1) of the master page in a pool plane, for agent g of the group
-__device__ __forceinline__ int64_t dest_row(const GroupSharedSeg& sh, uint32_t row_bytes, int g, int r) { return (int64_t)sh.row[g][r] * row_bytes; }
-__device__ __forceinline__ int64_t dest_row(const GroupShared& sh, uint32_t row_bytes, int g, int r) {
-  return (r < sh.cut[g] ? sh.b0[g] : sh.b1[g]) + (uint32_t)r * row_bytes;
+// Waits for the master page here.  Left to its first uses, the wait for the V rows stands in the loop over the agents, where the
+// compiler does not see the streaming stores that count with the loads: every agent then waits for the stores of the one before.  Worth
+// it for one access per page and wavefront (174 agents x 233 tokens, 1 head, restore 8.8 -> 7.4 us; 40 x 8000, 2 heads, collect 66.8 -> 66.2);
+// with more of them that wait costs nothing or helps, as fewer pages are being written at a time (25 agents x 5000 tokens, restore 102.3
+// against 100.5 us; ten sessions 0.998 times).
+template <int RPW, bool V, bool K>
+__device__ __forceinline__ void have_master(MasterRows<RPW>& M) {
+#pragma unroll
+  for (int k = 0; k < RPW; ++k) {
+    if (K) asm volatile("" : "+v"(M.kl[k]), "+v"(M.kh[k]));
+    if (V) asm volatile("" : "+v"(M.v0[k]), "+v"(M.v1[k]));
+  }
 }
+
+// Where the rows of the master page lie for an agent of the group, read once per agent (a read of b0 or b1 behind every row's comparison, as
+// a conditional expression on LDS compiles, makes every row wait for LDS twice).
+struct Origin { longlong2 b; int32_t cut; };
+__device__ __forceinline__ Origin origin_of(const GroupShared& sh, int g) { return Origin{sh.b[g], sh.cut[g]}; }
+struct OriginSeg { const int32_t* row; };
+__device__ __forceinline__ OriginSeg origin_of(const GroupSharedSeg& sh, int g) { return OriginSeg{sh.row[g]}; }
+
+// byte of row r (0..T-1) of the page in a pool plane
+__device__ __forceinline__ int64_t dest_row(const OriginSeg& o, uint32_t row_bytes, int r) { return (int64_t)o.row[r] * row_bytes; }
+__device__ __forceinline__ int64_t dest_row(const Origin& o, uint32_t row_bytes, int r) { return (r < o.cut ? o.b.x : o.b.y) + (uint32_t)r * row_bytes; }
 
 // where a row group's rows lie: one row for all lanes, or (PACK) each chunk's own
 struct Dest { int64_t k, v0, v1; };
-template <bool PACK, class Sh>
-__device__ __forceinline__ Dest dest_of(const Sh& sh, uint32_t row_bytes, int g, int r, const Lane& L) {
+template <bool PACK, class O>
+__device__ __forceinline__ Dest dest_of(const O& o, uint32_t row_bytes, int r, const Lane& L) {
   Dest d;
-  d.k = dest_row(sh, row_bytes, g, PACK ? r + L.rk : r);
-  d.v0 = PACK ? dest_row(sh, row_bytes, g, r + L.rv0) : d.k;
-  d.v1 = PACK ? dest_row(sh, row_bytes, g, r + L.rv1) : d.k;
+  d.k = dest_row(o, row_bytes, PACK ? r + L.rk : r);
+  d.v0 = PACK ? dest_row(o, row_bytes, r + L.rv0) : d.k;
+  d.v1 = PACK ? dest_row(o, row_bytes, r + L.rv1) : d.k;
   return d;
 }
 // chunk c of the row at that byte
@@ -345,13 +371,13 @@ constexpr int kPrefetchBlocks = 1024;   // workgroups that take part in the mast
 // measured at about twice its byte share).
 // Not where all workgroups of the launch run at once: then every master read stands before the writes anyway, and the sweep is a wait in front of
 // them (4 agents x 256 tokens, collect, restore and store 24.0 -> 23.6 us).
-template <bool LOOPING>
+template <bool LOOPING, int W>
 __device__ __forceinline__ void sweep_masters(const RoundDev& rd, const LayerDev& io, bool k, bool v) {
   if (blockIdx.x >= kPrefetchBlocks || (!LOOPING && (int)gridDim.x <= 3 * rd.n_cus)) return;
   const size_t n16 = (size_t)rd.master_rows * rd.heads * 16;
   const unsigned nb = min((unsigned)gridDim.x, (unsigned)kPrefetchBlocks);
   u32x4 acc = {0, 0, 0, 0};
-  for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n16; i += (size_t)nb * kBlock) {
+  for (size_t i = (size_t)blockIdx.x * (64 * W) + threadIdx.x; i < n16; i += (size_t)nb * (64 * W)) {
     if (k) acc ^= io.master_k[i];
     if (v) acc ^= io.master_v[i];
   }
@@ -466,12 +492,13 @@ struct Items {
 };
 
 template <int RPW, bool PACK, bool IL, bool NT, bool SEG, bool Q>
-__global__ __launch_bounds__(kBlock) void tdk_rerotate_kernel(const RoundDev rd, const LayerDev io) {
-  const int T = PACK ? rd.page_tokens : RPW * kWaves;
+__global__ __launch_bounds__(64 * waves_of(RPW, PACK)) void tdk_rerotate_kernel(const RoundDev rd, const LayerDev io) {
+  constexpr int W = waves_of(RPW, PACK);
+  const int T = PACK ? rd.page_tokens : RPW * W;
   __shared__ Shared<SEG> sh;
   __shared__ int s_item;
   const Lane L = lane_geometry<PACK>(rd.heads, T);
-  if (rd.nontemporal & 32) sweep_masters<Q>(rd, io, true, true);
+  if (rd.nontemporal & 32) sweep_masters<Q, W>(rd, io, true, true);
   const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
   u32x4* pk = io.pool_k;
   u32x4* pv = io.pool_v;
@@ -480,22 +507,24 @@ __global__ __launch_bounds__(kBlock) void tdk_rerotate_kernel(const RoundDev rd,
     stamp_begin(rd, item);
     const Item w(items.list(rd), item);
     Asked<SEG> asked;
-    ask_group(rd, w, T, sh, asked);
+    ask_group<W>(rd, w, T, sh, asked);
     MasterRows<RPW> M;
     load_master<RPW, PACK>(rd, io, w, T, L, M);
-    put_group(rd, w, T, sh, asked);
+    put_group<W>(rd, w, T, sh, asked);
+    if (RPW == 1) have_master<RPW, true, true>(M);
     lds_barrier();
     items.prefetch(rd);
     stamp_mid(rd, item, 2);
     for (int g = 0; g < w.count(); ++g) {
       if (g == 1) stamp_mid(rd, item, 3);
       float c[8], s[8];
+      const auto from = origin_of(sh, g);
       if (!SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
 #pragma unroll
       for (int k = 0; k < RPW; ++k) {
         if (!M.valid[k]) continue;
-        const int r = group_row<PACK>(k, rd.heads, T);
-        const Dest to = dest_of<PACK>(sh, row_bytes, g, r, L);
+        const int r = group_row<PACK, W>(k, rd.heads, T);
+        const Dest to = dest_of<PACK>(from, row_bytes, r, L);
         if (M.template kok<PACK>(L, k)) {
           if (SEG) load_tab<IL>(sh, g, PACK ? r + L.rk : r, L.jb, c, s);
           u32x4 olo, ohi;
@@ -552,8 +581,9 @@ __device__ __forceinline__ bool special_values(uint32_t largest) { return (large
 
 // PM: planes that take part (bit 0 = K, bit 1 = V); 3 is the paired diff, 1 / 2 the single-plane diffs
 template <int RPW, bool PACK, bool IL, int PM, bool SEG, bool NTL>
-__global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, const LayerDev io, const float eps) {
-  const int T = PACK ? rd.page_tokens : RPW * kWaves;
+__global__ __launch_bounds__(64 * waves_of(RPW, PACK)) void tdk_flag_kernel(const RoundDev rd, const LayerDev io, const float eps) {
+  constexpr int W = waves_of(RPW, PACK);
+  const int T = PACK ? rd.page_tokens : RPW * W;
   constexpr bool DOK = (PM & 1) != 0, DOV = (PM & 2) != 0;
   __shared__ Shared<SEG> sh;
   const Lane L = lane_geometry<PACK>(rd.heads, T);
@@ -565,10 +595,10 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
   const Item w(rd.rwork, item);
   const int count = w.count();
   Asked<SEG> asked;
-  ask_group(rd, w, T, sh, asked);
+  ask_group<W>(rd, w, T, sh, asked);
   MasterRows<RPW> M;
   load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
-  put_group(rd, w, T, sh, asked);
+  put_group<W>(rd, w, T, sh, asked);
   if ((int)threadIdx.x < count) sh.aux[threadIdx.x] = 0;
   lds_barrier();
   // Rolling requests (see tdk_keydiff_kernel): the rows of the next agent are asked for as the rows of this one
@@ -579,8 +609,8 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
   const u32x4* idle_v = DOV ? io.master_v + first_row + (threadIdx.x & 15) : nullptr;
   const u32x4 z = {0, 0, 0, 0};
   u32x4 akl[RPW], akh[RPW], av0[RPW], av1[RPW];
-  auto request = [&](int g, int k) {
-    const Dest at = dest_of<PACK>(sh, row_bytes, min(g, count - 1), group_row<PACK>(k, rd.heads, T), L);
+  auto request = [&](const auto& from, int g, int k) {
+    const Dest at = dest_of<PACK>(from, row_bytes, group_row<PACK, W>(k, rd.heads, T), L);
     const bool ok = g < count && M.valid[k];
     akl[k] = z; akh[k] = z; av0[k] = z; av1[k] = z;
     if (DOK) {
@@ -593,7 +623,7 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
     }
   };
 #pragma unroll
-  for (int k = 0; k < RPW; ++k) { request(0, k); __builtin_amdgcn_sched_barrier(0); }   // in the order the loop uses them
+  for (int k = 0; k < RPW; ++k) { request(origin_of(sh, 0), 0, k); __builtin_amdgcn_sched_barrier(0); }   // in the order the loop uses them
   uint32_t largest = 0;
 #pragma unroll
   for (int k = 0; k < RPW; ++k) {
@@ -603,13 +633,14 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
   const bool special = special_values(largest);
   for (int g = 0; g < count; ++g) {
     float c[8], s[8];
+    const auto next = origin_of(sh, min(g + 1, count - 1));
     if (DOK && !SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
     bool differs = false;
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
       if (M.valid[k]) {
         u32x4 rlo = z, rhi = z;
-        if (DOK && SEG) load_tab<IL>(sh, g, group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
+        if (DOK && SEG) load_tab<IL>(sh, g, group_row<PACK, W>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
         if (DOK) rotate16<IL>(M.kl[k], M.kh[k], c, s, rlo, rhi);
         // rows whose bits all match the reference (the common case) need no fp32 compare
         uint32_t x = 0;
@@ -624,7 +655,7 @@ __global__ __launch_bounds__(kBlock) void tdk_flag_kernel(const RoundDev rd, con
           if (DOV && M.template v1ok<PACK>(L, k)) differs |= chunk_differs(av1[k], M.v1[k], eps);
         }
       }
-      request(g + 1, k);
+      request(next, g + 1, k);
     }
     if (__any(differs) && (threadIdx.x & 63) == 0) atomicOr(&sh.aux[g], 1);
   }
@@ -726,8 +757,9 @@ struct SlotShared {
   int64_t row[32];     // pool row of each row of the page, -1 past the span / not listed
 };
 
+template <int W = kWaves>
 __device__ __forceinline__ void find_owner(const DiffDev& d, int A, int64_t slot, SlotShared& sh) {
-  for (int a = threadIdx.x; a < A; a += kBlock)
+  for (int a = threadIdx.x; a < A; a += 64 * W)
     if (d.offset[a] <= slot && slot < d.offset[a + 1]) sh.owner = a;
 }
 
@@ -751,19 +783,19 @@ constexpr int kCopyBatch = 8;
 // nothing to fetch repeats one of its page.  NT: streaming stores; NTL: non-temporal loads.  (The gather streams both:
 // with caches that change from call to call a store of 180 agents x 2166 tokens, one page in ten listed, took 277 us with
 // ordinary loads and 263 streamed; 30 agents x 2000, one in five, 69 and 70.)  share: this workgroup's part of the slot, of 1 << lg_shares.
-template <bool TO_PAYLOAD, bool NT, bool NTL>
+template <bool TO_PAYLOAD, bool NT, bool NTL, int W = kWaves>
 __device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io, u32x4* slot_data, int p0, int p1, const SlotShared& sh,
                                           int share = 0, int lg_shares = 0) {
   const int row_u4 = rd.heads * 16, page_u4 = rd.page_tokens * row_u4, all = (p1 - p0) * page_u4;
   const int n = (all * (share + 1)) >> lg_shares;
   const uint32_t inv = 0xffffffffu / (uint32_t)row_u4 + 1u;      // i / row_u4 == __umulhi(i, inv) for i < 2^13 (row_u4 <= 128)
-  for (int i0 = ((all * share) >> lg_shares) + threadIdx.x; i0 < n; i0 += kBlock * kCopyBatch) {
+  for (int i0 = ((all * share) >> lg_shares) + threadIdx.x; i0 < n; i0 += 64 * W * kCopyBatch) {
     u32x4 v[kCopyBatch];
     u32x4* at[kCopyBatch];
     bool there[kCopyBatch];
 #pragma unroll
     for (int j = 0; j < kCopyBatch; ++j) {
-      const int i = min(i0 + j * kBlock, n - 1);
+      const int i = min(i0 + j * (64 * W), n - 1);
       const int plane = p0 + (i >= page_u4), q = i >= page_u4 ? i - page_u4 : i;
       const int r = (int)__umulhi((uint32_t)q, inv);
       const int64_t row = sh.row[r];
@@ -773,7 +805,7 @@ __device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io
     }
 #pragma unroll
     for (int j = 0; j < kCopyBatch; ++j) {
-      const int i = i0 + j * kBlock;
+      const int i = i0 + j * (64 * W);
       if (TO_PAYLOAD) {
         if (!there[j]) v[j] = u32x4{0, 0, 0, 0};
         if (i < n) st16<NT>(slot_data + i, v[j]);
@@ -785,8 +817,8 @@ __device__ __forceinline__ void copy_slot(const RoundDev& rd, const LayerDev& io
 }
 
 // batches of accesses in a slot (copy_slot)
-__device__ __host__ __forceinline__ int slot_batches(const RoundDev& rd, int planes) {
-  return (planes == 3 ? 2 : 1) * rd.page_tokens * rd.heads * 16 / (kBlock * kCopyBatch);
+__device__ __host__ __forceinline__ int slot_batches(const RoundDev& rd, int planes, int waves = kWaves) {
+  return (planes == 3 ? 2 : 1) * rd.page_tokens * rd.heads * 16 / (64 * waves * kCopyBatch);
 }
 
 // does a restore share its slots out? (scatter_slots)
@@ -934,13 +966,14 @@ struct ScatterShared {
 };
 
 // Workgroup `first` of `stride` workgroups: walks the payload slots first, first + stride, ...
-template <bool IL>
+template <bool IL, int W = kWaves>
 __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev& io, const DiffDev& d, const int planes,
                                               ScatterShared& ss, const int64_t first, const int64_t stride) {
   SlotShared& sh = ss.sh;
   float (&s_tab)[2][2 * kHalf] = ss.s_tab;
   uint32_t& s_sel = ss.s_sel;
   uint32_t& s_moved = ss.s_moved;
+  constexpr int kRows = 4 * kWaves / W;            // rows of a wavefront in flight: 16 of the workgroup, which divide the page
   const int T = rd.page_tokens;
   const int A = rd.n_agents;
   if (A == 0) return;
@@ -964,13 +997,13 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
   // the shifts small calls on one plane lost 1 to 3 %.)
   int lg_shares = 0;
   if (slots_shared(rd))
-    while ((2 << lg_shares) <= slot_batches(rd, planes) && total << (lg_shares + 1) <= stride) ++lg_shares;
+    while ((2 << lg_shares) <= slot_batches(rd, planes, W) && total << (lg_shares + 1) <= stride) ++lg_shares;
   for (int64_t unit = first; unit < total << lg_shares; unit += stride) {
     const int64_t slot = unit >> lg_shares;
     const int share = (int)unit & ((1 << lg_shares) - 1);
     if (threadIdx.x == 0) sh.owner = -1;
     __syncthreads();
-    find_owner(d, A, slot, sh);
+    find_owner<W>(d, A, slot, sh);
     __syncthreads();
     bool rot = false;
     int t0 = 0, t1 = 0;
@@ -1001,7 +1034,7 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
       }
       sh.row[threadIdx.x] = row;
     }
-    if (rot) {
+    if (rot && threadIdx.x < 4 * kHalf) {
       const int which = threadIdx.x >> 7, e = threadIdx.x & (2 * kHalf - 1);
       s_tab[which][e] = tabs[(size_t)(which ? t1 : t0) * (2 * kHalf) + e];
     }
@@ -1012,17 +1045,17 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
     if (p0 == 0 && rot) {
       // stored at another position: K rows are re-rotated, a wavefront per row, both members of a pair in one lane
       // (the page kernels' lane layout); four rows of the wavefront are requested before the first is used
-      for (int r0 = threadIdx.x >> 6; r0 < T; r0 += 4 * kWaves) {
-        u32x4 lo[4], hi[4];
+      for (int r0 = threadIdx.x >> 6; r0 < T; r0 += kRows * W) {
+        u32x4 lo[kRows], hi[kRows];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const u32x4* src = data + (r0 + kWaves * k) * row_u4;          // (T is a multiple of 16)
+        for (int k = 0; k < kRows; ++k) {
+          const u32x4* src = data + (r0 + W * k) * row_u4;          // (T is a multiple of 16)
           lo[k] = src[L.kok ? L.klo : 0];
           hi[k] = src[L.kok ? L.khi : 0];
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int r = r0 + kWaves * k;
+        for (int k = 0; k < kRows; ++k) {
+          const int r = r0 + W * k;
           const int64_t row = sh.row[r];
           const int which = (s_sel >> r) & 1u;
           if ((s_moved >> which) & 1u) {           // a run that did not move is a bit copy
@@ -1050,9 +1083,9 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
       data += page_u4;
     }
     if (p0 < p1) {
-      if (stream) copy_slot<false, true, true>(rd, io, data, p0, p1, sh, share, lg_shares);
-      else if (rd.nontemporal & 8) copy_slot<false, true, false>(rd, io, data, p0, p1, sh, share, lg_shares);
-      else copy_slot<false, false, false>(rd, io, data, p0, p1, sh, share, lg_shares);
+      if (stream) copy_slot<false, true, true, W>(rd, io, data, p0, p1, sh, share, lg_shares);
+      else if (rd.nontemporal & 8) copy_slot<false, true, false, W>(rd, io, data, p0, p1, sh, share, lg_shares);
+      else copy_slot<false, false, false, W>(rd, io, data, p0, p1, sh, share, lg_shares);
     }
     __syncthreads();
   }
@@ -1099,9 +1132,10 @@ __device__ __forceinline__ void find_listed(const RoundDev& rd, const DiffDev& d
 }
 
 template <int RPW, bool PACK, bool IL, bool NT, int PM, bool SEG, bool Q>
-__global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
+__global__ __launch_bounds__(64 * waves_of(RPW, PACK)) void tdk_decode_kernel(const RoundDev rd, const LayerDev io, const DiffDev d,
                                                             const int n_scatter) {
-  const int T = PACK ? rd.page_tokens : RPW * kWaves;
+  constexpr int W = waves_of(RPW, PACK);
+  const int T = PACK ? rd.page_tokens : RPW * W;
   __shared__ Shared<SEG> sh;
   __shared__ int s_item;
   constexpr bool DOK = (PM & 1) != 0, DOV = (PM & 2) != 0;
@@ -1111,11 +1145,11 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
     // page items drain, instead of paying for a launch of their own.  (On large rounds two launches are faster:
     // payload reads among the page items' writes cost more than the second launch.)
     __shared__ ScatterShared ss;
-    scatter_slots<IL>(rd, io, d, PM, ss, (int64_t)blockIdx.x - (rd.dyn_begin + rd.dyn_count), n_scatter);
+    scatter_slots<IL, W>(rd, io, d, PM, ss, (int64_t)blockIdx.x - (rd.dyn_begin + rd.dyn_count), n_scatter);
     return;
   }
   const Lane L = lane_geometry<PACK>(rd.heads, T);
-  if (rd.nontemporal & 64) sweep_masters<Q>(rd, io, DOK, DOV);
+  if (rd.nontemporal & 64) sweep_masters<Q, W>(rd, io, DOK, DOV);
   const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
   u32x4* pk = io.pool_k;
   u32x4* pv = io.pool_v;
@@ -1124,22 +1158,24 @@ __global__ __launch_bounds__(kBlock) void tdk_decode_kernel(const RoundDev rd, c
     stamp_begin(rd, item);
     const Item w(items.list(rd), item);
     Asked<SEG> asked;
-    ask_group(rd, w, T, sh, asked);
+    ask_group<W>(rd, w, T, sh, asked);
     MasterRows<RPW> M;
     load_master<RPW, PACK, DOV, DOK>(rd, io, w, T, L, M);
     find_listed(rd, d, w, sh.aux);
-    put_group(rd, w, T, sh, asked);
+    put_group<W>(rd, w, T, sh, asked);
+    if (RPW == 1) have_master<RPW, DOV, DOK>(M);
     lds_barrier();
     items.prefetch(rd);
     for (int g = 0; g < w.count(); ++g) {
       if (sh.aux[g] != 0) continue;   // listed in the diff: the scatter kernel writes this page
       float c[8], s[8];
+      const auto from = origin_of(sh, g);
       if (DOK && !SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
 #pragma unroll
       for (int k = 0; k < RPW; ++k) {
         if (!M.valid[k]) continue;
-        const int r = group_row<PACK>(k, rd.heads, T);
-        const Dest to = dest_of<PACK>(sh, row_bytes, g, r, L);
+        const int r = group_row<PACK, W>(k, rd.heads, T);
+        const Dest to = dest_of<PACK>(from, row_bytes, r, L);
         if (DOK && M.template kok<PACK>(L, k)) {
           if (SEG) load_tab<IL>(sh, g, PACK ? r + L.rk : r, L.jb, c, s);
           u32x4 olo, ohi;
@@ -1197,20 +1233,21 @@ __device__ __forceinline__ float row_sum_to_last_lane(float v, int width) {
 // rolling requests below (482 -> 415 us on 250 agents x 5000 tokens; at a budget of 128 registers the compiler
 // spills, and a reload from scratch waits for every load issued before it, so the kernel runs at 3 waves per SIMD).
 template <int RPW, bool PACK, bool IL, bool SEG, bool NTL>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4 ? 3 : 1))) void tdk_keydiff_kernel(const RoundDev rd, const LayerDev io, const PlanDev pl) {
-  const int T = PACK ? rd.page_tokens : RPW * kWaves;
+__global__ __launch_bounds__(64 * waves_of(RPW, PACK)) __attribute__((amdgpu_waves_per_eu(RPW <= 4 ? 3 : 1))) void tdk_keydiff_kernel(const RoundDev rd, const LayerDev io, const PlanDev pl) {
+  constexpr int W = waves_of(RPW, PACK);
+  const int T = PACK ? rd.page_tokens : RPW * W;
   __shared__ Shared<SEG> sh;
-  __shared__ float s_score[kMaxGroup][PACK ? 32 : RPW * kWaves];
+  __shared__ float s_score[kMaxGroup][PACK ? 32 : RPW * waves_of(RPW, PACK)];
   const Lane L = lane_geometry<PACK>(rd.heads, T);
   const uint32_t row_bytes = (uint32_t)rd.heads * (kHeadDim * 2);
   const u32x4* pk = io.pool_k;
   const Item w(rd.rwork, blockIdx.x);
   const int count = w.count();
   Asked<SEG> asked;
-  ask_group(rd, w, T, sh, asked);
+  ask_group<W>(rd, w, T, sh, asked);
   MasterRows<RPW> M;
   load_master<RPW, PACK, false>(rd, io, w, T, L, M);
-  put_group(rd, w, T, sh, asked);
+  put_group<W>(rd, w, T, sh, asked);
   if ((int)threadIdx.x < count) sh.aux[threadIdx.x] = w.score(rd, threadIdx.x);
   lds_barrier();
   // Rolling requests: row k of the next agent is asked for as soon as row k of this one has been used, into the
@@ -1221,21 +1258,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4
   // counts the outstanding loads exactly and waits for the oldest pair only.
   const u32x4* idle = io.master_k + w.d.row0 * ((int64_t)rd.heads * 16) + L.jb;
   u32x4 akl[RPW], akh[RPW];
-  auto request = [&](int g, int k) {
-    const int64_t base = dest_row(sh, row_bytes, min(g, count - 1), group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0));
+  auto request = [&](const auto& from, int g, int k) {
+    const int64_t base = dest_row(from, row_bytes, group_row<PACK, W>(k, rd.heads, T) + (PACK ? L.rk : 0));
     const bool ok = g < count && M.valid[k] && M.template kok<PACK>(L, k);
     const u32x4* lo = ok ? chunk_at(pk, base, L.klo) : idle;
     const u32x4* hi = ok ? chunk_at(pk, base, L.khi) : idle + 8;
     akl[k] = ld16<NTL>(lo); akh[k] = ld16<NTL>(hi);
   };
 #pragma unroll
-  for (int k = 0; k < RPW; ++k) { request(0, k); __builtin_amdgcn_sched_barrier(0); }   // in the order the loop uses them
+  for (int k = 0; k < RPW; ++k) { request(origin_of(sh, 0), 0, k); __builtin_amdgcn_sched_barrier(0); }   // in the order the loop uses them
   for (int g = 0; g < count; ++g) {
     float c[8], s[8];
+    const auto next = origin_of(sh, min(g + 1, count - 1));
     if (!SEG) load_tab<IL>(sh, g, 0, L.jb, c, s);
 #pragma unroll
     for (int k = 0; k < RPW; ++k) {
-      if (SEG) load_tab<IL>(sh, g, group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
+      if (SEG) load_tab<IL>(sh, g, group_row<PACK, W>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
       u32x4 rlo, rhi;
       rotate16<IL>(M.kl[k], M.kh[k], c, s, rlo, rhi);
       float acc = 0.f;
@@ -1246,15 +1284,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RPW <= 4
         acc = __builtin_fmaf(d0, d0, acc); acc = __builtin_fmaf(d1, d1, acc);
         acc = __builtin_fmaf(d2, d2, acc); acc = __builtin_fmaf(d3, d3, acc);
       }
-      request(g + 1, k);
+      request(next, g + 1, k);
       const int width = PACK ? 8 * rd.heads : 64;
       acc = row_sum_to_last_lane(L.kok ? acc : 0.f, width);
-      if ((threadIdx.x & (width - 1)) == width - 1 && (!PACK || L.kok)) s_score[g][group_row<PACK>(k, rd.heads, T) + (PACK ? L.rk : 0)] = acc;   // (no store to memory among the loads: the count of outstanding accesses stays exact)
+      if ((threadIdx.x & (width - 1)) == width - 1 && (!PACK || L.kok)) s_score[g][group_row<PACK, W>(k, rd.heads, T) + (PACK ? L.rk : 0)] = acc;   // (no store to memory among the loads: the count of outstanding accesses stays exact)
     }
   }
   lds_barrier();
   const int rows = w.rows();
-  for (int i = threadIdx.x; i < count * T; i += kBlock) {
+  for (int i = threadIdx.x; i < count * T; i += 64 * W) {
     const int g = T == 16 ? i >> 4 : i >> 5, r = i & (T - 1);
     if (r < rows) pl.score[sh.aux[g] + r] = s_score[g][r];
   }
@@ -1530,9 +1568,9 @@ __global__ __launch_bounds__(kBlock) void tdk_page_read_product_kernel(const u32
 // `extra` static workgroups behind the page items (decode's payload copies on small rounds); returns whether they
 // were launched (only the static form takes them).
 template <class KernelQ, class KernelS, class... Args>
-static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, KernelS static_kernel, bool half_pages, int extra, hipStream_t st, Args... args) {
-  int n = 0;
-  {
+static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, KernelS static_kernel, int threads, bool half_pages, int extra, hipStream_t st, Args... args) {
+  int n = 2;
+  if (threads == kBlock) {
     static std::mutex mu;
     static std::map<const void*, int> per_cu;
     std::lock_guard<std::mutex> lock(mu);
@@ -1548,8 +1586,8 @@ static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, Kernel
   const int64_t resident = (int64_t)n * std::max(rd.n_cus, 1);
   // long enough for the looping form: at least four items and at least 32 (agent, page) pairs per resident
   // workgroup (a round cut into many small items, such as one agent per item, is no longer than its pairs)
-  const bool large = (int64_t)rd.n_work >= 4 * resident && rd.agent_pages >= 32 * resident;
-  if ((rd.nontemporal & 128) && (large || (rd.nontemporal & 512))) {
+  const bool large = threads == kBlock && (int64_t)rd.n_work >= 4 * resident && rd.agent_pages >= 32 * resident;
+  if ((rd.nontemporal & 128) && (large || (threads == kBlock && (rd.nontemporal & 512)))) {
     // Two looping workgroups per compute unit, although three fit: memory is saturated with one per unit already,
     // and the fewer pages are being written at a time, the better DRAM takes it (batched250: decode 876 us with
     // three per unit, 868 with two, 860 with one; rerotate 958 / 953 / 962; `long` loses 7 % with one).
@@ -1571,7 +1609,7 @@ static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, Kernel
     rs.dyn_begin = rs.n_work - tail;
     rs.dyn_count = 2 * tail;
   }
-  hipLaunchKernelGGL(static_kernel, dim3((unsigned)(rs.dyn_begin + rs.dyn_count) + (ride ? (unsigned)extra : 0u)), dim3(kBlock), 0, st, rs, args...);
+  hipLaunchKernelGGL(static_kernel, dim3((unsigned)(rs.dyn_begin + rs.dyn_count) + (ride ? (unsigned)extra : 0u)), dim3((unsigned)threads), 0, st, rs, args...);
   return ride;
 }
 
@@ -1583,14 +1621,32 @@ template <class F> static void with_rpw(int page_tokens, F f) { if (page_tokens 
 // (37 agents x 2999 tokens, 4 heads, both planes stored and restored one at a time: 169 us with one row per access, 149
 // with two; drawn rounds with 1 or 2 heads up to 1.8 times); 3 heads keep one row (rows of 24 lanes do not divide the
 // page), 5 and more fill the wavefront by themselves.
-template <class F> static void with_rows(const RoundDev& rd, F f) {
+template <class F> static void with_rows(const RoundDev& rd, bool wide, F f) {
   const int H = rd.heads, T = rd.page_tokens;
-  if (H != 1 && H != 2 && H != 4) { with_rpw(T, [&](auto rpw) { f(rpw, std::false_type{}); }); return; }
+  if (H != 1 && H != 2 && H != 4) {
+    if (wide) f(ic<2>{}, std::false_type{});
+    else with_rpw(T, [&](auto rpw) { f(rpw, std::false_type{}); });
+    return;
+  }
   switch (T / (kWaves * rows_per_access(H, T))) {
     case 1: f(ic<1>{}, std::true_type{}); break;
     case 2: f(ic<2>{}, std::true_type{}); break;
     default: f(ic<4>{}, std::true_type{}); break;
   }
+}
+// Eight wavefronts per workgroup, two rows of every page each, instead of four with four rows?  16-token pages whose rows fill an access.
+//   Kernels that read: while every item has a compute unit to itself.  What an item takes is then what one of its wavefronts does one
+//   after the other (store of 40 to 100 pairs 14.1 -> 13.0 us, check layer of 40 to 270 13.0 -> 12.7; from one and a half items per unit on
+//   0.95 to 1.06 times, no rule found).
+//   Kernels that write both planes: launches of 6 (agent, page) pairs per compute unit and more whose items have several agents, up to
+//   those that loop.  Twice the wavefronts hide the items' starts, and an item's pages are written by as many (25 agents x 5000 tokens, collect
+//   98.1 -> 96.2 us, restore 100.5 -> 99.1; 2 x 35 x 949 57.5 -> 56.2; over 40 such launches 1.00 to 1.05).  Items of two agents end too
+//   soon for it (ten sessions of 2 x 1040 tokens 27.2 -> 28.6), and smaller launches have too few items (12 agents x 600 tokens, restore 9.5 -> 11.3).
+static bool wide_item_rows(const RoundDev& rd) { const int H = rd.heads; return H != 1 && H != 2 && H != 4 && rd.page_tokens == 16; }
+static bool wide_reads(const RoundDev& rd) { return wide_item_rows(rd) && rd.n_rwork <= rd.n_cus; }
+static bool wide_writes(const RoundDev& rd) {
+  const int64_t cus = rd.n_cus;
+  return wide_item_rows(rd) && !(rd.nontemporal & 512) && rd.agent_pages >= 6 * cus && rd.agent_pages < 64 * cus && 2 * rd.agent_pages >= 5 * (int64_t)rd.n_work;
 }
 template <class F> static void with_bool(bool b, F f) { if (b) f(std::true_type{}); else f(std::false_type{}); }
 template <class F> static void with_planes(int planes, F f) {
@@ -1605,11 +1661,12 @@ hipError_t launch_places(const RoundDev& rd, PlaceDev* places, hipStream_t st) {
 
 hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
-  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 1) != 0, [&](auto nt) {
+  with_rows(rd, wide_writes(rd), [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 1) != 0, [&](auto nt) {
     with_bool(rd.seg != 0, [&](auto sg) {
       constexpr int R = decltype(rpw)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
-      launch_write_pages(rd, tdk_rerotate_kernel<R, P, I, N, G, true>, tdk_rerotate_kernel<R, P, I, N, G, false>, false, 0, st, io);
+      constexpr bool kQueues = waves_of(R, P) == kWaves;
+      launch_write_pages(rd, tdk_rerotate_kernel<R, P, I, N, G, kQueues>, tdk_rerotate_kernel<R, P, I, N, G, false>, 64 * waves_of(R, P), false, 0, st, io);
     });
   }); }); });
   return hipGetLastError();
@@ -1617,10 +1674,10 @@ hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t s
 
 hipError_t launch_flag(const RoundDev& rd, const LayerDev& io, float eps, int planes, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
-  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_planes(planes, [&](auto pm) {
+  with_rows(rd, wide_reads(rd), [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_planes(planes, [&](auto pm) {
     with_bool(rd.seg != 0, [&](auto sg) { with_bool((rd.nontemporal & 4) != 0, [&](auto ntl) {
       hipLaunchKernelGGL((tdk_flag_kernel<decltype(rpw)::value, decltype(pack)::value, decltype(il)::value, decltype(pm)::value, decltype(sg)::value,
-                                          decltype(ntl)::value>), dim3(rd.n_rwork), dim3(kBlock), 0, st, rd, io, eps);
+                                          decltype(ntl)::value>), dim3(rd.n_rwork), dim3(64 * waves_of(decltype(rpw)::value, decltype(pack)::value)), 0, st, rd, io, eps);
     }); });
   }); }); });
   return hipGetLastError();
@@ -1654,19 +1711,21 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
                          hipStream_t st) {
   *scattered = false;
   if (rd.n_work == 0) return hipSuccess;
+  const bool wide = planes == 3 && wide_writes(rd);
   if (rd.n_agents == 0 || d.capacity == 0) scatter_blocks = 0;
   if (slots_shared(rd)) {
     // (three workgroups of the kernels for both planes fit a compute unit; the page items are launched with those that stand by for the
     // last fifth.  Of the kernels for one plane more fit, and no limit showed: 60 agents x 700 tokens, pages of 32, stored and restored
     // one plane at a time 109.7 us, 111.9 with a limit of four.)
     const int left = planes == 3 ? 3 * rd.n_cus - rd.n_work - rd.n_work / 5 : -1;
-    scatter_blocks = plan_copy_workgroups(scatter_blocks, slot_batches(rd, planes), rd.n_cus, left);
+    scatter_blocks = plan_copy_workgroups(scatter_blocks, slot_batches(rd, planes, wide ? 2 * kWaves : kWaves), rd.n_cus, left);
   }
-  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 2) != 0, [&](auto nt) {
+  with_rows(rd, wide, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool((rd.nontemporal & 2) != 0, [&](auto nt) {
     with_planes(planes, [&](auto pm) { with_bool(rd.seg != 0, [&](auto sg) {
       constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
-      *scattered = launch_write_pages(rd, tdk_decode_kernel<R, P, I, N, M, G, true>, tdk_decode_kernel<R, P, I, N, M, G, false>,
+      constexpr bool kQueues = waves_of(R, P) == kWaves;
+      *scattered = launch_write_pages(rd, tdk_decode_kernel<R, P, I, N, M, G, kQueues>, tdk_decode_kernel<R, P, I, N, M, G, false>, 64 * waves_of(R, P),
                                       planes != 3, scatter_blocks, st, io, d, scatter_blocks);
     }); });
   }); }); });
@@ -1682,10 +1741,10 @@ hipError_t launch_scatter(const RoundDev& rd, const LayerDev& io, const DiffDev&
 
 hipError_t launch_keydiff(const RoundDev& rd, const LayerDev& io, const PlanDev& pl, hipStream_t st) {
   if (rd.n_work == 0) return hipSuccess;
-  with_rows(rd, [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool(rd.seg != 0, [&](auto sg) {
+  with_rows(rd, wide_reads(rd), [&](auto rpw, auto pack) { with_bool(rd.interleaved != 0, [&](auto il) { with_bool(rd.seg != 0, [&](auto sg) {
     with_bool((rd.nontemporal & 4) != 0, [&](auto ntl) {
       hipLaunchKernelGGL((tdk_keydiff_kernel<decltype(rpw)::value, decltype(pack)::value, decltype(il)::value, decltype(sg)::value, decltype(ntl)::value>),
-                         dim3(rd.n_rwork), dim3(kBlock), 0, st, rd, io, pl);
+                         dim3(rd.n_rwork), dim3(64 * waves_of(decltype(rpw)::value, decltype(pack)::value)), 0, st, rd, io, pl);
     });
   }); }); });
   return hipGetLastError();
