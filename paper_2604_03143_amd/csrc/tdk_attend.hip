@@ -420,16 +420,18 @@ __device__ __forceinline__ void turn_back16(bf16x8 (&qf)[4], const float* tab, b
 }
 
 // A query row as it is, in the order of the B operands for the 32-row tiles: fragment kk of a lane holds elements
-// 16 kk + 8 hh .. + 7.  A negative scale's sign travels with the rows.
-__device__ __forceinline__ void raw_queries(const AttendDev& at, int64_t out, bool on, int lane, u32x4 (&raw)[8]) {
-  const uint32_t flip = at.q_flip ? 0x80008000u : 0u;
+// 16 kk + 8 hh .. + 7.  Only the loads: own_rows() is called where they are used, so that nothing in between waits for them.
+__device__ __forceinline__ void raw_queries(const AttendDev& at, int64_t out, int lane, u32x4 (&raw)[8]) {
   const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim);
-  const uint32_t keep = on ? 0xffffffffu : 0u;             // (a row that does not exist reads another and is zero)
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
-    const u32x4 v = qp[2 * kk + (lane >> 5)];
-    raw[kk] = u32x4{(v.x ^ flip) & keep, (v.y ^ flip) & keep, (v.z ^ flip) & keep, (v.w ^ flip) & keep};
-  }
+  for (int kk = 0; kk < 8; ++kk) raw[kk] = qp[2 * kk + (lane >> 5)];
+}
+// A negative scale's sign travels with the rows; a row that does not exist has read another and is zero.
+__device__ __forceinline__ void own_rows(const AttendDev& at, bool on, u32x4 (&raw)[8]) {
+  const uint32_t flip = at.q_flip ? 0x80008000u : 0u, keep = on ? 0xffffffffu : 0u;
+#pragma unroll
+  for (int kk = 0; kk < 8; ++kk)
+    raw[kk] = u32x4{(raw[kk].x ^ flip) & keep, (raw[kk].y ^ flip) & keep, (raw[kk].z ^ flip) & keep, (raw[kk].w ^ flip) & keep};
 }
 
 // Those rows turned back by the rotation whose table the wavefront's lanes hold (entries 2 lane and 2 lane + 1 of its
@@ -475,7 +477,8 @@ __device__ __forceinline__ void load_queries(const AttendDev& at, bool interleav
   float2 t2 = make_float2(1.f, 0.f);
   if (tab) t2 = reinterpret_cast<const float2*>(tab)[lane];
   u32x4 raw[8];
-  raw_queries(at, out, on, lane, raw);
+  raw_queries(at, out, lane, raw);
+  own_rows(at, on, raw);
   if (tab) {
     turn_queries(raw, interleaved, t2, lds_tab, lane, qf);
   } else {
@@ -1340,43 +1343,60 @@ __device__ __forceinline__ void rows_step(const unsigned char* Ks, const unsigne
 // is a chain of reads per tile.
 constexpr int kListedLds = 2 * kTile * kHeadDim * 2;
 
-template <bool SEGMOVED, class LoadQ>
-__device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d, const AttendDev& at, const SessionDev& sd, unsigned char* lds,
-                                            int h, const PageTab* pages, int seg_base, int64_t l0, int n_pages, int lane, bf16x8 (&qf)[8],
-                                            LoadQ load_q, RowState& st) {
-  if (n_pages <= 0) return;
-  unsigned char* Ks = lds;
-  unsigned char* Vs = lds + kTile * kHeadDim * 2;
-  const int T = rd.page_tokens, lg = T == 16 ? 4 : 5, n = lane & 31, hh = lane >> 5, st_row = lane >> 4, st_pc = lane & 15;
-  const int n_tok = n_pages * T;
-  // (offsets inside the chunk's part of the payload fit 32 bits: at most 2 x 1024 pages of 64 KB or less)
-  const u32x4* pay = d.payload + (l0 * 2 * T * rd.heads + h) * 16 + st_pc;
-  const uint32_t row_u = (uint32_t)rd.heads * 16u, page_u = (uint32_t)T * row_u;
-  u32x4 kreg[8], vreg[8];
-  int p_next = -1;
-  auto fetch = [&](int t0) __attribute__((always_inline)) {      // (a token past the list's end reads the last one: no branch around the loads)
-    p_next = t0 + n < n_tok ? d.idx[l0 + ((t0 + n) >> lg)] : -1;
+// 32 tokens of a list on their way to registers: four rows per access, sixteen lanes per 256-byte row.
+struct ListedTile {
+  u32x4 k[8], v[8];
+  int page;                                      // master page of token lane % 32 (-1: no such token)
+};
+struct ListedRows {
+  const u32x4* pay;                              // this lane's piece of the first row
+  const int32_t* idx;
+  uint32_t row_u, page_u;
+  int n_tok, last, lg, T;                        // last: the list's last token (0 for an empty list)
+  // elsewhere: memory to read where the list is empty
+  __device__ __forceinline__ ListedRows(const RoundDev& rd, const DiffDev& d, int h, int64_t l0, int n_pages, int lane, const void* elsewhere) {
+    T = rd.page_tokens;
+    lg = T == 16 ? 4 : 5;
+    n_tok = max(n_pages, 0) * T;
+    last = max(n_tok - 1, 0);
+    // (offsets inside the chunk's part of the payload fit 32 bits: at most 2 x 1024 pages of 64 KB or less)
+    pay = n_pages > 0 ? d.payload + (l0 * 2 * T * rd.heads + h) * 16 + (lane & 15) : reinterpret_cast<const u32x4*>(elsewhere);
+    idx = d.idx + l0;
+    row_u = n_pages > 0 ? (uint32_t)rd.heads * 16u : 0u;
+    page_u = (uint32_t)T * row_u;
+  }
+  __device__ __forceinline__ void fetch(int t0, int lane, ListedTile& x) const {      // (a token past the list's end reads the last one: no branch around the loads)
+    x.page = t0 + (lane & 31) < n_tok ? idx[(t0 + (lane & 31)) >> lg] : -1;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int t = min(t0 + 4 * j + st_row, n_tok - 1);
+      const int t = min(t0 + 4 * j + (lane >> 4), last);
       const u32x4* p = pay + (uint32_t)(t >> lg) * 2u * page_u + (uint32_t)(t & (T - 1)) * row_u;
-      kreg[j] = p[0];
-      vreg[j] = p[page_u];
+      x.k[j] = p[0];
+      x.v[j] = p[page_u];
     }
-  };
-  fetch(0);
-  if (!SEGMOVED) load_q(0);
+  }
+};
+
+// x: the first tile, asked for earlier; qf: the rows that it meets (SEGMOVED: load_q)
+template <bool SEGMOVED, class LoadQ>
+__device__ __forceinline__ void rows_listed(const AttendDev& at, const SessionDev& sd, unsigned char* lds, const ListedRows& list, ListedTile& x,
+                                            const PageTab* pages, int seg_base, int lane, bf16x8 (&qf)[8], LoadQ load_q, RowState& st) {
+  if (list.n_tok <= 0) return;
+  unsigned char* Ks = lds;
+  unsigned char* Vs = lds + kTile * kHeadDim * 2;
+  const int T = list.T, lg = list.lg, n_tok = list.n_tok, n = lane & 31, hh = lane >> 5, st_row = lane >> 4, st_pc = lane & 15;
+  auto fetch = [&](int t0) __attribute__((always_inline)) { list.fetch(t0, lane, x); };
   int loaded = -1;                               // SEGMOVED: the segment whose turned rows qf holds
   for (int t0 = 0; t0 < n_tok; t0 += kTile) {
     wave_sync();                                 // the previous tile has been consumed
     int seg_cur = 0;
     bool ok = false;
     {
-      const int m = (p_next << lg) + ((t0 + n) & (T - 1));
-      if (p_next >= 0 && p_next < sd.pages && m < sd.span) {
+      const int m = (x.page << lg) + ((t0 + n) & (T - 1));
+      if (x.page >= 0 && x.page < sd.pages && m < sd.span) {
         ok = true;
         if (SEGMOVED) {
-          const PageTab pt = pages[p_next];
+          const PageTab pt = pages[x.page];
           seg_cur = (((uint32_t)pt.z >> (m & (T - 1))) & 1u ? pt.y : pt.x) - seg_base;
         }
       }
@@ -1384,26 +1404,26 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
     const uint32_t valid = (uint32_t)__ballot(ok);
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      u32x4 v = vreg[j];
+      u32x4 v = x.v[j];
       if (!((valid >> (4 * j + st_row)) & 1u)) v = u32x4{0, 0, 0, 0};      // rows of tokens that do not count
-      *reinterpret_cast<u32x4*>(Ks + k_place(4 * j + st_row, st_pc)) = kreg[j];
+      *reinterpret_cast<u32x4*>(Ks + k_place(4 * j + st_row, st_pc)) = x.k[j];
       *reinterpret_cast<u32x4*>(Vs + v_place(4 * j + st_row, st_pc)) = v;
     }
     wave_sync();                                 // the tile is complete
     if (!SEGMOVED && t0 + kTile < n_tok) fetch(t0 + kTile);
     f32x16 s[1];
-    auto scores = [&](f32x16 (&x)[1]) __attribute__((always_inline)) {
+    auto scores = [&](f32x16 (&sc)[1]) __attribute__((always_inline)) {
       f32x16 y;                                  // two chains of products
 #pragma unroll
-      for (int i = 0; i < 16; ++i) { x[0][i] = 0.f; y[i] = 0.f; }
+      for (int i = 0; i < 16; ++i) { sc[0][i] = 0.f; y[i] = 0.f; }
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         const bf16x8 a = k_operand(Ks, kk, n, hh);
         if (kk & 1) y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], y, 0, 0, 0);
-        else x[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], x[0], 0, 0, 0);
+        else sc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], sc[0], 0, 0, 0);
       }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) x[0][i] += y[i];
+      for (int i = 0; i < 16; ++i) sc[0][i] += y[i];
     };
     if (!SEGMOVED) {
       scores(s);
@@ -1419,12 +1439,12 @@ __device__ __forceinline__ void rows_listed(const RoundDev& rd, const DiffDev& d
         rest &= ~mine;
         if (cand != loaded) load_q(cand);        // (lists ascend: the segment of the last tile often goes on in this one)
         loaded = cand;
-        f32x16 x[1];
-        scores(x);
+        f32x16 one[1];
+        scores(one);
         const uint32_t ms = mine >> (4 * hh);    // score i of a lane belongs to token 8 (i / 4) + 4 hh + i % 4
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if ((ms >> (8 * (i >> 2) + (i & 3))) & 1u) s[0][i] = x[0][i];
+          if ((ms >> (8 * (i >> 2) + (i & 3))) & 1u) s[0][i] = one[0][i];
       }
       // (only now, although the rows arrive later: in flight during the loop above they cost registers that spill)
       if (t0 + kTile < n_tok) fetch(t0 + kTile);
@@ -1451,7 +1471,7 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   const int wb = rest % rg.blocks, sc = rest / rg.blocks;
   const int n_ch = max(at.n_chunks, 1);
   const int s_local = sc / n_ch, chunk = sc - s_local * n_ch, session = rg.session0 + s_local;
-  const SessionDev sd = rd.sess[session];
+  const SessionDev sd = scalar_read(rd.sess + session);
   if (wb * kWaves >= sd.n_agents * rg.per_agent) return;
   const int T = rd.page_tokens;
   const int tok_begin = chunk * at.chunk_tokens;
@@ -1462,7 +1482,7 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   const int a_local = (wb * kWaves + wave) / rg.per_agent;
   const int r0 = (wb * kWaves + wave - a_local * rg.per_agent) * kRowsPerWave;
   const bool active = a_local < sd.n_agents;            // (a wavefront without rows only helps to stage the tiles)
-  const int agent = active ? __builtin_amdgcn_readfirstlane(rd.order[sd.order_begin + a_local]) : 0;
+  const int agent = active ? scalar_read(rd.order + sd.order_begin + a_local) : 0;
   const int per_agent_rows = at.n_q * at.group;
 
   // this lane's query row
@@ -1473,11 +1493,17 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   auto load_q = [&](const float* tab) __attribute__((always_inline)) {      // tab: turn the rows back by this rotation (NULL: as they are)
     load_queries(at, rd.interleaved, out, row_ok, tab, sh.tab[wave], lane, qf);
   };
-  const int moved = __builtin_amdgcn_readfirstlane(rd.agents[agent].diff_rot);
+  const int moved = scalar_read(&rd.agents[agent].diff_rot);
+  // the agent's list, by scalar reads too: a vector read would wait for the tiles asked for below
+  int64_t lo = scalar_read(d.offset + agent), hi = lo + scalar_read(d.count + agent);
+  if (lo < 0) lo = 0;
+  if (hi > d.capacity) hi = d.capacity;
+  const int len = hi > lo ? (int)min<int64_t>(hi - lo, 1 << 30) : 0;
+  const int32_t* list = d.idx + lo;
   int seg_base = 0, seg_n = 1, seg_k = 0;
   if (SEG && active) {
-    seg_base = __builtin_amdgcn_readfirstlane(rd.seg_off[agent]);
-    seg_n = __builtin_amdgcn_readfirstlane(rd.seg_off[agent + 1]) - seg_base;
+    seg_base = scalar_read(rd.seg_off + agent);
+    seg_n = scalar_read(rd.seg_off + agent + 1) - seg_base;
   }
 
   RowState st;
@@ -1512,9 +1538,11 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   // end: with this and the rows written whole, 2 x 32 agents x 132 tokens, 128 rows 25.8 -> 23.5 us, 189 agents x 68 tokens, 256 rows
   // 121.7 -> 114.9; the tiles alone asked for first: no gain, they then delay the rows.)
   u32x4 raw0[8];
+  int first = 0x7fffffff;                                // the first 64 entries of the list
   if (tok_end > tok_begin) {
     if (active) {
-      raw_queries(at, out, row_ok, lane, raw0);
+      if (lane < len) first = list[lane];
+      raw_queries(at, out, lane, raw0);
       if (SEG) window(0);
       else seg_tab = reinterpret_cast<const float2*>(rd.tab + (size_t)agent * (2 * kHalf))[lane];
     }
@@ -1527,12 +1555,7 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   int64_t l0 = 0, l1 = 0;
   const int pg0 = tok_begin / T;
   if (active && tok_end > tok_begin) {
-    int64_t lo = d.offset[agent], hi = lo + d.count[agent];
-    if (lo < 0) lo = 0;
-    if (hi > d.capacity) hi = d.capacity;
-    const int32_t* list = d.idx + lo;
-    const int len = hi > lo ? (int)min<int64_t>(hi - lo, 1 << 30) : 0, pg1 = (tok_end - 1) / T + 1;
-    const int first = lane < len ? list[lane] : 0x7fffffff;
+    const int pg1 = (tok_end - 1) / T + 1;
     if (lane < kRowsMaskWords) sh.mask[wave][lane] = 0u;
     int i0, i1;
     if (len <= 64) {
@@ -1546,9 +1569,14 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     l0 = lo + i0;
     l1 = lo + i1;
     wave_sync();
-    for (int i = i0 + lane; i < i1; i += 64) {
-      const int rel = list[i] - pg0;
+    auto mark = [&](int page) __attribute__((always_inline)) {
+      const int rel = page - pg0;
       if (rel >= 0 && rel < kRowsMaxPages) atomicOr(&sh.mask[wave][rel >> 5], 1u << (rel & 31));
+    };
+    if (len <= 64) {
+      if (lane >= i0 && lane < i1) mark(first);
+    } else {
+      for (int i = i0 + lane; i < i1; i += 64) mark(list[i]);
     }
     wave_sync();
   }
@@ -1600,7 +1628,8 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
       const int b = seg_next - p;                        // the first token of the step that belongs to the next segment
       {
         u32x4 raw[8];
-        raw_queries(at, out, row_ok, lane, raw);
+        raw_queries(at, out, lane, raw);
+        own_rows(at, row_ok, raw);
         enter(seg_next, raw);
       }
       if (b >= kBigTile) break;
@@ -1626,6 +1655,7 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     // starts of this step and of the next one
     int p1 = tok_begin, p2 = min(p1 + kBigTile, tok_end);
     if (active) {
+      own_rows(at, row_ok, raw0);
       if (SEG) {
         seg_k = -1;
         enter(p1, raw0);
@@ -1676,6 +1706,8 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
         odd ^= 1;
       }
     } else {
+      // (A last step without scores, with the first listed tile on its way to the registers that it leaves free, gains 3 to 6 % on spans
+      // of a few steps, but the steps before it lose 2.5 %, which 25 agents x 5000 tokens, 320 rows do not get back.)
       while (p1 < tok_end) {
         step(0, s0, s1);
         if (p1 < tok_end) step(1, s1, s0);
@@ -1686,15 +1718,30 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   // ---- the listed pages, from the payload ----
   if (active) {
     unsigned char* lds = sh.k[0] + wave * kListedLds;
+    const ListedRows listed(rd, d, h, l0, (int)(l1 - l0), lane, mk);
     // Segments that have moved together meet the same rows, so one turn serves the whole list; only lists whose segments have
     // moved by different distances need a turn per segment.
+    ListedTile tile;
     if (SEG && APART && moved == 1) {
-      rows_listed<true>(rd, d, at, sd, lds, h, rd.pagetab + rd.agents[agent].flag_off, seg_base, l0, (int)(l1 - l0), lane, qf,
+      listed.fetch(0, lane, tile);
+      rows_listed<true>(at, sd, lds, listed, tile, rd.pagetab + rd.agents[agent].flag_off, seg_base, lane, qf,
                             [&](int k) __attribute__((always_inline)) { load_q(rd.segtab_diff + (size_t)(seg_base + k) * (2 * kHalf)); }, st);
-    } else {
+    } else if (listed.n_tok > 0) {
       const float* turn = moved == 0 ? nullptr : SEG ? rd.segtab_diff + (size_t)seg_base * (2 * kHalf) : rd.tab_diff + (size_t)agent * (2 * kHalf);
-      rows_listed<false>(rd, d, at, sd, lds, h, nullptr, 0, l0, (int)(l1 - l0), lane, qf,
-                             [&](int) __attribute__((always_inline)) { load_q(turn); }, st);
+      // (the rows and their table travel with the first tile: nothing waits in between)
+      float2 t2 = make_float2(1.f, 0.f);
+      u32x4 raw[8];
+      if (turn) t2 = reinterpret_cast<const float2*>(turn)[lane];
+      raw_queries(at, out, lane, raw);
+      listed.fetch(0, lane, tile);
+      own_rows(at, row_ok, raw);
+      if (turn) {
+        turn_queries(raw, rd.interleaved, t2, sh.tab[wave], lane, qf);
+      } else {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, raw[kk]);
+      }
+      rows_listed<false>(at, sd, lds, listed, tile, nullptr, 0, lane, qf, [](int) {}, st);
     }
   }
 

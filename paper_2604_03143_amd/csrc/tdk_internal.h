@@ -108,6 +108,19 @@ struct AttendDev {
   int32_t q_flip;                    // the caller's scale was negative: the query copies carry the sign
 };
 
+// What the kernel at hand does not write, at an address that is the same for the whole wavefront: one scalar read.
+template <class T>
+__device__ __forceinline__ T scalar_read(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "read in words");
+  const auto* q = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p;
+  T v;
+  uint32_t w[sizeof(T) / 4];
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(T) / 4); ++k) w[k] = q[k];
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
+}
+
 // launchers (tdk_kernels.hip); each enqueues exactly one kernel
 hipError_t launch_places(const RoundDev& rd, PlaceDev* places, hipStream_t st);
 hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t st);

@@ -108,19 +108,6 @@ struct GroupSharedSeg {
   int32_t  aux[kMaxGroup];
 };
 
-// Descriptors that no kernel writes, at an address that is the same for the whole workgroup: one scalar read.
-template <class T>
-__device__ __forceinline__ T scalar_read(const T* p) {
-  static_assert(sizeof(T) % 4 == 0, "read in words");
-  const auto* q = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p;
-  T v;
-  uint32_t w[sizeof(T) / 4];
-#pragma unroll
-  for (int k = 0; k < (int)(sizeof(T) / 4); ++k) w[k] = q[k];
-  __builtin_memcpy(&v, w, sizeof(T));
-  return v;
-}
-
 // A work item in scalar registers.
 struct Item {
   ItemDev d;
