@@ -111,14 +111,17 @@ tdk_status upload_work(tdk_round* r, int named) {
   const int read_group = named ? named : plan_auto_group(r->sessions, true, page_bytes, r->n_cus);
   const int plane_group = named ? named : plan_auto_group(r->sessions, false, page_bytes, r->n_cus, 1);
   std::vector<WorkItem> work, rwork, pwork;
-  plan_work(r->sessions, group, (r->flags & TDK_TUNE_TAPER) != 0, work);
-  plan_work(r->sessions, read_group, false, rwork);
-  plan_work(r->sessions, plane_group, (r->flags & TDK_TUNE_TAPER) != 0, pwork);
+  const bool taper = (r->flags & TDK_TUNE_TAPER) != 0;
+  const bool same_read = read_group == group && !taper, same_plane = plane_group == group;      // (large rounds: one list serves all)
+  plan_work(r->sessions, group, taper, work);
+  if (!same_read) plan_work(r->sessions, read_group, false, rwork);
+  if (!same_plane) plan_work(r->sessions, plane_group, taper, pwork);
   if (work.size() > r->work_capacity || rwork.size() > r->work_capacity || pwork.size() > r->work_capacity) return fail(TDK_ERR_INVALID_ARG, "work list larger than reserved");
   std::vector<WorkItem> queued;
   plan_queues(work, queued, r->rd.q_begin);
-  // the four lists one behind the other, in one upload
+  // the lists one behind the other, in one upload
   std::vector<ItemDev> items;
+  items.reserve(work.size() + queued.size() + rwork.size() + pwork.size());
   const ItemDev* at[4];
   const std::vector<WorkItem>* lists[4] = {&work, &queued, &rwork, &pwork};
   for (int k = 0; k < 4; ++k) {
@@ -129,10 +132,12 @@ tdk_status upload_work(tdk_round* r, int named) {
     const hipError_t e = hipMemcpy(r->work_region, items.data(), items.size() * sizeof(ItemDev), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy(work lists)");
   }
-  r->rd.work = at[0]; r->rd.qwork = at[1]; r->rd.rwork = at[2]; r->rd.pwork = at[3];
+  r->rd.work = at[0]; r->rd.qwork = at[1];
+  r->rd.rwork = same_read ? at[0] : at[2];
+  r->rd.pwork = same_plane ? at[0] : at[3];
   r->rd.n_work = (int32_t)work.size();
-  r->rd.n_rwork = (int32_t)rwork.size();
-  r->rd.n_pwork = (int32_t)pwork.size();
+  r->rd.n_rwork = (int32_t)(same_read ? work : rwork).size();
+  r->rd.n_pwork = (int32_t)(same_plane ? work : pwork).size();
   r->rd.dyn_begin = r->rd.n_work;   // (a launch that shares its tail sets these in its own copy)
   r->rd.dyn_count = 0;
   r->group = group;
@@ -359,10 +364,27 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   e = hipMalloc(&r->blob, r->blob_bytes);
   if (e != hipSuccess) { return e == hipErrorOutOfMemory ? fail(TDK_ERR_NOMEM, "device allocation failed") : hip_fail(e, "hipMalloc"); }
   char* base = static_cast<char*>(r->blob);
-  // the tables from o_sess to o_flags go up in one piece (a dozen blocking copies of a few KB take longer than the rest of the call)
-  std::vector<char> tables(o_flags - o_sess);
+  // The tables from o_sess to o_flags: small ones together, one behind the other (a blocking copy each takes longer than the rest of the
+  // call), large ones from where they are.
+  constexpr size_t kLargeTable = 64 * 1024;
+  std::vector<char> small;
+  size_t small_begin = o_sess;
+  auto flush = [&]() -> hipError_t {
+    const hipError_t f = small.empty() ? hipSuccess : hipMemcpy(base + small_begin, small.data(), small.size(), hipMemcpyHostToDevice);
+    small.clear();
+    return f;
+  };
   auto put = [&](size_t o, const auto& v) {
-    if (!v.empty()) std::memcpy(tables.data() + (o - o_sess), v.data(), v.size() * sizeof(v[0]));
+    const size_t bytes = v.size() * sizeof(v[0]);
+    if (e != hipSuccess || bytes == 0) return;
+    if (bytes >= kLargeTable) {
+      e = hipMemcpy(base + o, v.data(), bytes, hipMemcpyHostToDevice);
+      return;
+    }
+    if (!small.empty() && o - small_begin > small.size() + 255) e = flush();      // (a large one lay in between)
+    if (small.empty()) small_begin = o;
+    small.resize(o - small_begin + bytes);
+    std::memcpy(small.data() + (o - small_begin), v.data(), bytes);
   };
   put(o_sess, sess_dev);
   put(o_agents, agent_dev);
@@ -378,7 +400,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
     put(o_seg_off, seg_off);
     put(o_seg_src, seg_src);
   }
-  if (!tables.empty()) e = hipMemcpy(base + o_sess, tables.data(), tables.size(), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = flush();
   if (e == hipSuccess) e = hipMemset(base + o_flags, 0, o_tickets - o_flags + (size_t)n_sessions * sizeof(int32_t));   // flags, queue state, tickets
   if (e != hipSuccess) return hip_fail(e, "upload of round descriptors");
 
