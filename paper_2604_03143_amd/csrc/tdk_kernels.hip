@@ -2,12 +2,12 @@
 // ballot/prefix compaction, payload gather and fused diff restore.
 //
 // Data movement plan shared by the three page kernels (rerotate, flag, decode):
-//   - a workgroup of 4 wavefronts owns one master page (T rows of H*D bf16, K and V) and a group
+//   - a workgroup of 4 wavefronts (8 where wide_reads or wide_writes says so) owns one master page (T rows of H*D bf16, K and V) and a group
 //     of up to 32 agents of that page's session;
 //   - the master page is read from HBM once, 16 bytes per lane, and stays in registers while the
 //     workgroup walks its agents (Sec. 4.2: the cost of a shared block is paid once per group);
-//   - the per-agent cos/sin tables, the two physical pages a master page can land on and the
-//     page's row offset are staged in LDS once per workgroup;
+//   - the item's record is one scalar read; the per-agent cos/sin tables and where the page's rows lie in each
+//     agent's pool are then asked for beside the master page and staged in LDS once per workgroup;
 //   - a wavefront always handles whole rows: lane l holds 8 consecutive elements of the low half
 //     and the 8 matching elements of the high half of head l/8, so both members of every rotation
 //     pair sit in the same lane and each load/store instruction covers whole 128-byte segments;

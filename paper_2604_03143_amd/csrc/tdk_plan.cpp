@@ -290,7 +290,8 @@ int plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels,
   // than the coarser end of their launch (the same session: compare kernel 87 us with 9 agents per item, 91 with 3),
   // so they stop splitting at ~900 items.
   //
-  // An item must also be worth its start: about 8 us of dependent reads, during which the compute unit's other two
+  // An item must also be worth its start: about 8 us of dependent reads when these figures were taken (about half of that since one record holds
+  // what they depended on), during which the compute unit's other two
   // workgroups have to keep its share of the memory busy (about 64 KB in 3 us each).  So an item that writes takes at
   // least 1.3 x 64 KB of pages, and with fewer than 3 agents the re-reads of the master page weigh as much as the
   // pages.  25 agents x 5000 tokens, collect: 1 KV head (8 KB pages) 23 us with 3 agents per item, 18 with 9; 2 heads,
