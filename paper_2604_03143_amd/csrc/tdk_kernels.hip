@@ -321,10 +321,11 @@ __device__ __forceinline__ void have_master(MasterRows<RPW>& M) {
 }
 
 // The compiler takes the K rows apart into fp32 in front of the loop over the agents, which costs 16 registers per row on top of the 8 that
-// hold it: 128 with eight rows per wavefront, and the kernels of the master's order then need more than 256 (one wavefront per SIMD).  KEEP:
-// the rows are taken apart again for every agent.  8 heads, 32-token pages, 25 agents x 5000 tokens: check layer 66.1 -> 61.9 us; 100 agents
-// x 5000, collect 388.5 -> 378.0; 16 x 850, collect, restore and store 64.1 -> 59.5.  Where two wavefronts per SIMD fit without it, it costs
-// up to 1.3 % (own orders, collect of 100 x 5000 381.7 -> 386.9; four-head stores 0.997 times for three instead of two).
+// hold it: 128 with eight rows per wavefront, and the kernels of the master's order then need more than 256 (one wavefront per SIMD), the
+// paired compare with own orders scratch.  KEEP: the rows are taken apart again for every agent.  8 heads, 32-token pages, 25 agents x 5000
+// tokens: check layer 66.1 -> 61.9 us, store with own orders 121.5 -> 113.8; 100 agents x 5000, collect 388.5 -> 378.0; 16 x 850, collect,
+// restore and store 64.1 -> 59.5.  Where two wavefronts per SIMD fit without it, it costs up to 1.3 % (own orders, collect of 100 x 5000
+// 381.7 -> 386.9; four-head stores 0.997 times for three instead of two).
 template <bool KEEP>
 __device__ __forceinline__ void keep_packed(u32x4& lo, u32x4& hi) {
   if (KEEP) asm("" : "+v"(lo), "+v"(hi));
@@ -639,7 +640,7 @@ __global__ __launch_bounds__(64 * waves_of(RPW, PACK)) void tdk_flag_kernel(cons
       if (M.valid[k]) {
         u32x4 rlo = z, rhi = z;
         if (DOK && SEG) load_tab<IL>(sh, g, group_row<PACK, W>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
-        if (DOK) keep_packed<RPW == 8 && !SEG>(M.kl[k], M.kh[k]);
+        if (DOK) keep_packed<RPW == 8 && (PM == 3 || !SEG)>(M.kl[k], M.kh[k]);
         if (DOK) rotate16<IL>(M.kl[k], M.kh[k], c, s, rlo, rhi);
         // rows whose bits all match the reference (the common case) need no fp32 compare
         uint32_t x = 0;

@@ -62,3 +62,10 @@ def test_long_pages_in_the_masters_order_have_two_wavefronts_per_simd(kernels):
                       flag={**unpacked, 3: "1", 4: "false"}))
     assert len(some) == 2 * 2 * 2 + 2 * 2 + 2 * 2 * 3 * 2 + 2 * 2
     assert not {k: v for k, v in some if waves_per_simd(v[0]) < 2}
+
+
+def test_page_kernels_have_no_scratch(kernels):
+    """A reload from scratch waits for every load issued before it, and these kernels count on loads in flight."""
+    some = list(forms(kernels, rerotate={}, decode={}, flag={}, keydiff={}))
+    assert len(some) > 300
+    assert not {k: v for k, v in some if v[1]}
