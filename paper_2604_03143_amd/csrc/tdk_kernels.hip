@@ -1562,38 +1562,19 @@ __global__ __launch_bounds__(kBlock) void tdk_page_read_product_kernel(const u32
 // ---------------------------------------------------------------------------------------------
 
 // Launch of a page kernel that writes (rerotate, decode).  Static distribution: one workgroup per work item.
-// Queued (TDK_TUNE_XCD_QUEUES, and only when every resident workgroup gets at least four items: below that the
-// launch is over before an imbalance between the XCDs can build up, and the hardware's own dispatch of fresh
-// workgroups fills freed wavefront slots sooner than a looping workgroup does): two workgroups per compute unit
-// that loop over the items (see below).  `queued_kernel` / `static_kernel` are the two instantiations.
+// Queued (TDK_TUNE_XCD_QUEUES, and only for long launches, see plan_loops: a short one is over before an imbalance between the XCDs can build
+// up, and the hardware's own dispatch of fresh workgroups fills freed wavefront slots sooner than a looping workgroup does): two workgroups
+// per compute unit that loop over the items (see below).  `queued_kernel` / `static_kernel` are the two instantiations; `large`: a long launch.
 // `half_pages`: the call writes one of the two planes only.
 // `extra` static workgroups behind the page items (decode's payload copies on small rounds); returns whether they
 // were launched (only the static form takes them).
 template <class KernelQ, class KernelS, class... Args>
-static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, KernelS static_kernel, int threads, bool half_pages, int extra, hipStream_t st, Args... args) {
-  int n = 2;
-  if (threads == kBlock) {
-    static std::mutex mu;
-    static std::map<const void*, int> per_cu;
-    std::lock_guard<std::mutex> lock(mu);
-    const void* id = reinterpret_cast<const void*>(queued_kernel);
-    auto it = per_cu.find(id);
-    if (it == per_cu.end()) {
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, queued_kernel, kBlock, 0) != hipSuccess || n < 1) n = 2;
-      per_cu[id] = n;
-    } else {
-      n = it->second;
-    }
-  }
-  const int64_t resident = (int64_t)n * std::max(rd.n_cus, 1);
-  // long enough for the looping form: at least four items and at least 32 (agent, page) pairs per resident
-  // workgroup (a round cut into many small items, such as one agent per item, is no longer than its pairs)
-  const bool large = threads == kBlock && (int64_t)rd.n_work >= 4 * resident && rd.agent_pages >= 32 * resident;
+static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, KernelS static_kernel, int threads, bool large, bool half_pages, int extra, hipStream_t st, Args... args) {
   if ((rd.nontemporal & 128) && (large || (threads == kBlock && (rd.nontemporal & 512)))) {
     // Two looping workgroups per compute unit, although three fit: memory is saturated with one per unit already,
     // and the fewer pages are being written at a time, the better DRAM takes it (batched250: decode 876 us with
     // three per unit, 868 with two, 860 with one; rerotate 958 / 953 / 962; `long` loses 7 % with one).
-    const int64_t looping = std::min<int64_t>(resident, 2 * (int64_t)std::max(rd.n_cus, 1));
+    const int64_t looping = 2 * (int64_t)std::max(rd.n_cus, 1);
     hipLaunchKernelGGL(queued_kernel, dim3((unsigned)std::min<int64_t>(rd.n_work, looping)), dim3(kBlock), 0, st, rd, args...);
     return false;
   }
@@ -1668,7 +1649,8 @@ hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t s
       constexpr int R = decltype(rpw)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
       constexpr bool kQueues = waves_of(R, P) == kWaves;
-      launch_write_pages(rd, tdk_rerotate_kernel<R, P, I, N, G, kQueues>, tdk_rerotate_kernel<R, P, I, N, G, false>, 64 * waves_of(R, P), false, 0, st, io);
+      const bool large = kQueues && plan_loops(rd.n_work, rd.agent_pages, rd.n_cus, R, P, 3, G);
+      launch_write_pages(rd, tdk_rerotate_kernel<R, P, I, N, G, kQueues>, tdk_rerotate_kernel<R, P, I, N, G, false>, 64 * waves_of(R, P), large, false, 0, st, io);
     });
   }); }); });
   return hipGetLastError();
@@ -1727,8 +1709,9 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
       constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
       constexpr bool kQueues = waves_of(R, P) == kWaves;
+      const bool large = kQueues && plan_loops(rd.n_work, rd.agent_pages, rd.n_cus, R, P, M, G);
       *scattered = launch_write_pages(rd, tdk_decode_kernel<R, P, I, N, M, G, kQueues>, tdk_decode_kernel<R, P, I, N, M, G, false>, 64 * waves_of(R, P),
-                                      planes != 3, scatter_blocks, st, io, d, scatter_blocks);
+                                      large, planes != 3, scatter_blocks, st, io, d, scatter_blocks);
     }); });
   }); }); });
   return hipGetLastError();

@@ -340,6 +340,19 @@ int plan_copy_workgroups(int slots, int batches, int n_cus, int left) {
   return (int)std::max<int64_t>(slots, std::min<int64_t>((int64_t)slots * std::max(1, batches), most));
 }
 
+bool plan_loops(int64_t items, int64_t pairs, int n_cus, int rows, bool pack, int planes, bool seg) {
+  // At least four items and 32 pairs (a round cut into many small items, such as one agent per item, is no longer than its pairs) for every
+  // workgroup that fits the chip.  Numbers, for K, V and both, of what fitted when the line was measured: asked for at run time it
+  // moves with every few registers that a kernel takes, and on the wrong side of it the looping form is slower (120 agents x 5000 tokens, 4 heads,
+  // 32-token pages, collect 239.7 us looping and 228.5 with a workgroup per item, restore 260.1 and 244.0).
+  constexpr int fit[3][4] = {{8, 5, 4, 2}, {8, 8, 6, 4}, {6, 4, 3, 2}};       // 1, 2, 4, 8 rows
+  int n = fit[planes - 1][rows >= 8 ? 3 : rows >= 4 ? 2 : rows - 1];
+  if (planes == 2 && rows == 4 && !pack) n = 7;
+  if (seg) n = planes == 3 && rows == 4 && pack ? 2 : std::min(n, 4);          // (their tables: four workgroups' LDS fits)
+  const int64_t resident = n * (int64_t)std::max(n_cus, 1);
+  return items >= 4 * resident && pairs >= 32 * resident;
+}
+
 void plan_queues(const std::vector<WorkItem>& work, std::vector<WorkItem>& queued, int32_t (&q_begin)[9]) {
   queued.clear();
   queued.reserve(work.size());

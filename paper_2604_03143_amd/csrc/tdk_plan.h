@@ -63,6 +63,9 @@ int  plan_auto_group(const std::vector<PlanSession>& sessions, bool read_kernels
 // Workgroups that copy listed pages, for at most so many slots: more than one per slot where the kernel shares them out, down to one of
 // its batches of accesses per thread.  left: places on the chip that the launch's other workgroups leave
 int  plan_copy_workgroups(int slots, int batches, int n_cus, int left);
+// Is a launch of the kernels that write long enough for the form that loops?  items, pairs: work items and (agent, page) pairs; rows: accesses
+// per page and wavefront; pack: several rows per access; planes: bit 0 = K, bit 1 = V; seg: some agent has a block order of its own
+bool plan_loops(int64_t items, int64_t pairs, int n_cus, int rows, bool pack, int planes, bool seg);
 
 // Attention over mirrors that are never restored: what the planner needs to know of a round.
 struct AttendShape {

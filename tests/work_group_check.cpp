@@ -51,6 +51,17 @@ int main() {
   REQUIRE(plan_copy_workgroups(383, 2, 256, 238) == 766 && plan_copy_workgroups(800, 2, 256, -700) == 1024 && plan_copy_workgroups(1500, 2, 256, -700) == 1500);
   // four batches
   REQUIRE(plan_copy_workgroups(350, 4, 256, 400) == 1024 && plan_copy_workgroups(96, 4, 256, 100) == 384);
+  // long launches: four items and 32 pairs per workgroup that fits the chip, by numbers that no build moves
+  struct { int rows; bool pack; int planes; bool seg; int64_t fits; } lines[] = {
+      {4, false, 3, false, 3}, {8, false, 3, false, 2}, {4, true, 3, false, 3}, {4, true, 3, true, 2}, {2, true, 3, false, 4}, {1, true, 3, false, 6}, {1, true, 3, true, 4},
+      {8, false, 3, true, 2}, {4, false, 3, true, 3}, {4, false, 2, false, 7}, {4, true, 2, false, 6}, {8, false, 2, false, 4}, {2, true, 2, false, 8}, {4, false, 2, true, 4},
+      {4, true, 1, false, 4}, {8, false, 1, false, 2}, {2, true, 1, false, 5}, {1, true, 1, true, 4}};
+  for (const auto& l : lines)
+    for (int cus : {64, 256}) {
+      const int64_t wg = l.fits * cus;
+      REQUIRE(plan_loops(4 * wg, 32 * wg, cus, l.rows, l.pack, l.planes, l.seg));
+      REQUIRE(!plan_loops(4 * wg - 1, 32 * wg, cus, l.rows, l.pack, l.planes, l.seg) && !plan_loops(4 * wg, 32 * wg - 1, cus, l.rows, l.pack, l.planes, l.seg));
+    }
   std::printf("work groups: clean\n");
   return 0;
 }
