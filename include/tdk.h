@@ -133,7 +133,9 @@ size_t     tdk_scratch_bytes(const tdk_round* r);       /* device bytes the roun
  * through L2 and written back early instead of lingering as dirty lines that the next kernel has to
  * flush); the default was measured best for the whole rerotate / decode / encode sequence.
  * Synchronises the device (the work list it replaces may still be in use).  Results never depend on
- * these settings. */
+ * these settings.  Work lists longer than the automatic ones (smaller groups, TDK_TUNE_TAPER) need device
+ * memory of their own, once per round: 192 bytes per (agent, page) pair, else NOMEM.  Calls captured in a
+ * graph keep the lengths of their time: capture them again after lists have become longer. */
 #define TDK_TUNE_NT_REROTATE_STORES 1
 #define TDK_TUNE_NT_DECODE_STORES   2
 #define TDK_TUNE_NT_COMPARE_LOADS   4

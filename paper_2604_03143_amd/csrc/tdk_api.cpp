@@ -80,7 +80,11 @@ struct tdk_round {
   void*  blob = nullptr;           // one device allocation for everything below
   size_t blob_bytes = 0;
   size_t work_capacity = 0;        // items that a work list can have
-  ItemDev* work_region = nullptr;  // the four lists, one behind the other
+  // The work lists (WorkLists), each at a place of its own: in `blob` as large as the round was created with, in `more`, for lists that
+  // do not fit there, as large as a list can be.  (A captured call names places and lengths: shorter lists put there later are still whole.)
+  ItemDev* list_at[4] = {nullptr, nullptr, nullptr, nullptr};
+  size_t   list_room[4] = {0, 0, 0, 0};
+  void*    more = nullptr;
   RoundDev rd{};
 
   // ping-pong restore: one "loaded" and one "free" event per staging buffer, one "done" per call
@@ -103,44 +107,76 @@ struct tdk_round {
 
 namespace {
 
+// The work lists of a round: all items, the same by queues, those of the kernels that only read, those of the calls that write one plane.
+struct WorkLists {
+  std::vector<WorkItem> list[4];
+  int32_t q_begin[9] = {0};
+  bool same_read = false, same_plane = false;      // (large rounds: one list serves all)
+  int32_t group = 0;
+};
+
 // named: agents per work item, 0 = automatic (the kernels that only read and the calls that write one plane then have
 // numbers of their own)
-tdk_status upload_work(tdk_round* r, int named) {
+void plan_lists(const tdk_round* r, int named, WorkLists& w) {
   const int64_t page_bytes = (int64_t)r->model.page_tokens * r->model.num_kv_heads * r->model.head_dim * 4;      // K and V
-  const int group = named ? named : plan_auto_group(r->sessions, false, page_bytes, r->n_cus);
+  w.group = named ? named : plan_auto_group(r->sessions, false, page_bytes, r->n_cus);
   const int read_group = named ? named : plan_auto_group(r->sessions, true, page_bytes, r->n_cus);
   const int plane_group = named ? named : plan_auto_group(r->sessions, false, page_bytes, r->n_cus, 1);
-  std::vector<WorkItem> work, rwork, pwork;
   const bool taper = (r->flags & TDK_TUNE_TAPER) != 0;
-  const bool same_read = read_group == group && !taper, same_plane = plane_group == group;      // (large rounds: one list serves all)
-  plan_work(r->sessions, group, taper, work);
-  if (!same_read) plan_work(r->sessions, read_group, false, rwork);
-  if (!same_plane) plan_work(r->sessions, plane_group, taper, pwork);
-  if (work.size() > r->work_capacity || rwork.size() > r->work_capacity || pwork.size() > r->work_capacity) return fail(TDK_ERR_INVALID_ARG, "work list larger than reserved");
-  std::vector<WorkItem> queued;
-  plan_queues(work, queued, r->rd.q_begin);
-  // the lists one behind the other, in one upload
-  std::vector<ItemDev> items;
-  items.reserve(work.size() + queued.size() + rwork.size() + pwork.size());
-  const ItemDev* at[4];
-  const std::vector<WorkItem>* lists[4] = {&work, &queued, &rwork, &pwork};
-  for (int k = 0; k < 4; ++k) {
-    at[k] = r->work_region + items.size();
-    plan_items(r->sessions, r->order, r->agents, r->model.page_tokens, *lists[k], items);
+  w.same_read = read_group == w.group && !taper;
+  w.same_plane = plane_group == w.group;
+  plan_work(r->sessions, w.group, taper, w.list[0]);
+  plan_queues(w.list[0], w.list[1], w.q_begin);
+  if (!w.same_read) plan_work(r->sessions, read_group, false, w.list[2]);
+  if (!w.same_plane) plan_work(r->sessions, plane_group, taper, w.list[3]);
+}
+
+tdk_status upload_lists(tdk_round* r, const WorkLists& w) {
+  bool fit = true;
+  for (int k = 0; k < 4; ++k) fit = fit && w.list[k].size() <= r->list_room[k];
+  if (!fit) {
+    for (int k = 0; k < 4; ++k)
+      if (w.list[k].size() > r->work_capacity) return fail(TDK_ERR_INVALID_ARG, "work list larger than reserved");
+    const size_t bytes = 4 * r->work_capacity * sizeof(ItemDev);
+    int device = r->device;                       // (a caller may tune a round with another device current)
+    (void)hipGetDevice(&device);
+    if (device != r->device) (void)hipSetDevice(r->device);
+    const hipError_t e = hipMalloc(&r->more, bytes);
+    if (device != r->device) (void)hipSetDevice(device);
+    if (e != hipSuccess) { return e == hipErrorOutOfMemory ? fail(TDK_ERR_NOMEM, "device allocation failed") : hip_fail(e, "hipMalloc"); }
+    r->blob_bytes += bytes;
+    for (int k = 0; k < 4; ++k) {
+      r->list_at[k] = static_cast<ItemDev*>(r->more) + k * r->work_capacity;
+      r->list_room[k] = r->work_capacity;
+    }
   }
-  if (!items.empty()) {
-    const hipError_t e = hipMemcpy(r->work_region, items.data(), items.size() * sizeof(ItemDev), hipMemcpyHostToDevice);
+  std::vector<ItemDev> items;
+  size_t first[5];
+  items.reserve(w.list[0].size() + w.list[1].size() + w.list[2].size() + w.list[3].size());
+  for (int k = 0; k < 4; ++k) {
+    first[k] = items.size();
+    plan_items(r->sessions, r->order, r->agents, r->model.page_tokens, w.list[k], items);
+  }
+  first[4] = items.size();
+  // (lists that follow one another go up together: a blocking copy each takes longer than planning them)
+  for (int k = 0, next; k < 4; k = next) {
+    for (next = k + 1; next < 4 && r->list_at[next] == r->list_at[k] + (first[next] - first[k]); ++next) {}
+    const size_t n = first[next] - first[k];
+    if (n == 0) continue;
+    const hipError_t e = hipMemcpy(r->list_at[k], items.data() + first[k], n * sizeof(ItemDev), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy(work lists)");
   }
-  r->rd.work = at[0]; r->rd.qwork = at[1];
-  r->rd.rwork = same_read ? at[0] : at[2];
-  r->rd.pwork = same_plane ? at[0] : at[3];
-  r->rd.n_work = (int32_t)work.size();
-  r->rd.n_rwork = (int32_t)(same_read ? work : rwork).size();
-  r->rd.n_pwork = (int32_t)(same_plane ? work : pwork).size();
+  const int read = w.same_read ? 0 : 2, plane = w.same_plane ? 0 : 3;
+  std::copy(std::begin(w.q_begin), std::end(w.q_begin), std::begin(r->rd.q_begin));
+  r->rd.work = r->list_at[0]; r->rd.qwork = r->list_at[1];
+  r->rd.rwork = r->list_at[read];
+  r->rd.pwork = r->list_at[plane];
+  r->rd.n_work = (int32_t)w.list[0].size();
+  r->rd.n_rwork = (int32_t)w.list[read].size();
+  r->rd.n_pwork = (int32_t)w.list[plane].size();
   r->rd.dyn_begin = r->rd.n_work;   // (a launch that shares its tail sets these in its own copy)
   r->rd.dyn_count = 0;
-  r->group = group;
+  r->group = w.group;
   return TDK_OK;
 }
 
@@ -316,7 +352,6 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   r->n_agents = n_agents;
   const int T = model->page_tokens;
   const bool any_segments = p.any_segments;
-  const size_t work_cap = p.work_capacity;
   const int64_t flag_off = p.total_pages;
   const auto& sess_dev = p.sess;
   const auto& order = p.order;
@@ -333,10 +368,21 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   const auto& seg_off = p.seg_off;
   const auto& seg_src = p.seg_src;
 
+  hipError_t e = hipGetDevice(&r->device);
+  if (e != hipSuccess) { return hip_fail(e, "hipGetDevice"); }
+  {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, r->device) == hipSuccess && cus > 0) r->n_cus = cus;
+  }
+  WorkLists lists;
+  plan_lists(r, 0, lists);
+
   // ---- device memory: one allocation ----
   size_t off = 0;
   auto place = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
-  const size_t o_work = place(4 * work_cap * sizeof(ItemDev));
+  size_t n_items = 0;
+  for (const auto& list : lists.list) n_items += list.size();
+  const size_t o_work = place(n_items * sizeof(ItemDev));
   const size_t o_places = place(any_segments ? 0 : (size_t)flag_off * sizeof(PlaceDev));
   const size_t o_sess = place(sess_dev.size() * sizeof(SessionDev));
   const size_t o_agents = place(agent_dev.size() * sizeof(AgentDev));
@@ -355,12 +401,6 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   const size_t o_tickets = place((size_t)n_sessions * sizeof(int32_t));
   r->blob_bytes = std::max<size_t>(off, 256);
 
-  hipError_t e = hipGetDevice(&r->device);
-  if (e != hipSuccess) { return hip_fail(e, "hipGetDevice"); }
-  {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, r->device) == hipSuccess && cus > 0) r->n_cus = cus;
-  }
   e = hipMalloc(&r->blob, r->blob_bytes);
   if (e != hipSuccess) { return e == hipErrorOutOfMemory ? fail(TDK_ERR_NOMEM, "device allocation failed") : hip_fail(e, "hipMalloc"); }
   char* base = static_cast<char*>(r->blob);
@@ -404,7 +444,12 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
   if (e == hipSuccess) e = hipMemset(base + o_flags, 0, o_tickets - o_flags + (size_t)n_sessions * sizeof(int32_t));   // flags, queue state, tickets
   if (e != hipSuccess) return hip_fail(e, "upload of round descriptors");
 
-  r->work_region = reinterpret_cast<ItemDev*>(base + o_work);
+  n_items = 0;
+  for (int k = 0; k < 4; ++k) {
+    r->list_at[k] = reinterpret_cast<ItemDev*>(base + o_work) + n_items;
+    r->list_room[k] = lists.list[k].size();
+    n_items += r->list_room[k];
+  }
   r->rd.sess = reinterpret_cast<const SessionDev*>(base + o_sess);
   r->rd.agents = reinterpret_cast<const AgentDev*>(base + o_agents);
   r->rd.oagents = r->rd.agents + n_agents;
@@ -440,7 +485,7 @@ tdk_status round_create(const tdk_model* model, const tdk_session* sessions, int
     e = launch_places(r->rd, reinterpret_cast<PlaceDev*>(base + o_places), nullptr);
     if (e != hipSuccess) return hip_fail(e, "places of the pages");
   }
-  st = upload_work(r, 0);
+  st = upload_lists(r, lists);
   if (st != TDK_OK) return st;
   for (int b = 0; b < 2 && e == hipSuccess; ++b) {
     e = hipEventCreateWithFlags(&r->ev_loaded[b], hipEventDisableTiming);
@@ -481,6 +526,7 @@ void tdk_round_destroy(tdk_round* r) {
     if (r->ev_free[b]) (void)hipEventDestroy(r->ev_free[b]);
   }
   if (r->blob) (void)hipFree(r->blob);
+  if (r->more) (void)hipFree(r->more);
   delete r;
 }
 
@@ -497,7 +543,9 @@ tdk_status tdk_round_tune(tdk_round* r, int32_t agents_per_group, int32_t flags)
     if (e != hipSuccess) return hip_fail(e, "hipDeviceSynchronize");
     r->flags = flags;
     r->rd.nontemporal = flags & TDK_TUNE_ALL;
-    return upload_work(r, agents_per_group);
+    WorkLists lists;
+    plan_lists(r, agents_per_group, lists);
+    return upload_lists(r, lists);
   });
 }
 
