@@ -367,8 +367,11 @@ constexpr int kPrefetchBlocks = 1024;   // workgroups that take part in the mast
 // writes: the reads then come from DRAM as one sequential stream into the memory-side cache instead
 // of arriving one page at a time among the writes (a read among writes costs DRAM a bus turnaround;
 // measured at about twice its byte share).
-// Not where all workgroups of the launch run at once: then every master read stands before the writes anyway, and the sweep is a wait in front of
-// them (4 agents x 256 tokens, collect, restore and store 24.0 -> 23.6 us).
+// Not in launches of at most three workgroups per compute unit, those that stand by for the tail and those that copy listed pages among them:
+// nearly all their master reads stand before the writes anyway, and the sweep is a wait in front of them (4 agents x 256 tokens, collect,
+// restore and store 24.0 -> 23.7 us).  Of the forms with eight wavefronts or 32-token pages only two fit a compute unit, but the line at two
+// was no better for them: 691 workgroups of eight wavefronts, collect of 16 agents x 1536 tokens 21.8 us without the sweep and 22.8 with it,
+// five heads 15.8 and 16.2, own orders 23.9 and 23.7, six restores 0.99 to 1.00; 32-token pages, six launches within 0.3 %.
 template <bool LOOPING, int W>
 __device__ __forceinline__ void sweep_masters(const RoundDev& rd, const LayerDev& io, bool k, bool v) {
   if (blockIdx.x >= kPrefetchBlocks || (!LOOPING && (int)gridDim.x <= 3 * rd.n_cus)) return;
@@ -1698,8 +1701,8 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
   const bool wide = planes == 3 && wide_writes(rd);
   if (rd.n_agents == 0 || d.capacity == 0) scatter_blocks = 0;
   if (slots_shared(rd)) {
-    // (three workgroups of the kernels for both planes fit a compute unit; the page items are launched with those that stand by for the
-    // last fifth.  Of the kernels for one plane more fit, and no limit showed: 60 agents x 700 tokens, pages of 32, stored and restored
+    // (three workgroups of the kernels for both planes fit a compute unit, of those for 32-token pages whose rows fill an access two, and of
+    // those with eight wavefronts, whose slots are one batch; the page items are launched with those that stand by for the last fifth.  Of the kernels for one plane more fit, and no limit showed: 60 agents x 700 tokens, pages of 32, stored and restored
     // one plane at a time 109.7 us, 111.9 with a limit of four.)
     const int left = planes == 3 ? 3 * rd.n_cus - rd.n_work - rd.n_work / 5 : -1;
     scatter_blocks = plan_copy_workgroups(scatter_blocks, slot_batches(rd, planes, wide ? 2 * kWaves : kWaves), rd.n_cus, left);
