@@ -1641,8 +1641,10 @@ template <class F> static void with_planes(int planes, F f) {
 
 hipError_t launch_places(const RoundDev& rd, PlaceDev* places, hipStream_t st) {
   if (rd.n_agents == 0) return hipSuccess;
-  hipLaunchKernelGGL(tdk_places_kernel, dim3((unsigned)rd.n_agents), dim3(kBlock), 0, st, rd, places);
-  return hipGetLastError();
+  // (its own status: an error that the caller's calls have left behind is not this one's)
+  RoundDev r = rd;
+  void* args[] = {&r, &places};
+  return hipLaunchKernel(reinterpret_cast<const void*>(tdk_places_kernel), dim3((unsigned)rd.n_agents), dim3(kBlock), args, 0, st);
 }
 
 hipError_t launch_rerotate(const RoundDev& rd, const LayerDev& io, hipStream_t st) {
