@@ -1714,9 +1714,11 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
       constexpr int R = decltype(rpw)::value, M = decltype(pm)::value;
       constexpr bool P = decltype(pack)::value, I = decltype(il)::value, N = decltype(nt)::value, G = decltype(sg)::value;
       constexpr bool kQueues = waves_of(R, P) == kWaves;
-      const bool large = kQueues && plan_loops(rd.n_work, rd.agent_pages, rd.n_cus, R, P, M, G);
-      *scattered = launch_write_pages(rd, tdk_decode_kernel<R, P, I, N, M, G, kQueues>, tdk_decode_kernel<R, P, I, N, M, G, false>, 64 * waves_of(R, P),
-                                      large, planes != 3, scatter_blocks, st, io, d, scatter_blocks);
+      if constexpr (kQueues || M == 3) {        // (eight wavefronts: both planes only)
+        const bool large = kQueues && plan_loops(rd.n_work, rd.agent_pages, rd.n_cus, R, P, M, G);
+        *scattered = launch_write_pages(rd, tdk_decode_kernel<R, P, I, N, M, G, kQueues>, tdk_decode_kernel<R, P, I, N, M, G, false>, 64 * waves_of(R, P),
+                                        large, planes != 3, scatter_blocks, st, io, d, scatter_blocks);
+      }
     }); });
   }); }); });
   return hipGetLastError();

@@ -69,3 +69,11 @@ def test_page_kernels_have_no_scratch(kernels):
     some = list(forms(kernels, rerotate={}, decode={}, flag={}, keydiff={}))
     assert len(some) > 300
     assert not {k: v for k, v in some if v[1]}
+
+
+def test_no_form_is_built_that_nothing_launches(kernels):
+    """Eight wavefronts per workgroup: the restore takes them for both planes, and nothing with eight loops."""
+    eight = {0: "2", 1: "false"}
+    assert list(forms(kernels, decode={**eight, 4: "3", 6: "false"})) and list(forms(kernels, rerotate={**eight, 5: "false"}))
+    assert not list(forms(kernels, decode={**eight, 4: "1"})) + list(forms(kernels, decode={**eight, 4: "2"}))
+    assert not list(forms(kernels, decode={**eight, 6: "true"})) + list(forms(kernels, rerotate={**eight, 5: "true"}))
