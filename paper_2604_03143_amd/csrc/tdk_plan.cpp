@@ -261,11 +261,12 @@ void plan_work(const std::vector<PlanSession>& sessions, int group, bool taper, 
 void plan_items(const std::vector<PlanSession>& sessions, const std::vector<int32_t>& order, const std::vector<AgentDev>& agents, int page_tokens,
                 const std::vector<WorkItem>& work, std::vector<ItemDev>& items) {
   items.reserve(items.size() + work.size());
+  std::vector<int32_t> ascend(order.size());       // agents from this place of the order on whose ids ascend by one
+  for (size_t k = order.size(); k-- > 0;) ascend[k] = k + 1 < order.size() && order[k + 1] == order[k] + 1 ? ascend[k + 1] + 1 : 1;
   for (const WorkItem& w : work) {
     const PlanSession& s = sessions[(size_t)w.session];
     const int32_t first = order[(size_t)w.ag_begin], m0 = w.page * page_tokens;
-    bool consecutive = true;
-    for (int32_t g = 1; g < w.ag_count; ++g) consecutive = consecutive && order[(size_t)(w.ag_begin + g)] == first + g;
+    const bool consecutive = ascend[(size_t)w.ag_begin] >= w.ag_count;
     ItemDev it{};
     it.row0 = s.master_row0 + m0;
     it.page = w.page;
