@@ -38,7 +38,7 @@ struct RoundDev {
   const ItemDev*    pwork;                 // the work list of static launches that write one plane only (an item holds half the bytes)
   int32_t           n_pwork;
   int32_t           dyn_begin, dyn_count;  // static launches of the write kernels: workgroups [dyn_begin, dyn_begin + dyn_count) take the items from dyn_begin on in the order they start (set per launch; dyn_begin = n_work, dyn_count = 0: none)
-  int32_t           q_begin[9];  // XCD x's queue is work[q_begin[x] .. q_begin[x + 1])
+  int32_t           q_begin[9];  // XCD x's queue is qwork[q_begin[x] .. q_begin[x + 1])
   int32_t           n_cus;
   int32_t n_work, n_agents, n_sessions;
   int32_t heads;             // H

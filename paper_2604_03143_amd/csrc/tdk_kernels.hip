@@ -1047,7 +1047,7 @@ __device__ __forceinline__ void scatter_slots(const RoundDev& rd, const LayerDev
     u32x4* data = d.payload + slot * (p1 - p0) * (int64_t)page_u4;
     if (p0 == 0 && rot) {
       // stored at another position: K rows are re-rotated, a wavefront per row, both members of a pair in one lane
-      // (the page kernels' lane layout); four rows of the wavefront are requested before the first is used
+      // (the page kernels' lane layout); four rows of the wavefront (two where it is one of eight) are requested before the first is used
       for (int r0 = threadIdx.x >> 6; r0 < T; r0 += kRows * W) {
         u32x4 lo[kRows], hi[kRows];
 #pragma unroll
@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(kBlock) void tdk_scatter_kernel(const RoundDev rd, 
 // latency in front of the item's first store: 37 agents x 2999 tokens, 4 heads, one plane after the other 127.5 -> 125.6 us,
 // 4 x 12 agents x 3001 tokens with moved diffs and own orders 104.2 -> 101.9, 13 agents x 19322 tokens, 4 heads 292 -> 275.
 __device__ __forceinline__ void find_listed(const RoundDev& rd, const DiffDev& d, const Item& w, int32_t* listed) {
-  const int count = w.count(), page = w.d.page, lg = count <= 4 ? 6 : count <= 8 ? 5 : count <= 16 ? 4 : 3;      // kMaxGroup << 3 == kBlock
+  const int count = w.count(), page = w.d.page, lg = count <= 4 ? 6 : count <= 8 ? 5 : count <= 16 ? 4 : 3;      // (four wavefronts reach kMaxGroup agents; of eight the rest has none)
   const int g = threadIdx.x >> lg, lanes = 1 << lg, l = threadIdx.x & (lanes - 1), shift = threadIdx.x & 63 & ~(lanes - 1);
   const uint64_t mine = (lanes == 64 ? ~0ull : (1ull << lanes) - 1ull) << shift;
   const int32_t* v = d.idx;
@@ -1574,7 +1574,7 @@ __global__ __launch_bounds__(kBlock) void tdk_page_read_product_kernel(const u32
 template <class KernelQ, class KernelS, class... Args>
 static bool launch_write_pages(const RoundDev& rd, KernelQ queued_kernel, KernelS static_kernel, int threads, bool large, bool half_pages, int extra, hipStream_t st, Args... args) {
   if ((rd.nontemporal & 128) && (large || (threads == kBlock && (rd.nontemporal & 512)))) {
-    // Two looping workgroups per compute unit, although three fit: memory is saturated with one per unit already,
+    // Two looping workgroups per compute unit, although three may fit: memory is saturated with one per unit already,
     // and the fewer pages are being written at a time, the better DRAM takes it (batched250: decode 876 us with
     // three per unit, 868 with two, 860 with one; rerotate 958 / 953 / 962; `long` loses 7 % with one).
     const int64_t looping = 2 * (int64_t)std::max(rd.n_cus, 1);
