@@ -325,7 +325,9 @@ __device__ __forceinline__ void have_master(MasterRows<RPW>& M) {
 // paired compare with own orders scratch.  KEEP: the rows are taken apart again for every agent.  8 heads, 32-token pages, 25 agents x 5000
 // tokens: check layer 66.1 -> 61.9 us, store with own orders 121.5 -> 113.8; 100 agents x 5000, collect 388.5 -> 378.0; 16 x 850, collect,
 // restore and store 64.1 -> 59.5.  Where two wavefronts per SIMD fit without it, it costs up to 1.3 % (own orders, collect of 100 x 5000
-// 381.7 -> 386.9; four-head stores 0.997 times for three instead of two).
+// 381.7 -> 386.9), but for the paired compare kernel with two accesses of several rows, where it is what makes the third fit: 4 heads, 16-token
+// pages, store of 40 x 4000 69.8 -> 66.3 us, 200 x 1500 119.6 -> 117.9, 37 x 9000 133.0 -> 131.0 (launches with fewer than two items per
+// place gain nothing: 64 x 700 25.7 -> 26.4); 2 heads, 32-token pages, 100 x 3000 67.7 -> 64.7.
 template <bool KEEP>
 __device__ __forceinline__ void keep_packed(u32x4& lo, u32x4& hi) {
   if (KEEP) asm("" : "+v"(lo), "+v"(hi));
@@ -643,7 +645,7 @@ __global__ __launch_bounds__(64 * waves_of(RPW, PACK)) void tdk_flag_kernel(cons
       if (M.valid[k]) {
         u32x4 rlo = z, rhi = z;
         if (DOK && SEG) load_tab<IL>(sh, g, group_row<PACK, W>(k, rd.heads, T) + (PACK ? L.rk : 0), L.jb, c, s);
-        if (DOK) keep_packed<RPW == 8 && (PM == 3 || !SEG)>(M.kl[k], M.kh[k]);
+        if (DOK) keep_packed<(RPW == 8 && (PM == 3 || !SEG)) || (RPW == 2 && PACK && PM == 3 && !SEG)>(M.kl[k], M.kh[k]);
         if (DOK) rotate16<IL>(M.kl[k], M.kh[k], c, s, rlo, rhi);
         // rows whose bits all match the reference (the common case) need no fp32 compare
         uint32_t x = 0;

@@ -64,6 +64,13 @@ def test_long_pages_in_the_masters_order_have_two_wavefronts_per_simd(kernels):
     assert not {k: v for k, v in some if waves_per_simd(v[0]) < 2}
 
 
+def test_paired_compare_of_two_accesses_has_three_wavefronts_per_simd(kernels):
+    """Several rows per access, two accesses per page and wavefront (four heads with 16-token pages, two with 32), master's order."""
+    some = list(forms(kernels, flag={0: "2", 1: "true", 3: "3", 4: "false"}))
+    assert len(some) == 4
+    assert not {k: v for k, v in some if waves_per_simd(v[0]) < 3}
+
+
 def test_page_kernels_have_no_scratch(kernels):
     """A reload from scratch waits for every load issued before it, and these kernels count on loads in flight."""
     some = list(forms(kernels, rerotate={}, decode={}, flag={}, keydiff={}))
