@@ -420,7 +420,8 @@ __device__ __forceinline__ void turn_back16(bf16x8 (&qf)[4], const float* tab, b
 }
 
 // A query row as it is, in the order of the B operands for the 32-row tiles: fragment kk of a lane holds elements
-// 16 kk + 8 hh .. + 7.  Only the loads: own_rows() is called where they are used, so that nothing in between waits for them.
+// 16 kk + 8 hh .. + 7.  Only the loads: where others are asked for before the rows are
+// used, own_rows() is called behind those.
 __device__ __forceinline__ void raw_queries(const AttendDev& at, int64_t out, int lane, u32x4 (&raw)[8]) {
   const u32x4* qp = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(at.q) + out * kHeadDim);
 #pragma unroll
@@ -1494,12 +1495,6 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     load_queries(at, rd.interleaved, out, row_ok, tab, sh.tab[wave], lane, qf);
   };
   const int moved = scalar_read(&rd.agents[agent].diff_rot);
-  // the agent's list, by scalar reads too: a vector read would wait for the tiles asked for below
-  int64_t lo = scalar_read(d.offset + agent), hi = lo + scalar_read(d.count + agent);
-  if (lo < 0) lo = 0;
-  if (hi > d.capacity) hi = d.capacity;
-  const int len = hi > lo ? (int)min<int64_t>(hi - lo, 1 << 30) : 0;
-  const int32_t* list = d.idx + lo;
   int seg_base = 0, seg_n = 1, seg_k = 0;
   if (SEG && active) {
     seg_base = scalar_read(rd.seg_off + agent);
@@ -1536,13 +1531,15 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
   };
   // Asked for before anything else is looked up: the rows, their table, the first tiles.  (Short spans are all start-up and
   // end: with this and the rows written whole, 2 x 32 agents x 132 tokens, 128 rows 25.8 -> 23.5 us, 189 agents x 68 tokens, 256 rows
-  // 121.7 -> 114.9; the tiles alone asked for first: no gain, they then delay the rows.)
+  // 121.7 -> 114.9; the tiles alone asked for first: no gain, they then delay the rows.  Tiles behind rows that have not arrived yet, and
+  // the list in front of them, cost spans of a few steps with masters of several sessions: 10 sessions of 3 agents x 275 tokens, 160 rows 24.9
+  // against 24.3 us, nothing listed 19.9 against 19.6; other calls 0.99 to 1.01.)
   u32x4 raw0[8];
   int first = 0x7fffffff;                                // the first 64 entries of the list
   if (tok_end > tok_begin) {
     if (active) {
-      if (lane < len) first = list[lane];
       raw_queries(at, out, lane, raw0);
+      own_rows(at, row_ok, raw0);
       if (SEG) window(0);
       else seg_tab = reinterpret_cast<const float2*>(rd.tab + (size_t)agent * (2 * kHalf))[lane];
     }
@@ -1550,6 +1547,14 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     fetch_v(tok_begin, 0);
     fetch_k(min(tok_begin + kBigTile, tok_end), 1);
   }
+  __builtin_amdgcn_sched_barrier(0);
+  // the agent's list, by scalar reads: vector reads would wait for the tiles
+  int64_t lo = scalar_read(d.offset + agent), hi = lo + scalar_read(d.count + agent);
+  if (lo < 0) lo = 0;
+  if (hi > d.capacity) hi = d.capacity;
+  const int len = hi > lo ? (int)min<int64_t>(hi - lo, 1 << 30) : 0;
+  const int32_t* list = d.idx + lo;
+  if (active && tok_end > tok_begin && lane < len) first = list[lane];
 
   // the part of the agent's list that falls into this chunk, and its page mask
   int64_t l0 = 0, l1 = 0;
@@ -1655,7 +1660,6 @@ void tdk_attend_rows_kernel(const RoundDev rd, const LayerDev io, const DiffDev 
     // starts of this step and of the next one
     int p1 = tok_begin, p2 = min(p1 + kBigTile, tok_end);
     if (active) {
-      own_rows(at, row_ok, raw0);
       if (SEG) {
         seg_k = -1;
         enter(p1, raw0);
