@@ -1705,9 +1705,11 @@ hipError_t launch_decode(const RoundDev& rd, const LayerDev& io, const DiffDev& 
   const bool wide = planes == 3 && wide_writes(rd);
   if (rd.n_agents == 0 || d.capacity == 0) scatter_blocks = 0;
   if (slots_shared(rd)) {
-    // (three workgroups of the kernels for both planes fit a compute unit, of those for 32-token pages whose rows fill an access two, and of
-    // those with eight wavefronts, whose slots are one batch; the page items are launched with those that stand by for the last fifth.  Of the kernels for one plane more fit, and no limit showed: 60 agents x 700 tokens, pages of 32, stored and restored
-    // one plane at a time 109.7 us, 111.9 with a limit of four.)
+    // (Three workgroups of the kernels for both planes fit a compute unit; the page items are launched with those that stand by for the last
+    // fifth.  Only two fit of the kernels with eight wavefronts and of those for 32-token pages whose rows fill an access, but the limit is for
+    // slots of two batches: with eight wavefronts a slot is one batch, and 32-token pages have two with five heads only.  Of the kernels for one
+    // plane more fit, and no limit showed: 60 agents x 700 tokens, pages of 32, stored and restored one plane at a time 109.7 us, 111.9 with a
+    // limit of four.)
     const int left = planes == 3 ? 3 * rd.n_cus - rd.n_work - rd.n_work / 5 : -1;
     scatter_blocks = plan_copy_workgroups(scatter_blocks, slot_batches(rd, planes, wide ? 2 * kWaves : kWaves), rd.n_cus, left);
   }
